@@ -15,7 +15,7 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
   size_t status, logits, rec_cstar, rec_ids, rec_p, rec_Z, rec_lane, flexmask, fixed_cnt, tile_mask, base, chain_bits,
-      chain_cum, flex_list, flex_ord, flex_tok_base, flex_slot, rec_cids, rec_pref, lin_copy, pool, seg, split, needed, total;
+      chain_cum, flex_tok_base, flex_slot, rec_cids, rec_pref, lin_copy, pool, seg, split, needed, total;
 };
 
 // cw: candidates per token record (record_width(c)).  The status words come first, so
@@ -44,8 +44,6 @@ static Layout layout(int T, int E, int cw) {
   L.chain_cum = off;  off += align_up(words * 64 * 4);
   L.rec_cids = off;   off += align_up(slots * 16);
   L.rec_pref = off;   off += align_up(slots * 16);
-  L.flex_list = off;  off += align_up(ntiles * 4);
-  L.flex_ord = off;   off += align_up(ntiles * 4);
   L.flex_tok_base = off; off += align_up((ntiles + 1) * 4);
   L.flex_slot = off;  off += align_up(((size_t)T + 32 * ntiles) * 4);
   L.lin_copy = off;   off += align_up(64 * 4);
@@ -79,8 +77,6 @@ Workspace carve_workspace(void* base, int T, int E, int cw) {
   w.chain_cum = reinterpret_cast<int32_t*>(b + L.chain_cum);
   w.rec_cids = reinterpret_cast<uint8_t*>(b + L.rec_cids);
   w.rec_pref = reinterpret_cast<uint8_t*>(b + L.rec_pref);
-  w.flex_list = reinterpret_cast<int32_t*>(b + L.flex_list);
-  w.flex_ord = reinterpret_cast<int32_t*>(b + L.flex_ord);
   w.flex_tok_base = reinterpret_cast<int32_t*>(b + L.flex_tok_base);
   w.flex_slot = reinterpret_cast<int32_t*>(b + L.flex_slot);
   w.lin_copy = reinterpret_cast<int32_t*>(b + L.lin_copy);

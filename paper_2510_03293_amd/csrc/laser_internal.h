@@ -88,8 +88,6 @@ struct Workspace {
   uint8_t* rec_cids;           // [slot,16] lanes the chain reads: candidates by rank, padded
   uint8_t* rec_pref;           // [slot,16] per candidate (by rank): earlier fixed tokens of the
                                //           tile assigned to it (<= 63); 0xFF beyond the working set
-  int32_t* flex_list;          // [ntiles]  tiles that hold flexible tokens, ascending
-  int32_t* flex_ord;           // [ntiles]  number of such tiles before this tile
   int32_t* flex_tok_base;      // [ntiles+1] flexible tokens in earlier tiles; [ntiles] = all
   int32_t* flex_slot;          // [T]       slot of the f-th flexible token (token order)
   uint32_t* chain_bits;        // [T/32+1,64] per expert: bit f%32 of word f/32 = chosen for
@@ -133,8 +131,6 @@ __device__ __forceinline__ Workspace problem_workspace(const Workspace& w0, size
   w.tile_base = shifted(w0.tile_base, bytes);
   w.rec_cids = shifted(w0.rec_cids, bytes);
   w.rec_pref = shifted(w0.rec_pref, bytes);
-  w.flex_list = shifted(w0.flex_list, bytes);
-  w.flex_ord = shifted(w0.flex_ord, bytes);
   w.flex_tok_base = shifted(w0.flex_tok_base, bytes);
   w.flex_slot = shifted(w0.flex_slot, bytes);
   w.chain_bits = shifted(w0.chain_bits, bytes);

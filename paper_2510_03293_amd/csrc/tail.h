@@ -16,9 +16,8 @@ namespace laser {
 //
 // Chain workgroup (4 wavefronts):
 //   prefix  (all waves)  exclusive prefix over tiles of the fixed tokens' per-expert
-//           counts -> tile_base; ordered list of the tiles that hold flexible tokens;
-//           for every tile the number of flexible tokens before it.  Then flag 1 is
-//           published: everything is final if no tile holds a flexible token.
+//           counts -> tile_base; for every tile the number of flexible tokens before it,
+//           and the list of those tokens.  Then flag 1 is published: everything is final if no tile holds a flexible token.
 //   chain   decides the flexible tokens in token order.  The counters a flexible token
 //           sees are loads_in + fixed prefix of its tile + fixed tokens before it
 //           inside the tile (carried by its record) + flexible choices so far.
@@ -27,9 +26,8 @@ namespace laser {
 //           - window (wave 0, lane = token): 64 consecutive flexible tokens per sweep,
 //             see "window evaluation" below; used first when there are enough tokens;
 //           - sequential (wave 0, lane = expert): an expert is chosen iff fewer than k
-//             candidate keys are smaller than its own; the candidates' keys are fetched
-//             with one lane read each (CP reads per token, CP = c rounded up to 4, 8 or
-//             16).  Takes over where the window evaluation stops paying.
+//             candidate keys are smaller than its own, see "sequential walk" below.  Takes
+//             over where the window evaluation stops paying.
 //           The other waves stage the records in LDS ahead of wave 0.
 //   totals  loads and offsets, then flag 2.
 //   Output of the chain, per expert: one bit per flexible token of the call in token
@@ -53,7 +51,6 @@ namespace laser {
 
 constexpr int kChainWaves = 4;
 constexpr int kTailThreads = kChainWaves * 64;
-constexpr int kChainBatch = 3;  // flexible tiles per LDS batch
 constexpr int kSelfPrefixTiles = 1024;  // up to here finishing workgroups sum the counts themselves
 // (see "a handful of flexible tokens" below)
 constexpr int kFastMaxTiles = 256;
@@ -67,14 +64,7 @@ __device__ __forceinline__ bool fast_path_applies(int ntiles, int nflex_tiles, i
 }
 
 
-struct ChainBatch {
-  int tile[kChainBatch];
-  int nflex[kChainBatch];
-  int base[kChainBatch][64];
-  uint4 cids[kChainBatch][kTile];              // 16 candidate lanes per record
-  uint16_t rec[kChainBatch][kTile * kMaxE];    // per record and expert: prefix<<4 | rank
-};
-constexpr int kChainLdsBytes = 2 * (int)sizeof(ChainBatch);
+constexpr int kChainLdsBytes = 56 * 1024;  // dynamic LDS of a chain workgroup, used by one phase after the other
 constexpr int kChainStageTiles = kChainLdsBytes / 64;  // tiles of byte counts that fit the LDS
 
 // Data published by the chain workgroup is read with agent-scope atomic loads: they
@@ -119,26 +109,6 @@ __device__ __forceinline__ bool poll_flag(const int* flag, int want, long long l
   return false;
 }
 
-__device__ __forceinline__ void chain_prefetch(ChainBatch* dst, int batch, int ft0, int nflex_tiles, const RouteArgs& a,
-                               const Workspace& ws, int hwave, int lane) {
-  for (int tl = hwave; tl < kChainBatch; tl += kChainWaves - 1) {
-    const int f = ft0 + batch * kChainBatch + tl;
-    if (f >= nflex_tiles) return;
-    const int tile = ws.flex_list[f];
-    const int n = __builtin_popcountll(ws.flexmask[tile]);
-    if (lane == 0) {
-      dst->tile[tl] = tile;
-      dst->nflex[tl] = n;
-    }
-    dst->base[tl][lane] = ws.tile_base[(size_t)tile * 64 + lane];
-    if (lane < n) dst->cids[tl][lane] = reinterpret_cast<const uint4*>(ws.rec_cids)[(size_t)tile * kTile + lane];
-    const int words = (n * a.EP) >> 1;  // EP is even
-    const unsigned* src = reinterpret_cast<const unsigned*>(ws.rec_lane + (size_t)tile * kTile * a.EP);
-    unsigned* d32 = reinterpret_cast<unsigned*>(dst->rec[tl]);
-    for (int wd = lane; wd < words; wd += 64) d32[wd] = src[wd];
-  }
-}
-
 // cnt += number of the 4 lanes named by the bytes of `w` whose key is smaller than this
 // lane's key.  Written in assembly because the order of the instructions is the
 // point: on gfx950 a vector instruction that reads an SGPR written by the vector
@@ -173,17 +143,16 @@ __device__ __forceinline__ void count_smaller4(unsigned key, unsigned w, int& cn
       : "scc");  // (the scalar bit-field extracts and the shift set SCC)
 }
 
-// One flexible token: returns whether this lane's expert is chosen.
-template <int CP>
+// One flexible token of up to 16 candidates (lanes named by the bytes of `ids`): returns
+// whether this lane's expert is chosen.  Needs nothing in LDS; for the few tokens that a
+// finishing workgroup resolves by itself.
 __device__ __forceinline__ bool chain_step(unsigned key, bool cand, const uint4 ids, int k) {
   // (two counts: the second group's additions do not wait for the first group's)
   int smaller = 0, more = 0;
   count_smaller4(key, __builtin_amdgcn_readfirstlane(ids.x), smaller);
-  if (CP > 4) count_smaller4(key, __builtin_amdgcn_readfirstlane(ids.y), more);
-  if (CP > 8) {
-    count_smaller4(key, __builtin_amdgcn_readfirstlane(ids.z), smaller);
-    count_smaller4(key, __builtin_amdgcn_readfirstlane(ids.w), more);
-  }
+  count_smaller4(key, __builtin_amdgcn_readfirstlane(ids.y), more);
+  count_smaller4(key, __builtin_amdgcn_readfirstlane(ids.z), smaller);
+  count_smaller4(key, __builtin_amdgcn_readfirstlane(ids.w), more);
   return cand && smaller + more < k;
 }
 
@@ -201,117 +170,305 @@ __device__ __forceinline__ unsigned wave_min_u32(unsigned v) {
   return min(min(r0, r1), min(r2, r3));
 }
 
-// One flexible token of a wide call (up to 64 candidates), lane = expert: the k
-// candidates with the smallest (load, rank), found in k rounds -- the least load among
-// the remaining candidates, then the least rank among those that have it.  Any loads
-// below 2^32 - 1; not tuned (the trimming sizes the paper evaluates are at most 10).
-__device__ __forceinline__ bool chain_step_wide(unsigned load, unsigned rank, bool cand, int k) {
-  bool remaining = cand, chosen = false;
-  for (int r = 0; r < k; ++r) {
-    const unsigned lmin = wave_min_u32(remaining ? load : 0xFFFFFFFFu);
-    const bool tie = remaining && load == lmin;
-    const unsigned rmin = wave_min_u32(tie ? rank : 0xFFFFFFFFu);
-    const bool pick = tie && rank == rmin;
-    chosen = chosen || pick;
-    remaining = remaining && !pick;
-  }
-  return chosen;
+// x summed over the four quarters of the wavefront: lane l gets the sum over lanes l % 16 + 16 q.
+__device__ __forceinline__ unsigned add_quarters(unsigned x) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 p = __builtin_amdgcn_permlane32_swap(x, x, false, false);  // (both halves of x, in both halves)
+  x = p[0] + p[1];
+  p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return p[0] + p[1];
 }
 
-// Sequential walk (wave 0, lane = expert) over the flexible tiles from flexible tile
-// `ft0`, record `r_start` of that tile, which is flexible token `f0` of the call;
-// `hist0` holds the bits of output word f0/32 that are decided already.  The output
-// (chain_bits, chain_cum) is indexed by the flexible token's number within the call.
-// CP = 0: a wide call (records of up to 64 candidates, per-expert rows only).
+// One flexible token of a wide call (up to 64 candidates): the k candidates with the smallest
+// (load, rank).  The candidates are taken level by level of their counters, from the lowest one
+// up, a whole level at a time as long as all of it is wanted; of the last level the lowest ranks.
+// Sets of experts are masks in scalar registers; the ranks of a level's experts are counted in
+// the lanes of the ranks (`id`: expert of rank = lane) and taken back to the lanes of the
+// experts (`rank`).  `level`: where the token before ended; the walk that load-balancing itself
+// produces -- k of the candidates on the level where the last token left off, and nobody below
+// it -- needs no search.  (A wave-wide minimum over loads and another one over ranks for each of
+// the k picks took 860 ns per token, 64 candidates, k = 6; now below 120.)
+// Returns 1 in the lanes of the chosen experts, else 0.
+__device__ __forceinline__ unsigned chain_step_wide(unsigned load, unsigned rank, unsigned id, int k, unsigned& level) {
+  unsigned long long at = __builtin_amdgcn_ballot_w64(load == level);
+  const unsigned long long below = __builtin_amdgcn_ballot_w64(load < level);
+  // lane = rank: the `want` lowest ranks of the level `at`, then back to lane = expert
+  auto lowest = [&](int want) {
+    const unsigned here = (unsigned)(at >> id) & 1u;
+    const unsigned long long ranks = __builtin_amdgcn_ballot_w64(here != 0u);
+    const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(ranks >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ranks, 0));
+    const unsigned long long won = __builtin_amdgcn_ballot_w64(before < want) & ranks;
+    return (unsigned)(won >> rank) & 1u;
+  };
+  if (__builtin_expect(__builtin_popcountll(below != 0ull ? 0ull : at) >= k, 1)) return lowest(k);
+  if (below != 0ull) {
+    level = wave_min_u32(load);
+    at = __builtin_amdgcn_ballot_w64(load == level);
+  }
+  unsigned long long taken = 0ull;
+  int want = k;
+  // (there are more than k candidates, so the levels of the others are not reached)
+  for (int n = __builtin_popcountll(at); n < want; n = __builtin_popcountll(at)) {
+    taken |= at;
+    want -= n;
+    at = __builtin_amdgcn_ballot_w64(load == level + 1);
+    if (at != 0ull) {
+      ++level;
+    } else {
+      level = wave_min_u32(load > level ? load : 0xFFFFFFFFu);
+      at = __builtin_amdgcn_ballot_w64(load == level);
+    }
+  }
+  return lowest(want) | ((unsigned)(taken >> (threadIdx.x & 63)) & 1u);
+}
+
+// ---- sequential walk ---------------------------------------------------------------------
+//
+// One dependent step per flexible token, by wave 0 (lane = expert, G = the flexible choices of
+// the lane's expert so far); the other waves turn the records into what the step reads, a batch
+// ahead, in LDS.  What bounds it is the dependent instructions of a step: a lone wavefront issues
+// one every 4.2 to 5 cycles, an LDS lane exchange takes 57 (measured at 2.4 GHz), so the step is
+// built to have few of both on the path from one token's choice to the next one's.
+//
+// Up to 8 candidates: all pairs at once.  The keys of the candidates are gathered from the
+// lanes of their experts twice, by rank i = lane / 8 and by rank j = lane % 8 (two exchanges in
+// flight together); one compare then leaves the 8 x 8 matrix "key j < key i" in a scalar
+// register pair, and a lane that holds the candidate of rank r counts the bits of byte r: it is
+// chosen iff there are fewer than k.  Reading the eight keys into scalar registers and comparing
+// with one after the other took 170 ns per token (16384 tokens, 64 experts, k = 6, c = 8); now
+// 69, of which the bare chain of dependent instructions is 55.
+// Up to 16 candidates: lane 16 q + i compares the key of rank i with those of ranks 4 q .. 4 q + 3
+// and the four quarters are added across the wavefront (c = 16: 258 -> 132 ns).
+constexpr int kSeqBatch = 96;  // flexible tokens per LDS batch (whole output words)
+struct SeqTok {
+  unsigned rec[64];   // per expert: (counter without flexible choices) << 4 | rank, or kSeqNoCand
+  uint8_t addr[16];   // per rank: 4 * the candidate's lane (padded with a lane that holds none)
+};
+// (compares above every key; byte selector 13 of v_perm reads as 0xFF, a count of 8)
+constexpr unsigned kSeqNoCand = 0x8000000Du;
+static_assert((2 * kSeqBatch + 1) * (int)sizeof(SeqTok) <= kChainLdsBytes, "two batches and a token of read-ahead");
+
+// Wide calls (up to 64 candidates).
+constexpr int kSeqWideBatch = 64;
+struct SeqTokWide {
+  unsigned base[64];  // per expert: its counter without flexible choices, or kSeqWideNoCand
+  uint8_t rank[64];   // per expert: rank (63 for experts that are no candidates)
+  uint8_t id[64];     // per rank: the candidate's lane (padded with a lane that holds none)
+};
+constexpr unsigned kSeqWideNoCand = 0x40000000u;
+static_assert((2 * kSeqWideBatch + 1) * (int)sizeof(SeqTokWide) <= kChainLdsBytes, "two batches and a token of read-ahead");
+
 template <int CP>
-__device__ __forceinline__ void chain_walk(ChainBatch* buf, int ft0, int r_start, int f0,
-                                           unsigned hist0, int nflex_tiles, const RouteArgs& a, const Workspace& ws,
-                                           int wave, int lane, int lin, int& gflex) {
+struct SeqTraits {
+  typedef SeqTok Tok;
+  static constexpr int batch = kSeqBatch;
+  static constexpr int half = 16;  // tokens whose records a producer wave has in flight together:
+};                                 // half of its share of a batch
+template <>
+struct SeqTraits<0> {
+  typedef SeqTokWide Tok;
+  static constexpr int batch = kSeqWideBatch;
+  static constexpr int half = 11;
+};
+
+// What a producer wave needs of some tokens, on its way from memory.
+template <int N>
+struct SeqLoads {
+  unsigned rec[N], cids[N];
+  int base[N];
+};
+
+// Producer wave pw (0, 1, 2) takes tokens pw, pw + 3, ... of every batch, in two halves.
+// Lane i: where the record of its i-th token of batch `batch` is.
+template <int CP>
+__device__ __forceinline__ int seq_slots(int batch, int nflex_tok, const Workspace& ws, int pw, int lane) {
+  constexpr int NB = SeqTraits<CP>::batch;
+  const int f = batch * NB + pw + 3 * lane;
+  return (pw + 3 * lane < NB && f < nflex_tok) ? ws.flex_slot[f] : 0;
+}
+template <int CP, int N>
+__device__ __forceinline__ void seq_load(SeqLoads<N>& L, int slots, int i0, const RouteArgs& a, const Workspace& ws,
+                                         int lane) {
+#pragma unroll
+  for (int u = 0; u < N; ++u) {  // (slot 0 stands in for tokens that do not exist)
+    const int slot = __builtin_amdgcn_readlane(slots, i0 + u);
+    L.rec[u] = lane < a.EP ? ws.rec_lane[(size_t)slot * a.EP + lane] : 0xFFFFu;
+    L.base[u] = ws.tile_base[(size_t)(slot >> 6) * 64 + lane];
+    if constexpr (CP != 0) L.cids[u] = ws.rec_cids[(size_t)slot * 16 + (lane & 15)];
+  }
+}
+template <int CP, int N>
+__device__ __forceinline__ void seq_store(typename SeqTraits<CP>::Tok* dst, const SeqLoads<N>& L, int i0, int pw,
+                                          int lane, int lin) {
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    if (pw + 3 * (i0 + u) >= SeqTraits<CP>::batch) break;
+    auto* tok = dst + pw + 3 * (i0 + u);
+    const bool cand = L.rec[u] != 0xFFFFu;
+    const unsigned base = (unsigned)(lin + L.base[u]);
+    if constexpr (CP != 0) {
+      tok->rec[lane] = cand ? (base << 4) + L.rec[u] : kSeqNoCand;
+      if (lane < 16) tok->addr[lane] = (uint8_t)(4 * L.cids[u]);
+    } else {
+      const unsigned long long all = __builtin_amdgcn_ballot_w64(cand);
+      const int pad = ~all != 0ull ? __builtin_ctzll(~all) : 0;  // (no ranks to pad if every lane is a candidate)
+      tok->base[lane] = cand ? base + (L.rec[u] >> 6) : kSeqWideNoCand;
+      tok->rank[lane] = (uint8_t)(cand ? L.rec[u] & 63u : 63u);
+      tok->id[lane] = (uint8_t)pad;
+      lds_wave_fence();
+      if (cand) tok->id[L.rec[u] & 63u] = (uint8_t)lane;
+    }
+  }
+}
+
+// Walks the flexible tokens from token `f0` of the call on.  `hist0`: the bits of output word
+// f0 / 32 that are decided already.  The output (chain_bits, chain_cum) is indexed by the
+// flexible token's number within the call.  CP: 8 or 16 candidates, 0: a wide call.
+template <int CP>
+__device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
+                                           const Workspace& ws, int wave, int lane, int lin, int& gflex) {
+  typedef typename SeqTraits<CP>::Tok Tok;
+  constexpr int NB = SeqTraits<CP>::batch;
+  Tok* const buf = reinterpret_cast<Tok*>(lds);
   // wave-uniform values that arrive through LDS or memory: tell the compiler so, or the
   // loops below are compiled as divergent ones
-  ft0 = __builtin_amdgcn_readfirstlane(ft0);
-  r_start = __builtin_amdgcn_readfirstlane(r_start);
-  nflex_tiles = __builtin_amdgcn_readfirstlane(nflex_tiles);
-  const int nbatch = (nflex_tiles - ft0 + kChainBatch - 1) / kChainBatch;
-  const int mypos = lane;  // a record row is in expert order
-  const bool lane_ok = lane < a.EP;
-  const int EP = a.EP;
-  const int k = a.k;
-  int f = __builtin_amdgcn_readfirstlane(f0);
-  unsigned hist = hist0;  // bits of the current output word decided before this walk
-  if (wave != 0) chain_prefetch(&buf[0], 0, ft0, nflex_tiles, a, ws, wave - 1, lane);
-  __syncthreads();
-  for (int b = 0; b < nbatch; ++b) {
+  f0 = __builtin_amdgcn_readfirstlane(f0);
+  nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
+  const int b0 = f0 / NB, b1 = (nflex_tok + NB - 1) / NB;
+  const unsigned k = (unsigned)a.k;
+  int f = f0;
+  unsigned G = (unsigned)gflex;
+  // bits of the current output word, the last token's lowest
+  unsigned hist = (f0 & 31) != 0 ? __builtin_bitreverse32(hist0) >> (32 - (f0 & 31)) : 0u;
+  unsigned level = 0xFFFFFFFFu;  // (wide: no counter of a candidate is known to be below)
+  // The producers are two batches ahead with the list of records, and half a batch ahead with
+  // the records themselves: a batch is decided in a few microseconds, a record is two dependent
+  // memory round trips away.  (The barriers leave loads in flight alone.)
+  constexpr int NH = SeqTraits<CP>::half;
+  const int pw = wave - 1;
+  int slots = 0, slots_n = 0;  // of the batch being stored, of the next one
+  SeqLoads<NH> first, second;
+  if (wave != 0) {
+    slots = seq_slots<CP>(b0, nflex_tok, ws, pw, lane);
+    slots_n = seq_slots<CP>(b0 + 1, nflex_tok, ws, pw, lane);
+    seq_load<CP, NH>(first, slots, 0, a, ws, lane);
+    seq_load<CP, NH>(second, slots, NH, a, ws, lane);
+    Tok* dst = buf + (b0 & 1) * NB;
+    seq_store<CP, NH>(dst, first, 0, pw, lane, lin);
+    seq_load<CP, NH>(first, slots_n, 0, a, ws, lane);
+    seq_store<CP, NH>(dst, second, NH, pw, lane, lin);
+  }
+  lds_barrier();
+  for (int b = b0; b < b1; ++b) {
     if (wave != 0) {
-      if (b + 1 < nbatch) chain_prefetch(&buf[(b + 1) & 1], b + 1, ft0, nflex_tiles, a, ws, wave - 1, lane);
+      if (b + 1 < b1) {
+        slots = slots_n;
+        slots_n = seq_slots<CP>(b + 2, nflex_tok, ws, pw, lane);
+        seq_load<CP, NH>(second, slots, NH, a, ws, lane);
+        Tok* dst = buf + ((b + 1) & 1) * NB;
+        seq_store<CP, NH>(dst, first, 0, pw, lane, lin);
+        seq_load<CP, NH>(first, slots_n, 0, a, ws, lane);
+        seq_store<CP, NH>(dst, second, NH, pw, lane, lin);
+      }
     } else {
-      const ChainBatch* cur = &buf[b & 1];
-      for (int tl = 0; tl < kChainBatch; ++tl) {
-        const int ft = ft0 + b * kChainBatch + tl;
-        if (ft >= nflex_tiles) break;
-        const int n = __builtin_amdgcn_readfirstlane(cur->nflex[tl]);
-        const int fb = cur->base[tl][lane];
-        int lsum = lin + fb + gflex;
-        int r = (ft == ft0) ? r_start : 0;
-        if (r >= n) continue;
-        const uint16_t* recp = cur->rec[tl] + (lane_ok ? mypos : 0);
-        const uint4* cidp = cur->cids[tl];
-        // the record of token r is in (rec_a, ids_a) at the top of every round; the next
-        // record's LDS reads fly during a step.  Two tokens per round, so that the records
-        // alternate between two sets of registers instead of being copied.
-        unsigned rec_a = recp[r * EP], rec_b = 0;
-        uint4 ids_a = cidp[r], ids_b = make_uint4(0, 0, 0, 0);
-        auto step = [&](unsigned rec, const uint4 ids, int sh) {
-          const bool cand = lane_ok && rec != 0xFFFFu;
+      const Tok* cur = buf + (b & 1) * NB;
+      const int n = min(NB, nflex_tok - b * NB);
+      int r = f - b * NB;
+      if constexpr (CP != 0) {
+        constexpr int kPer = CP == 8 ? 1 : 4;  // keys a lane compares with
+        unsigned rec = cur[r].rec[lane];
+        unsigned ai = cur[r].addr[CP == 8 ? lane >> 3 : lane & 15], aj[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) aj[u] = cur[r].addr[CP == 8 ? lane & 7 : 4 * (lane >> 4) + u];
+        // (the next token's record is read while this one is decided; behind the last one of a
+        // batch it is read and not used)
+        auto step = [&](const Tok& next) {
+          const unsigned key = (G << 4) + rec;
+          const unsigned ki = (unsigned)__builtin_amdgcn_ds_bpermute((int)ai, (int)key);
+          unsigned kj[kPer];
+#pragma unroll
+          for (int u = 0; u < kPer; ++u) kj[u] = (unsigned)__builtin_amdgcn_ds_bpermute((int)aj[u], (int)key);
+          __builtin_amdgcn_sched_barrier(0);
+          const unsigned rec_n = next.rec[lane];
+          const unsigned ai_n = next.addr[CP == 8 ? lane >> 3 : lane & 15];
+          unsigned aj_n[kPer];
+#pragma unroll
+          for (int u = 0; u < kPer; ++u) aj_n[u] = next.addr[CP == 8 ? lane & 7 : 4 * (lane >> 4) + u];
+          __builtin_amdgcn_sched_barrier(0);
           bool chosen;
-          if constexpr (CP == 0) {
-            chosen = chain_step_wide((unsigned)lsum + (rec >> 6), rec & 63u, cand, k);
+          if constexpr (CP == 8) {
+            const unsigned sel = (rec & 15u) | 0x0C0C0C00u;
+            const unsigned long long less = __builtin_amdgcn_ballot_w64(kj[0] < ki);
+            const unsigned row = __builtin_amdgcn_perm((unsigned)(less >> 32), (unsigned)less, sel);
+            chosen = (unsigned)__builtin_popcount(row) < k;
           } else {
-            const unsigned key = cand ? (((unsigned)lsum << 4) + rec) : 0xFFFFFFFFu;
-            chosen = chain_step<CP>(key, cand, ids, k);
+            const unsigned shift = (rec & 15u) | ((rec >> 27) & 16u);  // (no candidate: a bit that is not set)
+            unsigned cnt = 0;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) cnt += kj[u] < ki ? 1u : 0u;
+            cnt = add_quarters(cnt);
+            const unsigned won = (unsigned)__builtin_amdgcn_ballot_w64(cnt < k) & 0xFFFFu;
+            chosen = ((won >> shift) & 1u) != 0u;
           }
-          lsum += chosen ? 1 : 0;
-          hist |= (chosen ? 1u : 0u) << sh;
+          G += chosen ? 1u : 0u;
+          hist = hist + hist + (chosen ? 1u : 0u);
+          rec = rec_n;
+          ai = ai_n;
+#pragma unroll
+          for (int u = 0; u < kPer; ++u) aj[u] = aj_n[u];
         };
         while (r < n) {
-          // up to the end of the tile or of the 32-token output word, whichever is first
-          const int sh0 = f & 31;
-          const int seg = min(n - r, 32 - sh0);
-          const int end = sh0 + seg;
-          int sh = sh0;
-          for (; sh + 2 <= end; sh += 2, r += 2) {
-            rec_b = recp[(r + 1) * EP];  // (r + 1 < n: two tokens are left)
-            ids_b = cidp[r + 1];
-            step(rec_a, ids_a, sh);
-            if (r + 2 < n) {
-              rec_a = recp[(r + 2) * EP];
-              ids_a = cidp[r + 2];
-            }
-            step(rec_b, ids_b, sh + 1);
+          // up to the end of the batch or of the 32-token output word, whichever is first
+          const int end = min(n, r + 32 - (f & 31));
+          f += end - r;
+          for (; r + 4 <= end; r += 4) {
+            step(cur[r + 1]);
+            step(cur[r + 2]);
+            step(cur[r + 3]);
+            step(cur[r + 4]);
           }
-          if (sh < end) {
-            if (r + 1 < n) {
-              rec_b = recp[(r + 1) * EP];
-              ids_b = cidp[r + 1];
-            }
-            step(rec_a, ids_a, sh);
-            rec_a = rec_b;
-            ids_a = ids_b;
-            ++r;
-          }
-          f += seg;
+          for (; r < end; ++r) step(cur[r + 1]);
           if ((f & 31) == 0) {
-            ws.chain_bits[(size_t)((f >> 5) - 1) * 64 + lane] = hist;
-            ws.chain_cum[(size_t)(f >> 5) * 64 + lane] = lsum - lin - fb;
+            ws.chain_bits[(size_t)((f >> 5) - 1) * 64 + lane] = __builtin_bitreverse32(hist);
+            ws.chain_cum[(size_t)(f >> 5) * 64 + lane] = (int)G;
             hist = 0;
           }
         }
-        gflex = lsum - lin - fb;
+      } else {
+        unsigned base = cur[r].base[lane], rank = cur[r].rank[lane], id = cur[r].id[lane];
+        auto step = [&](const Tok& next) {
+          const unsigned load = base + G;
+          const unsigned base_n = next.base[lane], rank_n = next.rank[lane], id_n = next.id[lane];
+          const unsigned chosen = chain_step_wide(load, rank, id, (int)k, level);
+          G += chosen;
+          hist = hist + hist + chosen;
+          base = base_n;
+          rank = rank_n;
+          id = id_n;
+        };
+        while (r < n) {
+          const int end = min(n, r + 32 - (f & 31));
+          f += end - r;
+          for (; r + 2 <= end; r += 2) {
+            step(cur[r + 1]);
+            step(cur[r + 2]);
+          }
+          for (; r < end; ++r) step(cur[r + 1]);
+          if ((f & 31) == 0) {
+            ws.chain_bits[(size_t)((f >> 5) - 1) * 64 + lane] = __builtin_bitreverse32(hist);
+            ws.chain_cum[(size_t)(f >> 5) * 64 + lane] = (int)G;
+            hist = 0;
+          }
+        }
       }
     }
-    __syncthreads();
+    lds_barrier();
   }
-  if (wave == 0 && (f & 31) != 0) ws.chain_bits[(size_t)(f >> 5) * 64 + lane] = hist;
+  if (wave == 0) {
+    gflex = (int)G;
+    if ((f & 31) != 0)
+      ws.chain_bits[(size_t)(f >> 5) * 64 + lane] = __builtin_bitreverse32(hist) >> (32 - (f & 31));
+  }
 }
 
 // ------------------------------------------------ window evaluation of the chain ----
@@ -346,7 +503,8 @@ constexpr unsigned kSpecInvalid = 1u << 27;   // counter of a rank beyond the wo
 constexpr int kSpecMinTokens = 256;           // fewer flexible tokens: sequential walk
 constexpr int kSpecCheckSweeps = 8;           // progress is judged over this many sweeps ...
 // ... in which at least this many tokens must retire (measured: a sweep costs about
-// 0.56 / 0.96 us for 4 / 8 candidates, a sequential step 0.12 / 0.17 us)
+// 0.56 / 0.96 us for 4 / 8 candidates, a sequential step 0.07 us; the switch is one-way, so
+// the line lies below break-even)
 constexpr int kSpecGuessProgress = 26 * kSpecCheckSweeps;  // (without guesses at most 32 per sweep retire)
 constexpr int spec_min_progress(int cp) { return cp <= 4 ? 40 : cp <= 8 ? 48 : 56; }
 
@@ -1057,7 +1215,6 @@ struct ChainSeg {
 __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
                                 int32_t* __restrict__ loads_inout,
                                 int32_t* __restrict__ expert_offsets, const ChainSeg seg) {
-  ChainBatch* buf = reinterpret_cast<ChainBatch*>(lds);
   __shared__ int wave_tot[kChainWaves][64];
   __shared__ __align__(16) int tb_rows[kChainWaves][4 * 64];
   __shared__ int wave_flex[kChainWaves], wave_tok[kChainWaves];
@@ -1119,10 +1276,9 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
     wave_tok[wave] = ntok;
   }
   __syncthreads();
-  int fbefore = 0, nflex_tiles = 0, tokbefore = 0, nflex_tok = 0;  // nflex_tok: flexible tokens of the call
+  int nflex_tiles = 0, tokbefore = 0, nflex_tok = 0;  // nflex_tok: flexible tokens of the call
   for (int w = 0; w < kChainWaves; ++w) {
     const int fl = wave_flex[w], tk = wave_tok[w];
-    fbefore += w < wave ? fl : 0;
     tokbefore += w < wave ? tk : 0;
     nflex_tiles += fl;
     nflex_tok += tk;
@@ -1192,15 +1348,12 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
   const bool wide = a.cw > kMaxC;
   const bool use_spec = nflex_tok >= kSpecMinTokens && !wide;
-  // order of the flexible tiles, and for every tile the number of flexible tokens before it
+  // for every tile the number of flexible tokens before it, and the list of those tokens
   const int fbase = seg.on ? seg.fbase : 0;
   for (int g = ga; g < gb && (nflex_tiles > 0 || seg.on); ++g) {
     const int tile = g * 64 + lane;
     const unsigned long long fm =
         g == ga ? first_fm : g == ga + 1 ? second_fm : (tile < ntiles ? ws.flexmask[tile] : 0ull);
-    const bool f = fm != 0ull;
-    const unsigned long long bal = __builtin_amdgcn_ballot_w64(f);
-    const int ord = fbefore + __builtin_popcountll(bal & lanes_below(lane));
     const int np = __builtin_popcountll(fm);
     int incl = np;
 #pragma unroll
@@ -1209,19 +1362,14 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
       if (lane >= d) incl += up;
     }
     if (tile < ntiles) {
-      ws.flex_ord[tile] = ord;
       ws.flex_tok_base[tile] = fbase + tokbefore + incl - np;  // (read by the finishing pass only)
       if (tile == ntiles - 1 && !seg.on) ws.flex_tok_base[ntiles] = tokbefore + incl;
     }
-    if (f) ws.flex_list[ord] = tile;
-    if (use_spec) {
-      // slot (tile * 64 + rank among the tile's flexible tokens) of every flexible token:
-      // every lane lists its own tile's
-      const int mybase = tokbefore + incl - np;
-      for (int i = 0; __builtin_amdgcn_ballot_w64(i < np) != 0ull; ++i)
-        if (i < np) ws.flex_slot[mybase + i] = (tile << 6) + i;
-    }
-    fbefore += __builtin_popcountll(bal);
+    // slot (tile * 64 + rank among the tile's flexible tokens) of every flexible token: every
+    // lane lists its own tile's
+    const int mybase = tokbefore + incl - np;
+    for (int i = 0; __builtin_amdgcn_ballot_w64(i < np) != 0ull; ++i)
+      if (i < np) ws.flex_slot[mybase + i] = (tile << 6) + i;
     tokbefore += __shfl(incl, 63, 64);
   }
 
@@ -1254,10 +1402,10 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
       if (wave == 0) segment_result();
       return;
     }
-    __syncthreads();  // tile_base, flex_list, flex_ord, flex_slot written by every wave
+    __syncthreads();  // tile_base, flex_slot written by every wave
   } else {
     if (nflex_tiles == 0 && wave == 0) write_totals();  // already final
-    __syncthreads();  // tile_base, flex_list, flex_ord (and the totals) written by every wave
+    __syncthreads();  // tile_base, flex_slot (and the totals) written by every wave
     if (threadIdx.x == 0) {
       ws.status[kStatusFlexTiles] = nflex_tiles;
       __hip_atomic_store(&ws.status[kStatusPhase], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -1285,20 +1433,12 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   }
   if (decided < nflex_tok) {
     // the rest (or everything) one token after the other
-    int ft0 = 0, r0 = 0;
-    if (decided > 0) {
-      const int slot = ws.flex_slot[decided];
-      ft0 = ws.flex_ord[slot >> 6];
-      r0 = slot & 63;
-    }
     if (wide)
-      chain_walk<0>(buf, ft0, r0, decided, hist0, nflex_tiles, a, ws, wave, lane, lin, gflex);
-    else if (a.c <= 4)
-      chain_walk<4>(buf, ft0, r0, decided, hist0, nflex_tiles, a, ws, wave, lane, lin, gflex);
+      chain_walk<0>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
     else if (a.c <= 8)
-      chain_walk<8>(buf, ft0, r0, decided, hist0, nflex_tiles, a, ws, wave, lane, lin, gflex);
+      chain_walk<8>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
     else
-      chain_walk<16>(buf, ft0, r0, decided, hist0, nflex_tiles, a, ws, wave, lane, lin, gflex);
+      chain_walk<16>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
   }
   if (seg.on) {
     if (wave == 0) segment_result();
@@ -1330,11 +1470,11 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
 // tile_base carries the earlier segments' choices -- the finishing pass reads all of it
 // exactly as in a call that is not pipelined.
 
-// The chain numbers the tiles, the flexible tokens and the tiles with flexible tokens of a
-// segment from 0.  `v` becomes the view of the arrays in which those are dtiles tiles,
-// dflex flexible tokens (a multiple of 32) and dord flexible tiles further on than in `v`.
+// The chain numbers the tiles and the flexible tokens of a segment from 0.  `v` becomes the
+// view of the arrays in which those are dtiles tiles and dflex flexible tokens (a multiple of
+// 32) further on than in `v`.
 // (Advanced in place from segment to segment: one set of pointers in scalar registers.)
-__device__ __forceinline__ void advance_view(Workspace& v, const RouteArgs& a, int dtiles, int dflex, int dord) {
+__device__ __forceinline__ void advance_view(Workspace& v, const RouteArgs& a, int dtiles, int dflex) {
   const size_t tok = (size_t)dtiles * kTile;  // tokens and record slots
   v.rec_cstar += tok;
   v.rec_ids += tok * a.cw;
@@ -1347,8 +1487,6 @@ __device__ __forceinline__ void advance_view(Workspace& v, const RouteArgs& a, i
   v.tile_base += (size_t)dtiles * 64;
   v.rec_cids += tok * 16;
   v.rec_pref += tok * 16;
-  v.flex_list += dord;
-  v.flex_ord += dtiles;
   v.flex_tok_base += dtiles;
   v.flex_slot += dflex;
   v.chain_bits += (size_t)(dflex >> 5) * 64;
@@ -1388,7 +1526,7 @@ __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a,
     fbase = __builtin_amdgcn_readfirstlane(segw[kSegFlexBase]);
     ordbase = __builtin_amdgcn_readfirstlane(segw[kSegOrdBase]);
     carry = segw[kSegCarry + lane];
-    advance_view(wv, a, min(segment_start(a, j), a.ntiles), fbase, ordbase);
+    advance_view(wv, a, min(segment_start(a, j), a.ntiles), fbase);
   }
   const int rounds = sg.on ? a.nseg : 1;
   for (; j < rounds; ++j) {
@@ -1422,7 +1560,7 @@ __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a,
     // (as scalars: the next segment's view is then computed in scalar registers)
     const int dord = __builtin_amdgcn_readfirstlane(seg_out[64]);
     const int dflex = (__builtin_amdgcn_readfirstlane(seg_out[65]) + 32) & ~31;
-    advance_view(wv, a, av.ntiles, dflex, dord);
+    advance_view(wv, a, av.ntiles, dflex);
     ordbase += dord;
     fbase += dflex;
     __syncthreads();  // (seg_out is written again in the next round)
@@ -1886,7 +2024,7 @@ __device__ __forceinline__ int finish_fast(int block, FastShared& fs, unsigned l
       const unsigned rec = fs.rec[n][lane];
       const bool cand = lane < a.EP && rec != 0xFFFFu;
       const unsigned key = cand ? (((unsigned)base << 4) + rec) : 0xFFFFFFFFu;
-      const bool chosen = chain_step<16>(key, cand, fs.cids[n], a.k);
+      const bool chosen = chain_step(key, cand, fs.cids[n], a.k);
       gflex += chosen ? 1 : 0;
       const unsigned long long em = __builtin_amdgcn_ballot_w64(chosen);
       if (lane == 0) fs.emask[n] = em;

@@ -113,6 +113,21 @@ def test_window_chain_variants(T, E, k, c):
         u.check_from_logits(logits, k, c, 2.0, 1e-30, loads_in, label=f"window variant T{T} E{E} k{k} c{c} s{scale}")
 
 
+# The sequential walk stages its tokens in batches of 96 (64 where there are more than 16
+# candidates), a producer wave's share of a batch in two halves, output words of 32 tokens.
+@pytest.mark.parametrize("T", [1, 2, 3, 31, 32, 33, 47, 48, 49, 63, 64, 65, 95, 96, 97, 191, 192, 193, 250])
+@pytest.mark.parametrize("E,k,c", [(64, 6, 8), (8, 2, 4), (64, 9, 16), (16, 4, 12), (9, 8, 9), (64, 6, 64), (20, 3, 18)])
+def test_sequential_walk_sizes(T, E, k, c):
+    """Every token load-dependent, fewer than the window evaluation takes: counters equal,
+    slightly apart and far apart (the wide walk goes level by level of the counters)."""
+    u = _util()
+    rng = np.random.default_rng(T * 13 + E + c)
+    for hi in (1, 3, 100):
+        logits = wl.random_logits(T + E + c + hi, T, E, kind="normal", scale=0.3)
+        loads_in = rng.integers(0, hi, size=E).astype(np.int32)
+        u.check_from_logits(logits, k, c, 2.0, 1e-30, loads_in, label=f"walk T{T} E{E} k{k} c{c} loads<{hi}")
+
+
 @pytest.mark.parametrize("E,k,c,T1,T2", [(64, 6, 8, 3001, 3000), (8, 2, 4, 1237, 5000),
                                          (64, 6, 12, 700, 2500), (16, 4, 8, 5000, 0)])
 def test_window_chain_gives_way_to_sequential(E, k, c, T1, T2):
