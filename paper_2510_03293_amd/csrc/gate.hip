@@ -236,41 +236,4 @@ hipError_t launch_gate_analyse_bf16(const void* hidden, const void* w, int H, co
   }
 }
 
-// fp32 path: one thread per (token, expert) dot product, float4 loads, fused
-// multiply-add accumulation in h order.  Meant for small fp32 problems.
-__global__ __launch_bounds__(256) void gate_f32_kernel(const float* __restrict__ hidden,
-                                                       const float* __restrict__ w, int T, int H,
-                                                       int E, float* __restrict__ logits,
-                                                       size_t logits_stride) {
-  hidden += (size_t)blockIdx.y * T * H;
-  w += (size_t)blockIdx.y * E * H;
-  logits += (size_t)blockIdx.y * logits_stride;
-  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (long long)T * E) return;
-  const int t = (int)(idx / E);
-  const int e = (int)(idx - (long long)t * E);
-  const float4* h4 = reinterpret_cast<const float4*>(hidden + (size_t)t * H);
-  const float4* w4 = reinterpret_cast<const float4*>(w + (size_t)e * H);
-  float acc = 0.0f;
-  for (int i = 0; i < (H >> 2); ++i) {
-    const float4 x = h4[i], y = w4[i];
-    acc = __builtin_fmaf(x.x, y.x, acc);
-    acc = __builtin_fmaf(x.y, y.y, acc);
-    acc = __builtin_fmaf(x.z, y.z, acc);
-    acc = __builtin_fmaf(x.w, y.w, acc);
-  }
-  logits[idx] = acc;
-}
-
-hipError_t launch_gate_f32(const float* hidden, const float* w, int T, int H, int E, int nbatch,
-                           float* logits, size_t logits_stride, hipStream_t s) {
-  const long long total = (long long)T * E;
-  if (total == 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((total + 255) / 256);
-  clear_stale_error();
-  hipLaunchKernelGGL(gate_f32_kernel, dim3(blocks, nbatch), dim3(256), 0, s, hidden, w, T, H, E, logits,
-                     logits_stride);
-  return hipGetLastError();
-}
-
 }  // namespace laser
