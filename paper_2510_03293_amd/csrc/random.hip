@@ -13,23 +13,27 @@
 // the score order swaps position i with i + floor(r_i * (m - i) / 2^32) for
 // i = 0..c-1; the first c positions, in ascending order, are the candidates.
 //
-// Two kernels.  analyse_general_kernel is the whole analysis in either trimming mode:
-// one workgroup per tile of 64 tokens, lane = token, per-token arrays in LDS, order
-// statistics by counting (E^2 compares per token, shared by four waves), everything
-// after that one wavefront's work; written for clarity.  It is used for RANDOM trimming
-// where c == k (a sampled token is then not load-dependent, but its experts are the
-// sample), and in both modes for trimming sizes above the 16 candidates that the fast
-// analysis carries ("wide" calls: up to 64 candidates per token, e.g. the load-only
-// baseline of the paper's evaluation, c = n).  Where 16 >= c > k the deterministic
-// analysis already gives everything but the candidates of the tokens it trimmed, and
+// Two kernels.  analyse_general_kernel is the whole analysis in either trimming mode.  It is
+// used for RANDOM trimming where c == k (a sampled token is then not load-dependent, but its
+// experts are the sample), and in both modes for trimming sizes above the 16 candidates that
+// the fast analysis carries ("wide" calls: up to 64 candidates per token, e.g. the load-only
+// baseline of the paper's evaluation, c = n).  Where 16 >= c > k the deterministic analysis
+// already gives everything but the candidates of the tokens it trimmed, and
 // random_resample_kernel only redoes those.
+//
+// Both give a token to one wavefront, lane = expert: the rank of the lane's expert is counted
+// against the 64 keys read out one after the other (two lane reads, one compare, one add each);
+// the shuffle's positions are lanes, its draws and swaps scalars; the sample is a mask of
+// positions, so that its ascending order costs nothing.  What bounds them is the issue of those
+// instructions, about 400 per token, and waves enough to fill it: 16 per tile in the general
+// kernel, 4 in the other one, where few tokens of a tile are sampled.  (With lane = token, one
+// wavefront per tile behind a counting pass over E^2 values in LDS: 56 us for the
+// resampling of 12345 tokens, a tenth of them sampled -- the call 114 us, now 71 --, 65 us for
+// the whole analysis of 8192 tokens, 64 experts -- the load-only call 1020 us, now 977.)
 #include "analyse.h"
 #include "laser_internal.h"
 
 namespace laser {
-
-constexpr int kRowF = 65;  // floats per token row in LDS (64 + 1: no bank conflicts)
-constexpr int kRowB = 68;  // bytes per token row of the byte arrays (17 words)
 
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t (&out)[4]) {
@@ -51,11 +55,87 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
   out[3] = c3;
 }
 
-constexpr int kRandomWaves = 4;  // the counting pass is shared by 4 waves, the rest is wave 0's
+// Lane = expert: the number of experts before this lane's in the score order (logit
+// descending, equal logits by lower index).  Lanes without an expert hold kPadKey, which is
+// before nobody.
+__device__ __forceinline__ int rank_of(double key, int E) {
+  const long long b = __double_as_longlong(key);
+  const int lo = (int)b, hi = (int)(b >> 32);
+  int before = 0;
+  for (int j0 = 0; j0 < E; j0 += 8) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const unsigned l = (unsigned)__builtin_amdgcn_readlane(lo, j0 + u), h = (unsigned)__builtin_amdgcn_readlane(hi, j0 + u);
+      before += __longlong_as_double((long long)(((unsigned long long)h << 32) | l)) > key ? 1 : 0;
+    }
+  }
+  return before;
+}
+
+// The sample of a token (`g`: its number in the caller's numbering): c of the positions
+// [0, m), m <= 64, as a mask.
+__device__ __forceinline__ unsigned long long sample_positions(const RandomArgs& rnd, unsigned long long g, int m,
+                                                               int c, int lane) {
+  uint32_t w[4];  // lane b: block b of the token's generator (at most 64 draws: 16 blocks)
+  philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), rnd.stream, (uint32_t)(lane & 15), (uint32_t)rnd.seed,
+                (uint32_t)(rnd.seed >> 32), w);
+  int at = lane;  // lane = place in the shuffled array: the position it holds
+  unsigned long long picked = 0ull;
+  for (int i = 0; i < c; ++i) {
+    const int q = i & 3;
+    const unsigned r = (unsigned)__builtin_amdgcn_readlane((int)(q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3]), i >> 2);
+    const int j = i + (int)(((unsigned long long)r * (unsigned)(m - i)) >> 32);  // i <= j < m
+    // (place i is not looked at again: what it held goes to place j, what j held is drawn)
+    const int ai = __builtin_amdgcn_readlane(at, i), aj = __builtin_amdgcn_readlane(at, j);
+    at = lane == j ? ai : at;
+    picked |= 1ull << aj;
+  }
+  return picked;
+}
+
+// Wave-uniform 64-bit value as a scalar.
+__device__ __forceinline__ unsigned long long scalar64(unsigned long long x) {
+  return ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
+         (unsigned)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+// The records of a flexible token, lane = expert: `in` the expert is candidate number j (its
+// position among the `ncand` candidates in score order) with the softmax numerator p; `pref`
+// fixed tokens of the tile before the token were assigned to it.
+__device__ __forceinline__ void write_records(const RouteArgs& a, const Workspace& ws, int t, int slot, int lane, bool in,
+                                              int j, float p, int pref, int ncand) {
+  const int cw = a.cw;
+  const bool wide = cw > kMaxC;  // (the wide chain reads the per-expert rows only)
+  // ranks beyond the working set point the chain at a lane that holds no candidate
+  // (at most 16 of the 32 low experts are candidates unless the call is wide)
+  const unsigned low = (unsigned)__builtin_amdgcn_ballot_w64(in);
+  const int padlane = a.E < 64 ? a.E : wide ? 0 : __builtin_ctz(~low);
+  if (in) {
+    ws.rec_ids[(size_t)t * cw + j] = (uint8_t)lane;
+    ws.rec_p[(size_t)t * cw + j] = p;
+    if (!wide) {
+      ws.rec_cids[(size_t)slot * 16 + j] = (uint8_t)lane;
+      ws.rec_pref[(size_t)slot * 16 + j] = (uint8_t)pref;
+    }
+  }
+  if (lane >= ncand && lane < cw) {
+    ws.rec_ids[(size_t)t * cw + lane] = 0;
+    ws.rec_p[(size_t)t * cw + lane] = 0.0f;
+    if (!wide) {
+      ws.rec_cids[(size_t)slot * 16 + lane] = (uint8_t)padlane;
+      ws.rec_pref[(size_t)slot * 16 + lane] = 0xFF;
+    }
+  }
+  if (lane < a.EP)
+    ws.rec_lane[(size_t)slot * a.EP + lane] = in ? (uint16_t)((pref << (wide ? 6 : 4)) | j) : (uint16_t)0xFFFF;
+}
+
+constexpr int kGeneralWaves = 16;
+constexpr int kGeneralTokens = kTile / kGeneralWaves;  // tokens of a wavefront
 
 // SAMPLE: trimming mode RANDOM (otherwise the c best of the pool are kept).
 template <bool SAMPLE>
-__global__ __launch_bounds__(64 * kRandomWaves) void analyse_general_kernel(const float* __restrict__ logits,
+__global__ __launch_bounds__(64 * kGeneralWaves) void analyse_general_kernel(const float* __restrict__ logits,
                                                             size_t logits_stride, const RouteArgs a0,
                                                             const Workspace ws0, const RandomArgs rnd0,
                                                             int32_t* __restrict__ expert_ids,
@@ -69,160 +149,108 @@ __global__ __launch_bounds__(64 * kRandomWaves) void analyse_general_kernel(cons
   logits += (size_t)prob * logits_stride;
   expert_ids += (size_t)prob * a.T * a.k;
   weights += (size_t)prob * a.T * a.k;
-  __shared__ float zl[kTile * kRowF], pl[kTile * kRowF], tl[kTile * kRowF];
-  __shared__ uint8_t ordl[kTile * kRowB], arrl[kTile * kRowB];
-  __shared__ unsigned long long maskl[64];
+  __shared__ unsigned long long maskl[64], flexl;
   const int tile = blockIdx.x, lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t = tile * kTile + lane;
-  const bool live = t < a.T;
   const int E = a.E, k = a.k, c = a.c;
 
   // the tail kernel of this call polls these words; they are cleared here, one
   // kernel earlier on the same stream
   if (tile == 0 && threadIdx.x < 4) ws.status[threadIdx.x] = 0;
   if (tile == 0 && threadIdx.x < 64) ws.lin_copy[threadIdx.x] = (int)threadIdx.x < a.E ? a.loads_in[threadIdx.x] : 0;
+  if (threadIdx.x < 64) maskl[threadIdx.x] = 0ull;
+  if (threadIdx.x == 0) flexl = 0ull;
 
-  const int rows = min(kTile, a.T - tile * kTile);
-  const float* src = logits + (size_t)tile * kTile * E;
-  for (int idx = threadIdx.x; idx < kTile * E; idx += 64 * kRandomWaves) {
-    const int tok = idx / E;
-    zl[tok * kRowF + (idx - tok * E)] = tok < rows ? src[idx] : 0.0f;
+  // wave w has the tokens w, w + 16, ... of the tile
+  const bool real = lane < E;
+  float z[kGeneralTokens];
+#pragma unroll
+  for (int n = 0; n < kGeneralTokens; ++n) {
+    const int t = tile * kTile + wave + n * kGeneralWaves;
+    z[n] = (real && t < a.T) ? logits[(size_t)t * E + lane] : 0.0f;
   }
+  // what the second half of the kernel needs of a token
+  int rank[kGeneralTokens], ncand[kGeneralTokens];   // (ncand 0: not load-dependent)
+  float p[kGeneralTokens];
+  unsigned long long picked[kGeneralTokens];         // the candidates' positions in the score order
+  unsigned long long mine = 0ull;                    // the wave's fixed tokens assigned to the lane's expert
+  unsigned long long fm = 0ull;
   __syncthreads();
-
-  float* z = zl + lane * kRowF;
-  float* p = pl + lane * kRowF;
-  float* tr = tl + lane * kRowF;
-  uint8_t* ord = ordl + lane * kRowB;  // expert at each position of the score order
-  uint8_t* arr = arrl + lane * kRowB;  // candidate positions
-
-  // ---- order: logit descending, equal logits by lower index -------------------
-  // (wave w places experts w, w + 4, ...; every wave sees all 64 tokens)
-  for (int i = wave; i < E; i += kRandomWaves) {
-    const float zi = z[i];
-    int before = 0;
-    for (int j = 0; j < E; ++j) {
-      const float zj = z[j];
-      before += (zj > zi || (zj == zi && j < i)) ? 1 : 0;
-    }
-    ord[before] = (uint8_t)i;
-  }
-  __syncthreads();
-  if (wave != 0) return;  // (a barrier counts only the waves that are still running)
-  const float zmax = z[ord[0]];
-
-  // ---- scores, normaliser (fixed tree), top-k mass, pool ------------------------
-  int inpool = 0;
-  for (int i = 0; i < E; ++i) {
-    const float d = z[i] - zmax;
-    p[i] = exp_fixed(clamp_exp_arg(d));
-    inpool += d >= a.tau_ln ? 1 : 0;
-  }
-  int P = 1;
-  while (P < E) P <<= 1;
-  for (int i = 0; i < P; ++i) tr[i] = i < E ? p[i] : 0.0f;
-  for (int s = P >> 1; s >= 1; s >>= 1)
-    for (int i = 0; i < s; ++i) tr[i] = tr[i] + tr[i + s];
-  const float zsum = tr[0];
-  float sk = p[ord[0]];
-  for (int i = 1; i < k; ++i) sk = sk + p[ord[i]];
-  const bool mass_ok = sk >= a.eps_high * zsum;
-  const int m = inpool > k ? inpool : k;
-  const int cstar = mass_ok ? k : (c < m ? c : m);
-
-  // ---- candidates: positions in the score order, ascending ----------------------
-  if (SAMPLE && !mass_ok && m > c) {
-    for (int i = 0; i < m; ++i) arr[i] = (uint8_t)i;
-    const unsigned long long g = rnd.token_offset + (unsigned long long)t;
-    uint32_t wv[4] = {0u, 0u, 0u, 0u};
-    for (int i = 0; i < c; ++i) {
-      if ((i & 3) == 0)
-        philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), rnd.stream, (uint32_t)(i >> 2),
-                      (uint32_t)rnd.seed, (uint32_t)(rnd.seed >> 32), wv);
-      const uint32_t r = (i & 3) == 0 ? wv[0] : (i & 3) == 1 ? wv[1] : (i & 3) == 2 ? wv[2] : wv[3];
-      const int j = i + (int)__umulhi(r, (uint32_t)(m - i));
-      const uint8_t tmp = arr[i];
-      arr[i] = arr[j];
-      arr[j] = tmp;
-    }
-    for (int i = 1; i < c; ++i) {  // insertion sort of the first c
-      const uint8_t x = arr[i];
-      int j = i - 1;
-      while (j >= 0 && arr[j] > x) {
-        arr[j + 1] = arr[j];
-        --j;
+#pragma unroll
+  for (int n = 0; n < kGeneralTokens; ++n) {
+    const int itok = wave + n * kGeneralWaves, t = tile * kTile + itok;
+    rank[n] = ncand[n] = 0;
+    p[n] = 0.0f;
+    picked[n] = 0ull;
+    if (t < a.T) {
+      // ---- scores, normaliser (fixed tree over the expert index), top-k mass, pool ----
+      rank[n] = rank_of(real ? make_key(z[n], lane) : kPadKey, E);
+      rank[n] = real ? rank[n] : lane;
+      const int best = __builtin_ctzll(__builtin_amdgcn_ballot_w64(real && rank[n] == 0));
+      const float d = z[n] - __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z[n]), best));
+      p[n] = real ? exp_fixed(clamp_exp_arg(d)) : 0.0f;
+      float tr = p[n];
+#pragma unroll
+      for (int s = 32; s >= 1; s >>= 1) tr = tr + __shfl_down(tr, s, 64);  // (lane 0 holds the tree's sum)
+      const float zsum = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tr)));
+      // lane = rank
+      const float ranked = __int_as_float(__builtin_amdgcn_ds_permute(4 * rank[n], __float_as_int(p[n])));
+      auto at_rank = [&](int r) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ranked), r)); };
+      float sk = at_rank(0);
+      for (int i = 1; i < k; ++i) sk = sk + at_rank(i);
+      const bool mass_ok = sk >= a.eps_high * zsum;
+      const int inpool = __builtin_popcountll(__builtin_amdgcn_ballot_w64(real && d >= a.tau_ln));
+      const int m = inpool > k ? inpool : k;
+      const int cstar = mass_ok ? k : (c < m ? c : m);
+      // ---- candidates ------------------------------------------------------------------
+      if (SAMPLE && !mass_ok && m > c)
+        picked[n] = sample_positions(rnd, rnd.token_offset + (unsigned long long)t, m, c, lane);
+      else
+        picked[n] = cstar >= 64 ? ~0ull : (1ull << cstar) - 1ull;
+      const bool flex = !mass_ok && cstar > k;
+      const bool in = real && ((picked[n] >> rank[n]) & 1ull) != 0ull;
+      if (flex) {
+        ncand[n] = cstar;
+        fm |= 1ull << itok;
+      } else {  // (exactly k positions are picked)
+        float denom = zsum;
+        if (a.renormalize) {
+          unsigned long long left = picked[n];
+          denom = at_rank(__builtin_ctzll(left));
+          for (left &= left - 1ull; left != 0ull; left &= left - 1ull) denom = denom + at_rank(__builtin_ctzll(left));
+        }
+        if (in) {
+          const int j = __builtin_popcountll(picked[n] & lanes_below(rank[n]));
+          expert_ids[(size_t)t * k + j] = lane;
+          weights[(size_t)t * k + j] = p[n] / denom;
+          mine |= 1ull << itok;
+        }
       }
-      arr[j + 1] = x;
-    }
-  } else {
-    for (int i = 0; i < cstar; ++i) arr[i] = (uint8_t)i;
-  }
-  const bool flex = live && !mass_ok && cstar > k;
-  const bool fixed = live && !flex;
-
-  // ---- tokens whose experts are final ------------------------------------------
-  if (fixed) {
-    float denom = zsum;
-    if (a.renormalize) {
-      denom = p[ord[arr[0]]];
-      for (int j = 1; j < k; ++j) denom = denom + p[ord[arr[j]]];
-    }
-    for (int j = 0; j < k; ++j) {
-      const int e = ord[arr[j]];
-      expert_ids[(size_t)t * k + j] = e;
-      weights[(size_t)t * k + j] = p[e] / denom;
+      if (lane == 0) {
+        ws.rec_cstar[t] = (uint8_t)ncand[n];
+        ws.rec_Z[t] = zsum;
+      }
     }
   }
-  // per expert: the fixed tokens of the tile assigned to it
-  unsigned long long mymask = 0ull;
-  for (int e = 0; e < 64; ++e) {
-    bool has = false;
-    if (fixed)
-      for (int j = 0; j < k; ++j) has = has || (int)ord[arr[j]] == e;
-    const unsigned long long bal = __builtin_amdgcn_ballot_w64(has);
-    if (lane == e) mymask = bal;
-  }
-  maskl[lane] = mymask;
-  ws.tile_fixed_cnt[(size_t)tile * 64 + lane] = (uint8_t)__builtin_popcountll(mymask);
-  ws.tile_mask[(size_t)tile * 64 + lane] = mymask;
-  const unsigned long long fm = __builtin_amdgcn_ballot_w64(flex);
-  if (lane == 0) ws.flexmask[tile] = fm;
-  if (live) {
-    ws.rec_cstar[t] = flex ? (uint8_t)cstar : (uint8_t)0;
-    ws.rec_Z[t] = zsum;
-  }
+  if (mine != 0ull) atomicOr(&maskl[lane], mine);
+  if (lane == 0 && fm != 0ull) atomicOr(&flexl, fm);
   __syncthreads();
-
+  const unsigned long long all = maskl[lane];  // per expert: the fixed tokens of the tile assigned to it
+  fm = scalar64(flexl);
+  if (wave == 0) {
+    ws.tile_fixed_cnt[(size_t)tile * 64 + lane] = (uint8_t)__builtin_popcountll(all);
+    ws.tile_mask[(size_t)tile * 64 + lane] = all;
+    if (lane == 0) ws.flexmask[tile] = fm;
+  }
   // ---- records of the flexible tokens -------------------------------------------
-  if (flex) {
-    const int slot = tile * kTile + __builtin_popcountll(fm & lanes_below(lane));
-    const unsigned long long below = lanes_below(lane);
-    const int cw = a.cw;
-    const bool wide = cw > kMaxC;  // (the wide chain reads the per-expert rows only)
-    // ranks beyond the working set point the chain at a lane that holds no candidate
-    int padlane = E;
-    if (E == 64 && !wide) {
-      unsigned used = 0;
-      for (int j = 0; j < cstar; ++j) {
-        const int e = ord[arr[j]];
-        if (e < 32) used |= 1u << e;
-      }
-      padlane = __builtin_ctz(~used);  // at most 16 of the 32 low experts are candidates
-    }
-    uint16_t* row = ws.rec_lane + (size_t)slot * a.EP;
-    for (int e = 0; e < a.EP; ++e) row[e] = (uint16_t)0xFFFF;
-    for (int j = 0; j < cw; ++j) {
-      const bool in = j < cstar;
-      const int e = in ? (int)ord[arr[j]] : 0;
-      const int pref = in ? __builtin_popcountll(maskl[e] & below) : 0xFF;
-      ws.rec_ids[(size_t)t * cw + j] = (uint8_t)e;
-      ws.rec_p[(size_t)t * cw + j] = in ? p[e] : 0.0f;
-      if (!wide) {
-        ws.rec_cids[(size_t)slot * 16 + j] = (uint8_t)(in ? e : padlane);
-        ws.rec_pref[(size_t)slot * 16 + j] = (uint8_t)pref;
-      }
-      if (in) row[e] = (uint16_t)(wide ? ((pref << 6) | j) : ((pref << 4) | j));
+#pragma unroll
+  for (int n = 0; n < kGeneralTokens; ++n) {
+    if (ncand[n] > 0) {
+      const int itok = wave + n * kGeneralWaves;
+      const bool in = real && ((picked[n] >> rank[n]) & 1ull) != 0ull;
+      write_records(a, ws, tile * kTile + itok, tile * kTile + __builtin_popcountll(fm & lanes_below(itok)), lane, in,
+                    __builtin_popcountll(picked[n] & lanes_below(rank[n])), p[n],
+                    __builtin_popcountll(all & lanes_below(itok)), ncand[n]);
     }
   }
 }
@@ -235,7 +263,9 @@ __global__ __launch_bounds__(64 * kRandomWaves) void analyse_general_kernel(cons
 // records are written again.  Fixed tokens, masks, counts and the flexible-token masks
 // are not touched: none of them depends on which candidates a flexible token has.
 // One workgroup per tile; tiles without such a token cost two loads per lane.
-__global__ __launch_bounds__(64 * kRandomWaves) void random_resample_kernel(const float* __restrict__ logits,
+constexpr int kResampleWaves = 4;
+
+__global__ __launch_bounds__(64 * kResampleWaves) void random_resample_kernel(const float* __restrict__ logits,
                                                              size_t logits_stride, const RouteArgs a0,
                                                              const Workspace ws0, const RandomArgs rnd0) {
   const int prob = blockIdx.y;  // the problem of a batched call; it draws with its own stream id
@@ -244,100 +274,38 @@ __global__ __launch_bounds__(64 * kRandomWaves) void random_resample_kernel(cons
   RandomArgs rnd = rnd0;
   rnd.stream += (uint32_t)prob;
   logits += (size_t)prob * logits_stride;
-  __shared__ float zl[kTile * kRowF];
-  __shared__ uint8_t ordl[kTile * kRowB], arrl[kTile * kRowB];
-  __shared__ unsigned long long maskl[64];
   const int tile = blockIdx.x, lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t = tile * kTile + lane;
-  const bool live = t < a.T;
   const int E = a.E, c = a.c;
   const int32_t* pool = a.pool_in_ws ? ws.pool : a.st_pool;
 
-  const int cst = live ? (int)ws.rec_cstar[t] : 0;
-  const int m = live ? pool[t] : 0;
-  const bool sampled = cst > 0 && m > c;  // (then cst == c)
-  const unsigned long long smask = __builtin_amdgcn_ballot_w64(sampled);  // the same in all four waves
-  if (smask == 0ull) return;
+  // lane = token
+  const bool live = tile * kTile + lane < a.T;
+  const int cst = live ? (int)ws.rec_cstar[tile * kTile + lane] : 0;
+  const int m_lane = live ? pool[tile * kTile + lane] : 0;
+  // (then cst == c)
+  unsigned long long todo = __builtin_amdgcn_ballot_w64(cst > 0 && m_lane > c);  // the same in all four waves
+  if (todo == 0ull) return;
+  const unsigned long long fm = scalar64(ws.flexmask[tile]);
 
-  const int rows = min(kTile, a.T - tile * kTile);
+  // lane = expert; wave w takes the sampled tokens number w, w + 4, ...
+  const bool real = lane < E;
+  const unsigned long long all = ws.tile_mask[(size_t)tile * 64 + lane];
   const float* src = logits + (size_t)tile * kTile * E;
-  for (int idx = threadIdx.x; idx < kTile * E; idx += 64 * kRandomWaves) {
-    const int tok = idx / E;
-    zl[tok * kRowF + (idx - tok * E)] = tok < rows ? src[idx] : 0.0f;
-  }
-  if (wave == 0) maskl[lane] = ws.tile_mask[(size_t)tile * 64 + lane];
-  const unsigned long long fm = ws.flexmask[tile];
-  __syncthreads();
-
-  const float* z = zl + lane * kRowF;
-  uint8_t* ord = ordl + lane * kRowB;  // expert at each position of the score order
-  uint8_t* arr = arrl + lane * kRowB;  // candidate positions
-
-  // ---- order: logit descending, equal logits by lower index (wave w places experts
-  // w, w + 4, ...) -----------------------------------------------------------------
-  if (sampled) {
-    for (int i = wave; i < E; i += kRandomWaves) {
-      const float zi = z[i];
-      int before = 0;
-      for (int j = 0; j < E; ++j) {
-        const float zj = z[j];
-        before += (zj > zi || (zj == zi && j < i)) ? 1 : 0;
-      }
-      ord[before] = (uint8_t)i;
-    }
-  }
-  __syncthreads();
-  if (wave != 0 || !sampled) return;
-  const float zmax = z[ord[0]];
-
-  // ---- the sample: positions in the score order, ascending -----------------------
-  for (int i = 0; i < m; ++i) arr[i] = (uint8_t)i;
-  const unsigned long long g = rnd.token_offset + (unsigned long long)t;
-  uint32_t wv[4] = {0u, 0u, 0u, 0u};
-  for (int i = 0; i < c; ++i) {
-    if ((i & 3) == 0)
-      philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), rnd.stream, (uint32_t)(i >> 2), (uint32_t)rnd.seed,
-                    (uint32_t)(rnd.seed >> 32), wv);
-    const uint32_t r = (i & 3) == 0 ? wv[0] : (i & 3) == 1 ? wv[1] : (i & 3) == 2 ? wv[2] : wv[3];
-    const int j = i + (int)__umulhi(r, (uint32_t)(m - i));
-    const uint8_t tmp = arr[i];
-    arr[i] = arr[j];
-    arr[j] = tmp;
-  }
-  for (int i = 1; i < c; ++i) {  // insertion sort of the first c
-    const uint8_t x = arr[i];
-    int j = i - 1;
-    while (j >= 0 && arr[j] > x) {
-      arr[j + 1] = arr[j];
-      --j;
-    }
-    arr[j + 1] = x;
-  }
-
-  // ---- the token's records, as the analysis writes them --------------------------
-  const int slot = tile * kTile + __builtin_popcountll(fm & lanes_below(lane));
-  const unsigned long long below = lanes_below(lane);
-  int padlane = E;  // ranks beyond the working set point the chain at a lane that holds no candidate
-  if (E == 64) {
-    unsigned used = 0;
-    for (int j = 0; j < c; ++j) {
-      const int e = ord[arr[j]];
-      if (e < 32) used |= 1u << e;
-    }
-    padlane = __builtin_ctz(~used);  // at most 16 of the 32 low experts are candidates
-  }
-  uint16_t* row = ws.rec_lane + (size_t)slot * a.EP;
-  for (int e = 0; e < a.EP; ++e) row[e] = (uint16_t)0xFFFF;
-  for (int j = 0; j < kMaxC; ++j) {
-    const bool in = j < c;
-    const int e = in ? (int)ord[arr[j]] : 0;
-    const int pref = in ? __builtin_popcountll(maskl[e] & below) : 0xFF;
-    ws.rec_ids[(size_t)t * 16 + j] = (uint8_t)e;
-    ws.rec_p[(size_t)t * 16 + j] = in ? exp_fixed(clamp_exp_arg(z[e] - zmax)) : 0.0f;
-    ws.rec_cids[(size_t)slot * 16 + j] = (uint8_t)(in ? e : padlane);
-    ws.rec_pref[(size_t)slot * 16 + j] = (uint8_t)pref;
-    if (in) row[e] = (uint16_t)((pref << 4) | j);
+  for (int n = 0; todo != 0ull; ++n, todo &= todo - 1ull) {
+    if ((n & (kResampleWaves - 1)) != wave) continue;
+    const int itok = __builtin_ctzll(todo), t = tile * kTile + itok;
+    const int m = __builtin_amdgcn_readlane(m_lane, itok);
+    const float z = real ? src[itok * E + lane] : 0.0f;
+    int rank = rank_of(real ? make_key(z, lane) : kPadKey, E);
+    rank = real ? rank : lane;
+    const int best = __builtin_ctzll(__builtin_amdgcn_ballot_w64(real && rank == 0));
+    const float zmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z), best));
+    const unsigned long long picked = sample_positions(rnd, rnd.token_offset + (unsigned long long)t, m, c, lane);
+    const bool in = real && ((picked >> rank) & 1ull) != 0ull;
+    write_records(a, ws, t, tile * kTile + __builtin_popcountll(fm & lanes_below(itok)), lane, in,
+                  __builtin_popcountll(picked & lanes_below(rank)), exp_fixed(clamp_exp_arg(z - zmax)),
+                  __builtin_popcountll(all & lanes_below(itok)), c);
   }
 }
 
@@ -345,7 +313,7 @@ hipError_t launch_random_resample(const float* logits, size_t logits_stride, con
                                   const Workspace& ws, const RandomArgs& rnd, hipStream_t s) {
   if (a.ntiles == 0) return hipSuccess;
   clear_stale_error();
-  hipLaunchKernelGGL(random_resample_kernel, dim3(a.ntiles, a.nbatch), dim3(64 * kRandomWaves), 0, s, logits,
+  hipLaunchKernelGGL(random_resample_kernel, dim3(a.ntiles, a.nbatch), dim3(64 * kResampleWaves), 0, s, logits,
                      logits_stride, a, ws, rnd);
   return hipGetLastError();
 }
@@ -356,10 +324,10 @@ hipError_t launch_analyse_general(const float* logits, size_t logits_stride, con
   if (a.ntiles == 0) return hipSuccess;
   clear_stale_error();
   if (sample)
-    hipLaunchKernelGGL(analyse_general_kernel<true>, dim3(a.ntiles, a.nbatch), dim3(64 * kRandomWaves), 0, s,
+    hipLaunchKernelGGL(analyse_general_kernel<true>, dim3(a.ntiles, a.nbatch), dim3(64 * kGeneralWaves), 0, s,
                        logits, logits_stride, a, ws, rnd, expert_ids, weights);
   else
-    hipLaunchKernelGGL(analyse_general_kernel<false>, dim3(a.ntiles, a.nbatch), dim3(64 * kRandomWaves), 0, s,
+    hipLaunchKernelGGL(analyse_general_kernel<false>, dim3(a.ntiles, a.nbatch), dim3(64 * kGeneralWaves), 0, s,
                        logits, logits_stride, a, ws, rnd, expert_ids, weights);
   return hipGetLastError();
 }
