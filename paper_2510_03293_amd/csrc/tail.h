@@ -230,22 +230,16 @@ __device__ __forceinline__ unsigned chain_step_wide(unsigned load, unsigned rank
 // one every 4.2 to 5 cycles, an LDS lane exchange takes 57 (measured at 2.4 GHz), so the step is
 // built to have few of both on the path from one token's choice to the next one's.
 //
-// Up to 8 candidates: all pairs at once.  The keys of the candidates are gathered from the
-// lanes of their experts twice, by rank i = lane / 8 and by rank j = lane % 8 (two exchanges in
-// flight together); one compare then leaves the 8 x 8 matrix "key j < key i" in a scalar
-// register pair, and a lane that holds the candidate of rank r counts the bits of byte r: it is
-// chosen iff there are fewer than k.  Reading the eight keys into scalar registers and comparing
-// with one after the other took 170 ns per token (16384 tokens, 64 experts, k = 6, c = 8); now
-// 69, of which the bare chain of dependent instructions is 55.
-// Up to 16 candidates: lane 16 q + i compares the key of rank i with those of ranks 4 q .. 4 q + 3
-// and the four quarters are added across the wavefront (c = 16: 258 -> 132 ns).
+// Up to 8 candidates: chain_walk_pairs and chain_walk_lag, further down.
+// Up to 16 candidates: the keys of the candidates are gathered from the lanes of their experts;
+// lane 16 q + i compares the key of rank i with those of ranks 4 q .. 4 q + 3 and the four quarters
+// are added across the wavefront (c = 16: 258 -> 132 ns per token).
 constexpr int kSeqBatch = 96;  // flexible tokens per LDS batch (whole output words)
 struct SeqTok {
   unsigned rec[64];   // per expert: (counter without flexible choices) << 4 | rank, or kSeqNoCand
   uint8_t addr[16];   // per rank: 4 * the candidate's lane (padded with a lane that holds none)
 };
-// (compares above every key; byte selector 13 of v_perm reads as 0xFF, a count of 8)
-constexpr unsigned kSeqNoCand = 0x8000000Du;
+constexpr unsigned kSeqNoCand = 0x8000000Du;  // (compares above every key)
 static_assert((2 * kSeqBatch + 1) * (int)sizeof(SeqTok) <= kChainLdsBytes, "two batches and a token of read-ahead");
 
 // Wide calls (up to 64 candidates).
@@ -323,7 +317,7 @@ __device__ __forceinline__ void seq_store(typename SeqTraits<CP>::Tok* dst, cons
 
 // Walks the flexible tokens from token `f0` of the call on.  `hist0`: the bits of output word
 // f0 / 32 that are decided already.  The output (chain_bits, chain_cum) is indexed by the
-// flexible token's number within the call.  CP: 8 or 16 candidates, 0: a wide call.
+// flexible token's number within the call.  CP: 16 candidates, 0: a wide call.
 template <int CP>
 __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
                                            const Workspace& ws, int wave, int lane, int lin, int& gflex) {
@@ -375,11 +369,11 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
       const int n = min(NB, nflex_tok - b * NB);
       int r = f - b * NB;
       if constexpr (CP != 0) {
-        constexpr int kPer = CP == 8 ? 1 : 4;  // keys a lane compares with
+        constexpr int kPer = 4;  // keys a lane compares with
         unsigned rec = cur[r].rec[lane];
-        unsigned ai = cur[r].addr[CP == 8 ? lane >> 3 : lane & 15], aj[kPer];
+        unsigned ai = cur[r].addr[lane & 15], aj[kPer];
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) aj[u] = cur[r].addr[CP == 8 ? lane & 7 : 4 * (lane >> 4) + u];
+        for (int u = 0; u < kPer; ++u) aj[u] = cur[r].addr[4 * (lane >> 4) + u];
         // (the next token's record is read while this one is decided; behind the last one of a
         // batch it is read and not used)
         auto step = [&](const Tok& next) {
@@ -390,26 +384,18 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
           for (int u = 0; u < kPer; ++u) kj[u] = (unsigned)__builtin_amdgcn_ds_bpermute((int)aj[u], (int)key);
           __builtin_amdgcn_sched_barrier(0);
           const unsigned rec_n = next.rec[lane];
-          const unsigned ai_n = next.addr[CP == 8 ? lane >> 3 : lane & 15];
+          const unsigned ai_n = next.addr[lane & 15];
           unsigned aj_n[kPer];
 #pragma unroll
-          for (int u = 0; u < kPer; ++u) aj_n[u] = next.addr[CP == 8 ? lane & 7 : 4 * (lane >> 4) + u];
+          for (int u = 0; u < kPer; ++u) aj_n[u] = next.addr[4 * (lane >> 4) + u];
           __builtin_amdgcn_sched_barrier(0);
-          bool chosen;
-          if constexpr (CP == 8) {
-            const unsigned sel = (rec & 15u) | 0x0C0C0C00u;
-            const unsigned long long less = __builtin_amdgcn_ballot_w64(kj[0] < ki);
-            const unsigned row = __builtin_amdgcn_perm((unsigned)(less >> 32), (unsigned)less, sel);
-            chosen = (unsigned)__builtin_popcount(row) < k;
-          } else {
-            const unsigned shift = (rec & 15u) | ((rec >> 27) & 16u);  // (no candidate: a bit that is not set)
-            unsigned cnt = 0;
+          const unsigned shift = (rec & 15u) | ((rec >> 27) & 16u);  // (no candidate: a bit that is not set)
+          unsigned cnt = 0;
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) cnt += kj[u] < ki ? 1u : 0u;
-            cnt = add_quarters(cnt);
-            const unsigned won = (unsigned)__builtin_amdgcn_ballot_w64(cnt < k) & 0xFFFFu;
-            chosen = ((won >> shift) & 1u) != 0u;
-          }
+          for (int u = 0; u < kPer; ++u) cnt += kj[u] < ki ? 1u : 0u;
+          cnt = add_quarters(cnt);
+          const unsigned won = (unsigned)__builtin_amdgcn_ballot_w64(cnt < k) & 0xFFFFu;
+          const bool chosen = ((won >> shift) & 1u) != 0u;
           G += chosen ? 1u : 0u;
           hist = hist + hist + (chosen ? 1u : 0u);
           rec = rec_n;
@@ -468,6 +454,411 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
     gflex = (int)G;
     if ((f & 31) != 0)
       ws.chain_bits[(size_t)(f >> 5) * 64 + lane] = __builtin_bitreverse32(hist) >> (32 - (f & 31));
+  }
+}
+
+// ---- walks of up to 8 candidates --------------------------------------------------------
+//
+// All pairs of candidates at once.  Candidate j is before candidate i exactly if
+//     G[j] - G[i] <= U,
+// with G the flexible choices so far and U a number that the counters without them and the ranks
+// give beforehand.  There are 28 pairs i < j, one per lane; the comparison leaves them as bits in a
+// scalar register, and the number of candidates before any one of them is a bit count: of its
+// pairs' bits, those flipped in which it is the second one.  It is chosen iff there are fewer
+// than k.  A lone wavefront issues a vector instruction every 4.2 to 4.7 cycles, whether it needs
+// the result of the one before or not (measured, 2.4 GHz); a lane exchange through LDS takes 56,
+// and a vector instruction that reads the scalar of the comparison before it waits for two
+// others in between.  So what counts is the number of instructions, that none waits for an
+// exchange, and that other work stands behind the comparisons.
+
+// The pair of this lane (lanes 28 and up: 0, 0).
+__device__ __forceinline__ void lane_pair(int lane, int& i, int& j) {
+  int rest = lane;
+  i = 0;
+  while (i < 7 && rest >= 7 - i) {
+    rest -= 7 - i;
+    ++i;
+  }
+  j = i + 1 + rest;
+  if (lane >= 28) i = j = 0;
+}
+// How many are before number e: the bits of (pairs ^ flip) & mask.
+struct PairCount {
+  unsigned flip, mask;
+};
+__device__ __forceinline__ PairCount pair_count(int e, int i, int j, int lane) {
+  PairCount c = {0u, 0u};
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    const unsigned second = (unsigned)__builtin_amdgcn_ballot_w64(lane < 28 && j == n);
+    const unsigned first = (unsigned)__builtin_amdgcn_ballot_w64(lane < 28 && i == n);
+    c.flip = e == n ? second : c.flip;
+    c.mask = e == n ? first | second : c.mask;
+  }
+  return c;
+}
+__device__ __forceinline__ int count_before(unsigned pairs, const PairCount& c, int start) {
+  // (the instruction adds as well; the compiler would make an instruction of its own of it)
+  int n;
+  asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(n) : "v"((pairs ^ c.flip) & c.mask), "v"(start));
+  return n;
+}
+// U of a pair with the keys ki, kj ((counter << 4) + rank, below 2^31; negative: no candidate):
+// kj + 16 G[j] < ki + 16 G[i].  Who is no candidate is behind every candidate, of which there
+// are more than k.
+__device__ __forceinline__ int pair_bound(int ki, int kj) {
+  constexpr int kBeyond = 1 << 30;  // (every difference of the choices)
+  const int u = (ki + ~kj) >> 4;
+  return kj < 0 ? -kBeyond : ki < 0 ? kBeyond : u;
+}
+
+// More than 8 experts.  A pair is one of ranks, and G lives in the lanes of the experts: the
+// difference would have to be exchanged for every token on the path from one choice to the
+// next.  Instead it is gathered a token early, before the choice of the token in between
+// is known; that one enters as two bits of W, the mask of its chosen ranks: whether ci, and
+// whether cj, was among them, at places that are known beforehand.
+// All of that is prepared by waves 1 and 2, 16 tokens at a time in an LDS ring of three such
+// batches (the consumer looks four tokens ahead, so the batch behind the current one is complete
+// before the current one is begun).
+// What bounds the step: 16 vector instructions, four LDS instructions -- a lane exchange keeps the
+// wavefront from issuing for about 15 cycles --, waits; 105 cycles, and 9 of the batch's barrier.
+// (A scalar move that reads the comparison's result costs 16 more.)
+// 16384 tokens, 64 experts, k = 6, c = 8: 69 -> 53 ns per token, the call
+// 1156 -> 878 us (1.15 -> 0.85 ms of it the walk).
+constexpr int kLagBatch = 16;
+struct LagTok {
+  int4 v[32];  // per pair: U; 4 * lane of ci; 4 * lane of cj; their places in the W of the token
+};             // before, a byte each
+constexpr unsigned kLagNone = 15;  // (a bit of W that is never set)
+// Per expert its place in the token's W: rows of 64 bytes, for each of the two producers of a batch
+// that of the token before its eight and theirs.
+constexpr int kLagPlaceRows = 9;
+constexpr int kLagPlaceOffset = 3 * kLagBatch * (int)sizeof(LagTok);
+static_assert(kLagPlaceOffset + 3 * 2 * kLagPlaceRows * 64 <= kChainLdsBytes, "ring of three batches");
+
+// The loads of the producers have no conditions (any token of the call stands in for none): those
+// stay in flight where one behind a branch would be waited for at its end.
+__device__ __forceinline__ int lag_slot(int f, int nflex_tok, const Workspace& ws) {
+  return ws.flex_slot[min(max(f, 0), nflex_tok - 1)];
+}
+
+// What a producer needs of its eight tokens, lane (s, r) = (lane / 8, lane % 8): candidate of
+// rank r of token s.
+struct LagCand {
+  unsigned cid, pref;
+  unsigned cid_before;  // candidate of rank r of the token before the eight
+  int base;             // assignments in the tiles before the token's
+};
+// f: number of the first of the eight; at_i, at_j: see below.
+__device__ __forceinline__ void lag_store(LagTok* dst, uint8_t* places, const LagCand& c, int f, int f0, int nflex_tok,
+                                          int lane, int at_i, int at_j, int lin) {
+  const int tok = f + (lane >> 3), r = lane & 7;
+  const bool live = tok >= f0 && tok < nflex_tok;
+  // ---- the places: rank of the expert, or none ----------------------------------------
+  constexpr unsigned kNone4 = kLagNone * 0x01010101u;
+  reinterpret_cast<uint2*>(places)[lane] = make_uint2(kNone4, kNone4);
+  if (lane < 16) reinterpret_cast<unsigned*>(places)[128 + lane] = kNone4;
+  asm volatile("" ::: "memory");  // (a wavefront's LDS traffic stays in order)
+  // (ranks beyond the working set share a lane that holds no candidate; their bits of W are 0)
+  if (live) places[(1 + (lane >> 3)) * 64 + c.cid] = (uint8_t)r;
+  if (lane < 8 && f > f0 && f <= nflex_tok) places[c.cid_before] = (uint8_t)r;
+  asm volatile("" ::: "memory");
+  // ---- the pairs, lane (h, p) = (lane / 32, lane % 32): pair p of tokens 2 q + h ---------------
+  const int before = c.base + __builtin_amdgcn_ds_bpermute(4 * (int)c.cid, lin) + (int)c.pref;
+  const int key = (c.pref != 0xFFu && live) ? (before << 4) + r : -1;
+  int ci[4], cj[4], ki[4], kj[4], wi[4], wj[4];  // (all exchanges in flight together)
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    ci[q] = __builtin_amdgcn_ds_bpermute(at_i + 64 * q, (int)c.cid);
+    cj[q] = __builtin_amdgcn_ds_bpermute(at_j + 64 * q, (int)c.cid);
+    ki[q] = __builtin_amdgcn_ds_bpermute(at_i + 64 * q, key);
+    kj[q] = __builtin_amdgcn_ds_bpermute(at_j + 64 * q, key);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const int h = lane >> 5;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    wi[q] = places[(2 * q + h) * 64 + ci[q]];
+    wj[q] = places[(2 * q + h) * 64 + cj[q]];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    dst[2 * q + h].v[lane & 31] = make_int4(pair_bound(ki[q], kj[q]), 4 * ci[q], 4 * cj[q], wi[q] | (wj[q] << 8));
+}
+
+__device__ __forceinline__ void chain_walk_lag(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
+                                               const Workspace& ws, int wave, int lane, int lin, int& gflex) {
+  LagTok* const ring = reinterpret_cast<LagTok*>(lds);
+  uint8_t* const places = lds + kLagPlaceOffset;
+  f0 = __builtin_amdgcn_readfirstlane(f0);
+  nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
+  const int b0 = f0 / kLagBatch, b1 = (nflex_tok + kLagBatch - 1) / kLagBatch;
+  int pi, pj;
+  lane_pair(lane & 31, pi, pj);
+  if (wave == 1 || wave == 2) {
+    // ---- producers: two batches ahead of the consumer in LDS, and two more with every load that
+    // leads to another one -- where the records are, the records, the counters of the candidates
+    // (the barriers leave loads in flight alone) ----
+    const int pw = wave - 1, tok = 8 * pw + (lane >> 3);
+    const int at_i = 32 * (lane >> 5) + 4 * pi, at_j = 32 * (lane >> 5) + 4 * pj;
+    struct Slots {
+      int own, before;
+    };
+    auto slot_of = [&](int n) {
+      return Slots{lag_slot(n * kLagBatch + tok, nflex_tok, ws), lag_slot(n * kLagBatch + 8 * pw - 1, nflex_tok, ws)};
+    };
+    auto records = [&](LagCand& c, const Slots& s) {
+      c.cid = ws.rec_cids[(size_t)s.own * 16 + (lane & 7)];
+      c.pref = ws.rec_pref[(size_t)s.own * 16 + (lane & 7)];
+      c.cid_before = ws.rec_cids[(size_t)s.before * 16 + (lane & 7)];
+      c.base = s.own >> 6;  // (the tile, until the counter is loaded)
+    };
+    auto counter = [&](LagCand& c, const LagCand& r) {
+      c.cid = r.cid;
+      c.pref = r.pref;
+      c.cid_before = r.cid_before;
+      c.base = ws.tile_base[(size_t)r.base * 64 + r.cid];
+    };
+    Slots s0 = slot_of(b0), s1 = slot_of(b0 + 1);
+    LagCand r0, r1, c0, c1;
+    records(r0, s0);
+    records(r1, s1);
+    s0 = slot_of(b0 + 2);
+    s1 = slot_of(b0 + 3);
+    counter(c0, r0);
+    counter(c1, r1);
+    records(r0, s0);
+    records(r1, s1);
+    s0 = slot_of(b0 + 4);
+    s1 = slot_of(b0 + 5);
+    int buf = 0;  // of batch n
+    auto fill = [&](int n, LagCand& c, LagCand& r, Slots& s) {
+      lag_store(ring + buf * kLagBatch + 8 * pw, places + (2 * buf + pw) * kLagPlaceRows * 64, c, n * kLagBatch + 8 * pw, f0,
+                nflex_tok, lane, at_i, at_j, lin);
+      buf = buf == 2 ? 0 : buf + 1;
+      counter(c, r);
+      records(r, s);
+      s = slot_of(n + 6);
+    };
+    fill(b0, c0, r0, s0);
+    fill(b0 + 1, c1, r1, s1);
+    lds_barrier();
+    // (what is filled behind the last batch is not read)
+    for (int b = b0; b < b1; b += 2) {
+      fill(b + 2, c0, r0, s0);
+      lds_barrier();
+      if (b + 1 >= b1) break;
+      fill(b + 3, c1, r1, s1);
+      lds_barrier();
+    }
+  } else if (wave != 0) {
+    lds_barrier();
+    for (int b = b0; b < b1; ++b) lds_barrier();
+  } else {
+    // ---- consumer ----------------------------------------------------------------------
+    int G = gflex;
+    unsigned hist = 0;  // the choices of the output word's tokens so far, the last one lowest
+    const int k = a.k;
+    // lane r < 8 counts for rank r; the others' bits of W stay 0
+    const PairCount rank = pair_count(lane, pi, pj, lane);
+    const int pair = lane & 31;
+    const int start = lane < 8 ? 0 : 64;
+    auto gather = [&](int from) { return __builtin_amdgcn_ds_bpermute(from, G); };
+    lds_barrier();
+    const LagTok* cur = ring;
+    const uint8_t* cur_places = places + lane;  // row of the batch's token 0
+    auto row = [](int u) { return ((u >> 3) * kLagPlaceRows + 1 + (u & 7)) * 64; };
+    const LagTok* const ring_end = ring + 3 * kLagBatch;
+    int4 d0 = cur[0].v[pair], d1 = cur[1].v[pair], d2 = cur[2].v[pair], d3 = cur[3].v[pair];
+    unsigned place = cur_places[row(0)], place1 = cur_places[row(1)];
+    int i1 = gather(d1.y), j1 = gather(d1.z);
+    // (the choice before the first token is in G)
+    int diff = gather(d0.z) - gather(d0.y);
+    unsigned chosen = 0u;  // (lane = expert: of the token before)
+    for (int b = b0; b < b1; ++b) {
+      const bool wrap = cur + kLagBatch == ring_end;
+      const LagTok* const next = wrap ? ring : cur + kLagBatch;
+      const uint8_t* const next_places = wrap ? places + lane : cur_places + 2 * kLagPlaceRows * 64;
+#pragma unroll
+      for (int u = 0; u < kLagBatch; ++u) {
+        // From the difference to W and the choice of the lane's expert, in assembly because the
+        // order is the point: what is read out of a comparison's scalar must be two instructions
+        // behind it, and these do something.
+        unsigned next_j;
+        unsigned long long won;
+        asm("v_cmp_le_i32 vcc, %[diff], %[U]\n\t"
+            "v_lshl_or_b32 %[hist], %[hist], 1, %[chosen]\n\t"  // (the token before)
+            "v_lshrrev_b32 %[nj], 8, %[w1]\n\t"
+            "v_bitop3_b32 %[diff], %[flip], %[mask], vcc_lo bitop3:0x48\n\t"  // (pairs ^ flip) & mask
+            "v_bcnt_u32_b32 %[diff], %[diff], %[start]\n\t"
+            "v_cmp_gt_i32 s[98:99], %[k], %[diff]\n\t"
+            : [diff] "+v"(diff), [hist] "+v"(hist), [nj] "=&v"(next_j), [won] "={s[98:99]}"(won)
+            : [chosen] "v"(chosen), [U] "v"(d0.x), [w1] "v"(d1.w), [flip] "v"(rank.flip), [mask] "v"(rank.mask),
+              [start] "v"(start), [k] "s"(k)
+            : "vcc");
+        // (two blocks, so that the difference gathered for the next token is waited for here only)
+        asm("v_sub_u32 %[diff], %[j1], %[i1]\n\t"
+            "s_nop 0\n\t"
+            "v_bfe_u32 %[chosen], s98, %[place], 1\n\t"
+            "v_add_u32 %[G], %[G], %[chosen]\n\t"
+            : [diff] "=&v"(diff), [chosen] "=&v"(chosen), [G] "+v"(G)
+            : [i1] "v"(i1), [j1] "v"(j1), [place] "v"(place), [won] "{s[98:99]}"(won));
+        // (a scalar instruction that read it would wait for 16 cycles)
+        const unsigned W = (unsigned)won;
+        const int i2 = gather(d2.y), j2 = gather(d2.z);
+        __builtin_amdgcn_sched_barrier(0);
+        const int next_chose_i = (int)__builtin_amdgcn_sbfe((int)W, (unsigned)d1.w, 1);
+        const int next_chose_j = (int)__builtin_amdgcn_ubfe(W, next_j, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        diff = diff + next_chose_i + next_chose_j;
+        place = place1;
+        place1 = u + 2 < kLagBatch ? cur_places[row(u + 2)] : next_places[row(u + 2 - kLagBatch)];
+        i1 = i2;
+        j1 = j2;
+        d0 = d1;
+        d1 = d2;
+        d2 = d3;
+        // (behind the last token of the call: read and not used)
+        d3 = u + 4 < kLagBatch ? cur[u + 4].v[pair] : next[u + 4 - kLagBatch].v[pair];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const int w = b >> 1;
+      if ((b & 1) != 0 || b + 1 == b1) {
+        hist = (hist << 1) | chosen;
+        if ((b & 1) == 0) hist <<= kLagBatch;
+        const unsigned word = __builtin_bitreverse32(hist) | (w == (f0 >> 5) ? hist0 : 0u);
+        ws.chain_bits[(size_t)w * 64 + lane] = word;
+        if (32 * (w + 1) <= nflex_tok) ws.chain_cum[(size_t)(w + 1) * 64 + lane] = G;
+        hist = chosen = 0u;
+      }
+      cur = next;
+      cur_places = next_places;
+      lds_barrier();
+    }
+    gflex = G;
+  }
+}
+
+// Up to 8 experts (all of a call's flexible tokens).  A pair is one of experts: the lane itself
+// keeps the difference of their choices, counts for both and adds (j chosen) - (i chosen); nothing
+// is exchanged at all, nine instructions per token.  Lanes 28 to 35 count for one expert each,
+// for the output.
+// Waves 1 to 3 prepare U, eight tokens per memory instruction, 96 tokens per batch.
+// 8 experts, k = 2, c = 4: 21 ns per token (the window evaluation took 50: four layers of 16384 tokens,
+// a tenth of them load-dependent, 471 -> 322 us).
+constexpr int kPairBatch = 96;  // tokens per LDS batch: 32 per producer wave
+struct PairGroup {
+  int4 v[64];  // U of four tokens
+};
+static_assert((2 * (kPairBatch / 4) + 1) * (int)sizeof(PairGroup) <= kChainLdsBytes, "two batches and a group of read-ahead");
+
+__device__ __forceinline__ void chain_walk_pairs(uint8_t* lds, int nflex_tok, const Workspace& ws, int k, int wave,
+                                                 int lane, int lin, int& gflex) {
+  PairGroup* const buf = reinterpret_cast<PairGroup*>(lds);
+  constexpr int kGroups = kPairBatch / 4;
+  nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
+  const int nb = (nflex_tok + kPairBatch - 1) / kPairBatch;
+  int pi, pj;
+  lane_pair(lane, pi, pj);
+  if (wave != 0) {
+    // ---- producers: lane (s, e): token s of eight, expert e -------------------------------
+    const int pw = wave - 1;
+    const int lin_e = __builtin_amdgcn_ds_bpermute(4 * (lane & 7), lin);
+    int slot[4], base[4];
+    unsigned rec[4];
+    auto first = [&](int n, int r) { return n * kPairBatch + 32 * pw + 8 * r; };
+    auto load_slots = [&](int n) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) slot[r] = lag_slot(first(n, r) + (lane >> 3), nflex_tok, ws);
+    };
+    auto load_records = [&]() {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        rec[r] = ws.rec_lane[(size_t)slot[r] * 8 + (lane & 7)];
+        base[r] = ws.tile_base[(size_t)(slot[r] >> 6) * 64 + (lane & 7)];
+      }
+    };
+    auto store = [&](int n) {
+      int* dst = reinterpret_cast<int*>(buf + (n & 1) * kGroups + 8 * pw) + 4 * lane;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        // (tokens behind the last one: whatever comes out, their bits are not taken)
+        const int key = rec[r] != 0xFFFFu ? ((lin_e + base[r]) << 4) + (int)rec[r] : -1;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const int ki = __builtin_amdgcn_ds_bpermute(4 * (8 * s + pi), key);
+          const int kj = __builtin_amdgcn_ds_bpermute(4 * (8 * s + pj), key);
+          dst[(2 * r + (s >> 2)) * 256 + (s & 3)] = pair_bound(ki, kj);
+        }
+      }
+    };
+    load_slots(0);
+    load_records();
+    load_slots(1);
+    store(0);
+    load_records();
+    load_slots(2);
+    lds_barrier();
+    for (int n = 0; n < nb; ++n) {
+      store(n + 1);  // (behind the last batch: not read)
+      load_records();
+      load_slots(n + 3);
+      lds_barrier();
+    }
+  } else {
+    // ---- consumer ----------------------------------------------------------------------
+    int D = 0, G = 0;  // (G: of the output lane's expert)
+    const bool output = lane >= 28 && lane < 36;
+    const PairCount count_i = pair_count(output ? lane - 28 : pi, pi, pj, lane), count_j = pair_count(pj, pi, pj, lane);
+    const int minus_k = -k;
+    unsigned hist = 0;
+    int ci = 0, cj;
+    // (in assembly for the order, see chain_walk_lag; the counts, of which byte 3 is the sign, are
+    // added to D as they are)
+#define LASER_PAIR_STEP(U_)                                                                      \
+  "v_cmp_le_i32 vcc, %[D], " U_ "\n\t"                                                  \
+  "v_alignbit_b32 %[hist], %[hist], %[ci], 31\n\t" /* (the token before) */                     \
+  "s_nop 0\n\t"                                                                                 \
+  "v_bitop3_b32 %[ci], %[fi], %[mi], vcc_lo bitop3:0x48\n\t" /* (pairs ^ flip) & mask */     \
+  "v_bitop3_b32 %[cj], %[fj], %[mj], vcc_lo bitop3:0x48\n\t"                                 \
+  "v_bcnt_u32_b32 %[ci], %[ci], %[mk]\n\t" /* (negative: chosen) */                             \
+  "v_bcnt_u32_b32 %[cj], %[cj], %[mk]\n\t"                                                      \
+  "v_add_u32_sdwa %[D], %[D], sext(%[ci]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3\n\t" \
+  "v_sub_u32_sdwa %[D], %[D], sext(%[cj]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3\n\t"
+    auto steps = [&](const int4& x) {
+      asm(LASER_PAIR_STEP("%[x0]") LASER_PAIR_STEP("%[x1]") LASER_PAIR_STEP("%[x2]") LASER_PAIR_STEP("%[x3]")
+          : [D] "+v"(D), [hist] "+v"(hist), [ci] "+v"(ci), [cj] "=&v"(cj)
+          : [x0] "v"(x.x), [x1] "v"(x.y), [x2] "v"(x.z), [x3] "v"(x.w), [fi] "v"(count_i.flip), [mi] "v"(count_i.mask),
+            [fj] "v"(count_j.flip), [mj] "v"(count_j.mask), [mk] "s"(minus_k)
+          : "vcc");
+    };
+#undef LASER_PAIR_STEP
+    lds_barrier();
+    for (int n = 0; n < nb; ++n) {
+      const PairGroup* cur = buf + (n & 1) * kGroups;
+      int4 x = cur->v[lane];
+      for (int f = n * kPairBatch; f < min(nflex_tok, (n + 1) * kPairBatch); f += 32) {
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+          ++cur;
+          const int4 x_n = cur->v[lane];  // (behind the last group of a batch: read and not used)
+          steps(x);
+          x = x_n;
+        }
+        // (32 bits went in, the first of them the last one of the word before, or nothing)
+        const unsigned all = __builtin_amdgcn_alignbit(hist, (unsigned)ci, 31);
+        const int left = nflex_tok - f;
+        const unsigned word = output ? __builtin_bitreverse32(all) & (left < 32 ? (1u << left) - 1u : ~0u) : 0u;
+        G += __builtin_popcount(word);
+        const size_t at = (size_t)(f >> 5) * 64 + ((lane + 36) & 63);  // (lane 28: expert 0)
+        ws.chain_bits[at] = word;
+        if (left >= 32) ws.chain_cum[at + 64] = G;
+      }
+      lds_barrier();
+    }
+    gflex = __builtin_amdgcn_ds_bpermute(4 * (28 + (lane & 7)), G);
+    gflex = lane < 8 ? gflex : 0;
   }
 }
 
@@ -603,13 +994,9 @@ __device__ __forceinline__ unsigned long long rotr64(unsigned long long x, int s
 }
 
 // Producer: tokens seg*192 + half*64 + lane of the call -> ring (half = 0, 1, 2).
-// Bit 31 of a counter marks the rank as part of the token's first tentative choice: the
-// k least loaded candidates by the counters without any flexible choice.  Any first
-// guess gives the same final result; a good one saves the sweep a token otherwise
-// needs only to get a tentative choice, and lets the tokens behind it retire with it.
-template <int CP, int KK, bool GUESS>
+template <int CP, int KK>
 __device__ __forceinline__ void spec_fill(SpecTok<CP>* ring, int seg, int half, int nflex_tok, const Workspace& ws,
-                          const int* lin_tab, int lane, int k) {
+                          const int* lin_tab, int lane) {
   const int f = seg * kSpecSeg + half * 64 + lane;
   if (f >= nflex_tok) return;
   const int slot = ws.flex_slot[f];
@@ -626,16 +1013,11 @@ __device__ __forceinline__ void spec_fill(SpecTok<CP>* ring, int seg, int half, 
     const int e = (idw[j >> 2] >> (8 * (j & 3))) & 255;
     base[j] = ws.tile_base[(size_t)tile * 64 + e] + lin_tab[e];
   }
-  unsigned bj[CP], key[CP];
 #pragma unroll
   for (int j = 0; j < CP; ++j) {
     const unsigned pf = (pfw[j >> 2] >> (8 * (j & 3))) & 255u;
-    bj[j] = pf == 0xFFu ? kSpecInvalid : (unsigned)base[j] + pf;
-    key[j] = (bj[j] << 4) | (unsigned)j;
+    dst->b[j] = pf == 0xFFu ? kSpecInvalid : (unsigned)base[j] + pf;
   }
-  const unsigned guess = GUESS ? smallest_k_slots<CP, KK>(key, k) : 0u;
-#pragma unroll
-  for (int j = 0; j < CP; ++j) dst->b[j] = bj[j] | (((guess >> j) & 1u) << 31);
 }
 
 // Runs the window evaluation from flexible token 0.  All four waves call it.  Returns
@@ -649,7 +1031,7 @@ struct SpecShared {
   int sh_done[2], sh_bail[2];  // by segment parity: written before, read after a barrier
 };
 
-template <int CP, int KK, bool GUESS>
+template <int CP, int KK>
 __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex_tok, const RouteArgs& a,
                          const Workspace& ws, int wave, int lane, int lin, int& gflex, unsigned& hist) {
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
@@ -667,8 +1049,8 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
   __syncthreads();
   const bool producer = wave != 0;
   if (producer) {
-    spec_fill<CP, KK, GUESS>(ring, 0, wave - 1, nflex_tok, ws, lin_tab, lane, k);
-    spec_fill<CP, KK, GUESS>(ring, 1, wave - 1, nflex_tok, ws, lin_tab, lane, k);
+    spec_fill<CP, KK>(ring, 0, wave - 1, nflex_tok, ws, lin_tab, lane);
+    spec_fill<CP, KK>(ring, 1, wave - 1, nflex_tok, ws, lin_tab, lane);
   }
   __syncthreads();
 
@@ -689,17 +1071,13 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
   int pn = 0, w = 0, gflushed = 0;
   int sweeps = 0, done_mark = 0, total_sweeps = 0;
   bool bail = false;
-  // First guesses pay where whole windows retire at once (tokens that rarely compete);
-  // where a sweep ends at an early conflict anyway they only add their insertion.  They
-  // are used while the last run of sweeps retired more than kSpecGuessProgress tokens.
-  bool guess_on = GUESS;
   int decided = 0;
   const unsigned long long lb = lanes_below(lane);
 
   const int nep = (nflex_tok + kSpecSeg - 1) / kSpecSeg;
   for (int ep = 0; ep < nep; ++ep) {
     if (producer) {
-      spec_fill<CP, KK, GUESS>(ring, ep + 2, wave - 1, nflex_tok, ws, lin_tab, lane, k);
+      spec_fill<CP, KK>(ring, ep + 2, wave - 1, nflex_tok, ws, lin_tab, lane);
     } else {
       const int avail = min(nflex_tok, (ep + 2) * kSpecSeg);
       const int target = min(nflex_tok, (ep + 1) * kSpecSeg);
@@ -718,27 +1096,12 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
 #pragma unroll
           for (int j = 0; j < CP; ++j) {
             ex[j] = (idw[j >> 2] >> (8 * (j & 3))) & 255;
-            b[j] = src->b[j];  // (bit 31, the guess, drops out of the key's shift below)
-          }
-          if (GUESS && guess_on) {
-#pragma unroll
-            for (int j = 0; j < CP; ++j) sel |= (b[j] >> 31) << j;  // the producer's first guess
+            b[j] = src->b[j];
           }
           cur_f = f_lane;
         }
         const bool valid = cur_f == f_lane;
         if (!valid) sel = 0;
-        if (GUESS && guess_on && __builtin_amdgcn_ballot_w64(enters) != 0ull) {
-          // the guesses join the masks before anybody counts (the lane's bit is clear:
-          // the token that held the lane took its bits along when it retired)
-          if (enters) {
-#pragma unroll
-            for (int j = 0; j < CP; ++j)
-              if ((sel >> j) & 1u) flip_lane_bit(&M[ex[j]].mask, lane);
-          }
-          lds_wave_fence();
-          __builtin_amdgcn_wave_barrier();
-        }
         const unsigned long long hb = lanes_below(head);
         const unsigned long long earlier = lane >= head ? (lb & ~hb) : (~hb | lb);
         unsigned key[CP];
@@ -763,34 +1126,28 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
         // tokens up to the first changed one are final
         const unsigned long long rot = rotr64(bal, head);
         const int q = rot ? __builtin_ctzll(rot) : 64;
-        // (without guesses more than 32 is rare: a token needs a sweep to get a choice)
-        const int fin = min(min(q + 1, avail - done), GUESS ? 64 : 32);
+        // (more than 32 is rare: a token needs a sweep to get a choice)
+        const int fin = min(min(q + 1, avail - done), 32);
         lds_wave_fence();
         __builtin_amdgcn_wave_barrier();
         {  // lane = expert
           unsigned long long mk = M[lane].mask;
-          // tokens done + off .. + part - 1 (part <= 32: what the output takes at a time)
-          auto retire = [&](int off, int part) {
-            const int h2 = (head + off) & 63;
-            const unsigned long long finmask = rotl64((1ull << part) - 1ull, h2);
-            const unsigned long long fbits = mk & finmask;
-            G += __builtin_popcountll(fbits);
-            mk &= ~finmask;
-            const unsigned ob = (unsigned)rotr64(fbits, h2);  // bit i: token done + off + i
-            pend |= (unsigned long long)ob << pn;             // pn < 32 bits were held
-            pn += part;
-            if (pn >= 32) {
-              const unsigned word = (unsigned)pend;
-              gflushed += __builtin_popcount(word);
-              ws.chain_bits[(size_t)w * 64 + lane] = word;
-              ws.chain_cum[(size_t)(w + 1) * 64 + lane] = gflushed;
-              pend >>= 32;
-              pn -= 32;
-              ++w;
-            }
-          };
-          retire(0, min(fin, 32));
-          if (GUESS && fin > 32) retire(32, fin - 32);
+          const unsigned long long finmask = rotl64((1ull << fin) - 1ull, head);
+          const unsigned long long fbits = mk & finmask;
+          G += __builtin_popcountll(fbits);
+          mk &= ~finmask;
+          const unsigned ob = (unsigned)rotr64(fbits, head);  // bit i: token done + i
+          pend |= (unsigned long long)ob << pn;               // pn < 32 bits were held
+          pn += fin;
+          if (pn >= 32) {
+            const unsigned word = (unsigned)pend;
+            gflushed += __builtin_popcount(word);
+            ws.chain_bits[(size_t)w * 64 + lane] = word;
+            ws.chain_cum[(size_t)(w + 1) * 64 + lane] = gflushed;
+            pend >>= 32;
+            pn -= 32;
+            ++w;
+          }
           M[lane].mask = mk;
           M[lane].G = G;
         }
@@ -805,7 +1162,6 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
               done * kSpecCheckSweeps < spec_min_progress(CP) * total_sweeps &&
               nflex_tok - done > 2 * kSpecSeg)
             bail = true;
-          if (GUESS) guess_on = done - done_mark >= kSpecGuessProgress;
           sweeps = 0;
           done_mark = done;
         }
@@ -1416,29 +1772,33 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   int decided = 0;
   unsigned hist0 = 0;
   if (use_spec) {
-    // First guesses and the window of 128 where tokens rarely compete: many experts per
-    // candidate.  With few experts every sweep ends at an early conflict and the guesses
-    // only cost: one consumer wave, a window of 64.
-#define LASER_SPEC_WALK(CP_, KK_)                                                                   \
-  (a.E >= 4 * CP_ ? spec_walk2<CP_, KK_>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0) \
-                  : spec_walk<CP_, KK_, false>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0))
+    // With many experts per candidate tokens rarely compete: first guesses and the window of 128.
+    // With fewer every sweep ends at an early conflict, and then the walk of up to 8 candidates is
+    // the faster one (8 experts: 50 ns per token against 21).
     if (a.c <= 4) {
-      decided = a.k == 2 ? LASER_SPEC_WALK(4, 2) : LASER_SPEC_WALK(4, 0);
+      if (a.E >= 16)
+        decided = a.k == 2 ? spec_walk2<4, 2>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
+                           : spec_walk2<4, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else if (a.c <= 8) {
-      decided = a.k == 6 ? LASER_SPEC_WALK(8, 6) : LASER_SPEC_WALK(8, 0);
+      if (a.E >= 32)
+        decided = a.k == 6 ? spec_walk2<8, 6>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
+                           : spec_walk2<8, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+    } else if (a.E == 64) {
+      decided = spec_walk2<16, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else {
-      decided = LASER_SPEC_WALK(16, 0);
+      decided = spec_walk<16, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     }
-#undef LASER_SPEC_WALK
   }
   if (decided < nflex_tok) {
     // the rest (or everything) one token after the other
     if (wide)
       chain_walk<0>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
-    else if (a.c <= 8)
-      chain_walk<8>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
-    else
+    else if (a.c > 8)
       chain_walk<16>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
+    else if (a.EP > 8)
+      chain_walk_lag(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
+    else  // (nothing is decided yet)
+      chain_walk_pairs(lds, nflex_tok, ws, a.k, wave, lane, lin, gflex);
   }
   if (seg.on) {
     if (wave == 0) segment_result();
