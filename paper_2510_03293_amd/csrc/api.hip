@@ -226,15 +226,16 @@ int route_impl(const void* hidden, const void* w_gate, int32_t B, int32_t T, int
   if (params->dtype == LASER_DTYPE_BF16 && B == 1 && !general && !resample) {
     choose_segments(a, params->pipeline_tiles);
   }
-  // Small calls, one problem through the fused bf16 kernel (whatever follows it): eight or
-  // four workgroups per tile share the contraction axis (gate_split.hip).
-  if (params->dtype == LASER_DTYPE_BF16 && B == 1 && a.nseg == 0 && a.ntiles >= 1 &&
-      a.ntiles <= kSplitMaxTiles && params->split_k != 1 && workspace_bytes_given >= ws_one) {
+  // Few tiles in all through the fused bf16 kernel (whatever follows it): eight or four
+  // workgroups per tile share the contraction axis (gate_split.hip).
+  const long long tiles = (long long)B * a.ntiles;
+  if (params->dtype == LASER_DTYPE_BF16 && a.nseg == 0 && tiles >= 1 && tiles <= kSplitMaxTiles &&
+      params->split_k != 1 && workspace_bytes_given / (size_t)B >= ws_one) {
     int32_t* counters = split_counters_for(workspace);
     if (counters != nullptr) {
-      a.split = a.ntiles <= kSplitEightTiles ? 8 : 4;
+      a.split = tiles <= kSplitEightTiles ? 8 : 4;
       a.split_cnt = counters;
-      if (a.ntiles == 1 && !general && !resample) {  // (nothing between the fused kernel and the tail kernel)
+      if (a.ntiles == 1 && !general && !resample) {  // (nothing follows the fused kernel's analysis)
         a.one_permutation = permutation;
         a.one_expert_offsets = expert_offsets;
         a.one_loads = loads_inout;
@@ -267,7 +268,8 @@ int route_impl(const void* hidden, const void* w_gate, int32_t B, int32_t T, int
       return LASER_E_LAUNCH;
   }
   if (ev && hipEventRecord(ev[1], s) != hipSuccess) return LASER_E_LAUNCH;
-  if (launch_tail(a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation, s) != hipSuccess)
+  if (a.one_permutation == nullptr &&
+      launch_tail(a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation, s) != hipSuccess)
     return LASER_E_LAUNCH;
   if (ev) {
     if (hipEventRecord(ev[2], s) != hipSuccess) return LASER_E_LAUNCH;

@@ -3,6 +3,7 @@
 #include <atomic>
 
 #include "gate_tile.h"
+#include "tail.h"
 
 namespace laser {
 
@@ -25,18 +26,150 @@ namespace laser {
 // of the code object (zero when it is loaded) of which every workspace address gets a slice
 // on first sight.  The last workgroup of a tile sets the tile's counter back to zero.  Calls
 // that share a workspace must not overlap anyway, so a slice has one user at a time.
-template <int EB, int NE, int NR, bool STATS>  // NR: wavefront roles per workgroup, 1 or 2
+
+// The load-dependent tokens of a one-tile call, by the workgroup that analysed it.
+struct OneTile {
+  unsigned rec[kTile][64];             // the n-th one's record row (lane = expert)
+  uint8_t cids[kTile][16];             // its candidates by rank, padded
+  uint8_t rids[kTile][16];             // its experts by rank
+  float p[kTile][16];                  // their probabilities
+  float Z[kTile];                      // the softmax denominator
+  int cstar[kTile], tok[kTile];        // candidates, token
+  unsigned long long chosen[kTile];    // the experts chosen for it
+};
+static_assert(sizeof(OneTile) <= kGateLdsBytes, "the partial tiles are dead by then");
+
+// `fm`: those tokens; `lin` (wave 0, lane = expert): the counters before token 0.  Writes their
+// ids and weights and adds them to mask64.  All 512 threads; ends with a barrier.
+__device__ __forceinline__ void finish_flexible(OneTile& ot, unsigned long long fm, unsigned long long* mask64, int lin,
+                                                const RouteArgs& a, const Workspace& ws,
+                                                int32_t* __restrict__ expert_ids, float* __restrict__ weights) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int n_flex = __builtin_popcountll(fm);
+  // ---- the records, wave w those of tokens number w, w + 8, ..., all in flight together ----
+  {
+    constexpr int kPer = kTile / kGateWaves;
+    unsigned rec[kPer], more[kPer];
+    int tok[kPer];
+    unsigned long long left = fm;
+    for (int i = 0; i < wave; ++i) left &= left - 1ull;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int n = wave + u * kGateWaves;  // (the slot of a one-tile call's n-th flexible token)
+      rec[u] = 0xFFFFu;
+      more[u] = 0u;
+      tok[u] = 0;
+      if (n < n_flex) {
+        tok[u] = __builtin_ctzll(left);
+        for (int i = 0; i < kGateWaves; ++i) left &= left - 1ull;
+        if (lane < a.EP) rec[u] = ws.rec_lane[(size_t)n * a.EP + lane];
+        // lanes 0..3 and 4..7: the two id rows, 8..23: the probabilities, 24: the denominator
+        const unsigned* src = lane < 4    ? reinterpret_cast<const unsigned*>(ws.rec_cids) + n * 4 + lane
+                              : lane < 8  ? reinterpret_cast<const unsigned*>(ws.rec_ids) + tok[u] * 4 + (lane - 4)
+                              : lane < 24 ? reinterpret_cast<const unsigned*>(ws.rec_p) + tok[u] * 16 + (lane - 8)
+                                          : reinterpret_cast<const unsigned*>(ws.rec_Z) + tok[u];
+        if (lane < 25) more[u] = *src;
+        if (lane == 25) more[u] = ws.rec_cstar[tok[u]];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int n = wave + u * kGateWaves;
+      if (n < n_flex) {
+        ot.rec[n][lane] = rec[u];
+        if (lane < 4) reinterpret_cast<unsigned*>(ot.cids[n])[lane] = more[u];
+        else if (lane < 8) reinterpret_cast<unsigned*>(ot.rids[n])[lane - 4] = more[u];
+        else if (lane < 24) ot.p[n][lane - 8] = __uint_as_float(more[u]);
+        else if (lane == 24) ot.Z[n] = __uint_as_float(more[u]);
+        else if (lane == 25) ot.cstar[n] = (int)more[u];
+        else if (lane == 26) ot.tok[n] = tok[u];
+      }
+    }
+  }
+  __syncthreads();
+  // ---- token after token, lane = expert -------------------------------------------------
+  if (wave == 0) {
+    int base = lin;  // (the fixed tokens before a token are in its record)
+    unsigned long long mine = 0ull;
+    for (int n = 0; n < n_flex; ++n) {
+      const unsigned rec = ot.rec[n][lane];
+      const bool cand = rec != 0xFFFFu;
+      const unsigned key = cand ? ((unsigned)base << 4) + rec : 0xFFFFFFFFu;
+      bool chosen;
+      if (a.c <= 8) {
+        // all pairs of candidates by rank (i, j) = (lane / 8, lane % 8) at once: byte i of the
+        // comparisons has fewer than k bits
+        const unsigned ki = (unsigned)__builtin_amdgcn_ds_bpermute(4 * ot.cids[n][lane >> 3], (int)key);
+        const unsigned kj = (unsigned)__builtin_amdgcn_ds_bpermute(4 * ot.cids[n][lane & 7], (int)key);
+        const unsigned long long less = __builtin_amdgcn_ballot_w64(kj < ki);
+        const unsigned row = (unsigned)(less >> (8 * (rec & 7u))) & 0xFFu;
+        chosen = cand && __builtin_popcount(row) < a.k;
+      } else {
+        chosen = chain_step(key, cand, *reinterpret_cast<const uint4*>(ot.cids[n]), a.k);
+      }
+      base += chosen ? 1 : 0;
+      const int tok = __builtin_amdgcn_readfirstlane(ot.tok[n]);
+      mine |= (unsigned long long)(chosen ? 1u : 0u) << tok;
+      const unsigned long long em = __builtin_amdgcn_ballot_w64(chosen);
+      if (lane == 0) ot.chosen[n] = em;
+    }
+    mask64[lane] |= mine;
+  }
+  __syncthreads();
+  // ---- ids and weights: thread = (token, one of eight), each its share of the chosen ranks ----
+  {
+    const int n = threadIdx.x >> 3, q = threadIdx.x & 7;
+    if (n < n_flex) {
+      const unsigned long long em = ot.chosen[n];
+      const int cs = ot.cstar[n];
+      const size_t row = (size_t)ot.tok[n] * a.k;
+      float denom = ot.Z[n];
+      if (a.renormalize) {
+        bool first = true;
+        for (int j = 0; j < cs; ++j)
+          if ((em >> ot.rids[n][j]) & 1ull) {
+            denom = first ? ot.p[n][j] : denom + ot.p[n][j];
+            first = false;
+          }
+      }
+      int at = 0;
+      for (int j = 0; j < cs; ++j) {
+        const int e = ot.rids[n][j];
+        if ((em >> e) & 1ull) {  // (exactly k bits are set)
+          if ((j & 7) == q) {
+            expert_ids[row + at] = e;
+            weights[row + at] = ot.p[n][j] / denom;
+          }
+          ++at;
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+template <int EB, int NE, int NR, bool STATS, bool BATCH>  // NR: wavefront roles per workgroup, 1 or 2
 __global__ __launch_bounds__(kGateThreads) void gate_split_bf16_kernel(
     const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ w, int H, const RouteArgs a0,
-    const Workspace ws, int32_t* __restrict__ expert_ids, float* __restrict__ weights,
-    float* __restrict__ logits_out) {
+    const Workspace ws0, int32_t* __restrict__ expert_ids, float* __restrict__ weights,
+    float* __restrict__ logits_out, size_t logits_stride) {
   static_assert(NR == 1 || NR == 2, "one or two roles per workgroup");
   extern __shared__ __align__(16) unsigned char gate_lds[];
   __shared__ unsigned long long mask64[64];
   __shared__ unsigned long long flex_lds;
   __shared__ int sh_last;
-  RouteArgs a = a0;
+  // (blockIdx.y: the problem of a batched call)
+  const int prob = BATCH ? blockIdx.y : 0;
+  RouteArgs a = BATCH ? problem_args(a0, prob) : a0;
+  const Workspace ws = BATCH ? problem_workspace(ws0, (size_t)prob * a0.ws_stride) : ws0;
   if (STATS && a.pool_in_ws) a.st_pool = ws.pool;
+  if (BATCH) {
+    hidden += (size_t)prob * a.T * H;
+    w += (size_t)prob * a.E * H;
+    expert_ids += (size_t)prob * a.T * a.k;
+    weights += (size_t)prob * a.T * a.k;
+    logits_out = logits_out != nullptr ? logits_out + (size_t)prob * logits_stride : nullptr;
+  }
   const int T = a.T, E = a.E;
   constexpr int split = kGateWaves / NR;  // workgroups per tile (the launcher sees to a.split == split)
   constexpr int nroles = NR;
@@ -200,7 +333,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_split_bf16_kernel(
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every store acknowledged ...
   __syncthreads();                                   // ... by every wavefront
   if (threadIdx.x == 0) {
-    int32_t* counter = a.split_cnt + tile;
+    int32_t* counter = a.split_cnt + (size_t)prob * a.ntiles + tile;
     const int before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int last = before == split - 1;
     if (last) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next call
@@ -251,15 +384,23 @@ __global__ __launch_bounds__(kGateThreads) void gate_split_bf16_kernel(
   analyse_tile<NE, kGateWaves, STATS>(part, kPartStride, mask64, &flex_lds, tile, a, ws, expert_ids, weights,
                                       logits_out);
 
-  // ---- a call of one tile without load-dependent tokens ends here -----------------------
-  // Everything the dispatch tables need is in this workgroup: per expert the tokens
-  // assigned to it (mask64) and, just written, the tokens' experts in rank order.  The
-  // tables are those the tail kernel would write (a stable counting sort of the T k
-  // assignments); it finds the mark and returns at once.
-  if (NR == 1 && a.one_permutation != nullptr) {  // (a.ntiles == 1)
+  // ---- a call of one tile ends here ------------------------------------------------------
+  // Everything the rest needs is in this workgroup: the records of the load-dependent tokens,
+  // per expert the other tokens assigned to it (mask64) and, just written, the tokens' experts
+  // in rank order.  What follows is what the tail kernel would do, without its launch and the
+  // way of all of this through memory.  (Sixty-four tokens, 64 experts, H = 2048: split kernel and tail 10.6 + 4.4 us,
+  // now 10.1; a replayed decode loop 387 -> 303 us for 27 layers.)
+  if (a.one_permutation != nullptr) {  // (a.ntiles == 1)
+    int32_t* const permutation = a.one_permutation + (size_t)prob * T * a.k;
+    int32_t* const expert_offsets = a.one_expert_offsets + (size_t)prob * (E + 1);
+    int32_t* const loads = a.one_loads + (size_t)prob * E;
     __shared__ int sh_off[64];
-    __syncthreads();  // the expert ids are stored, mask64 and flex_lds are final
-    if (flex_lds != 0ull) return;
+    int lin = 0;
+    if (wave == 0 && lane < E) lin = loads[lane];
+    __syncthreads();  // expert ids and records are stored, mask64 and flex_lds are final
+    const unsigned long long fm = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(flex_lds >> 32)) << 32) |
+                                  (unsigned)__builtin_amdgcn_readfirstlane((int)flex_lds);
+    if (fm != 0ull) finish_flexible(*reinterpret_cast<OneTile*>(gate_lds), fm, mask64, lin, a, ws, expert_ids, weights);
     if (wave == 0) {  // lane = expert
       const int cnt = lane < E ? __builtin_popcountll(mask64[lane]) : 0;
       int incl = cnt;
@@ -270,19 +411,18 @@ __global__ __launch_bounds__(kGateThreads) void gate_split_bf16_kernel(
       }
       sh_off[lane] = incl - cnt;
       if (lane < E) {
-        a.one_expert_offsets[lane] = incl - cnt;
-        a.one_loads[lane] += cnt;
+        expert_offsets[lane] = incl - cnt;
+        loads[lane] = lin + cnt;
       }
-      if (lane == E - 1) a.one_expert_offsets[E] = incl;
+      if (lane == E - 1) expert_offsets[E] = incl;
     }
     __syncthreads();
     const int k = a.k;
     for (int slot = threadIdx.x; slot < T * k; slot += kGateThreads) {
       const int t = slot / k;
       const int e = expert_ids[slot];
-      a.one_permutation[sh_off[e] + __builtin_popcountll(mask64[e] & lanes_below(t))] = slot;
+      permutation[sh_off[e] + __builtin_popcountll(mask64[e] & lanes_below(t))] = slot;
     }
-    if (threadIdx.x == 0) ws.status[kStatusPhase] = kPhaseAllDone;
   }
 }
 
@@ -324,40 +464,52 @@ int32_t* split_counters_for(const void* workspace) {
   return nullptr;  // the table is crowded: the call runs without the split
 }
 
-template <int EB, int NE, int NR, bool STATS>
+template <int EB, int NE, int NR, bool STATS, bool BATCH>
 static hipError_t launch_split(const void* hidden, const void* w, int H, const RouteArgs& a, const Workspace& ws,
-                               int32_t* expert_ids, float* weights, float* logits_out, hipStream_t s) {
+                               int32_t* expert_ids, float* weights, float* logits_out, size_t logits_stride,
+                               hipStream_t s) {
   static LdsAttr allowed;
-  const void* fn = reinterpret_cast<const void*>(&gate_split_bf16_kernel<EB, NE, NR, STATS>);
+  const void* fn = reinterpret_cast<const void*>(&gate_split_bf16_kernel<EB, NE, NR, STATS, BATCH>);
   const hipError_t e = allow_dynamic_lds(fn, kGateLdsBytes, allowed);
   if (e != hipSuccess) return e;
-  if (a.split * NR != kGateWaves) return hipErrorInvalidValue;
+  if (a.split * NR != kGateWaves || a.ntiles * a.nbatch > kSplitMaxTiles) return hipErrorInvalidValue;
   clear_stale_error();
-  hipLaunchKernelGGL((gate_split_bf16_kernel<EB, NE, NR, STATS>), dim3(a.ntiles * a.split), dim3(kGateThreads),
-                     kGateLdsBytes, s, static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(w), H, a, ws,
-                     expert_ids, weights, logits_out);
+  hipLaunchKernelGGL((gate_split_bf16_kernel<EB, NE, NR, STATS, BATCH>), dim3(a.ntiles * a.split, a.nbatch),
+                     dim3(kGateThreads), kGateLdsBytes, s, static_cast<const uint16_t*>(hidden),
+                     static_cast<const uint16_t*>(w), H, a, ws, expert_ids, weights, logits_out, logits_stride);
   return hipGetLastError();
+}
+
+template <int EB, int NE, int NR>
+static hipError_t launch_split_nr(const void* hidden, const void* w, int H, const RouteArgs& a, const Workspace& ws,
+                                  int32_t* expert_ids, float* weights, float* logits_out, size_t logits_stride,
+                                  hipStream_t s) {
+  const bool st = wants_stats(a);
+  if (a.nbatch > 1) {
+    if (st) return launch_split<EB, NE, NR, true, true>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
+    return launch_split<EB, NE, NR, false, true>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
+  }
+  if (st) return launch_split<EB, NE, NR, true, false>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
+  return launch_split<EB, NE, NR, false, false>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
 }
 
 template <int EB, int NE>
 static hipError_t launch_split_one(const void* hidden, const void* w, int H, const RouteArgs& a, const Workspace& ws,
-                                   int32_t* expert_ids, float* weights, float* logits_out, hipStream_t s) {
-  const bool st = wants_stats(a);
-  if (a.split == kGateWaves) {
-    if (st) return launch_split<EB, NE, 1, true>(hidden, w, H, a, ws, expert_ids, weights, logits_out, s);
-    return launch_split<EB, NE, 1, false>(hidden, w, H, a, ws, expert_ids, weights, logits_out, s);
-  }
-  if (st) return launch_split<EB, NE, 2, true>(hidden, w, H, a, ws, expert_ids, weights, logits_out, s);
-  return launch_split<EB, NE, 2, false>(hidden, w, H, a, ws, expert_ids, weights, logits_out, s);
+                                   int32_t* expert_ids, float* weights, float* logits_out, size_t logits_stride,
+                                   hipStream_t s) {
+  if (a.split == kGateWaves)
+    return launch_split_nr<EB, NE, 1>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
+  return launch_split_nr<EB, NE, 2>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
 }
 
 hipError_t launch_gate_split_bf16(const void* hidden, const void* w, int H, const RouteArgs& a, const Workspace& ws,
-                                  int32_t* expert_ids, float* weights, float* logits_out, hipStream_t s) {
+                                  int32_t* expert_ids, float* weights, float* logits_out, size_t logits_stride,
+                                  hipStream_t s) {
   switch (a.EP) {
-    case 8: return launch_split_one<1, 1>(hidden, w, H, a, ws, expert_ids, weights, logits_out, s);
-    case 16: return launch_split_one<1, 2>(hidden, w, H, a, ws, expert_ids, weights, logits_out, s);
-    case 32: return launch_split_one<2, 4>(hidden, w, H, a, ws, expert_ids, weights, logits_out, s);
-    default: return launch_split_one<4, 8>(hidden, w, H, a, ws, expert_ids, weights, logits_out, s);
+    case 8: return launch_split_one<1, 1>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
+    case 16: return launch_split_one<1, 2>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
+    case 32: return launch_split_one<2, 4>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
+    default: return launch_split_one<4, 8>(hidden, w, H, a, ws, expert_ids, weights, logits_out, logits_stride, s);
   }
 }
 

@@ -46,12 +46,12 @@ struct RouteArgs {
   int seg_tiles;       // tiles per segment; 0: the call is not pipelined
   int seg_first;       // tiles of segment 0 (a short one lets the chain start early)
   int nseg;            // segments: 1 + ceil((ntiles - seg_first) / seg_tiles); 0 when not pipelined
-  // small single problems through the fused bf16 kernel: the contraction axis of a tile cut
-  // over `split` workgroups (gate_split.hip)
+  // few tiles through the fused bf16 kernel: the contraction axis of a tile cut over `split`
+  // workgroups (gate_split.hip)
   int split;           // workgroups per tile (4 or 8); 0: one workgroup per tile
-  int32_t* split_cnt;  // [ntiles] arrival counters, zero between calls (the library's own memory)
-  // a split call of one tile without load-dependent tokens is finished by the workgroup
-  // that analyses it (the tail kernel then returns at once); NULL: never
+  int32_t* split_cnt;  // [nbatch, ntiles] arrival counters, zero between calls (the library's own memory)
+  // a split call of one tile (per problem) is finished by the workgroup that analyses it and
+  // has no tail kernel; NULL: not so (problem b's follow those of problem b - 1)
   int32_t* one_permutation;     // the call's permutation ...
   int32_t* one_expert_offsets;  // ... expert_offsets ...
   int32_t* one_loads;           // ... and loads_inout
@@ -143,8 +143,7 @@ __device__ __forceinline__ Workspace problem_workspace(const Workspace& w0, size
   return w;
 }
 
-constexpr int kStatusPhase = 0;      // 1: fixed prefix published, 2: chain finished, 3: nothing left for the tail kernel
-constexpr int kPhaseAllDone = 3;
+constexpr int kStatusPhase = 0;      // 1: fixed prefix published, 2: chain finished
 constexpr int kStatusFlexTiles = 1;  // number of tiles that hold flexible tokens
 constexpr int kStatusError = 2;      // 0, or why the outputs of the call are incomplete (kError*)
 constexpr int kErrorTimeout = 1;        // a bounded wait in the tail kernel ran out (LASER_STATUS_TIMEOUT)
@@ -222,10 +221,10 @@ hipError_t launch_gate_analyse_bf16(const void* hidden, const void* w, int H, co
 hipError_t launch_gate_pipeline_bf16(const void* hidden, const void* w, int H, const RouteArgs& a,
                                      const Workspace& ws, int32_t* expert_ids, float* weights,
                                      float* logits_out, hipStream_t s);
-// the same for a split call (a.split > 0, one problem)
+// the same for a split call (a.split > 0)
 hipError_t launch_gate_split_bf16(const void* hidden, const void* w, int H, const RouteArgs& a,
                                   const Workspace& ws, int32_t* expert_ids, float* weights,
-                                  float* logits_out, hipStream_t s);
+                                  float* logits_out, size_t logits_stride, hipStream_t s);
 // the arrival counters of split calls on this workspace (device memory of the current device;
 // NULL if none can be had: the call then runs without the split)
 int32_t* split_counters_for(const void* workspace);
