@@ -28,10 +28,10 @@ def chains(hidden, w):
     return z
 
 
-# (edges: one chunk of 64 columns and its remainders, more chunks than are in flight, blocks of 16
+# (edges: one chunk of 128 columns and its remainders, more chunks than are in flight, blocks of 16
 # tokens and experts, one or two blocks of experts per workgroup)
 @pytest.mark.parametrize("values", ["normal", "exponents", "cancelling", "subnormal"])
-@pytest.mark.parametrize("T,E,H", [(1, 1, 4), (17, 9, 132), (33, 16, 64), (2, 17, 68), (19, 33, 60), (16, 64, 320),
+@pytest.mark.parametrize("T,E,H", [(1, 1, 4), (17, 9, 132), (33, 16, 128), (2, 17, 124), (19, 33, 60), (16, 64, 640),
                                    (5, 64, 604)])
 def test_logits_are_chains_of_fused_multiply_adds(T, E, H, values):
     rng = np.random.default_rng(1000 * T + E + H)
