@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_pipeline_bf16_kernel(
   if (STATS && a.pool_in_ws) a.st_pool = ws.pool;
   if (blockIdx.x == 0) {
     if (threadIdx.x < kTailThreads)
-      chain_segments<true>(gate_lds, a, ws, const_cast<int32_t*>(a.loads_in), nullptr);
+      chain_segments<true, 8 * NE>(gate_lds, a, ws, const_cast<int32_t*>(a.loads_in), nullptr);
     return;
   }
   const int T = a.T, E = a.E, ntiles = a.ntiles;

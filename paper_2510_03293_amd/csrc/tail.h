@@ -1568,6 +1568,9 @@ struct ChainSeg {
                   // with flexible tokens, [65] its flexible tokens
 };
 
+// EP: the padded number of experts where it is known (the gate kernel of a pipelined call, whose
+// registers the walks that cannot occur would cost), else 0.
+template <int EP>
 __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
                                 int32_t* __restrict__ loads_inout,
                                 int32_t* __restrict__ expert_offsets, const ChainSeg seg) {
@@ -1771,7 +1774,7 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
 
   int decided = 0;
   unsigned hist0 = 0;
-  if (use_spec) {
+  if (use_spec && EP != 8) {
     // With many experts per candidate tokens rarely compete: first guesses and the window of 128.
     // With fewer every sweep ends at an early conflict, and then the walk of up to 8 candidates is
     // the faster one (8 experts: 50 ns per token against 21).
@@ -1780,10 +1783,10 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
         decided = a.k == 2 ? spec_walk2<4, 2>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
                            : spec_walk2<4, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else if (a.c <= 8) {
-      if (a.E >= 32)
+      if ((EP == 0 || EP >= 32) && a.E >= 32)
         decided = a.k == 6 ? spec_walk2<8, 6>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
                            : spec_walk2<8, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
-    } else if (a.E == 64) {
+    } else if ((EP == 0 || EP == 64) && a.E == 64) {
       decided = spec_walk2<16, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else {
       decided = spec_walk<16, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
@@ -1791,14 +1794,14 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   }
   if (decided < nflex_tok) {
     // the rest (or everything) one token after the other
-    if (wide)
-      chain_walk<0>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
-    else if (a.c > 8)
-      chain_walk<16>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
-    else if (a.EP > 8)
-      chain_walk_lag(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
-    else  // (nothing is decided yet)
+    if (EP == 8 || (EP == 0 && a.EP == 8))  // (nothing is decided yet)
       chain_walk_pairs(lds, nflex_tok, ws, a.k, wave, lane, lin, gflex);
+    else if (a.c <= 8)
+      chain_walk_lag(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
+    else if (EP == 0 && wide)
+      chain_walk<0>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
+    else
+      chain_walk<16>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
   }
   if (seg.on) {
     if (wave == 0) segment_result();
@@ -1862,7 +1865,7 @@ constexpr int kGateSignals = 8;
 // The chain of a call, by the chain workgroup (kTailThreads threads) of the gate kernel
 // (IN_GATE: as far as the analysed tiles allow, nothing is published) or of the tail
 // kernel (the rest, then the totals and the flags the finishing workgroups wait for).
-template <bool IN_GATE>
+template <bool IN_GATE, int EP>  // EP: see chain_workgroup
 __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
                                                int32_t* __restrict__ loads_inout,
                                                int32_t* __restrict__ expert_offsets) {
@@ -1913,7 +1916,7 @@ __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a,
       sg.carry0 = carry;
       sg.fbase = fbase;
     }
-    chain_workgroup(lds, av, wv, loads_inout, expert_offsets, sg);
+    chain_workgroup<EP>(lds, av, wv, loads_inout, expert_offsets, sg);
     if (!sg.on) return;
     __syncthreads();  // seg_out written (wave 0); the chain's LDS is free again
     carry = seg_out[lane];
@@ -2437,7 +2440,7 @@ __device__ __forceinline__ void tail_role(int block, uint8_t* tail_lds, const Ro
                                           int32_t* __restrict__ expert_ids, float* __restrict__ weights,
                                           int32_t* __restrict__ permutation) {
   if (block == 0) {
-    chain_segments<false>(tail_lds, a, ws, loads_inout, expert_offsets);
+    chain_segments<false, 0>(tail_lds, a, ws, loads_inout, expert_offsets);
     return;
   }
   __shared__ int sh_before[kChainWaves][64], sh_all[kChainWaves][64];
