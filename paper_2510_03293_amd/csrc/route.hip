@@ -98,8 +98,10 @@ hipError_t launch_analyse(const float* logits, size_t logits_stride, const Route
 }
 
 template <bool BATCH>  // blockIdx.y is the problem of a batched call (a kernel of its own: the
-                       // longer prologue would delay the first loads of the single-problem kernel)
-__global__ __launch_bounds__(kTailThreads) void tail_kernel(const RouteArgs a0, const Workspace ws0,
+                       // longer prologue would delay the first loads of the single-problem kernel).
+                       // Two workgroups on a compute unit: with the registers of one a long
+                       // batch's finishing workgroups ran in two rounds (131072 tokens: 329 -> 339 us)
+__global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a0, const Workspace ws0,
                                                             int32_t* __restrict__ loads_inout,
                                                             int32_t* __restrict__ expert_offsets,
                                                             int32_t* __restrict__ expert_ids,

@@ -179,28 +179,25 @@ __device__ __forceinline__ unsigned add_quarters(unsigned x) {
   return p[0] + p[1];
 }
 
-// One flexible token of a wide call (up to 64 candidates): the k candidates with the smallest
-// (load, rank).  The candidates are taken level by level of their counters, from the lowest one
-// up, a whole level at a time as long as all of it is wanted; of the last level the lowest ranks.
-// Sets of experts are masks in scalar registers; the ranks of a level's experts are counted in
-// the lanes of the ranks (`id`: expert of rank = lane) and taken back to the lanes of the
-// experts (`rank`).  `level`: where the token before ended; the walk that load-balancing itself
-// produces -- k of the candidates on the level where the last token left off, and nobody below
-// it -- needs no search.  (A wave-wide minimum over loads and another one over ranks for each of
-// the k picks took 860 ns per token, 64 candidates, k = 6; now below 120.)
-// Returns 1 in the lanes of the chosen experts, else 0.
-__device__ __forceinline__ unsigned chain_step_wide(unsigned load, unsigned rank, unsigned id, int k, unsigned& level) {
+// One flexible token of a wide call (up to 64 candidates), in general: the k candidates with the
+// smallest (load, rank).  The candidates are taken level by level of their counters, from the
+// lowest one up, a whole level at a time as long as all of it is wanted; of the last level the
+// lowest ranks.  Sets of experts are masks in scalar registers; the ranks of a level's experts are
+// counted in the lanes of the ranks (`id`: the bit of the expert of rank = lane, 0 where there is
+// no candidate) and taken back to the lanes of the experts (`rank`: the bit of the expert's rank).
+// `level`: where the token before ended.  Returns 1 in the lanes of the chosen experts, else 0.
+__device__ __forceinline__ unsigned chain_step_wide(unsigned load, unsigned long long rank, unsigned long long id, int k,
+                                                    unsigned& level) {
   unsigned long long at = __builtin_amdgcn_ballot_w64(load == level);
   const unsigned long long below = __builtin_amdgcn_ballot_w64(load < level);
   // lane = rank: the `want` lowest ranks of the level `at`, then back to lane = expert
   auto lowest = [&](int want) {
-    const unsigned here = (unsigned)(at >> id) & 1u;
-    const unsigned long long ranks = __builtin_amdgcn_ballot_w64(here != 0u);
+    const unsigned long long ranks = __builtin_amdgcn_ballot_w64((at & id) != 0ull);
     const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(ranks >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ranks, 0));
     const unsigned long long won = __builtin_amdgcn_ballot_w64(before < want) & ranks;
-    return (unsigned)(won >> rank) & 1u;
+    return (won & rank) != 0ull ? 1u : 0u;
   };
-  if (__builtin_expect(__builtin_popcountll(below != 0ull ? 0ull : at) >= k, 1)) return lowest(k);
+  if (below == 0ull && __builtin_popcountll(at) >= k) return lowest(k);
   if (below != 0ull) {
     level = wave_min_u32(load);
     at = __builtin_amdgcn_ballot_w64(load == level);
@@ -222,6 +219,14 @@ __device__ __forceinline__ unsigned chain_step_wide(unsigned load, unsigned rank
   return lowest(want) | ((unsigned)(taken >> (threadIdx.x & 63)) & 1u);
 }
 
+// What a walk derives from the lane number is computed when the walk begins: the compiler would
+// otherwise do it ahead of the loop over a call's segments and keep all walks' masks and
+// addresses in registers across everything (51 registers above what two workgroups per
+// compute unit leave).
+__device__ __forceinline__ void own_lane(int& lane) {
+  asm volatile("" : "+v"(lane));
+}
+
 // ---- sequential walk ---------------------------------------------------------------------
 //
 // One dependent step per flexible token, by wave 0 (lane = expert, G = the flexible choices of
@@ -234,7 +239,7 @@ __device__ __forceinline__ unsigned chain_step_wide(unsigned load, unsigned rank
 // Up to 16 candidates: the keys of the candidates are gathered from the lanes of their experts;
 // lane 16 q + i compares the key of rank i with those of ranks 4 q .. 4 q + 3 and the four quarters
 // are added across the wavefront (c = 16: 258 -> 132 ns per token).
-constexpr int kSeqBatch = 96;  // flexible tokens per LDS batch (whole output words)
+constexpr int kSeqBatch = 48;  // flexible tokens per LDS batch
 struct SeqTok {
   unsigned rec[64];   // per expert: (counter without flexible choices) << 4 | rank, or kSeqNoCand
   uint8_t addr[16];   // per rank: 4 * the candidate's lane (padded with a lane that holds none)
@@ -243,11 +248,15 @@ constexpr unsigned kSeqNoCand = 0x8000000Du;  // (compares above every key)
 static_assert((2 * kSeqBatch + 1) * (int)sizeof(SeqTok) <= kChainLdsBytes, "two batches and a token of read-ahead");
 
 // Wide calls (up to 64 candidates).
-constexpr int kSeqWideBatch = 64;
+// The walk that load-balancing itself produces -- k of the candidates on the level where the last
+// token left off, and nobody below it -- needs no search: chain_step_wide written out for that
+// case, without a scalar instruction that reads a comparison's result (it would wait for 16
+// cycles); that it was the case is looked at when the choice is there.  (8192 tokens, 64
+// candidates, k = 6: 113 -> 99 ns per token, the call 952 -> 862 us)
+constexpr int kSeqWideBatch = 21;
 struct SeqTokWide {
+  uint4 bits[64];     // x, y: of the expert of rank = lane; z, w: of the rank of the lane's expert
   unsigned base[64];  // per expert: its counter without flexible choices, or kSeqWideNoCand
-  uint8_t rank[64];   // per expert: rank (63 for experts that are no candidates)
-  uint8_t id[64];     // per rank: the candidate's lane (padded with a lane that holds none)
 };
 constexpr unsigned kSeqWideNoCand = 0x40000000u;
 static_assert((2 * kSeqWideBatch + 1) * (int)sizeof(SeqTokWide) <= kChainLdsBytes, "two batches and a token of read-ahead");
@@ -256,13 +265,13 @@ template <int CP>
 struct SeqTraits {
   typedef SeqTok Tok;
   static constexpr int batch = kSeqBatch;
-  static constexpr int half = 16;  // tokens whose records a producer wave has in flight together:
+  static constexpr int half = 8;   // tokens whose records a producer wave has in flight together:
 };                                 // half of its share of a batch
 template <>
 struct SeqTraits<0> {
   typedef SeqTokWide Tok;
   static constexpr int batch = kSeqWideBatch;
-  static constexpr int half = 11;
+  static constexpr int half = 4;
 };
 
 // What a producer wave needs of some tokens, on its way from memory.
@@ -277,40 +286,43 @@ struct SeqLoads {
 template <int CP>
 __device__ __forceinline__ int seq_slots(int batch, int nflex_tok, const Workspace& ws, int pw, int lane) {
   constexpr int NB = SeqTraits<CP>::batch;
-  const int f = batch * NB + pw + 3 * lane;
-  return (pw + 3 * lane < NB && f < nflex_tok) ? ws.flex_slot[f] : 0;
+  const int f = batch * NB + pw + 3 * min(lane, (NB + 2) / 3);
+  // (loads without conditions stay in flight: any token of the call stands in for none)
+  return ws.flex_slot[min(f, nflex_tok - 1)];
 }
 template <int CP, int N>
 __device__ __forceinline__ void seq_load(SeqLoads<N>& L, int slots, int i0, const RouteArgs& a, const Workspace& ws,
                                          int lane) {
 #pragma unroll
-  for (int u = 0; u < N; ++u) {  // (slot 0 stands in for tokens that do not exist)
+  for (int u = 0; u < N; ++u) {
     const int slot = __builtin_amdgcn_readlane(slots, i0 + u);
-    L.rec[u] = lane < a.EP ? ws.rec_lane[(size_t)slot * a.EP + lane] : 0xFFFFu;
+    L.rec[u] = (ws.rec_lane + (size_t)slot * a.EP)[(unsigned)min(lane, a.EP - 1)];
     L.base[u] = ws.tile_base[(size_t)(slot >> 6) * 64 + lane];
     if constexpr (CP != 0) L.cids[u] = ws.rec_cids[(size_t)slot * 16 + (lane & 15)];
   }
 }
 template <int CP, int N>
 __device__ __forceinline__ void seq_store(typename SeqTraits<CP>::Tok* dst, const SeqLoads<N>& L, int i0, int pw,
-                                          int lane, int lin) {
+                                          int EP, int lane, int lin) {
 #pragma unroll
   for (int u = 0; u < N; ++u) {
     if (pw + 3 * (i0 + u) >= SeqTraits<CP>::batch) break;
     auto* tok = dst + pw + 3 * (i0 + u);
-    const bool cand = L.rec[u] != 0xFFFFu;
+    const bool cand = lane < EP && L.rec[u] != 0xFFFFu;
     const unsigned base = (unsigned)(lin + L.base[u]);
     if constexpr (CP != 0) {
       tok->rec[lane] = cand ? (base << 4) + L.rec[u] : kSeqNoCand;
       if (lane < 16) tok->addr[lane] = (uint8_t)(4 * L.cids[u]);
     } else {
+      // (the ranks of the candidates, then the others: every lane sends its number to one of its own)
       const unsigned long long all = __builtin_amdgcn_ballot_w64(cand);
-      const int pad = ~all != 0ull ? __builtin_ctzll(~all) : 0;  // (no ranks to pad if every lane is a candidate)
+      const int ncand = __builtin_popcountll(all);
+      const int other = lane - __builtin_amdgcn_mbcnt_hi((unsigned)(all >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)all, 0));
+      const int rank = cand ? (int)(L.rec[u] & 63u) : ncand + other;
+      const int id = __builtin_amdgcn_ds_permute(4 * rank, lane);
+      const unsigned long long id_bit = lane < ncand ? 1ull << id : 0ull, rank_bit = cand ? 1ull << rank : 0ull;
+      tok->bits[lane] = make_uint4((unsigned)id_bit, (unsigned)(id_bit >> 32), (unsigned)rank_bit, (unsigned)(rank_bit >> 32));
       tok->base[lane] = cand ? base + (L.rec[u] >> 6) : kSeqWideNoCand;
-      tok->rank[lane] = (uint8_t)(cand ? L.rec[u] & 63u : 63u);
-      tok->id[lane] = (uint8_t)pad;
-      lds_wave_fence();
-      if (cand) tok->id[L.rec[u] & 63u] = (uint8_t)lane;
     }
   }
 }
@@ -321,6 +333,7 @@ __device__ __forceinline__ void seq_store(typename SeqTraits<CP>::Tok* dst, cons
 template <int CP>
 __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
                                            const Workspace& ws, int wave, int lane, int lin, int& gflex) {
+  own_lane(lane);
   typedef typename SeqTraits<CP>::Tok Tok;
   constexpr int NB = SeqTraits<CP>::batch;
   Tok* const buf = reinterpret_cast<Tok*>(lds);
@@ -335,6 +348,7 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
   // bits of the current output word, the last token's lowest
   unsigned hist = (f0 & 31) != 0 ? __builtin_bitreverse32(hist0) >> (32 - (f0 & 31)) : 0u;
   unsigned level = 0xFFFFFFFFu;  // (wide: no counter of a candidate is known to be below)
+  unsigned chosen = 0u;          // (wide: of the last token, not in hist yet)
   // The producers are two batches ahead with the list of records, and half a batch ahead with
   // the records themselves: a batch is decided in a few microseconds, a record is two dependent
   // memory round trips away.  (The barriers leave loads in flight alone.)
@@ -348,9 +362,9 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
     seq_load<CP, NH>(first, slots, 0, a, ws, lane);
     seq_load<CP, NH>(second, slots, NH, a, ws, lane);
     Tok* dst = buf + (b0 & 1) * NB;
-    seq_store<CP, NH>(dst, first, 0, pw, lane, lin);
+    seq_store<CP, NH>(dst, first, 0, pw, a.EP, lane, lin);
     seq_load<CP, NH>(first, slots_n, 0, a, ws, lane);
-    seq_store<CP, NH>(dst, second, NH, pw, lane, lin);
+    seq_store<CP, NH>(dst, second, NH, pw, a.EP, lane, lin);
   }
   lds_barrier();
   for (int b = b0; b < b1; ++b) {
@@ -360,9 +374,9 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
         slots_n = seq_slots<CP>(b + 2, nflex_tok, ws, pw, lane);
         seq_load<CP, NH>(second, slots, NH, a, ws, lane);
         Tok* dst = buf + ((b + 1) & 1) * NB;
-        seq_store<CP, NH>(dst, first, 0, pw, lane, lin);
+        seq_store<CP, NH>(dst, first, 0, pw, a.EP, lane, lin);
         seq_load<CP, NH>(first, slots_n, 0, a, ws, lane);
-        seq_store<CP, NH>(dst, second, NH, pw, lane, lin);
+        seq_store<CP, NH>(dst, second, NH, pw, a.EP, lane, lin);
       }
     } else {
       const Tok* cur = buf + (b & 1) * NB;
@@ -421,16 +435,78 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
           }
         }
       } else {
-        unsigned base = cur[r].base[lane], rank = cur[r].rank[lane], id = cur[r].id[lane];
+        uint4 bits = cur[r].bits[lane];
+        unsigned base = cur[r].base[lane];
+        const unsigned none = 64u;
         auto step = [&](const Tok& next) {
           const unsigned load = base + G;
-          const unsigned base_n = next.base[lane], rank_n = next.rank[lane], id_n = next.id[lane];
-          const unsigned chosen = chain_step_wide(load, rank, id, (int)k, level);
+          const uint4 bits_n = next.bits[lane];
+          const unsigned base_n = next.base[lane];
+          // (what is read out of a comparison's scalar is at least two instructions behind it)
+          unsigned x;
+          unsigned long long kth;
+          asm("v_cmp_eq_u32 s[88:89], %[load], %[level]\n\t"           // on the level
+              "v_cmp_lt_u32 s[90:91], %[load], %[level]\n\t"
+              "v_lshl_or_b32 %[hist], %[hist], 1, %[chosen]\n\t"       // (the token before)
+              "v_and_b32 %[x], s88, %[id0]\n\t"
+              "v_bitop3_b32 %[x], %[id1], %[x], s89 bitop3:0xec\n\t"   // x | (s89 & id1): by rank
+              "v_cmp_ne_u32 s[92:93], 0, %[x]\n\t"
+              "s_cmp_lg_u64 s[90:91], 0\n\t"                           // somebody is below the level
+              "s_nop 0\n\t"
+              "v_mbcnt_lo_u32_b32 %[x], s92, 0\n\t"                    // how many of lower rank are
+              "v_mbcnt_hi_u32_b32 %[x], s93, %[x]\n\t"
+              "v_cndmask_b32 %[x], %[none], %[x], s[92:93]\n\t"
+              "v_cmp_gt_u32 s[94:95], %[k], %[x]\n\t"                  // chosen
+              "v_cmp_eq_u32 s[92:93], %[km1], %[x]\n\t"                // the last one of the k
+              "s_nop 0\n\t"
+              "v_and_b32 %[x], s94, %[r0]\n\t"
+              "v_bitop3_b32 %[x], %[r1], %[x], s95 bitop3:0xec\n\t"    // by expert
+              "v_min_u32 %[x], 1, %[x]\n\t"
+              "s_cselect_b64 s[92:93], 0, s[92:93]\n\t"
+              : [hist] "+v"(hist), [x] "=&v"(x), [kth] "={s[92:93]}"(kth)
+              : [load] "v"(load), [level] "v"(level), [chosen] "v"(chosen), [id0] "v"(bits.x), [id1] "v"(bits.y),
+                [r0] "v"(bits.z), [r1] "v"(bits.w), [none] "v"(none), [k] "s"(k), [km1] "s"(k - 1)
+              : "s88", "s89", "s90", "s91", "s94", "s95", "scc");
+          chosen = x;
+          if (__builtin_expect(kth == 0ull, 0)) {
+            // fewer than k on the level (or somebody below it): all of those, and the lowest ranks
+            // of the level above, in the same manner
+            unsigned n0;
+            unsigned long long below;
+            asm("v_cmp_eq_u32 s[90:91], %[load], %[level]\n\t"
+                "v_cmp_eq_u32 s[88:89], %[load], %[next]\n\t"
+                "s_nop 0\n\t"
+                "v_bcnt_u32_b32 %[n0], s90, 0\n\t"
+                "v_bcnt_u32_b32 %[n0], s91, %[n0]\n\t"
+                "v_and_b32 %[x], s88, %[id0]\n\t"
+                "v_bitop3_b32 %[x], %[id1], %[x], s89 bitop3:0xec\n\t"
+                "v_cmp_ne_u32 s[92:93], 0, %[x]\n\t"
+                "v_cmp_lt_u32 s[88:89], %[load], %[level]\n\t"
+                "s_nop 0\n\t"
+                "v_mbcnt_lo_u32_b32 %[x], s92, %[n0]\n\t"
+                "v_mbcnt_hi_u32_b32 %[x], s93, %[x]\n\t"
+                "v_cndmask_b32 %[x], %[none], %[x], s[92:93]\n\t"
+                "v_cmp_gt_u32 s[94:95], %[k], %[x]\n\t"
+                "v_cmp_eq_u32 s[92:93], %[km1], %[x]\n\t"
+                "s_nop 0\n\t"
+                "v_and_b32 %[x], s94, %[r0]\n\t"
+                "v_bitop3_b32 %[x], %[r1], %[x], s95 bitop3:0xec\n\t"
+                "v_min_u32 %[x], 1, %[x]\n\t"
+                "v_cndmask_b32 %[x], %[x], 1, s[90:91]\n\t"
+                : [x] "=&v"(x), [n0] "=&v"(n0), [below] "={s[88:89]}"(below), [kth] "={s[92:93]}"(kth)
+                : [load] "v"(load), [level] "v"(level), [next] "v"(level + 1u), [id0] "v"(bits.x), [id1] "v"(bits.y),
+                  [r0] "v"(bits.z), [r1] "v"(bits.w), [none] "v"(none), [k] "s"(k), [km1] "s"(k - 1)
+                : "s90", "s91", "s94", "s95");
+            chosen = x;
+            if (kth != 0ull && below == 0ull)
+              ++level;
+            else
+              chosen = chain_step_wide(load, ((unsigned long long)bits.w << 32) | bits.z,
+                                       ((unsigned long long)bits.y << 32) | bits.x, (int)k, level);
+          }
           G += chosen;
-          hist = hist + hist + chosen;
+          bits = bits_n;
           base = base_n;
-          rank = rank_n;
-          id = id_n;
         };
         while (r < n) {
           const int end = min(n, r + 32 - (f & 31));
@@ -441,9 +517,10 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
           }
           for (; r < end; ++r) step(cur[r + 1]);
           if ((f & 31) == 0) {
+            hist = (hist << 1) | chosen;
             ws.chain_bits[(size_t)((f >> 5) - 1) * 64 + lane] = __builtin_bitreverse32(hist);
             ws.chain_cum[(size_t)(f >> 5) * 64 + lane] = (int)G;
-            hist = 0;
+            hist = chosen = 0u;
           }
         }
       }
@@ -452,6 +529,7 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
   }
   if (wave == 0) {
     gflex = (int)G;
+    if constexpr (CP == 0) hist = (hist << 1) | chosen;
     if ((f & 31) != 0)
       ws.chain_bits[(size_t)(f >> 5) * 64 + lane] = __builtin_bitreverse32(hist) >> (32 - (f & 31));
   }
@@ -589,6 +667,7 @@ __device__ __forceinline__ void lag_store(LagTok* dst, uint8_t* places, const La
 
 __device__ __forceinline__ void chain_walk_lag(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
                                                const Workspace& ws, int wave, int lane, int lin, int& gflex) {
+  own_lane(lane);
   LagTok* const ring = reinterpret_cast<LagTok*>(lds);
   uint8_t* const places = lds + kLagPlaceOffset;
   f0 = __builtin_amdgcn_readfirstlane(f0);
@@ -755,6 +834,7 @@ static_assert((2 * (kPairBatch / 4) + 1) * (int)sizeof(PairGroup) <= kChainLdsBy
 
 __device__ __forceinline__ void chain_walk_pairs(uint8_t* lds, int nflex_tok, const Workspace& ws, int k, int wave,
                                                  int lane, int lin, int& gflex) {
+  own_lane(lane);
   PairGroup* const buf = reinterpret_cast<PairGroup*>(lds);
   constexpr int kGroups = kPairBatch / 4;
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
@@ -1034,6 +1114,7 @@ struct SpecShared {
 template <int CP, int KK>
 __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex_tok, const RouteArgs& a,
                          const Workspace& ws, int wave, int lane, int lin, int& gflex, unsigned& hist) {
+  own_lane(lane);
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
   SpecTok<CP>* ring = reinterpret_cast<SpecTok<CP>*>(lds);
   SpecExp* M = sp.M;
@@ -1234,6 +1315,7 @@ __device__ __forceinline__ void below128(int x, unsigned long long& lo, unsigned
 template <int CP, int KK>
 __device__ __forceinline__ int spec_walk2(uint8_t* lds, int nflex_tok, const RouteArgs& a, const Workspace& ws,
                                           int wave, int lane, int lin, int& gflex, unsigned& hist) {
+  own_lane(lane);
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
   SpecTok<CP>* ring = reinterpret_cast<SpecTok<CP>*>(lds);
   SpecShared2& S = *reinterpret_cast<SpecShared2*>(lds + kShared2Offset);
