@@ -2516,12 +2516,13 @@ __device__ __forceinline__ int finish_fast(int block, FastShared& fs, unsigned l
 
 // What workgroup `block` of the tail grid does (kTailThreads threads): 0 is the chain,
 // b >= 1 finishes tiles kChainWaves * (b - 1) ... .  tail_lds: kChainLdsBytes of LDS.
+template <bool CHAIN>  // block 0 is among them
 __device__ __forceinline__ void tail_role(int block, uint8_t* tail_lds, const RouteArgs& a,
                                           const Workspace& ws, int32_t* __restrict__ loads_inout,
                                           int32_t* __restrict__ expert_offsets,
                                           int32_t* __restrict__ expert_ids, float* __restrict__ weights,
                                           int32_t* __restrict__ permutation) {
-  if (block == 0) {
+  if (CHAIN && block == 0) {
     chain_segments<false, 0>(tail_lds, a, ws, loads_inout, expert_offsets);
     return;
   }
