@@ -25,9 +25,9 @@ namespace laser {
 //           k smallest keys win.  Two evaluations, same result:
 //           - window (wave 0, lane = token): 64 consecutive flexible tokens per sweep,
 //             see "window evaluation" below; used first when there are enough tokens;
-//           - sequential (wave 0, lane = expert): an expert is chosen iff fewer than k
-//             candidate keys are smaller than its own, see "sequential walk" below.  Takes
-//             over where the window evaluation stops paying.
+//           - sequential (wave 0): a candidate is chosen iff fewer than k candidate keys are
+//             smaller than its own, see "sequential walk" and "walks of up to 8 candidates"
+//             below.  Takes over where the window evaluation stops paying.
 //           The other waves stage the records in LDS ahead of wave 0.
 //   totals  loads and offsets, then flag 2.
 //   Output of the chain, per expert: one bit per flexible token of the call in token
@@ -974,7 +974,8 @@ constexpr unsigned kSpecInvalid = 1u << 27;   // counter of a rank beyond the wo
 constexpr int kSpecMinTokens = 256;           // fewer flexible tokens: sequential walk
 constexpr int kSpecCheckSweeps = 8;           // progress is judged over this many sweeps ...
 // ... in which at least this many tokens must retire (measured: a sweep costs about
-// 0.56 / 0.96 us for 4 / 8 candidates, a sequential step 0.07 us; the switch is one-way, so
+// 0.56 / 0.96 us for 4 / 8 candidates, 1.7 us with 128 tokens, a sequential step 0.05 us; a line at
+// 20 tokens per sweep instead changed none of eight regimes tried; the switch is one-way, so
 // the line lies below break-even)
 constexpr int kSpecGuessProgress = 26 * kSpecCheckSweeps;  // (without guesses at most 32 per sweep retire)
 constexpr int spec_min_progress(int cp) { return cp <= 4 ? 40 : cp <= 8 ? 48 : 56; }
