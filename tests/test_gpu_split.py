@@ -192,3 +192,34 @@ def test_split_call_with_random_or_wide_trimming(T, E, k, c, trim):
     else:
         ref = oracle.route(z, k, c, 2.0, 0.05, np.zeros(E, np.int32))
     u.assert_discrete_equal(outs[0], ref, trim)
+
+
+# (one tile each: the fused kernel finishes the call; more: the tail kernel does.  Eight workgroups
+# per tile up to 32 tiles in all, four up to 64, no split beyond)
+@pytest.mark.parametrize("nb,T", [(2, 1), (3, 64), (32, 17), (33, 64), (64, 5), (65, 3), (2, 65), (5, 200), (17, 129)])
+@pytest.mark.parametrize("E,k,c,eps", [(64, 6, 8, 0.4), (8, 2, 4, 2.0), (33, 3, 9, 2.0), (16, 4, 12, 0.6)])
+def test_batched_calls_of_few_tiles(nb, T, E, k, c, eps):
+    u = _util()
+    rng = np.random.default_rng(nb * T + E)
+    gates = [_gate(1000 * nb + T + E + b, T, 256, E, 0.4) for b in range(nb)]
+    loads = [rng.integers(0, 4, size=E).astype(np.int32) for _ in range(nb)]
+    got = u.run_route_batched([g[0] for g in gates], [g[1] for g in gates], wl.DTYPE_BF16, k, c, eps, 0.3, loads,
+                              renormalize=nb % 2 == 0)
+    for b in sorted({0, 1, nb // 2, nb - 1}):
+        one = u.run_route(*gates[b], wl.DTYPE_BF16, k, c, eps, 0.3, loads[b], renormalize=nb % 2 == 0, split_k=1)
+        _same(got[b], one, f"problem {b} of {nb}, T{T} E{E}")
+
+
+@pytest.mark.parametrize("T", [1, 2, 33, 63, 64])
+@pytest.mark.parametrize("E,k,c", [(64, 6, 8), (64, 9, 16), (8, 2, 4), (5, 2, 3), (33, 3, 9)])
+def test_one_tile_of_load_dependent_tokens(T, E, k, c):
+    """Every token load-dependent: walked by the workgroup that analysed the tile."""
+    u = _util()
+    hidden, w = _gate(T + E, T, 512, E, 0.5)
+    for hi in (1, 40):
+        loads = np.random.default_rng(T * hi).integers(0, hi, size=E).astype(np.int32)
+        for renorm in (True, False):
+            gpu, _ = u.check_route(hidden, w, wl.DTYPE_BF16, k, c, 2.0, 1e-30, loads, renormalize=renorm,
+                                   label=f"one tile T{T} E{E} c{c}")
+            whole = u.run_route(hidden, w, wl.DTYPE_BF16, k, c, 2.0, 1e-30, loads, renormalize=renorm, split_k=1)
+            _same(gpu, whole, f"one tile T{T} E{E} c{c}")
