@@ -135,7 +135,7 @@ __device__ __forceinline__ void finish_flexible(OneTile& ot, unsigned long long 
       int at = 0;
       for (int j = 0; j < cs; ++j) {
         const int e = ot.rids[n][j];
-        if ((em >> e) & 1ull) {  // (exactly k bits are set)
+        if (((em >> e) & 1ull) && at < a.k) {  // (exactly k bits are set; at < k keeps the row)
           if ((j & 7) == q) {
             expert_ids[row + at] = e;
             weights[row + at] = ot.p[n][j] / denom;
@@ -418,11 +418,18 @@ __global__ __launch_bounds__(kGateThreads) void gate_split_bf16_kernel(
     }
     __syncthreads();
     const int k = a.k;
+    bool kept = true;
     for (int slot = threadIdx.x; slot < T * k; slot += kGateThreads) {
       const int t = slot / k;
       const int e = expert_ids[slot];
-      permutation[sh_off[e] + __builtin_popcountll(mask64[e] & lanes_below(t))] = slot;
+      // (an expert's number, and a slot's, by construction; the checks turn any inconsistency of
+      // the inputs into a missing entry instead of a stray store)
+      const int pos = sh_off[e & 63] + __builtin_popcountll(mask64[e & 63] & lanes_below(t));
+      const bool ok = (unsigned)e < (unsigned)E && (unsigned)pos < (unsigned)(T * k);
+      if (ok) permutation[pos] = slot;
+      kept = kept && ok;
     }
+    if (!kept) ws.status[kStatusError] = kErrorInconsistent;
   }
 }
 

@@ -223,3 +223,63 @@ def test_one_tile_of_load_dependent_tokens(T, E, k, c):
                                    label=f"one tile T{T} E{E} c{c}")
             whole = u.run_route(hidden, w, wl.DTYPE_BF16, k, c, 2.0, 1e-30, loads, renormalize=renorm, split_k=1)
             _same(gpu, whole, f"one tile T{T} E{E} c{c}")
+
+
+def _guarded_one_tile_call(hidden, w, T, E, k, c, loads, nb=1):
+    """A call of one tile per problem with 64 guard words behind every output; returns
+    (status of each problem, the guards that were written over)."""
+    import torch
+    from paper_2510_03293_amd import binding as B
+    params = B.make_params(k, c, 2.0, 1e-30, dtype=wl.DTYPE_BF16)
+    H = w.shape[-1]
+    one = B.laser_workspace_bytes(T, H, E, params)
+    ws = torch.empty(nb * one, dtype=torch.uint8, device="cuda")
+    sizes = {"ids": nb * T * k, "weights": nb * T * k, "perm": nb * T * k, "offsets": nb * (E + 1), "loads": nb * E}
+    out = {n: torch.full((s + 64,), 123456789, dtype=torch.int32, device="cuda") for n, s in sizes.items()}
+    out["loads"][: nb * E] = torch.tensor(loads, dtype=torch.int32, device="cuda").repeat(nb)
+    args = (params, out["loads"], out["ids"], out["weights"], out["perm"], out["offsets"], None, ws)
+    if nb == 1:
+        B.laser_route(hidden, w, T, H, E, *args)
+    else:
+        B.laser_route_batched(hidden, w, nb, T, H, E, *args)
+    status = [B.laser_status(ws[b * one:]) for b in range(nb)]
+    torch.cuda.synchronize()
+    return status, [n for n, s in sizes.items() if not bool((out[n][s:] == 123456789).all())]
+
+
+@pytest.mark.parametrize("T", [1, 5, 64])
+@pytest.mark.parametrize("nb", [1, 3])
+def test_one_tile_call_keeps_its_rows_when_a_gate_row_is_nan(T, nb):
+    """Inputs must be finite; a NaN row in the gate all the same writes nothing outside the
+    call's buffers.  The sort loses a NaN and lists the expert beside it twice: here expert 1,
+    for NaN in row 0, which the counters make the sixth of the seven that compete for six
+    places, so that its two entries would give the row seven."""
+    import torch
+    E, H, k, c = 64, 512, 6, 8
+    u = torch.sign(torch.randn(H, generator=torch.Generator().manual_seed(T)))
+    scale = torch.full((E,), -0.01)
+    strong = [1, 9, 20, 33, 47, 50, 62]                       # logits 7, 6, ..., 1
+    scale[strong] = torch.arange(7, 0, -1).float() / H
+    w = scale[:, None] * u[None, :]
+    w[0] = float("nan")
+    w = w.to(torch.bfloat16).cuda().repeat(nb, 1, 1)
+    hidden = u.to(torch.bfloat16).cuda().repeat(nb, T, 1)
+    loads = [0] * E
+    loads[1], loads[62] = 100, 1000
+    status, overwritten = _guarded_one_tile_call(hidden, w, T, E, k, c, loads, nb)
+    assert not overwritten
+    assert all(s in (0, 2) for s in status)
+
+
+@pytest.mark.parametrize("T", [1, 64])
+def test_one_tile_call_reports_what_cannot_be_dispatched(T):
+    """A gate of NaN only: what fills the ranks of missing experts comes before them all, ids
+    of no expert are listed, and the call says that its tables are incomplete."""
+    import torch
+    from paper_2510_03293_amd import binding as B
+    E, H, k, c = 5, 256, 2, 3
+    w = torch.full((E, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hidden = torch.ones((T, H), dtype=torch.bfloat16, device="cuda")
+    status, overwritten = _guarded_one_tile_call(hidden, w, T, E, k, c, [0] * E)
+    assert not overwritten
+    assert status == [B.STATUS_INCONSISTENT]
