@@ -442,7 +442,8 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
           const unsigned load = base + G;
           const uint4 bits_n = next.bits[lane];
           const unsigned base_n = next.base[lane];
-          // (what is read out of a comparison's scalar is at least two instructions behind it)
+          // (what is read out of a comparison's scalar is at least two instructions behind it; the
+          // named registers are the blocks' own, since k and k - 1 are read after they are written)
           unsigned x;
           unsigned long long kth;
           asm("v_cmp_eq_u32 s[88:89], %[load], %[level]\n\t"           // on the level
@@ -462,11 +463,11 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
               "v_and_b32 %[x], s94, %[r0]\n\t"
               "v_bitop3_b32 %[x], %[r1], %[x], s95 bitop3:0xec\n\t"    // by expert
               "v_min_u32 %[x], 1, %[x]\n\t"
-              "s_cselect_b64 s[92:93], 0, s[92:93]\n\t"
-              : [hist] "+v"(hist), [x] "=&v"(x), [kth] "={s[92:93]}"(kth)
+              "s_cselect_b64 %[kth], 0, s[92:93]\n\t"
+              : [hist] "+v"(hist), [x] "=&v"(x), [kth] "=&s"(kth)
               : [load] "v"(load), [level] "v"(level), [chosen] "v"(chosen), [id0] "v"(bits.x), [id1] "v"(bits.y),
                 [r0] "v"(bits.z), [r1] "v"(bits.w), [none] "v"(none), [k] "s"(k), [km1] "s"(k - 1)
-              : "s88", "s89", "s90", "s91", "s94", "s95", "scc");
+              : "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95", "scc");
           chosen = x;
           if (__builtin_expect(kth == 0ull, 0)) {
             // fewer than k on the level (or somebody below it): all of those, and the lowest ranks
@@ -493,10 +494,12 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
                 "v_bitop3_b32 %[x], %[r1], %[x], s95 bitop3:0xec\n\t"
                 "v_min_u32 %[x], 1, %[x]\n\t"
                 "v_cndmask_b32 %[x], %[x], 1, s[90:91]\n\t"
-                : [x] "=&v"(x), [n0] "=&v"(n0), [below] "={s[88:89]}"(below), [kth] "={s[92:93]}"(kth)
+                "s_mov_b64 %[below], s[88:89]\n\t"
+                "s_mov_b64 %[kth], s[92:93]\n\t"
+                : [x] "=&v"(x), [n0] "=&v"(n0), [below] "=&s"(below), [kth] "=&s"(kth)
                 : [load] "v"(load), [level] "v"(level), [next] "v"(level + 1u), [id0] "v"(bits.x), [id1] "v"(bits.y),
                   [r0] "v"(bits.z), [r1] "v"(bits.w), [none] "v"(none), [k] "s"(k), [km1] "s"(k - 1)
-                : "s90", "s91", "s94", "s95");
+                : "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95");
             chosen = x;
             if (kth != 0ull && below == 0ull)
               ++level;
