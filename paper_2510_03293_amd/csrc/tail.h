@@ -823,123 +823,175 @@ __device__ __forceinline__ void chain_walk_lag(uint8_t* lds, int f0, unsigned hi
 }
 
 // Up to 8 experts (all of a call's flexible tokens).  A pair is one of experts: the lane itself
-// keeps the difference of their choices, counts for both and adds (j chosen) - (i chosen); nothing
-// is exchanged at all, nine instructions per token.  Lanes 28 to 35 count for one expert each,
-// for the output.
-// Waves 1 to 3 prepare U, eight tokens per memory instruction, 96 tokens per batch.
-// 8 experts, k = 2, c = 4: 21 ns per token (the window evaluation took 50: four layers of 16384 tokens,
-// a tenth of them load-dependent, 471 -> 322 us).
-constexpr int kPairBatch = 96;  // tokens per LDS batch: 32 per producer wave
+// keeps the difference D of their choices, counts for both and adds (j chosen) - (i chosen);
+// nothing is exchanged at all.  Eight instructions per token and none that only waits: the
+// comparison is T <= U - D, with T what the token before adds and U - D made behind that token's
+// comparison.  Lanes 28 to 35 count for one expert each, for the output: there D is shifted by
+// one per token, and holds the experts' last 32 choices.
+// What bounds a step: eight instructions at 4.7 cycles, and a sixteen-byte read per four tokens, issued
+// for about 16 (two groups ahead, held there against the compiler, which would sink it to its use).
+// Waves 1 and 2 prepare U, eight tokens per memory instruction, 96 tokens per batch; wave 3 writes
+// out the choices (whose stores the producers' loads would wait for).
+// 8 experts, k = 2, c = 4, every one of 16384 tokens load-dependent: 17.7 ns per token whatever the
+// counters are, the call 318 us.  (Nine instructions and a wait, and 32 lane exchanges and 32 writes per
+// 16 tokens in the producers: 21.6 ns, 379 us.  The window evaluation: 303 us where no tokens compete,
+// 1906 us where they do.)  Four layers of 16384 tokens, a tenth of them load-dependent: 316 -> 290 us.
+constexpr int kPairBatch = 96;  // tokens per LDS batch: 48 per producer wave
 struct PairGroup {
-  int4 v[64];  // U of four tokens
+  int4 v[32];  // per pair: U of four tokens
 };
-static_assert((2 * (kPairBatch / 4) + 1) * (int)sizeof(PairGroup) <= kChainLdsBytes, "two batches and a group of read-ahead");
+constexpr int kPairGroups = kPairBatch / 4, kPairWords = kPairBatch / 32;
+// A ring of three batches (the consumer reads two groups ahead, so the batch behind the current one is
+// complete before the current one is begun), and two batches' words of output.
+constexpr int kPairOutOffset = 3 * kPairGroups * (int)sizeof(PairGroup);
+static_assert(kPairOutOffset + 2 * kPairWords * 64 * 4 <= kChainLdsBytes, "ring and output");
+constexpr int kPairLoads = kPairBatch / 2 / 8;  // of eight tokens each, per producer and batch
 
 __device__ __forceinline__ void chain_walk_pairs(uint8_t* lds, int nflex_tok, const Workspace& ws, int k, int wave,
                                                  int lane, int lin, int& gflex) {
   own_lane(lane);
-  PairGroup* const buf = reinterpret_cast<PairGroup*>(lds);
-  constexpr int kGroups = kPairBatch / 4;
+  PairGroup* const ring = reinterpret_cast<PairGroup*>(lds);
+  unsigned (*const out)[64] = reinterpret_cast<unsigned (*)[64]>(lds + kPairOutOffset);
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
   const int nb = (nflex_tok + kPairBatch - 1) / kPairBatch;
   int pi, pj;
-  lane_pair(lane, pi, pj);
-  if (wave != 0) {
-    // ---- producers: lane (s, e): token s of eight, expert e -------------------------------
+  if (wave == 1 || wave == 2) {
+    // ---- producers: lane (s, e): token s of eight, expert e; then lane (h, p): pair p of tokens
+    // 4 h .. 4 h + 3 -----------------------------------------------------------------------
+    lane_pair(lane & 31, pi, pj);
     const int pw = wave - 1;
     const int lin_e = __builtin_amdgcn_ds_bpermute(4 * (lane & 7), lin);
-    int slot[4], base[4];
-    unsigned rec[4];
-    auto first = [&](int n, int r) { return n * kPairBatch + 32 * pw + 8 * r; };
+    const int at_i = 128 * (lane >> 5) + 4 * pi, at_j = 128 * (lane >> 5) + 4 * pj;
+    int slot[kPairLoads], base[kPairLoads];
+    unsigned rec[kPairLoads];
+    auto first = [&](int n, int r) { return n * kPairBatch + kPairBatch / 2 * pw + 8 * r; };
     auto load_slots = [&](int n) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) slot[r] = lag_slot(first(n, r) + (lane >> 3), nflex_tok, ws);
+      for (int r = 0; r < kPairLoads; ++r) slot[r] = lag_slot(first(n, r) + (lane >> 3), nflex_tok, ws);
     };
     auto load_records = [&]() {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
+      for (int r = 0; r < kPairLoads; ++r) {
         rec[r] = ws.rec_lane[(size_t)slot[r] * 8 + (lane & 7)];
         base[r] = ws.tile_base[(size_t)(slot[r] >> 6) * 64 + (lane & 7)];
       }
     };
-    auto store = [&](int n) {
-      int* dst = reinterpret_cast<int*>(buf + (n & 1) * kGroups + 8 * pw) + 4 * lane;
+    int buf = 0;  // of batch n
+    auto fill = [&](int n) {
+      PairGroup* dst = ring + buf * kPairGroups + kPairGroups / 2 * pw + (lane >> 5);
+      buf = buf == 2 ? 0 : buf + 1;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        // (tokens behind the last one: whatever comes out, their bits are not taken)
-        const int key = rec[r] != 0xFFFFu ? ((lin_e + base[r]) << 4) + (int)rec[r] : -1;
+      for (int r = 0; r < kPairLoads; ++r) {
+        // (counter << 3) + rank, below 2^30; who is no candidate is as far behind that as the choices
+        // can differ.  (Tokens behind the last one: whatever comes out, their bits are not taken)
+        const int key = rec[r] != 0xFFFFu ? ((lin_e + base[r] + (int)(rec[r] >> 4)) << 3) + (int)(rec[r] & 7u) : 0x7FFFFFF8;
+        int u[4];
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const int ki = __builtin_amdgcn_ds_bpermute(4 * (8 * s + pi), key);
-          const int kj = __builtin_amdgcn_ds_bpermute(4 * (8 * s + pj), key);
-          dst[(2 * r + (s >> 2)) * 256 + (s & 3)] = pair_bound(ki, kj);
+        for (int q = 0; q < 4; ++q) {
+          const int ki = __builtin_amdgcn_ds_bpermute(at_i + 32 * q, key);
+          const int kj = __builtin_amdgcn_ds_bpermute(at_j + 32 * q, key);
+          u[q] = (ki + ~kj) >> 3;  // kj + 8 G[j] < ki + 8 G[i]
         }
+        dst[2 * r].v[lane & 31] = make_int4(u[0], u[1], u[2], u[3]);
       }
     };
     load_slots(0);
     load_records();
     load_slots(1);
-    store(0);
+    fill(0);
     load_records();
     load_slots(2);
+    fill(1);
+    load_records();
+    load_slots(3);
     lds_barrier();
     for (int n = 0; n < nb; ++n) {
-      store(n + 1);  // (behind the last batch: not read)
+      fill(n + 2);  // (behind the last batch: not used)
       load_records();
-      load_slots(n + 3);
+      load_slots(n + 4);
       lds_barrier();
     }
+  } else if (wave == 3) {
+    // ---- output: the words that the consumer has left of a batch (lane = expert; the first token's
+    // bit is the highest, and set where the expert is not chosen) -----------------------------
+    int before = 0;
+    auto put_out = [&](int n) {
+#pragma unroll
+      for (int u = 0; u < kPairWords; ++u) {
+        const int w = n * kPairWords + u, left = nflex_tok - 32 * w;
+        if (left <= 0) break;
+        const unsigned all = ~out[(n & 1) * kPairWords + u][(28 + lane) & 63];
+        const unsigned word = lane < 8 ? __builtin_bitreverse32(all) & (left < 32 ? (1u << left) - 1u : ~0u) : 0u;
+        before += __builtin_popcount(word);
+        ws.chain_bits[(size_t)w * 64 + lane] = word;
+        if (left >= 32) ws.chain_cum[(size_t)(w + 1) * 64 + lane] = before;
+      }
+    };
+    lds_barrier();
+    for (int n = 0; n < nb; ++n) {
+      if (n > 0) put_out(n - 1);
+      lds_barrier();
+    }
+    put_out(nb - 1);
   } else {
     // ---- consumer ----------------------------------------------------------------------
-    int D = 0, G = 0;  // (G: of the output lane's expert)
+    lane_pair(lane, pi, pj);
+    int D = 0, T = 0, G = 0;  // (G: of the output lane's expert)
     const bool output = lane >= 28 && lane < 36;
-    const PairCount count_i = pair_count(output ? lane - 28 : pi, pi, pj, lane), count_j = pair_count(pj, pi, pj, lane);
+    const PairCount count_i = pair_count(output ? lane - 28 : pi, pi, pj, lane);
+    PairCount count_j = pair_count(pj, pi, pj, lane);
+    if (output) count_j = {0u, 0u};  // (fewer than k: T is 0 where the expert is chosen, else 1)
+    const int shift = output ? 1 : 0;
     const int minus_k = -k;
-    unsigned hist = 0;
-    int ci = 0, cj;
-    // (in assembly for the order, see chain_walk_lag; the counts, of which byte 3 is the sign, are
-    // added to D as they are)
-#define LASER_PAIR_STEP(U_)                                                                      \
-  "v_cmp_le_i32 vcc, %[D], " U_ "\n\t"                                                  \
-  "v_alignbit_b32 %[hist], %[hist], %[ci], 31\n\t" /* (the token before) */                     \
-  "s_nop 0\n\t"                                                                                 \
-  "v_bitop3_b32 %[ci], %[fi], %[mi], vcc_lo bitop3:0x48\n\t" /* (pairs ^ flip) & mask */     \
-  "v_bitop3_b32 %[cj], %[fj], %[mj], vcc_lo bitop3:0x48\n\t"                                 \
-  "v_bcnt_u32_b32 %[ci], %[ci], %[mk]\n\t" /* (negative: chosen) */                             \
-  "v_bcnt_u32_b32 %[cj], %[cj], %[mk]\n\t"                                                      \
-  "v_add_u32_sdwa %[D], %[D], sext(%[ci]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3\n\t" \
-  "v_sub_u32_sdwa %[D], %[D], sext(%[cj]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3\n\t"
-    auto steps = [&](const int4& x) {
-      asm(LASER_PAIR_STEP("%[x0]") LASER_PAIR_STEP("%[x1]") LASER_PAIR_STEP("%[x2]") LASER_PAIR_STEP("%[x3]")
-          : [D] "+v"(D), [hist] "+v"(hist), [ci] "+v"(ci), [cj] "=&v"(cj)
-          : [x0] "v"(x.x), [x1] "v"(x.y), [x2] "v"(x.z), [x3] "v"(x.w), [fi] "v"(count_i.flip), [mi] "v"(count_i.mask),
-            [fj] "v"(count_j.flip), [mj] "v"(count_j.mask), [mk] "s"(minus_k)
+    // (in assembly for the order, see chain_walk_lag; the counts are negative where the expert is
+    // chosen: byte 3 is the sign)
+#define LASER_PAIR_STEP(U_NEXT_)                                                               \
+  "v_cmp_le_i32 vcc, %[T], %[V]\n\t"                                                          \
+  "v_lshl_add_u32 %[D], %[D], %[shift], %[T]\n\t"                                             \
+  "v_sub_u32 %[V], " U_NEXT_ ", %[D]\n\t"                                                     \
+  "v_bitop3_b32 %[ci], %[fi], %[mi], vcc_lo bitop3:0x48\n\t" /* (pairs ^ flip) & mask */      \
+  "v_bitop3_b32 %[cj], %[fj], %[mj], vcc_lo bitop3:0x48\n\t"                                  \
+  "v_bcnt_u32_b32 %[ci], %[ci], %[mk]\n\t"                                                    \
+  "v_bcnt_u32_b32 %[cj], %[cj], %[mk]\n\t"                                                    \
+  "v_sub_u32_sdwa %[T], sext(%[ci]), sext(%[cj]) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:BYTE_3\n\t"
+    int V;
+    auto steps = [&](const int4& x, int next) {
+      int ci, cj;
+      asm(LASER_PAIR_STEP("%[x1]") LASER_PAIR_STEP("%[x2]") LASER_PAIR_STEP("%[x3]") LASER_PAIR_STEP("%[x4]")
+          : [D] "+v"(D), [T] "+v"(T), [V] "+v"(V), [ci] "=&v"(ci), [cj] "=&v"(cj)
+          : [x1] "v"(x.y), [x2] "v"(x.z), [x3] "v"(x.w), [x4] "v"(next), [fi] "v"(count_i.flip), [mi] "v"(count_i.mask),
+            [fj] "v"(count_j.flip), [mj] "v"(count_j.mask), [mk] "s"(minus_k), [shift] "v"(shift)
           : "vcc");
     };
 #undef LASER_PAIR_STEP
     lds_barrier();
+    const PairGroup* cur = ring;
+    int4 x = cur[0].v[lane & 31], x_1 = cur[1].v[lane & 31];
+    V = x.x;
+    unsigned all = 0;
     for (int n = 0; n < nb; ++n) {
-      const PairGroup* cur = buf + (n & 1) * kGroups;
-      int4 x = cur->v[lane];
-      for (int f = n * kPairBatch; f < min(nflex_tok, (n + 1) * kPairBatch); f += 32) {
+      const int words = min(kPairWords, (nflex_tok - n * kPairBatch + 31) >> 5);
+      for (int u = 0; u < words; ++u) {
+        const PairGroup* const next = cur + 8 == ring + 3 * kPairGroups ? ring : cur + 8;
 #pragma unroll
         for (int g = 0; g < 8; ++g) {
-          ++cur;
-          const int4 x_n = cur->v[lane];  // (behind the last group of a batch: read and not used)
-          steps(x);
-          x = x_n;
+          // (behind the call's last token: read and not used)
+          const int4 x_2 = g < 6 ? cur[g + 2].v[lane & 31] : next[g - 6].v[lane & 31];
+          __builtin_amdgcn_sched_barrier(0);
+          steps(x, x_1.x);
+          __builtin_amdgcn_sched_barrier(0);
+          x = x_1;
+          x_1 = x_2;
         }
-        // (32 bits went in, the first of them the last one of the word before, or nothing)
-        const unsigned all = __builtin_amdgcn_alignbit(hist, (unsigned)ci, 31);
-        const int left = nflex_tok - f;
-        const unsigned word = output ? __builtin_bitreverse32(all) & (left < 32 ? (1u << left) - 1u : ~0u) : 0u;
-        G += __builtin_popcount(word);
-        const size_t at = (size_t)(f >> 5) * 64 + ((lane + 36) & 63);  // (lane 28: expert 0)
-        ws.chain_bits[at] = word;
-        if (left >= 32) ws.chain_cum[at + 64] = G;
+        cur = next;
+        all = ((unsigned)D << 1) + (unsigned)T;  // (the last token's T is not in D yet)
+        out[(n & 1) * kPairWords + u][lane] = all;
+        G += 32 - __builtin_popcount(all);
       }
       lds_barrier();
     }
+    // (the bits behind the call's last token do not count)
+    G -= __builtin_popcount(~all & ((1u << (-nflex_tok & 31)) - 1u));
     gflex = __builtin_amdgcn_ds_bpermute(4 * (28 + (lane & 7)), G);
     gflex = lane < 8 ? gflex : 0;
   }
