@@ -754,6 +754,9 @@ __device__ __forceinline__ void chain_walk_lag(uint8_t* lds, int f0, unsigned hi
     const LagTok* const ring_end = ring + 3 * kLagBatch;
     int4 d0 = cur[0].v[pair], d1 = cur[1].v[pair], d2 = cur[2].v[pair], d3 = cur[3].v[pair];
     unsigned place = cur_places[row(0)], place1 = cur_places[row(1)];
+    // (no bytes from here on: carried as bytes they would be widened, hence waited for, at the head of
+    // every batch)
+    asm volatile("" : "+v"(place), "+v"(place1));
     int i1 = gather(d1.y), j1 = gather(d1.z);
     // (the choice before the first token is in G)
     int diff = gather(d0.z) - gather(d0.y);
@@ -1009,9 +1012,8 @@ __device__ __forceinline__ void chain_walk_pairs(uint8_t* lds, int nflex_tok, co
 // choices of tokens 0..q are final: each was computed from choices that did not change,
 // hence from final ones (induction from the window head, whose inputs are all final).
 // They leave the window, the next tokens enter with an empty tentative choice.  The
-// result is the sequential one exactly, whatever the order of evaluation.  A sweep
-// costs about as much as five sequential steps; if a run of sweeps retires fewer
-// tokens than that, the workgroup goes back to the sequential walk for the rest.
+// result is the sequential one exactly, whatever the order of evaluation.  If too few
+// tokens retire per sweep, the workgroup goes over to the sequential walk for the rest.
 //
 // Lane = token side: candidates by rank (ids), their counters without any flexible
 // choice (b: loads_in + fixed prefix of the tile + fixed tokens before it inside the
@@ -1027,12 +1029,22 @@ constexpr int kSpecSeg = 192;                 // tokens per segment (64 per prod
 constexpr int kSpecRing = 3 * kSpecSeg;       // tokens in the LDS ring
 constexpr unsigned kSpecInvalid = 1u << 27;   // counter of a rank beyond the working set
 constexpr int kSpecMinTokens = 256;           // fewer flexible tokens: sequential walk
-constexpr int kSpecCheckSweeps = 8;           // progress is judged over this many sweeps ...
-// ... in which at least this many tokens must retire (measured: a sweep costs about
-// 0.56 / 0.96 us for 4 / 8 candidates, 1.7 us with 128 tokens, a sequential step 0.05 us; a line at
-// 20 tokens per sweep instead changed none of eight regimes tried; the switch is one-way, so
-// the line lies below break-even)
+constexpr int kSpecCheckSweeps = 8;           // progress is judged over this many sweeps
 constexpr int kSpecGuessProgress = 26 * kSpecCheckSweeps;  // (without guesses at most 32 per sweep retire)
+// Window of 64, up to 8 candidates.  Break-even with the walk: a sweep costs 0.56 / 0.9 us for 4 / 8
+// candidates, a step of the walk 0.052, so 10.8 / 17.3 tokens per sweep.  It is given up when a run of
+// sweeps is below that and the sweeps so far have cost more than walking their tokens -- if the run
+// retired at least half of break-even, more by a walk over an eighth of the tokens that are left.
+// The first sweeps, of tokens that all come in without a choice, mostly also at counters that are
+// still equal, are not judged.  (16384 tokens, all load-dependent, 9 to 31 experts: 310..470 us in windows
+// where no tokens compete, 850 walked; where they do, 860 with the attempt.)
+constexpr int spec_break_even(int cp) { return cp <= 4 ? 88 : 140; }  // per kSpecCheckSweeps
+constexpr int kSpecWarmUp = 4;
+// All other windows: fewer than this many tokens in the last run of sweeps, and in all of them on the
+// average.  Far below break-even: these lines are from when a step of the walk cost 0.17 us.
+// A sweep costs 1.0 / 1.7 us in the window of 128 (4 / 8 candidates), so with up to 8 candidates that
+// window is held on to between about 6 and 20 to 32 tokens per sweep, where the walk would be the
+// faster one (16 experts, k = 2, c = 4, 9862 load-dependent tokens, 8 per sweep: 1196 us; walked 525).
 constexpr int spec_min_progress(int cp) { return cp <= 4 ? 40 : cp <= 8 ? 48 : 56; }
 
 template <int CP>
@@ -1292,13 +1304,20 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
         __builtin_amdgcn_wave_barrier();
         done += fin;
         ++total_sweeps;
-        if (++sweeps == kSpecCheckSweeps) {
-          // give up only if both the last run of sweeps and the average so far are
-          // below break-even: the switch is one-way
-          if (done - done_mark < spec_min_progress(CP) &&
-              done * kSpecCheckSweeps < spec_min_progress(CP) * total_sweeps &&
-              nflex_tok - done > 2 * kSpecSeg)
+        if (CP <= 8 && total_sweeps == kSpecWarmUp) {
+          sweeps = 0;
+          done_mark = done;
+        } else if (++sweeps == kSpecCheckSweeps) {
+          // (the switch is one-way)
+          const int progress = done - done_mark, left = nflex_tok - done;
+          if (CP <= 8) {
+            constexpr int line = spec_break_even(CP);
+            const int lost = total_sweeps * line / kSpecCheckSweeps - done;  // in tokens walked
+            if (left > 64 && progress < line && lost > (progress < line / 2 ? 0 : left / 8)) bail = true;
+          } else if (progress < spec_min_progress(CP) && done * kSpecCheckSweeps < spec_min_progress(CP) * total_sweeps &&
+                     left > 2 * kSpecSeg) {
             bail = true;
+          }
           sweeps = 0;
           done_mark = done;
         }
@@ -1912,18 +1931,24 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
 
   int decided = 0;
   unsigned hist0 = 0;
-  if (use_spec && EP != 8) {
+  if (use_spec && EP != 8 && a.EP != 8) {
     // With many experts per candidate tokens rarely compete: first guesses and the window of 128.
-    // With fewer every sweep ends at an early conflict, and then the walk of up to 8 candidates is
-    // the faster one (8 experts: 50 ns per token against 21).
+    // With fewer a sweep may end at an early conflict: the window of 64, which is given up where the
+    // walk is faster.  (Up to 8 experts the walk always is, or nearly: 17.7 ns per token against at least 16.)
     if (a.c <= 4) {
       if (a.E >= 16)
         decided = a.k == 2 ? spec_walk2<4, 2>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
                            : spec_walk2<4, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+      else if (EP == 0 || EP == 16)
+        decided = a.k == 2 ? spec_walk<4, 2>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
+                           : spec_walk<4, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else if (a.c <= 8) {
       if ((EP == 0 || EP >= 32) && a.E >= 32)
         decided = a.k == 6 ? spec_walk2<8, 6>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
                            : spec_walk2<8, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+      else if (EP <= 32)
+        decided = a.k == 6 ? spec_walk<8, 6>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
+                           : spec_walk<8, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else if ((EP == 0 || EP == 64) && a.E == 64) {
       decided = spec_walk2<16, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else {

@@ -16,6 +16,20 @@ def _check(T, E, k, c, logits, loads_in, eps, label):
     u.check_from_logits(logits, k, c, eps, 1e-30, loads_in, label=label)
 
 
+def _sweeps(T, E, k, c, logits, loads_in, label):
+    """_check with every token load-dependent; the sweeps of the window evaluation (the fourth of
+    the workspace's status words)."""
+    import oracle
+    import torch
+    from paper_2510_03293_amd import binding as B
+    from tests import gpu_util as u
+    loads = torch.from_numpy(np.ascontiguousarray(loads_in, dtype=np.int32)).cuda()
+    buf = B.route_from_logits(torch.from_numpy(logits).cuda(), B.make_params(k, c, 2.0, 1e-30), loads)
+    torch.cuda.synchronize()
+    u.assert_discrete_equal(u._collect(buf, loads, None), oracle.route(logits, k, c, 2.0, 1e-30, loads_in), label)
+    return int(buf.workspace[:16].view(torch.int32)[3])
+
+
 @pytest.mark.parametrize("T", [1, 15, 16, 17, 32, 33, 48, 95, 96, 97, 128, 193, 255, 256, 257, 700])
 @pytest.mark.parametrize("E,k,c", [(8, 2, 4), (8, 7, 8), (3, 1, 2), (9, 2, 3), (16, 4, 8), (33, 5, 7), (64, 1, 8), (64, 7, 8)])
 def test_walks_of_up_to_eight_candidates(T, E, k, c):
@@ -44,3 +58,46 @@ def test_walk_takes_over_inside_a_word():
         base = wl.random_logits(T, 1, E, kind="normal", scale=1.0)
         logits = (base + wl.random_logits(T + 1, T, E, kind="normal", scale=0.05)).astype(np.float32)
         _check(T, E, k, c, logits, np.zeros(E, np.int32), 2.0, f"handover T{T} E{E}")
+
+
+# (9 to 31 experts: the window of 64 tokens, for up to 4, 8 and 16 candidates, k fixed at compile time or not)
+WINDOW_64 = [(9, 2, 3), (15, 2, 4), (12, 3, 4), (12, 3, 6), (16, 4, 8), (24, 4, 8), (31, 6, 8), (31, 4, 12)]
+
+
+@pytest.mark.parametrize("E,k,c", WINDOW_64)
+def test_window_where_tokens_do_not_compete(E, k, c):
+    """Counters so far apart that no choice changes the order of the candidates: the window
+    decides every token, 32 per sweep."""
+    T = 2000
+    loads = (np.random.default_rng(E).permutation(E) * 10 * T).astype(np.int32)
+    n = _sweeps(T, E, k, c, wl.random_logits(E, T, E, kind="normal", scale=1.0), loads, f"far E{E} c{c}")
+    assert T // 32 <= n <= T // 32 + 4
+
+
+@pytest.mark.parametrize("T", [256, 300, 321, 2000])
+@pytest.mark.parametrize("E,k,c", [x for x in WINDOW_64 if x[2] <= 8])
+def test_window_is_given_up_where_tokens_compete(T, E, k, c):
+    """One row for all tokens, equal counters: a token or a few per sweep, so that the walk takes
+    over at the first look, after four sweeps that are not judged and eight that are."""
+    logits = np.repeat(wl.random_logits(E + T, 1, E, kind="normal", scale=1.0), T, axis=0)
+    n = _sweeps(T, E, k, c, logits, np.zeros(E, np.int32), f"competing E{E} c{c}")
+    assert n == 12
+
+
+@pytest.mark.parametrize("E,k,c", [(64, 6, 8), (64, 2, 4), (64, 9, 16), (40, 3, 16)] + WINDOW_64)
+def test_window_gives_way_inside_a_word(E, k, c):
+    """Tokens with unrelated candidates at counters far apart, then one row for all tokens at
+    counters that have come close: the window is entered, given up, and the walk goes on from wherever
+    that was."""
+    for T1 in (333, 901):
+        T = T1 + 1500
+        rng = np.random.default_rng(E + T1)
+        row = wl.random_logits(E + c, 1, E, kind="normal", scale=1.0)
+        far = wl.random_logits(E + T1, T1, E, kind="normal", scale=1.0)
+        loads = np.zeros(E, np.int32)
+        best = np.argsort(-row[0])[:c]          # the row's candidates: equal counters, the others behind
+        loads[np.setdiff1d(np.arange(E), best)] = rng.permutation(E - c) * 4000 + 20000
+        far[:, best] -= 50.0                    # (the first tokens do not have them, where there are others)
+        n = _sweeps(T, E, k, c, np.concatenate([far, np.repeat(row, T - T1, axis=0)]).astype(np.float32), loads,
+                    f"hand-over E{E} c{c} T1 {T1}")
+        assert 0 < n < T - 200                  # (fewer sweeps than tokens by far: the walk took the rest)
