@@ -29,10 +29,10 @@ namespace laser {
 
 // The load-dependent tokens of a one-tile call, by the workgroup that analysed it.
 struct OneTile {
-  unsigned rec[kTile][64];             // the n-th one's record row (lane = expert)
-  uint8_t cids[kTile][16];             // its candidates by rank, padded
-  uint8_t rids[kTile][16];             // its experts by rank
-  float p[kTile][16];                  // their probabilities
+  unsigned rec[kTile + 1][64];         // the n-th one's record row (lane = expert); kSeqNoCand: no candidate
+  uint8_t cids[kTile + 1][16];         // its candidates by rank, padded (one row of read-ahead)
+  __align__(16) uint8_t rids[kTile][16];  // its experts by rank
+  __align__(16) float p[kTile][16];    // their probabilities
   float Z[kTile];                      // the softmax denominator
   int cstar[kTile], tok[kTile];        // candidates, token
   unsigned long long chosen[kTile];    // the experts chosen for it
@@ -76,7 +76,7 @@ __device__ __forceinline__ void finish_flexible(OneTile& ot, unsigned long long 
     for (int u = 0; u < kPer; ++u) {
       const int n = wave + u * kGateWaves;
       if (n < n_flex) {
-        ot.rec[n][lane] = rec[u];
+        ot.rec[n][lane] = rec[u] == 0xFFFFu ? kSeqNoCand : rec[u];
         if (lane < 4) reinterpret_cast<unsigned*>(ot.cids[n])[lane] = more[u];
         else if (lane < 8) reinterpret_cast<unsigned*>(ot.rids[n])[lane - 4] = more[u];
         else if (lane < 24) ot.p[n][lane - 8] = __uint_as_float(more[u]);
@@ -88,59 +88,82 @@ __device__ __forceinline__ void finish_flexible(OneTile& ot, unsigned long long 
   }
   __syncthreads();
   // ---- token after token, lane = expert -------------------------------------------------
+  // What bounds it is one wavefront's chain of dependent instructions, as in the walks of the tail
+  // kernel, so the next token's record is read while this one's keys are exchanged.  (64 tokens,
+  // all load-dependent, 64 experts, c = 8, H = 2048: the call 37.7 -> 28.7 us, with 8 experts, c = 4,
+  // H = 4096 31.6 -> 24.8.)
   if (wave == 0) {
-    int base = lin;  // (the fixed tokens before a token are in its record)
-    unsigned long long mine = 0ull;
-    for (int n = 0; n < n_flex; ++n) {
-      const unsigned rec = ot.rec[n][lane];
-      const bool cand = rec != 0xFFFFu;
-      const unsigned key = cand ? ((unsigned)base << 4) + rec : 0xFFFFFFFFu;
-      bool chosen;
-      if (a.c <= 8) {
-        // all pairs of candidates by rank (i, j) = (lane / 8, lane % 8) at once: byte i of the
-        // comparisons has fewer than k bits
-        const unsigned ki = (unsigned)__builtin_amdgcn_ds_bpermute(4 * ot.cids[n][lane >> 3], (int)key);
-        const unsigned kj = (unsigned)__builtin_amdgcn_ds_bpermute(4 * ot.cids[n][lane & 7], (int)key);
-        const unsigned long long less = __builtin_amdgcn_ballot_w64(kj < ki);
-        const unsigned row = (unsigned)(less >> (8 * (rec & 7u))) & 0xFFu;
-        chosen = cand && __builtin_popcount(row) < a.k;
-      } else {
-        chosen = chain_step(key, cand, *reinterpret_cast<const uint4*>(ot.cids[n]), a.k);
-      }
-      base += chosen ? 1 : 0;
-      const int tok = __builtin_amdgcn_readfirstlane(ot.tok[n]);
-      mine |= (unsigned long long)(chosen ? 1u : 0u) << tok;
+    unsigned base = (unsigned)lin;  // (the fixed tokens before a token are in its record)
+    unsigned em_lo = 0, em_hi = 0;  // lane n: the experts chosen for token n
+    unsigned rec = ot.rec[0][lane];
+    auto keep = [&](int n, bool chosen) {
       const unsigned long long em = __builtin_amdgcn_ballot_w64(chosen);
-      if (lane == 0) ot.chosen[n] = em;
+      em_lo = lane == n ? (unsigned)em : em_lo;
+      em_hi = lane == n ? (unsigned)(em >> 32) : em_hi;
+      base += chosen ? 1u : 0u;
+    };
+    if (a.c <= 8) {
+      // all pairs of candidates by rank (i, j) = (lane / 8, lane % 8) at once: byte i of the
+      // comparisons has fewer than k bits
+      unsigned ai = ot.cids[0][lane >> 3], aj = ot.cids[0][lane & 7];
+      for (int n = 0; n < n_flex; ++n) {
+        const unsigned key = (base << 4) + rec;
+        const unsigned ki = (unsigned)__builtin_amdgcn_ds_bpermute((int)(4 * ai), (int)key);
+        const unsigned kj = (unsigned)__builtin_amdgcn_ds_bpermute((int)(4 * aj), (int)key);
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned rec_n = ot.rec[n + 1][lane];
+        const unsigned ai_n = ot.cids[n + 1][lane >> 3], aj_n = ot.cids[n + 1][lane & 7];
+        const int shift = 8 * (int)(rec & 7u), none = (int)rec < 0 ? 64 : 0;
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned long long less = __builtin_amdgcn_ballot_w64(kj < ki);
+        const int before = __builtin_popcount((unsigned)(less >> shift) & 0xFFu) + none;
+        keep(n, before < a.k);
+        rec = rec_n;
+        ai = ai_n;
+        aj = aj_n;
+      }
+    } else {
+      uint4 ids = *reinterpret_cast<const uint4*>(ot.cids[0]);
+      for (int n = 0; n < n_flex; ++n) {
+        const unsigned key = (base << 4) + rec;
+        const bool cand = (int)rec >= 0;
+        rec = ot.rec[n + 1][lane];
+        const uint4 ids_n = *reinterpret_cast<const uint4*>(ot.cids[n + 1]);
+        keep(n, chain_step(key, cand, ids, a.k));
+        ids = ids_n;
+      }
     }
-    mask64[lane] |= mine;
+    ot.chosen[lane] = ((unsigned long long)em_hi << 32) | em_lo;
   }
   __syncthreads();
-  // ---- ids and weights: thread = (token, one of eight), each its share of the chosen ranks ----
+  // ---- ids, weights, masks: thread = (token, one of eight), which has ranks q and q + 8 -----
   {
     const int n = threadIdx.x >> 3, q = threadIdx.x & 7;
     if (n < n_flex) {
       const unsigned long long em = ot.chosen[n];
-      const int cs = ot.cstar[n];
-      const size_t row = (size_t)ot.tok[n] * a.k;
-      float denom = ot.Z[n];
-      if (a.renormalize) {
-        bool first = true;
-        for (int j = 0; j < cs; ++j)
-          if ((em >> ot.rids[n][j]) & 1ull) {
-            denom = first ? ot.p[n][j] : denom + ot.p[n][j];
-            first = false;
-          }
+      const int cs = ot.cstar[n], tok = ot.tok[n];
+      const size_t row = (size_t)tok * a.k;
+      const uint4 ids4 = *reinterpret_cast<const uint4*>(ot.rids[n]);
+      const unsigned idw[4] = {ids4.x, ids4.y, ids4.z, ids4.w};
+      unsigned ranks = 0;  // the chosen ranks
+      float sum = 0.0f;    // their probabilities, added in the order of the ranks
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const unsigned e = (idw[j >> 2] >> (8 * (j & 3))) & 63u;
+        const bool chosen = j < cs && ((em >> e) & 1ull) != 0ull;
+        ranks |= chosen ? 1u << j : 0u;
+        sum = chosen ? sum + ot.p[n][j] : sum;
       }
-      int at = 0;
-      for (int j = 0; j < cs; ++j) {
-        const int e = ot.rids[n][j];
-        if (((em >> e) & 1ull) && at < a.k) {  // (exactly k bits are set; at < k keeps the row)
-          if ((j & 7) == q) {
-            expert_ids[row + at] = e;
-            weights[row + at] = ot.p[n][j] / denom;
-          }
-          ++at;
+      const float denom = a.renormalize ? sum : ot.Z[n];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int j = q + 8 * h;
+        const int at = __builtin_popcount(ranks & ((1u << j) - 1u));
+        if (((ranks >> j) & 1u) != 0u && at < a.k) {  // (exactly k are chosen; at < k keeps the row)
+          const int e = ot.rids[n][j];
+          expert_ids[row + at] = e;
+          weights[row + at] = ot.p[n][j] / denom;
+          atomicOr(&mask64[e], 1ull << tok);
         }
       }
     }
