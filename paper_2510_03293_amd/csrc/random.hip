@@ -25,11 +25,12 @@
 // against the 64 keys read out one after the other (two lane reads, one compare, one add each);
 // the shuffle's positions are lanes, its draws and swaps scalars; the sample is a mask of
 // positions, so that its ascending order costs nothing.  What bounds them is the issue of those
-// instructions, about 400 per token, and waves enough to fill it: 16 per tile in the general
-// kernel, 4 in the other one, where few tokens of a tile are sampled.  (With lane = token, one
-// wavefront per tile behind a counting pass over E^2 values in LDS: 56 us for the
-// resampling of 12345 tokens, a tenth of them sampled -- the call 114 us, now 71 --, 65 us for
-// the whole analysis of 8192 tokens, 64 experts -- the load-only call 1020 us, now 977.)
+// instructions, about 400 per token, and waves enough to fill it: 16 per tile, so that a wavefront
+// has four tokens at most, whose logits are all on their way together and whose random blocks are
+// drawn at once.  (12345 tokens, a tenth of them sampled, the call: 114 us with lane = token, one wavefront
+// per tile behind a counting pass over E^2 values in LDS; 72 with four waves per tile, a token after the
+// other; now 68.  64 tokens, all sampled, 16 experts: 44, 60, 42 us.  The whole analysis of 8192 tokens,
+// 64 experts: 65 us with lane = token, now 22.)
 #include "analyse.h"
 #include "laser_internal.h"
 
@@ -72,18 +73,21 @@ __device__ __forceinline__ int rank_of(double key, int E) {
   return before;
 }
 
-// The sample of a token (`g`: its number in the caller's numbering): c of the positions
-// [0, m), m <= 64, as a mask.
-__device__ __forceinline__ unsigned long long sample_positions(const RandomArgs& rnd, unsigned long long g, int m,
-                                                               int c, int lane) {
-  uint32_t w[4];  // lane b: block b of the token's generator (at most 64 draws: 16 blocks)
+// Block lane % 16 of a token's generator (`g`: its number in the caller's numbering; at most
+// 64 draws, so 16 blocks are all it can need).
+__device__ __forceinline__ void draw_blocks(const RandomArgs& rnd, unsigned long long g, int lane, uint32_t (&w)[4]) {
   philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), rnd.stream, (uint32_t)(lane & 15), (uint32_t)rnd.seed,
                 (uint32_t)(rnd.seed >> 32), w);
+}
+
+// The sample of a token whose blocks are in lanes first, first + 1, ...: c of the positions
+// [0, m), m <= 64, as a mask.
+__device__ __forceinline__ unsigned long long sample_positions(const uint32_t (&w)[4], int first, int m, int c, int lane) {
   int at = lane;  // lane = place in the shuffled array: the position it holds
   unsigned long long picked = 0ull;
   for (int i = 0; i < c; ++i) {
     const int q = i & 3;
-    const unsigned r = (unsigned)__builtin_amdgcn_readlane((int)(q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3]), i >> 2);
+    const unsigned r = (unsigned)__builtin_amdgcn_readlane((int)(q == 0 ? w[0] : q == 1 ? w[1] : q == 2 ? w[2] : w[3]), first + (i >> 2));
     const int j = i + (int)(((unsigned long long)r * (unsigned)(m - i)) >> 32);  // i <= j < m
     // (place i is not looked at again: what it held goes to place j, what j held is drawn)
     const int ai = __builtin_amdgcn_readlane(at, i), aj = __builtin_amdgcn_readlane(at, j);
@@ -203,10 +207,13 @@ __global__ __launch_bounds__(64 * kGeneralWaves) void analyse_general_kernel(con
       const int m = inpool > k ? inpool : k;
       const int cstar = mass_ok ? k : (c < m ? c : m);
       // ---- candidates ------------------------------------------------------------------
-      if (SAMPLE && !mass_ok && m > c)
-        picked[n] = sample_positions(rnd, rnd.token_offset + (unsigned long long)t, m, c, lane);
-      else
+      if (SAMPLE && !mass_ok && m > c) {
+        uint32_t w[4];
+        draw_blocks(rnd, rnd.token_offset + (unsigned long long)t, lane, w);
+        picked[n] = sample_positions(w, 0, m, c, lane);
+      } else {
         picked[n] = cstar >= 64 ? ~0ull : (1ull << cstar) - 1ull;
+      }
       const bool flex = !mass_ok && cstar > k;
       const bool in = real && ((picked[n] >> rank[n]) & 1ull) != 0ull;
       if (flex) {
@@ -263,7 +270,9 @@ __global__ __launch_bounds__(64 * kGeneralWaves) void analyse_general_kernel(con
 // records are written again.  Fixed tokens, masks, counts and the flexible-token masks
 // are not touched: none of them depends on which candidates a flexible token has.
 // One workgroup per tile; tiles without such a token cost two loads per lane.
-constexpr int kResampleWaves = 4;
+constexpr int kResampleWaves = 16;
+constexpr int kResampleTokens = kTile / kResampleWaves;  // of a wavefront, at most
+static_assert(kResampleTokens * 16 == 64, "all blocks of a wavefront's tokens are drawn at once");
 
 __global__ __launch_bounds__(64 * kResampleWaves) void random_resample_kernel(const float* __restrict__ logits,
                                                              size_t logits_stride, const RouteArgs a0,
@@ -284,28 +293,47 @@ __global__ __launch_bounds__(64 * kResampleWaves) void random_resample_kernel(co
   const int cst = live ? (int)ws.rec_cstar[tile * kTile + lane] : 0;
   const int m_lane = live ? pool[tile * kTile + lane] : 0;
   // (then cst == c)
-  unsigned long long todo = __builtin_amdgcn_ballot_w64(cst > 0 && m_lane > c);  // the same in all four waves
+  unsigned long long todo = __builtin_amdgcn_ballot_w64(cst > 0 && m_lane > c);  // the same in all waves
   if (todo == 0ull) return;
-  const unsigned long long fm = scalar64(ws.flexmask[tile]);
+  if (wave >= __builtin_popcountll(todo)) return;
+  // wave w takes the sampled tokens number w, w + 16, ... (-1: none)
+  const int number = ((todo >> lane) & 1ull) != 0ull ? __builtin_popcountll(todo & lanes_below(lane)) : -1;
+  int itok[kResampleTokens];
+#pragma unroll
+  for (int u = 0; u < kResampleTokens; ++u) {
+    const unsigned long long at = __builtin_amdgcn_ballot_w64(number == wave + u * kResampleWaves);
+    itok[u] = at != 0ull ? __builtin_ctzll(at) : -1;
+  }
 
-  // lane = expert; wave w takes the sampled tokens number w, w + 4, ...
+  // lane = expert
   const bool real = lane < E;
+  const float* src = logits + (size_t)tile * kTile * E + min(lane, E - 1);
+  float z[kResampleTokens];  // (all on their way together; loads without conditions stay in flight)
+#pragma unroll
+  for (int u = 0; u < kResampleTokens; ++u) z[u] = src[max(itok[u], 0) * E];
+  const unsigned long long fm_lane = ws.flexmask[tile];
   const unsigned long long all = ws.tile_mask[(size_t)tile * 64 + lane];
-  const float* src = logits + (size_t)tile * kTile * E;
-  for (int n = 0; todo != 0ull; ++n, todo &= todo - 1ull) {
-    if ((n & (kResampleWaves - 1)) != wave) continue;
-    const int itok = __builtin_ctzll(todo), t = tile * kTile + itok;
-    const int m = __builtin_amdgcn_readlane(m_lane, itok);
-    const float z = real ? src[itok * E + lane] : 0.0f;
-    int rank = rank_of(real ? make_key(z, lane) : kPadKey, E);
+  // lanes 16 u .. 16 u + 15: the blocks of token u
+  uint32_t w[4];
+  int mine = itok[0];
+#pragma unroll
+  for (int u = 1; u < kResampleTokens; ++u) mine = (lane >> 4) == u ? itok[u] : mine;
+  draw_blocks(rnd, rnd.token_offset + (unsigned long long)(tile * kTile + max(mine, 0)), lane, w);
+  const unsigned long long fm = scalar64(fm_lane);
+#pragma unroll
+  for (int u = 0; u < kResampleTokens; ++u) {
+    if (itok[u] < 0) break;
+    const int t = tile * kTile + itok[u];
+    const int m = __builtin_amdgcn_readlane(m_lane, itok[u]);
+    int rank = rank_of(real ? make_key(z[u], lane) : kPadKey, E);
     rank = real ? rank : lane;
     const int best = __builtin_ctzll(__builtin_amdgcn_ballot_w64(real && rank == 0));
-    const float zmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z), best));
-    const unsigned long long picked = sample_positions(rnd, rnd.token_offset + (unsigned long long)t, m, c, lane);
+    const float zmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z[u]), best));
+    const unsigned long long picked = sample_positions(w, 16 * u, m, c, lane);
     const bool in = real && ((picked >> rank) & 1ull) != 0ull;
-    write_records(a, ws, t, tile * kTile + __builtin_popcountll(fm & lanes_below(itok)), lane, in,
-                  __builtin_popcountll(picked & lanes_below(rank)), exp_fixed(clamp_exp_arg(z - zmax)),
-                  __builtin_popcountll(all & lanes_below(itok)), c);
+    write_records(a, ws, t, tile * kTile + __builtin_popcountll(fm & lanes_below(itok[u])), lane, in,
+                  __builtin_popcountll(picked & lanes_below(rank)), exp_fixed(clamp_exp_arg(z[u] - zmax)),
+                  __builtin_popcountll(all & lanes_below(itok[u])), c);
   }
 }
 

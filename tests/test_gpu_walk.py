@@ -101,3 +101,14 @@ def test_window_gives_way_inside_a_word(E, k, c):
         n = _sweeps(T, E, k, c, np.concatenate([far, np.repeat(row, T - T1, axis=0)]).astype(np.float32), loads,
                     f"hand-over E{E} c{c} T1 {T1}")
         assert 0 < n < T - 200                  # (fewer sweeps than tokens by far: the walk took the rest)
+
+
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 49, 64, 65, 127])
+@pytest.mark.parametrize("E,k,c", [(64, 6, 8), (8, 2, 4), (33, 3, 16)])
+def test_resampling_of_a_whole_tile(T, E, k, c):
+    """Every token's pool is larger than c: a wavefront draws for up to four tokens of a tile at once."""
+    from tests import gpu_util as u
+    logits = wl.random_logits(T + E, T, E, kind="normal", scale=0.3)
+    _, ref = u.check_random_from_logits(logits, k, c, 2.0, 1e-30, np.zeros(E, np.int32), seed=77 + T, stream=3,
+                                        token_offset=(1 << 32) - 5, label=f"resample T{T} E{E}")
+    assert (ref["cstar"] == c).all()
