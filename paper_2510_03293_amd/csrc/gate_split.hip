@@ -423,7 +423,10 @@ __global__ __launch_bounds__(kGateThreads) void gate_split_bf16_kernel(
     __syncthreads();  // expert ids and records are stored, mask64 and flex_lds are final
     const unsigned long long fm = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(flex_lds >> 32)) << 32) |
                                   (unsigned)__builtin_amdgcn_readfirstlane((int)flex_lds);
-    if (fm != 0ull) finish_flexible(*reinterpret_cast<OneTile*>(gate_lds), fm, mask64, lin, a, ws, expert_ids, weights);
+    // (out of the way of calls without any: 16 such problems in one call, 12.8 us with this code in the
+    // middle, 12.3 with it at the end)
+    if (__builtin_expect(fm != 0ull, 0))
+      finish_flexible(*reinterpret_cast<OneTile*>(gate_lds), fm, mask64, lin, a, ws, expert_ids, weights);
     if (wave == 0) {  // lane = expert
       const int cnt = lane < E ? __builtin_popcountll(mask64[lane]) : 0;
       int incl = cnt;
