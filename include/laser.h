@@ -116,9 +116,9 @@ typedef struct laser_params {
                          /* results do not depend on it.                                   */
   uint32_t split_k;      /* Small bf16 calls (up to 64 tiles of 64 tokens in all): the      */
                          /* contraction axis of the projection is cut over eight workgroups */
-                         /* per tile (four beyond 32 tiles).  0: the                        */
-                         /* library decides; 1: never.  The results, logits included, do    */
-                         /* not depend on it.                                               */
+                         /* per tile (four beyond 32 tiles; batched calls: where H is long  */
+                         /* enough for that to pay).  0: the library decides; 1: never.     */
+                         /* The results, logits included, do not depend on it.              */
 } laser_params_t;
 
 /* Bytes of device workspace a call with these sizes needs (0 on bad arguments).

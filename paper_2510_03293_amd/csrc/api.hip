@@ -163,6 +163,32 @@ static void choose_segments(RouteArgs& a, uint32_t wanted) {
   a.nseg = 1 + (a.ntiles - a.seg_first + a.seg_tiles - 1) / a.seg_tiles;
 }
 
+// Whether a batched call of few tiles gains by the split.  What it saves is time on one compute unit's
+// way to memory, which grows with H (less so where a tile has few tokens), and where a problem is one
+// tile the tail kernel.  What it costs is the way of 2 KiB per expert and tile of partial sums through
+// memory, for all tiles at once, and a counter's round trip.  The lines are where the two met (calls
+// replayed from a graph; us per call without and with the split):
+//   one tile per problem, 64 experts:  16 tiles, H = 256: 11.9, 11.0;  32 tiles, H = 512: 13.6, 14.6,
+//     H = 1024: 17.4, 15.1;  64 tiles, H = 512: 15.0, 16.4, H = 1024: 18.3, 17.6;     8 experts:  32 tiles,
+//     H = 1024: 12.1, 12.9, H = 1536: 13.7, 12.4;  33 tiles, H = 1024: 12.1, 11.0;  64 tiles, H = 1536: 14.6,
+//     14.9, H = 2048: 16.0, 15.8, with one token per problem 13.5, 14.9, H = 4096: 16.2, 16.1
+//   more than one, 64 experts:  16 tiles, H = 512: 13.2, 14.5, H = 1024: 16.1, 14.8;  40 tiles, H = 1024: 16.2,
+//     17.1, H = 1536: 19.3, 18.5;  2 x 32 tiles, H = 2048: 20.4, 19.5;  32 x 2, H = 2048: 21.0, 23.0, H = 3072:
+//     26.9, 24.4;     32 experts:  32 tiles, H = 1536: 15.4, 15.3;  64 tiles, H = 2048: 17.4, 19.3, H = 3072: 22.5,
+//     20.9;     8 experts:  16 tiles, H = 1536: 12.5, 12.6, H = 2048: 13.4, 12.8;  32 tiles, H = 2048: 13.9, 14.5,
+//     H = 3072: 17.0, 15.1;  64 tiles, H = 3072: 18.2, 19.1, H = 4096: 20.5, 20.0 to 21.6, 22.3
+static bool batched_split_pays(int nb, int ntiles, int T, int EP, int32_t H) {
+  const int tiles = nb * ntiles;
+  if (ntiles == 1) {
+    if (tiles <= 16) return tiles <= 8 || H >= 256;
+    const int line = tiles * (tiles <= 32 ? (EP == 64 ? 21 : 42) : (EP == 64 ? 15 : 31));
+    return H >= (T > 16 ? line : EP >= 32 ? line * 3 / 2 : line * 2);
+  }
+  if (EP == 64) return H >= (tiles <= 16 ? 1024 : tiles <= 40 ? 1536 : nb <= 4 ? 2048 : 3072);
+  if (EP == 32) return H >= (tiles <= 16 ? 1536 : tiles <= 32 ? 2048 : 3072);
+  return H >= (tiles <= 16 ? 2048 : tiles <= 32 ? 3072 : 4096);
+}
+
 // The fast analysis kernels carry at most kMaxC candidates per token.  A wide call runs
 // them with the trimming size cut to that (for the logits and the statistics, which do
 // not depend on c) and then the general analysis, which writes every record again.
@@ -230,7 +256,8 @@ int route_impl(const void* hidden, const void* w_gate, int32_t B, int32_t T, int
   // workgroups per tile share the contraction axis (gate_split.hip).
   const long long tiles = (long long)B * a.ntiles;
   if (params->dtype == LASER_DTYPE_BF16 && a.nseg == 0 && tiles >= 1 && tiles <= kSplitMaxTiles &&
-      params->split_k != 1 && workspace_bytes_given / (size_t)B >= ws_one) {
+      params->split_k != 1 && workspace_bytes_given / (size_t)B >= ws_one &&
+      (B == 1 || batched_split_pays(B, a.ntiles, T, a.EP, H))) {
     int32_t* counters = split_counters_for(workspace);
     if (counters != nullptr) {
       a.split = tiles <= kSplitEightTiles ? 8 : 4;

@@ -195,7 +195,8 @@ def test_split_call_with_random_or_wide_trimming(T, E, k, c, trim):
 
 
 # (one tile each: the fused kernel finishes the call; more: the tail kernel does.  Eight workgroups
-# per tile up to 32 tiles in all, four up to 64, no split beyond)
+# per tile up to 32 tiles in all, four up to 64, no split beyond, nor where the contraction axis is too short
+# for it to pay: H = 256 is on either side of that, the next test's lengths are long enough)
 @pytest.mark.parametrize("nb,T", [(2, 1), (3, 64), (32, 17), (33, 64), (64, 5), (65, 3), (2, 65), (5, 200), (17, 129)])
 @pytest.mark.parametrize("E,k,c,eps", [(64, 6, 8, 0.4), (8, 2, 4, 2.0), (33, 3, 9, 2.0), (16, 4, 12, 0.6)])
 def test_batched_calls_of_few_tiles(nb, T, E, k, c, eps):
@@ -208,6 +209,20 @@ def test_batched_calls_of_few_tiles(nb, T, E, k, c, eps):
     for b in sorted({0, 1, nb // 2, nb - 1}):
         one = u.run_route(*gates[b], wl.DTYPE_BF16, k, c, eps, 0.3, loads[b], renormalize=nb % 2 == 0, split_k=1)
         _same(got[b], one, f"problem {b} of {nb}, T{T} E{E}")
+
+
+@pytest.mark.parametrize("nb,T", [(2, 64), (17, 3), (33, 64), (64, 5), (2, 65), (3, 700), (17, 129)])
+@pytest.mark.parametrize("E,k,c,eps,H", [(64, 6, 8, 0.4, 3072), (8, 2, 4, 2.0, 6144), (33, 3, 9, 2.0, 3072), (30, 4, 12, 0.6, 3072)])
+def test_batched_calls_with_a_long_contraction_axis(nb, T, E, k, c, eps, H):
+    u = _util()
+    rng = np.random.default_rng(nb * T + E + H)
+    gates = [_gate(1000 * nb + T + E + b, T, H, E, 0.4) for b in range(min(nb, 3))]
+    gates = [gates[b % len(gates)] for b in range(nb)]     # (inputs repeat, counters do not)
+    loads = [rng.integers(0, 4, size=E).astype(np.int32) for _ in range(nb)]
+    got = u.run_route_batched([g[0] for g in gates], [g[1] for g in gates], wl.DTYPE_BF16, k, c, eps, 0.3, loads)
+    for b in sorted({0, nb // 2, nb - 1}):
+        one = u.run_route(*gates[b], wl.DTYPE_BF16, k, c, eps, 0.3, loads[b], split_k=1)
+        _same(got[b], one, f"problem {b} of {nb}, T{T} E{E} H{H}")
 
 
 @pytest.mark.parametrize("T", [1, 2, 33, 63, 64])
