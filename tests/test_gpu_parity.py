@@ -113,9 +113,11 @@ def test_window_chain_variants(T, E, k, c):
         u.check_from_logits(logits, k, c, 2.0, 1e-30, loads_in, label=f"window variant T{T} E{E} k{k} c{c} s{scale}")
 
 
-# The sequential walk stages its tokens in batches of 96 (64 where there are more than 16
-# candidates), a producer wave's share of a batch in two halves, output words of 32 tokens.
-@pytest.mark.parametrize("T", [1, 2, 3, 31, 32, 33, 47, 48, 49, 63, 64, 65, 95, 96, 97, 191, 192, 193, 250])
+# The sequential walks stage their tokens in batches: of 48 with 9 to 16 candidates, of 21 with
+# more, of 16 with up to 8, of 96 where there are no more than 8 experts; a producer wave's share of the
+# first two in two halves (of 8, and of 4 and 3); output words of 32 tokens.
+@pytest.mark.parametrize("T", [1, 2, 3, 7, 20, 21, 22, 31, 32, 33, 41, 42, 43, 47, 48, 49, 62, 63, 64, 65, 95, 96, 97,
+                               191, 192, 193, 250])
 @pytest.mark.parametrize("E,k,c", [(64, 6, 8), (8, 2, 4), (64, 9, 16), (16, 4, 12), (9, 8, 9), (64, 6, 64), (20, 3, 18)])
 def test_sequential_walk_sizes(T, E, k, c):
     """Every token load-dependent, fewer than the window evaluation takes: counters equal,
@@ -133,7 +135,8 @@ def test_sequential_walk_sizes(T, E, k, c):
 def test_window_chain_gives_way_to_sequential(E, k, c, T1, T2):
     """First T1 tokens with unrelated candidate sets (decided side by side), then T2
     identical tokens that all compete for the same experts at equal loads (one by
-    one): the hand-over happens wherever progress drops, mid word and mid tile."""
+    one): the hand-over happens wherever progress drops, mid word and mid tile.  (Up to 8
+    experts there is no window to give way: one walk through both kinds of tokens.)"""
     u = _util()
     rng = np.random.default_rng(E * 1000 + T1)
     a = wl.random_logits(E + T1, T1, E, kind="normal", scale=1.0)

@@ -55,6 +55,19 @@ CASES = [
     (2500, 1000, 33, 3, 9, 0.40, 6),
     (130, 2048, 64, 6, 8, 0.30, 2),     # two segments, the second one ragged tile only
     (6000, 128, 64, 6, 8, 0.90, 31),
+    # the gate kernel is compiled with the walks that its padded number of experts can reach: 32 and 16
+    # of them, with up to 4, 8 and 16 candidates, segments with fewer and with more than the 256
+    # load-dependent tokens from which the window evaluation is used
+    (3000, 256, 32, 4, 8, 0.30, 5),
+    (4097, 256, 32, 4, 8, 0.70, 13),
+    (3000, 256, 32, 4, 12, 0.60, 11),
+    (4097, 256, 24, 4, 8, 0.70, 13),
+    (3000, 512, 20, 2, 4, 0.60, 9),
+    (3000, 256, 16, 4, 8, 0.30, 4),
+    (4097, 256, 16, 4, 8, 0.70, 13),
+    (2500, 512, 16, 2, 4, 0.60, 9),
+    (4097, 256, 12, 2, 4, 0.90, 13),
+    (2500, 256, 11, 3, 6, 0.30, 6),
 ]
 
 
