@@ -26,6 +26,9 @@
 //   top-k branch S_k >= fl(eps_high * Z)
 //   pool member  z_i - z_max >= fl32(ln t_fix)
 #include "analyse.h"
+#include <cstddef>
+#include <type_traits>
+
 #include "laser_internal.h"
 #include "tail.h"
 
@@ -97,6 +100,13 @@ hipError_t launch_analyse(const float* logits, size_t logits_stride, const Route
   return hipGetLastError();
 }
 
+// The arguments of the tail kernel, in their order (what the chain workgroup reads of them).
+struct TailArgs {
+  RouteArgs a;
+  Workspace ws;
+  int32_t *loads_inout, *expert_offsets;
+};
+
 template <bool BATCH>  // blockIdx.y is the problem of a batched call (a kernel of its own: the
                        // longer prologue would delay the first loads of the single-problem kernel).
                        // Two workgroups on a compute unit: with the registers of one a long
@@ -112,14 +122,9 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
     // The chain reads its arguments for itself, through a pointer the compiler knows nothing of:
     // shared with the finishing workgroups they were all loaded, waited for and put aside (20
     // lane writes) before those could begin (27 layers of 16384 tokens, 64 experts: 663 -> 657 us).
-    struct Args {  // (as the kernel's own, in their order)
-      RouteArgs a;
-      Workspace ws;
-      int32_t *loads_inout, *expert_offsets;
-    };
     auto* kernarg = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(kernarg));
-    const Args* own = (const Args*)kernarg;
+    const TailArgs* own = (const TailArgs*)kernarg;
     const RouteArgs a = own->a;
     const Workspace ws = own->ws;
     chain_segments<false, 0>(tail_lds, a, ws, own->loads_inout, own->expert_offsets);
@@ -138,6 +143,14 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
   }
   tail_role<BATCH>(blockIdx.x, tail_lds, a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation);
 }
+// (TailArgs mirrors the signature: whoever changes one has to change the other)
+static_assert(std::is_same<decltype(&tail_kernel<false>), void (*)(RouteArgs, Workspace, int32_t*, int32_t*, int32_t*,
+                                                                    float*, int32_t*)>::value,
+              "TailArgs holds the first arguments of the tail kernel");
+static_assert(offsetof(TailArgs, ws) == sizeof(RouteArgs) &&
+                  offsetof(TailArgs, loads_inout) == sizeof(RouteArgs) + sizeof(Workspace) &&
+                  sizeof(RouteArgs) % 8 == 0 && sizeof(Workspace) % 8 == 0,
+              "kernel arguments follow each other without a gap, each at its own alignment");
 
 template <bool BATCH>
 static hipError_t launch_tail_b(const RouteArgs& a, const Workspace& ws, int32_t* loads_inout,
