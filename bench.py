@@ -31,9 +31,9 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, vendor figure
 # kernel sources it was taken on: the record carries their hash and `traffic` is
 # reported as null once the sources differ.
 PMC_TRAFFIC = {
-    "sources_sha256_16": "fe2af7228f7149c9",
+    "sources_sha256_16": "ea70463b24d577ba",
     "workload": "deepseek",
-    "fetch_kib": 33902.35, "fetch_scale": 1.9997,
+    "fetch_kib": 33892.99, "fetch_scale": 1.9997,
     "write_kib": 1024.23, "write_scale": 1.0,
 }
 GATE_SOURCES = ("paper_2510_03293_amd/csrc/gate.hip", "paper_2510_03293_amd/csrc/gate_tile.h",

@@ -34,9 +34,10 @@
  *   - Inputs must be finite; loads_inout[e] + T must stay below 2^27.
  *   - Limits: 1 <= k <= min(c, 16); c <= E <= 64; bf16 needs H % 8 == 0 and
  *     16-byte aligned hidden / w_gate; fp32 needs H % 4 == 0.  Trimming sizes
- *     c <= 16 (the paper evaluates c <= 10) run on the tuned kernels; 16 < c <= E
+ *     c <= 16 (the paper evaluates c <= 10) run on the fast kernels; 16 < c <= E
  *     (up to the load-only baseline of the paper's evaluation, c = n) is routed
- *     exactly by general kernels that are not tuned.
+ *     exactly by general ones: another kernel per call, and a walk of about 100 ns
+ *     per load-dependent token where up to 8 candidates take 18 to 53.
  *   - Completion.  The kernels of a call hand data to one another through the
  *     workspace; the workgroups that write the dispatch tables wait for the
  *     workgroup that walks the load-dependent tokens with a bounded number of
@@ -73,7 +74,7 @@ extern "C" {
 #define LASER_MAX_E 64
 #define LASER_MAX_K 16
 #define LASER_MAX_C 64      /* (c <= E) */
-#define LASER_FAST_C 16     /* trimming sizes up to here run on the tuned kernels */
+#define LASER_FAST_C 16     /* trimming sizes up to here run on the fast kernels */
 
 /* What laser_status() reports about the last call that used a workspace. */
 #define LASER_STATUS_COMPLETE 0

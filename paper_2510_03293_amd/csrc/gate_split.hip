@@ -411,8 +411,8 @@ __global__ __launch_bounds__(kGateThreads) void gate_split_bf16_kernel(
   // Everything the rest needs is in this workgroup: the records of the load-dependent tokens,
   // per expert the other tokens assigned to it (mask64) and, just written, the tokens' experts
   // in rank order.  What follows is what the tail kernel would do, without its launch and the
-  // way of all of this through memory.  (Sixty-four tokens, 64 experts, H = 2048: split kernel and tail 10.6 + 4.4 us,
-  // now 10.1; a replayed decode loop 387 -> 303 us for 27 layers.)
+  // way of all of this through memory.  (64 tokens, 64 experts, H = 2048: split kernel and tail
+  // 10.5 + 4.4 us, now 10.1; 27 such layers replayed from a graph 355 -> 301 us.)
   if (a.one_permutation != nullptr) {  // (a.ntiles == 1)
     int32_t* const permutation = a.one_permutation + (size_t)prob * T * a.k;
     int32_t* const expert_offsets = a.one_expert_offsets + (size_t)prob * (E + 1);

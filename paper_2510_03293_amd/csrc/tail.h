@@ -604,8 +604,8 @@ __device__ __forceinline__ int pair_bound(int ki, int kj) {
 // What bounds the step: 16 vector instructions, four LDS instructions -- a lane exchange keeps the
 // wavefront from issuing for about 15 cycles --, waits; 105 cycles, and 9 of the batch's barrier.
 // (A scalar move that reads the comparison's result costs 16 more.)
-// 16384 tokens, 64 experts, k = 6, c = 8: 69 -> 53 ns per token, the call
-// 1156 -> 878 us (1.15 -> 0.85 ms of it the walk).
+// 16384 tokens, 64 experts, k = 6, c = 8, all load-dependent: 69 -> 53 ns per token, the call 1156 ->
+// 878 us, all but about 30 of it the walk.
 constexpr int kLagBatch = 16;
 struct LagTok {
   int4 v[32];  // per pair: U; 4 * lane of ci; 4 * lane of cj; their places in the W of the token
