@@ -181,7 +181,7 @@ static bool batched_split_pays(int nb, int ntiles, int T, int EP, int32_t H) {
   const int tiles = nb * ntiles;
   if (ntiles == 1) {
     if (tiles <= 16) return tiles <= 8 || H >= 256;
-    const int line = tiles * (tiles <= 32 ? (EP == 64 ? 21 : 42) : (EP == 64 ? 15 : 31));
+    const int line = tiles * (tiles <= 32 ? (EP == 64 ? 21 : EP == 32 ? 31 : 40) : (EP == 64 ? 15 : 31));
     return H >= (T > 16 ? line : EP >= 32 ? line * 3 / 2 : line * 2);
   }
   if (EP == 64) return H >= (tiles <= 16 ? 1024 : tiles <= 40 ? 1536 : nb <= 4 ? 2048 : 3072);

@@ -25,9 +25,9 @@
 // against the 64 keys read out one after the other (two lane reads, one compare, one add each);
 // the shuffle's positions are lanes, its draws and swaps scalars; the sample is a mask of
 // positions, so that its ascending order costs nothing.  What bounds them is the issue of those
-// instructions, about 400 per token, and waves enough to fill it: 16 per tile, so that a wavefront
-// has four tokens at most, whose logits are all on their way together and whose random blocks are
-// drawn at once.  (12345 tokens, a tenth of them sampled, the call: 114 us with lane = token, one wavefront
+// instructions, about 400 per token, and waves enough to fill it: 16 per tile (see
+// random_resample_kernel for calls of many tiles), which take up to four tokens at a time, whose logits
+// are all on their way together and whose random blocks are drawn at once.  (12345 tokens, a tenth of them sampled, the call: 114 us with lane = token, one wavefront
 // per tile behind a counting pass over E^2 values in LDS; 72 with four waves per tile, a token after the
 // other; now 68.  64 tokens, all sampled, 16 experts: 44, 60, 42 us.  The whole analysis of 8192 tokens,
 // 64 experts: 65 us with lane = token, now 22.)
@@ -269,12 +269,15 @@ __global__ __launch_bounds__(64 * kGeneralWaves) void analyse_general_kernel(con
 // size > c); their c candidates are drawn instead of taken from the top, and their
 // records are written again.  Fixed tokens, masks, counts and the flexible-token masks
 // are not touched: none of them depends on which candidates a flexible token has.
-// One workgroup per tile; tiles without such a token cost two loads per lane.
-constexpr int kResampleWaves = 16;
-constexpr int kResampleTokens = kTile / kResampleWaves;  // of a wavefront, at most
-static_assert(kResampleTokens * 16 == 64, "all blocks of a wavefront's tokens are drawn at once");
+// One workgroup per tile; tiles without such a token cost two loads per lane.  WAVES: 16 in a call
+// of few tiles, where a tile's sampled tokens are the call's time; 4 beyond that, where the tiles' wavefronts
+// fill the chip by themselves and starting them is what a call with few such tokens pays for (55184 tokens
+// of 32 experts, none sampled: the call 23.2 us with 16, 22.2 with 4).
+constexpr int kResampleFewTiles = 512;
+constexpr int kResampleTokens = 4;  // of a wavefront at a time: 16 lanes draw the blocks of each
 
-__global__ __launch_bounds__(64 * kResampleWaves) void random_resample_kernel(const float* __restrict__ logits,
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void random_resample_kernel(const float* __restrict__ logits,
                                                              size_t logits_stride, const RouteArgs a0,
                                                              const Workspace ws0, const RandomArgs rnd0) {
   const int prob = blockIdx.y;  // the problem of a batched call; it draws with its own stream id
@@ -293,47 +296,49 @@ __global__ __launch_bounds__(64 * kResampleWaves) void random_resample_kernel(co
   const int cst = live ? (int)ws.rec_cstar[tile * kTile + lane] : 0;
   const int m_lane = live ? pool[tile * kTile + lane] : 0;
   // (then cst == c)
-  unsigned long long todo = __builtin_amdgcn_ballot_w64(cst > 0 && m_lane > c);  // the same in all waves
-  if (todo == 0ull) return;
-  if (wave >= __builtin_popcountll(todo)) return;
-  // wave w takes the sampled tokens number w, w + 16, ... (-1: none)
+  const unsigned long long todo = __builtin_amdgcn_ballot_w64(cst > 0 && m_lane > c);  // the same in all waves
+  const int total = __builtin_popcountll(todo);
+  if (wave >= total) return;
   const int number = ((todo >> lane) & 1ull) != 0ull ? __builtin_popcountll(todo & lanes_below(lane)) : -1;
-  int itok[kResampleTokens];
-#pragma unroll
-  for (int u = 0; u < kResampleTokens; ++u) {
-    const unsigned long long at = __builtin_amdgcn_ballot_w64(number == wave + u * kResampleWaves);
-    itok[u] = at != 0ull ? __builtin_ctzll(at) : -1;
-  }
 
   // lane = expert
   const bool real = lane < E;
   const float* src = logits + (size_t)tile * kTile * E + min(lane, E - 1);
-  float z[kResampleTokens];  // (all on their way together; loads without conditions stay in flight)
-#pragma unroll
-  for (int u = 0; u < kResampleTokens; ++u) z[u] = src[max(itok[u], 0) * E];
   const unsigned long long fm_lane = ws.flexmask[tile];
   const unsigned long long all = ws.tile_mask[(size_t)tile * 64 + lane];
-  // lanes 16 u .. 16 u + 15: the blocks of token u
-  uint32_t w[4];
-  int mine = itok[0];
+  // wave w takes the sampled tokens number w, w + WAVES, ...
+  for (int n0 = wave; n0 < total; n0 += WAVES * kResampleTokens) {
+    int itok[kResampleTokens];  // (-1: none)
 #pragma unroll
-  for (int u = 1; u < kResampleTokens; ++u) mine = (lane >> 4) == u ? itok[u] : mine;
-  draw_blocks(rnd, rnd.token_offset + (unsigned long long)(tile * kTile + max(mine, 0)), lane, w);
-  const unsigned long long fm = scalar64(fm_lane);
+    for (int u = 0; u < kResampleTokens; ++u) {
+      const unsigned long long at = __builtin_amdgcn_ballot_w64(number == n0 + u * WAVES);
+      itok[u] = at != 0ull ? __builtin_ctzll(at) : -1;
+    }
+    float z[kResampleTokens];  // (all on their way together; loads without conditions stay in flight)
 #pragma unroll
-  for (int u = 0; u < kResampleTokens; ++u) {
-    if (itok[u] < 0) break;
-    const int t = tile * kTile + itok[u];
-    const int m = __builtin_amdgcn_readlane(m_lane, itok[u]);
-    int rank = rank_of(real ? make_key(z[u], lane) : kPadKey, E);
-    rank = real ? rank : lane;
-    const int best = __builtin_ctzll(__builtin_amdgcn_ballot_w64(real && rank == 0));
-    const float zmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z[u]), best));
-    const unsigned long long picked = sample_positions(w, 16 * u, m, c, lane);
-    const bool in = real && ((picked >> rank) & 1ull) != 0ull;
-    write_records(a, ws, t, tile * kTile + __builtin_popcountll(fm & lanes_below(itok[u])), lane, in,
-                  __builtin_popcountll(picked & lanes_below(rank)), exp_fixed(clamp_exp_arg(z[u] - zmax)),
-                  __builtin_popcountll(all & lanes_below(itok[u])), c);
+    for (int u = 0; u < kResampleTokens; ++u) z[u] = src[max(itok[u], 0) * E];
+    // lanes 16 u .. 16 u + 15: the blocks of token u
+    uint32_t w[4];
+    int mine = itok[0];
+#pragma unroll
+    for (int u = 1; u < kResampleTokens; ++u) mine = (lane >> 4) == u ? itok[u] : mine;
+    draw_blocks(rnd, rnd.token_offset + (unsigned long long)(tile * kTile + max(mine, 0)), lane, w);
+    const unsigned long long fm = scalar64(fm_lane);
+#pragma unroll
+    for (int u = 0; u < kResampleTokens; ++u) {
+      if (itok[u] < 0) break;
+      const int t = tile * kTile + itok[u];
+      const int m = __builtin_amdgcn_readlane(m_lane, itok[u]);
+      int rank = rank_of(real ? make_key(z[u], lane) : kPadKey, E);
+      rank = real ? rank : lane;
+      const int best = __builtin_ctzll(__builtin_amdgcn_ballot_w64(real && rank == 0));
+      const float zmax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z[u]), best));
+      const unsigned long long picked = sample_positions(w, 16 * u, m, c, lane);
+      const bool in = real && ((picked >> rank) & 1ull) != 0ull;
+      write_records(a, ws, t, tile * kTile + __builtin_popcountll(fm & lanes_below(itok[u])), lane, in,
+                    __builtin_popcountll(picked & lanes_below(rank)), exp_fixed(clamp_exp_arg(z[u] - zmax)),
+                    __builtin_popcountll(all & lanes_below(itok[u])), c);
+    }
   }
 }
 
@@ -341,8 +346,12 @@ hipError_t launch_random_resample(const float* logits, size_t logits_stride, con
                                   const Workspace& ws, const RandomArgs& rnd, hipStream_t s) {
   if (a.ntiles == 0) return hipSuccess;
   clear_stale_error();
-  hipLaunchKernelGGL(random_resample_kernel, dim3(a.ntiles, a.nbatch), dim3(64 * kResampleWaves), 0, s, logits,
-                     logits_stride, a, ws, rnd);
+  if ((long long)a.ntiles * a.nbatch <= kResampleFewTiles)
+    hipLaunchKernelGGL(random_resample_kernel<16>, dim3(a.ntiles, a.nbatch), dim3(64 * 16), 0, s, logits, logits_stride,
+                       a, ws, rnd);
+  else
+    hipLaunchKernelGGL(random_resample_kernel<4>, dim3(a.ntiles, a.nbatch), dim3(64 * 4), 0, s, logits, logits_stride,
+                       a, ws, rnd);
   return hipGetLastError();
 }
 

@@ -103,7 +103,8 @@ def test_window_gives_way_inside_a_word(E, k, c):
         assert 0 < n < T - 200                  # (fewer sweeps than tokens by far: the walk took the rest)
 
 
-@pytest.mark.parametrize("T", [1, 15, 16, 17, 49, 64, 65, 127])
+# (above 512 tiles four wavefronts share a tile instead of sixteen)
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 49, 64, 65, 127, 512 * 64, 512 * 64 + 21])
 @pytest.mark.parametrize("E,k,c", [(64, 6, 8), (8, 2, 4), (33, 3, 16)])
 def test_resampling_of_a_whole_tile(T, E, k, c):
     """Every token's pool is larger than c: a wavefront draws for up to four tokens of a tile at once."""
