@@ -144,7 +144,7 @@ __device__ __forceinline__ Workspace problem_workspace(const Workspace& w0, size
 }
 
 constexpr int kStatusPhase = 0;      // 1: fixed prefix published, 2: chain finished
-constexpr int kStatusFlexTiles = 1;  // number of tiles that hold flexible tokens
+constexpr int kStatusFlexTiles = 1;  // number of tiles that hold flexible tokens; negative: the chain is cut into blocks
 constexpr int kStatusError = 2;      // 0, or why the outputs of the call are incomplete (kError*)
 constexpr int kErrorTimeout = 1;        // a bounded wait in the tail kernel ran out (LASER_STATUS_TIMEOUT)
 constexpr int kErrorInconsistent = 2;   // a dispatch slot fell outside the table (LASER_STATUS_INCONSISTENT)
@@ -153,7 +153,7 @@ constexpr int kErrorInconsistent = 2;   // a dispatch slot fell outside the tabl
 // plus an allowance per token of the call, far above the chain's cost per token.
 constexpr long long kSpinFloor = 1ll << 22;
 constexpr long long kSpinPerToken = 16;
-constexpr int kStatusSweeps = 3;     // sweeps of the chain's window evaluation (diagnostic)
+constexpr int kStatusSweeps = 3;     // sweeps of the chain's window evaluation, or walks of its last block (diagnostic)
 
 // Workspace::seg of a pipelined call.  Cleared by a small kernel before the gate kernel.
 constexpr int kSegNext = 0;     // segments the chain has finished

@@ -26,6 +26,7 @@
 //   top-k branch S_k >= fl(eps_high * Z)
 //   pool member  z_i - z_max >= fl32(ln t_fix)
 #include "analyse.h"
+#include <algorithm>
 #include <cstddef>
 #include <type_traits>
 
@@ -100,17 +101,22 @@ hipError_t launch_analyse(const float* logits, size_t logits_stride, const Route
   return hipGetLastError();
 }
 
-// The arguments of the tail kernel, in their order (what the chain workgroup reads of them).
+// The arguments of the tail kernel, in their order.
 struct TailArgs {
   RouteArgs a;
   Workspace ws;
-  int32_t *loads_inout, *expert_offsets;
+  int32_t *loads_inout, *expert_offsets, *expert_ids;
+  float* weights;
+  int32_t* permutation;
 };
 
-template <bool BATCH>  // blockIdx.y is the problem of a batched call (a kernel of its own: the
-                       // longer prologue would delay the first loads of the single-problem kernel).
-                       // Two workgroups on a compute unit: with the registers of one a long
-                       // batch's finishing workgroups ran in two rounds (131072 tokens: 329 -> 339 us)
+// BATCH: blockIdx.y is the problem of a batched call (a kernel of its own: the
+// longer prologue would delay the first loads of the single-problem kernel).
+// BLOCKS: the chain has the first kChainBlocks workgroups (chain_blocks_possible), otherwise the first
+// one (kernels of their own: a number that the kernel had to read first would delay them all).
+// Two workgroups on a compute unit: with the registers of one a long
+// batch's finishing workgroups ran in two rounds (131072 tokens: 329 -> 339 us)
+template <bool BATCH, bool BLOCKS>
 __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a0, const Workspace ws0,
                                                             int32_t* __restrict__ loads_inout,
                                                             int32_t* __restrict__ expert_offsets,
@@ -118,6 +124,35 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
                                                             float* __restrict__ weights,
                                                             int32_t* __restrict__ permutation) {
   extern __shared__ __align__(16) uint8_t tail_lds[];
+  __shared__ FinishShared finish_shared;
+  // Workgroup 0 is the chain, the others finish tiles.  BLOCKS: the grid has three layers.  Where the
+  // chain is cut into blocks, layer 0 leaves when the lists of tokens are there, the workgroups of
+  // layer 1 take the blocks, and those of layer 2 finish the tiles; otherwise layers 1 and 2 leave at
+  // once.  (A workgroup waits for earlier ones only.  27 layers of 16384 tokens, none of them
+  // load-dependent: 665 us without the layers and with them; with one layer, the blocks ahead of the
+  // finishing workgroups, 673, finishing workgroups that go on with a block, 671.)
+  if (BLOCKS && blockIdx.z != 0) {
+    // (arguments of its own, as below; the finishing pass a second time, for the sake of layer 0)
+    auto* kernarg = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kernarg));
+    const TailArgs* own = (const TailArgs*)kernarg;
+    const int prob = BATCH ? blockIdx.y : 0;
+    const RouteArgs a = BATCH ? problem_args(own->a, prob) : own->a;
+    const Workspace ws = BATCH ? problem_workspace(own->ws, (size_t)prob * a.ws_stride) : own->ws;
+    if (blockIdx.z == 1 ? blockIdx.x >= kChainBlocks : blockIdx.x == 0) return;
+    const int flex_tok = count_flexible(a.ntiles, ws);
+    if (flex_tok < kChainBlocksMinTokens) return;
+    int32_t* const loads = own->loads_inout + (size_t)prob * a.E;
+    int32_t* const offsets = own->expert_offsets + (size_t)prob * (a.E + 1);
+    if (blockIdx.z == 1) {
+      chain_block(tail_lds, a, ws, loads, offsets, blockIdx.x, flex_tok);
+    } else {
+      const size_t first = (size_t)prob * a.T * a.k;
+      finish_role<false>(blockIdx.x - 1, tail_lds, finish_shared, a, ws, loads, offsets, own->expert_ids + first, own->weights + first,
+                         own->permutation + first);
+    }
+    return;
+  }
   if (!BATCH && blockIdx.x == 0) {
     // The chain reads its arguments for itself, through a pointer the compiler knows nothing of:
     // shared with the finishing workgroups they were all loaded, waited for and put aside (20
@@ -127,7 +162,7 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
     const TailArgs* own = (const TailArgs*)kernarg;
     const RouteArgs a = own->a;
     const Workspace ws = own->ws;
-    chain_segments<false, 0>(tail_lds, a, ws, own->loads_inout, own->expert_offsets);
+    chain_segments<false, 0, BLOCKS>(tail_lds, a, ws, own->loads_inout, own->expert_offsets);
     return;
   }
   // (each problem has its own chain workgroup)
@@ -141,28 +176,43 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
     weights += (size_t)prob * a.T * a.k;
     permutation += (size_t)prob * a.T * a.k;
   }
-  tail_role<BATCH>(blockIdx.x, tail_lds, a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation);
+  if (BATCH && blockIdx.x == 0) {
+    chain_segments<false, 0, BLOCKS>(tail_lds, a, ws, loads_inout, expert_offsets);
+    return;
+  }
+  finish_role<BLOCKS>(blockIdx.x - 1, tail_lds, finish_shared, a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation);
 }
 // (TailArgs mirrors the signature: whoever changes one has to change the other)
-static_assert(std::is_same<decltype(&tail_kernel<false>), void (*)(RouteArgs, Workspace, int32_t*, int32_t*, int32_t*,
+static_assert(std::is_same<decltype(&tail_kernel<false, false>), void (*)(RouteArgs, Workspace, int32_t*, int32_t*, int32_t*,
                                                                     float*, int32_t*)>::value,
-              "TailArgs holds the first arguments of the tail kernel");
+              "TailArgs holds the arguments of the tail kernel");
 static_assert(offsetof(TailArgs, ws) == sizeof(RouteArgs) &&
                   offsetof(TailArgs, loads_inout) == sizeof(RouteArgs) + sizeof(Workspace) &&
                   sizeof(RouteArgs) % 8 == 0 && sizeof(Workspace) % 8 == 0,
               "kernel arguments follow each other without a gap, each at its own alignment");
 
-template <bool BATCH>
+// Whether a call may well have a chain that is worth cutting into blocks (how many of its tokens depend
+// on the counters is known on the device only).  The kernel that can do it is no slower where none
+// do, but where a window of tokens is evaluated (12345 tokens, 1200 of them load-dependent: 66.2 -> 66.9
+// us), so it is for calls whose thresholds send most tokens to the load-aware branch, and for
+// those in which the eighth part of the tokens is enough.
+static bool chain_blocks_possible(const RouteArgs& a) {
+  return a.EP > 8 && a.nseg == 0 && a.ntiles <= kSelfPrefixTiles &&
+         a.T >= (a.eps_high > 0.5f ? 1 : 8) * kChainBlocksMinTokens;
+}
+
+template <bool BATCH, bool BLOCKS>
 static hipError_t launch_tail_b(const RouteArgs& a, const Workspace& ws, int32_t* loads_inout,
                                 int32_t* expert_offsets, int32_t* expert_ids, float* weights,
                                 int32_t* permutation, hipStream_t s) {
   static LdsAttr allowed;
   const hipError_t e =
-      allow_dynamic_lds(reinterpret_cast<const void*>(&tail_kernel<BATCH>), kChainLdsBytes, allowed);
+      allow_dynamic_lds(reinterpret_cast<const void*>(&tail_kernel<BATCH, BLOCKS>), kChainLdsBytes, allowed);
   if (e != hipSuccess) return e;
-  const int grid = 1 + (a.ntiles + kChainWaves - 1) / kChainWaves;
+  // (every layer as wide as the widest)
+  const int width = std::max(1 + finish_groups(a.ntiles), BLOCKS ? kChainBlocks : 0);
   clear_stale_error();
-  hipLaunchKernelGGL(tail_kernel<BATCH>, dim3(grid, a.nbatch), dim3(kTailThreads), kChainLdsBytes, s, a, ws,
+  hipLaunchKernelGGL((tail_kernel<BATCH, BLOCKS>), dim3(width, a.nbatch, BLOCKS ? 3 : 1), dim3(kTailThreads), kChainLdsBytes, s, a, ws,
                      loads_inout, expert_offsets, expert_ids, weights, permutation);
   return hipGetLastError();
 }
@@ -170,9 +220,13 @@ static hipError_t launch_tail_b(const RouteArgs& a, const Workspace& ws, int32_t
 hipError_t launch_tail(const RouteArgs& a, const Workspace& ws, int32_t* loads_inout,
                        int32_t* expert_offsets, int32_t* expert_ids, float* weights,
                        int32_t* permutation, hipStream_t s) {
+  const bool blocks = chain_blocks_possible(a);
   if (a.nbatch > 1)
-    return launch_tail_b<true>(a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation, s);
-  return launch_tail_b<false>(a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation, s);
+    return blocks ? launch_tail_b<true, true>(a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation, s)
+                  : launch_tail_b<true, false>(a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation, s);
+  if (blocks)
+    return launch_tail_b<false, true>(a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation, s);
+  return launch_tail_b<false, false>(a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation, s);
 }
 
 }  // namespace laser

@@ -4,6 +4,8 @@
 // and by the fused kernel that runs a whole single-tile call in one launch.
 #pragma once
 
+#include <type_traits>
+
 #include "analyse.h"
 #include "laser_internal.h"
 
@@ -51,6 +53,8 @@ namespace laser {
 
 constexpr int kChainWaves = 4;
 constexpr int kTailThreads = kChainWaves * 64;
+// workgroups that finish the tiles of a call
+__host__ __device__ inline int finish_groups(int ntiles) { return (ntiles + kChainWaves - 1) / kChainWaves; }
 constexpr int kSelfPrefixTiles = 1024;  // up to here finishing workgroups sum the counts themselves
 // (see "a handful of flexible tokens" below)
 constexpr int kFastMaxTiles = 256;
@@ -1714,6 +1718,320 @@ __device__ __forceinline__ int spec_walk2(uint8_t* lds, int nflex_tok, const Rou
   return decided;
 }
 
+// ---- the chain in blocks, side by side ---------------------------------------------------
+//
+// A long chain of load-dependent tokens is cut into blocks of consecutive ones, a workgroup
+// each.  A block is walked from a guess of the choices before it, and the guesses are mended
+// in rounds until every block has begun where the one before it ended: then, block by block from
+// the first (whose beginning is known), all of it is what one walk would have decided.  Nothing
+// but that equality, expert by expert, ends the rounds, so the guesses decide about time only;
+// every round makes at least one more block final.
+//
+// The guess.  Block q says where it began (I_q), where it ended (N_q) and how closely its tokens were
+// decided.  A correction d_q of I_q moves N_q by A_q d_q, so the correction of the next block is
+//     d_(q+1) = A_q d_q + (N_q - I_(q+1)),     d_0 = 0
+// (Newton's method for "every block begins where the one before ends").  A_q: an expert whose
+// counter is far from those it is compared with keeps a correction; experts whose counters are
+// level with one another forget it, because whoever is ahead is passed over until it is not, and only
+// what all of them got together stays.  With g_e in [0, 1] for how far expert e is of the second kind,
+//     (A d)_e = (1 - g_e) d_e + g_e (sum_i g_i d_i) / (sum_i g_i).
+// g comes from a sample of the block's tokens: how often the expert was chosen or passed over with at
+// most one to spare.
+// (Rounds until 16384 load-dependent tokens of 64 experts are decided, k = 6, c = 8, blocks of 256: 8 to
+// 10; without A, 62 to 64 in a simulation.)
+// What bounds a round of that call, 25 us: the walk of 256 tokens 15, the sample 1.7, the rows' way
+// through memory and what is made of them 4, the correction over 63 blocks 4.  The call: 889 -> 239 us; with
+// c = 10, 2279 -> 420; 8192 tokens of 64 candidates each 837 -> 159 (two rounds).  At 3072 tokens the walk alone is
+// about as fast.
+constexpr int kChainBlocks = 64;         // blocks of a call, at most
+constexpr int kChainBlockMin = 128;      // tokens of a block, at least
+constexpr int kChainBlocksMinTokens = 3072;  // load-dependent tokens from which on a call is walked in blocks
+constexpr int kBlockSamples = 32;        // tokens of a block that are looked at for g
+constexpr int kSamplesPerWave = kBlockSamples / kChainWaves;
+constexpr float kForgetHalf = 4.0f;      // close decisions per block that make g one half
+
+// What a block tells the others, per expert: where it began (27 bits), what it added (11), close
+// decisions among its samples (6), the round (20; 0: nothing yet, kBlockFinal: it stays so).  Whole
+// words travel at once, a row of them that shows one round in all of its words is of one piece.
+constexpr unsigned kBlockFinal = 0xFFFFFu;
+static_assert(kSelfPrefixTiles * kTile / kChainBlocks < (1 << 11), "what a block adds fits its field");
+__device__ __forceinline__ unsigned long long block_word(int begin, int added, int close, unsigned round) {
+  return ((unsigned long long)(unsigned)begin << 37) | ((unsigned long long)(unsigned)added << 26) |
+         ((unsigned long long)(unsigned)close << 20) | round;
+}
+__device__ __forceinline__ unsigned block_round(unsigned long long w) { return (unsigned)w & 0xFFFFFu; }
+__device__ __forceinline__ int block_close(unsigned long long w) { return (int)((unsigned)w >> 20) & 63; }
+__device__ __forceinline__ int block_added(unsigned long long w) { return (int)(w >> 26) & 2047; }
+__device__ __forceinline__ int block_begin(unsigned long long w) { return (int)(w >> 37); }
+
+// The rows stand where the logits were: nothing reads those any more.  Behind the rows of
+// all blocks: per expert the assignments of all tokens that are not load-dependent, then how many
+// blocks have written out their final choices.
+__device__ __forceinline__ unsigned long long* block_rows(const Workspace& ws) {
+  return reinterpret_cast<unsigned long long*>(ws.logits);
+}
+__device__ __forceinline__ int* blocks_done(const Workspace& ws) {
+  return reinterpret_cast<int*>(block_rows(ws) + kChainBlocks * 64 + 64);
+}
+static_assert((kChainBlocks * 64 + 64 + 1) * 8 <= kChainBlocksMinTokens * 9 * 4, "the rows fit the logits (9 experts at least)");
+// (by the chain workgroup, before the first flag; fixed: lane = expert, every wave the same)
+__device__ __forceinline__ void clear_block_rows(const Workspace& ws, int lane, int wave, int fixed) {
+  unsigned long long* const rows = block_rows(ws);
+  for (int i = threadIdx.x; i < kChainBlocks * 64; i += kTailThreads)
+    __hip_atomic_store(&rows[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (wave == 0)
+    __hip_atomic_store(&rows[kChainBlocks * 64 + lane], (unsigned long long)fixed, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) __hip_atomic_store(blocks_done(ws), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int chain_block_tokens(int nflex_tok) {
+  return max(kChainBlockMin, ((nflex_tok + kChainBlocks - 1) / kChainBlocks + 31) & ~31);
+}
+
+// Sum over the wavefront, as a scalar: inside the rows of 16 lanes as in wave_min_u32, then along the rows.
+__device__ __forceinline__ float wave_sum(float v) {
+  constexpr int kRowMirror = 0x140, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+  v += dpp_float<kQuadXor1>(v);
+  v += dpp_float<kQuadXor2>(v);
+  v += dpp_float<kRowHalfMirror>(v);
+  v += dpp_float<kRowMirror>(v);
+  v += dpp_float<kRowBcast15>(v);
+  v += dpp_float<kRowBcast31>(v);
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// Inclusive prefix sum over the wavefront.
+__device__ __forceinline__ float wave_prefix(float v) {
+  auto moved = [](float x, auto ctrl, auto rows) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, decltype(rows)::value, 0xF, false));
+  };
+  typedef std::integral_constant<int, 0xF> AllRows;
+  v += moved(v, std::integral_constant<int, 0x111>{}, AllRows{});  // within a row of 16: from 1, 2, 4, 8 lanes before
+  v += moved(v, std::integral_constant<int, 0x112>{}, AllRows{});
+  v += moved(v, std::integral_constant<int, 0x114>{}, AllRows{});
+  v += moved(v, std::integral_constant<int, 0x118>{}, AllRows{});
+  v += moved(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});  // the row before
+  v += moved(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});  // the two rows before
+  return v;
+}
+
+// What a block's workgroup keeps in LDS beside that of the walks.
+struct BlockLds {
+  float inv[kChainBlocks];     // of each block before: 1 / (sum of g)
+  unsigned open[kChainWaves];  // bit u of wave w's: the boundary behind block 16 w + u does not match
+  int first_begin[kChainWaves][64];  // where the first block of a wave began
+  int begin[64], begin_next[64];
+  int close[kChainWaves][64];
+  int ok, state;                // state: 0 go on, 1 the next walk is the last one, 2 this one was
+};
+// In the LDS of the walks, between two of them, for every block before this one { N_q - I_(q+1), g_q }.
+typedef float2 BlockRow[64];
+static_assert((kChainBlocks + 8) * sizeof(BlockRow) <= kChainLdsBytes, "the rows of all blocks, and read-ahead, fit the LDS of a walk");
+
+// How often the decisions of the block's samples were close, lane = expert; wave w looks at samples
+// 8 w .. 8 w + 7 (`slots`: lane i the record of the wave's i-th sample).
+__device__ __forceinline__ int block_close_decisions(int f0, int n, int slots, int begin, const RouteArgs& a,
+                                                     const Workspace& ws, int wave, int lane, int lin) {
+  const int shift = a.cw > kMaxC ? 6 : 4;
+  unsigned rec[kSamplesPerWave], bits[kSamplesPerWave];
+  int base[kSamplesPerWave], cum[kSamplesPerWave];
+  auto token = [&](int u) { return f0 + (int)((unsigned)((wave * kSamplesPerWave + u) * n) / kBlockSamples); };
+#pragma unroll
+  for (int u = 0; u < kSamplesPerWave; ++u) {
+    const int slot = __builtin_amdgcn_readlane(slots, u);
+    const int word = token(u) >> 5;
+    rec[u] = (ws.rec_lane + (size_t)slot * a.EP)[(unsigned)min(lane, a.EP - 1)];
+    base[u] = ws.tile_base[(size_t)(slot >> 6) * 64 + lane];
+    bits[u] = ws.chain_bits[(size_t)word * 64 + lane];
+    cum[u] = ws.chain_cum[(size_t)word * 64 + lane];
+  }
+  int close = 0;
+#pragma unroll
+  for (int u = 0; u < kSamplesPerWave; ++u) {
+    const int f = token(u);
+    const bool cand = lane < a.EP && rec[u] != 0xFFFFu;
+    const bool chosen = ((bits[u] >> (f & 31)) & 1u) != 0u;
+    const int so_far = ((f >> 5) == (f0 >> 5) ? begin : cum[u]) + __builtin_popcount(bits[u] & ((1u << (f & 31)) - 1u));
+    const unsigned load = (unsigned)(lin + base[u] + (int)(rec[u] >> shift) + so_far);
+    const unsigned least_out = wave_min_u32(cand && !chosen ? load : 0x7FFFFFFFu);
+    const unsigned most_in = 0x7FFFFFFFu - wave_min_u32(chosen ? 0x7FFFFFFFu - load : 0x7FFFFFFFu);
+    close += cand && (chosen ? least_out <= load + 1u : load <= most_in + 1u) ? 1 : 0;
+  }
+  return close;
+}
+
+// After a walk of the block [f0, f0 + n) from `begin` to `end` (wave 0, lane = expert), which was walk
+// number `round`: tells the others, waits for the blocks before this one to have come as far, and
+// works out the next beginning.  (tokens: of every block but the last.)  Returns the state (see BlockLds), or -1 where a wait ran out.
+__device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int blk, int tokens, unsigned round,
+                                               bool last_walk, int f0, int n, int slots, int end, const RouteArgs& a, const Workspace& ws, int wave,
+                                               int lane, int lin) {
+  own_lane(lane);
+  unsigned long long* const rows = block_rows(ws);
+  __syncthreads();  // (the walk's choices are written; begin[] was)
+  const int begin = S.begin[lane];
+  auto tell = [&](int close, unsigned r) {
+    __hip_atomic_store(&rows[(size_t)blk * 64 + lane], block_word(begin, end - begin, close, r), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (last_walk) {
+    if (wave == 0) tell(0, kBlockFinal);
+    return 2;
+  }
+  const int mine = block_close_decisions(f0, n, slots, begin, a, ws, wave, lane, lin);
+  S.close[wave][lane] = mine;
+  if (threadIdx.x == 0) S.ok = 1;
+  __syncthreads();
+  if (wave == 0) {
+    int close = 0;
+#pragma unroll
+    for (int w = 0; w < kChainWaves; ++w) close += S.close[w][lane];
+    tell(min(close, 63), round);
+  }
+  // ---- the rows of the blocks before, and the boundaries behind them: wave w those from 16 w on ---
+  constexpr int kPer = kChainBlocks / kChainWaves;
+  const int r0 = wave * kPer, r1 = min(blk, r0 + kPer);
+  int last_end = 0;
+  if (r0 < r1) {
+    unsigned long long v[kPer];
+    bool there = false;
+    for (long long it = 0; it < a.spin_limit && !there; ++it) {
+      // (the last of them first: it is the one that is waited for)
+      const unsigned long long probe =
+          __hip_atomic_load(&rows[(size_t)(r1 - 1) * 64 + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__builtin_amdgcn_ballot_w64(block_round(probe) < round) != 0ull) {
+        __builtin_amdgcn_s_sleep(2);
+        continue;
+      }
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        v[u] = __hip_atomic_load(&rows[(size_t)min(r0 + u, r1 - 1) * 64 + lane], __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+      bool whole = true;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const unsigned r = block_round(v[u]);
+        whole = whole && r >= round && r == (unsigned)__builtin_amdgcn_readfirstlane(r);
+      }
+      there = __builtin_amdgcn_ballot_w64(!whole) == 0ull;
+    }
+    if (!there) {
+      S.ok = 0;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) v[u] = 0ull;
+    }
+    // (one reading of every row: a row that is written again meanwhile must not be seen as two)
+    S.first_begin[wave][lane] = block_begin(v[0]);
+    unsigned open = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int end_u = block_begin(v[u]) + block_added(v[u]);
+      const int gap = u + 1 < kPer ? end_u - block_begin(v[u + 1 < kPer ? u + 1 : u]) : 0;
+      const float close = (float)block_close(v[u]) * ((float)tokens / kBlockSamples);
+      const float g = close * __builtin_amdgcn_rcpf(close + kForgetHalf);
+      const float sum = wave_sum(g);
+      if (r0 + u < r1) {
+        if (r0 + u + 1 == r1) last_end = end_u;
+        row[r0 + u][lane] = make_float2((float)gap, g);
+        if (lane == 0) S.inv[r0 + u] = sum > 0.0f ? __builtin_amdgcn_rcpf(sum) : 0.0f;
+        open |= (__builtin_amdgcn_ballot_w64(gap != 0) != 0ull ? 1u : 0u) << u;
+      }
+    }
+    if (lane == 0) S.open[wave] = open;
+  } else if (lane == 0) {
+    S.open[wave] = 0u;
+  }
+  __syncthreads();
+  if (S.ok == 0) {
+    if (threadIdx.x == 0) ws.status[kStatusError] = kErrorTimeout;
+    return -1;
+  }
+  if (r0 < r1) {
+    // (of the wave's last row the one behind is another wave's, or this block's own)
+    const int gap = last_end - (r1 == blk ? begin : S.first_begin[min(wave + 1, kChainWaves - 1)][lane]);
+    row[r1 - 1][lane].x = (float)gap;
+    const unsigned open = __builtin_amdgcn_ballot_w64(gap != 0) != 0ull ? 1u : 0u;
+    if (lane == 0) S.open[wave] = (S.open[wave] & ~(1u << (r1 - 1 - r0))) | (open << (r1 - 1 - r0));
+  }
+  __syncthreads();
+  // ---- the correction of this block's beginning ------------------------------------------------
+  if (wave == 0) {
+    unsigned long long open = 0ull;
+#pragma unroll
+    for (int w = 0; w < kChainWaves; ++w) open |= (unsigned long long)S.open[w] << (kPer * w);
+    open = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(open >> 32)) << 32) |
+           (unsigned)__builtin_amdgcn_readfirstlane((unsigned)open);
+    int state = 0, next = begin;
+    if (open == 0ull) {
+      state = 2;  // (everything before this block is decided, and it began there)
+    } else {
+      const int q0 = __builtin_ctzll(open);
+      const unsigned inv = __float_as_uint(S.inv[lane]);
+      float d = 0.0f;
+      // what bounds a step: the 8 dependent instructions of the sum and the waits between them
+      auto step = [&](const float2& x, int q) {
+        const float share = x.y * __uint_as_float(__builtin_amdgcn_readlane(inv, q));
+        const float keep = fmaf(-x.y, d, d + x.x);
+        d = fmaf(share, wave_sum(x.y * d), keep);
+      };
+      // (four rows ahead; behind the last one: read and not used)
+      const float2* from = &row[q0][lane];
+      float2 x0 = from[0], x1 = from[64], x2 = from[128], x3 = from[192];
+      int q = q0;
+      for (; q + 4 <= blk; q += 4) {
+        from += 256;
+        const float2 y0 = from[0], y1 = from[64], y2 = from[128], y3 = from[192];
+        __builtin_amdgcn_sched_barrier(0);
+        step(x0, q);
+        step(x1, q + 1);
+        step(x2, q + 2);
+        step(x3, q + 3);
+        __builtin_amdgcn_sched_barrier(0);
+        x0 = y0;
+        x1 = y1;
+        x2 = y2;
+        x3 = y3;
+      }
+      if (q < blk) step(x0, q);
+      if (q + 1 < blk) step(x1, q + 1);
+      if (q + 2 < blk) step(x2, q + 2);
+      if (q0 == blk - 1) {
+        state = 1;  // (the block before ended where everything is decided: this is no guess)
+        next = begin + (int)d;
+      } else {
+        // whole numbers, of the same sum; a correction that is one stays as it is
+        const int sum = (int)floorf(wave_prefix(d) + 0.5f);
+        const int before = __shfl_up(sum, 1, 64);
+        next = max(begin + sum - (lane > 0 ? before : 0), 0);
+      }
+    }
+    S.begin_next[lane] = next;
+    if (lane == 0) S.state = state;
+    if (state == 2) tell(0, kBlockFinal);
+  }
+  __syncthreads();
+  const int state = __builtin_amdgcn_readfirstlane(S.state);
+  const int next = S.begin_next[lane];
+  __syncthreads();
+  if (wave == 0) S.begin[lane] = next;
+  return state;
+}
+
+// The call's totals (one wave, lane = expert): the counters, and the exclusive prefix over the experts.
+__device__ __forceinline__ void chain_totals(int lane, int lin, int cnt, int E, int32_t* __restrict__ loads_inout,
+                                             int32_t* __restrict__ expert_offsets) {
+  if (lane < E) loads_inout[lane] = lin + cnt;
+  int incl = cnt;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int up = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += up;
+  }
+  if (lane < E) expert_offsets[lane] = incl - cnt;
+  if (lane == E - 1) expert_offsets[E] = incl;
+}
+
 // One segment of a pipelined call, as chain_workgroup sees it: `a` and `ws` are then the
 // segment's own view (tile 0 = the segment's first tile, flexible token 0 = its first
 // flexible token), and what the earlier segments did comes in through here.
@@ -1726,8 +2044,9 @@ struct ChainSeg {
 };
 
 // EP: the padded number of experts where it is known (the gate kernel of a pipelined call, whose
-// registers the walks that cannot occur would cost), else 0.
-template <int EP>
+// registers the walks that cannot occur would cost), else 0.  BLOCKS: a long chain is left to the
+// workgroups of its blocks (chain_block) once the lists of tokens are there.
+template <int EP, bool BLOCKS>
 __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
                                 int32_t* __restrict__ loads_inout,
                                 int32_t* __restrict__ expert_offsets, const ChainSeg seg) {
@@ -1740,7 +2059,6 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int ntiles = a.ntiles;
-
   // (a call without tokens has no analysis kernel that would have cleared the status
   // words, and no finishing workgroup that polls them)
   if (!seg.on && ntiles == 0 && threadIdx.x < 4) ws.status[threadIdx.x] = 0;
@@ -1891,17 +2209,8 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
 
   int gflex = 0;  // flexible assignments so far (meaningful in wave 0)
 
-  auto write_totals = [&]() {  // wave 0: final loads and the exclusive prefix over experts
-    const int cnt = lane < a.E ? total_fixed + gflex : 0;
-    if (lane < a.E) loads_inout[lane] = lin + cnt;
-    int incl = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int up = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += up;
-    }
-    if (lane < a.E) expert_offsets[lane] = incl - cnt;
-    if (lane == a.E - 1) expert_offsets[a.E] = incl;
+  auto write_totals = [&]() {  // wave 0
+    chain_totals(lane, lin, lane < a.E ? total_fixed + gflex : 0, a.E, loads_inout, expert_offsets);
   };
 
   // A segment hands its results to the caller instead of publishing anything.
@@ -1912,6 +2221,7 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
       seg.out[65] = nflex_tok;
     }
   };
+
   if (wave == 0 && (nflex_tiles > 0 || seg.on)) ws.chain_cum[lane] = 0;  // nothing chosen before flexible token 0
   if (seg.on) {
     if (nflex_tiles == 0) {
@@ -1921,13 +2231,17 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
     __syncthreads();  // tile_base, flex_slot written by every wave
   } else {
     if (nflex_tiles == 0 && wave == 0) write_totals();  // already final
+    const bool blocks = BLOCKS && nflex_tok >= kChainBlocksMinTokens;
+    if (blocks) clear_block_rows(ws, lane, wave, total_fixed);
     __syncthreads();  // tile_base, flex_slot (and the totals) written by every wave
     if (threadIdx.x == 0) {
-      ws.status[kStatusFlexTiles] = nflex_tiles;
+      ws.status[kStatusFlexTiles] = blocks ? -nflex_tiles : nflex_tiles;
       __hip_atomic_store(&ws.status[kStatusPhase], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (blocks) return;
     if (nflex_tiles == 0) return;
   }
+
 
   int decided = 0;
   unsigned hist0 = 0;
@@ -1973,6 +2287,71 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   if (wave == 0) write_totals();
   __syncthreads();
   if (threadIdx.x == 0)
+    __hip_atomic_store(&ws.status[kStatusPhase], 2, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Block `blk` of a chain of nflex_tok tokens (kTailThreads threads), see "the chain in blocks".
+__device__ __forceinline__ void chain_block(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
+                                            int32_t* __restrict__ loads_inout, int32_t* __restrict__ expert_offsets,
+                                            int blk, int nflex_tok) {
+  __shared__ BlockLds S;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int tokens = chain_block_tokens(nflex_tok);  // of every block but the last
+  const int f0 = blk * tokens, f1 = min(nflex_tok, f0 + tokens);
+  if (f0 >= nflex_tok) return;
+  const int lin = ws.lin_copy[lane];
+  // the lists of tokens, from the chain workgroup
+  if (wave == 0) {
+    const bool ok = poll_flag(&ws.status[kStatusPhase], 1, a.spin_limit);
+    if (lane == 0) {
+      S.ok = ok ? 1 : 0;
+      if (!ok) ws.status[kStatusError] = kErrorTimeout;
+    }
+    S.begin[lane] = 0;
+  }
+  __syncthreads();
+  if (S.ok == 0) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  const int sample = wave * kSamplesPerWave + min(lane, kSamplesPerWave - 1);
+  const int slots = ws.flex_slot[f0 + (int)((unsigned)(sample * (f1 - f0)) / kBlockSamples)];
+  int gflex = 0;  // wave 0, lane = expert: choices by the tokens before the block, then by those of the block too
+  bool last_walk = blk == 0;
+  unsigned round = 1;
+  for (;; ++round) {
+    if (a.c <= 8)
+      chain_walk_lag(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex);
+    else if (a.cw > kMaxC)
+      chain_walk<0>(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex);
+    else
+      chain_walk<16>(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex);
+    const int state = block_round_end(S, reinterpret_cast<BlockRow*>(lds), blk, tokens, round, last_walk, f0, f1 - f0,
+                                      slots, gflex, a, ws, wave, lane, lin);
+    if (state < 0) return;
+    if (state == 2) break;
+    last_walk = state == 1;
+    gflex = S.begin_next[lane];
+  }
+  __syncthreads();  // (the choices are written)
+  int* const done = blocks_done(ws);
+  if (f1 < nflex_tok) {
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  // the last block: the totals and the second flag, when all the others have written theirs
+  if (wave == 0) {
+    const bool ok = poll_flag(done, blk, a.spin_limit);
+    if (lane == 0) {
+      S.ok = ok ? 1 : 0;
+      if (!ok) ws.status[kStatusError] = kErrorTimeout;
+      ws.status[kStatusSweeps] = (int)round;
+    }
+    const int fixed = (int)__hip_atomic_load(&block_rows(ws)[kChainBlocks * 64 + lane], __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+    if (ok) chain_totals(lane, lin, lane < a.E ? fixed + gflex : 0, a.E, loads_inout, expert_offsets);
+  }
+  __syncthreads();
+  if (S.ok != 0 && threadIdx.x == 0)
     __hip_atomic_store(&ws.status[kStatusPhase], 2, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -2028,7 +2407,7 @@ constexpr int kGateSignals = 8;
 // The chain of a call, by the chain workgroup (kTailThreads threads) of the gate kernel
 // (IN_GATE: as far as the analysed tiles allow, nothing is published) or of the tail
 // kernel (the rest, then the totals and the flags the finishing workgroups wait for).
-template <bool IN_GATE, int EP>  // EP: see chain_workgroup
+template <bool IN_GATE, int EP, bool BLOCKS = false>  // EP, BLOCKS, blk: see chain_workgroup
 __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
                                                int32_t* __restrict__ loads_inout,
                                                int32_t* __restrict__ expert_offsets) {
@@ -2079,7 +2458,7 @@ __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a,
       sg.carry0 = carry;
       sg.fbase = fbase;
     }
-    chain_workgroup<EP>(lds, av, wv, loads_inout, expert_offsets, sg);
+    chain_workgroup<EP, BLOCKS>(lds, av, wv, loads_inout, expert_offsets, sg);
     if (!sg.on) return;
     __syncthreads();  // seg_out written (wave 0); the chain's LDS is free again
     carry = seg_out[lane];
@@ -2104,16 +2483,7 @@ __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a,
   // the totals, and the flags of the finishing workgroups
   if (wave == 0) {
     const int lin = lane < a.E ? loads_inout[lane] : 0;
-    const int cnt = lane < a.E ? carry : 0;
-    if (lane < a.E) loads_inout[lane] = lin + cnt;
-    int incl = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int up = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += up;
-    }
-    if (lane < a.E) expert_offsets[lane] = incl - cnt;
-    if (lane == a.E - 1) expert_offsets[a.E] = incl;
+    chain_totals(lane, lin, lane < a.E ? carry : 0, a.E, loads_inout, expert_offsets);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -2147,6 +2517,14 @@ struct FastShared {
   int tok[kFastTokens];                         // token index
   int tokf[kFastTokens];                        // index of its flexible tile
   unsigned long long emask[kFastTokens];        // the experts chosen for it
+};
+
+// LDS of a finishing workgroup beside the dynamic part.
+struct FinishShared {
+  int sh_before[kChainWaves][64], sh_all[kChainWaves][64];
+  int own_base[kChainWaves][64], own_offsets[64];
+  int sh_anyflex[kChainWaves];  // per wave: some tile it looked at holds flexible tokens
+  FastShared fs;
 };
 
 struct FinishLds {
@@ -2192,6 +2570,8 @@ __device__ __forceinline__ void finish_commit(FinishLds* fl, const FinishPrologu
 // If `self` is set the caller has already computed, for every expert, the number of
 // assignments in earlier tiles (own_base, LDS, 64 words) and the exclusive prefix over
 // experts of the totals (own_offsets, LDS, 64 words); nothing is awaited then.
+// (EARLY: where the chain is cut into blocks the tile is left to another workgroup, see finish_role)
+template <bool EARLY>
 __device__ __forceinline__ void finish_tile(FinishLds* fl, int tile, const FinishPrologue pro, const RouteArgs& a,
                             const Workspace& ws, const int32_t* __restrict__ expert_offsets,
                             int32_t* __restrict__ expert_ids, float* __restrict__ weights,
@@ -2210,7 +2590,9 @@ __device__ __forceinline__ void finish_tile(FinishLds* fl, int tile, const Finis
       ws.status[kStatusError] = kErrorTimeout;
       return;
     }
-    any_flex = load_published(&ws.status[kStatusFlexTiles]) > 0;
+    const int flex_tiles = load_published(&ws.status[kStatusFlexTiles]);
+    if (EARLY && flex_tiles < 0) return;
+    any_flex = flex_tiles != 0;
     if (any_flex && !poll_flag(&ws.status[kStatusPhase], 2, a.spin_limit)) {
       ws.status[kStatusError] = kErrorTimeout;
       return;
@@ -2376,7 +2758,7 @@ __device__ __forceinline__ void self_prefix(int t0, const RouteArgs& a, const Wo
 // per-token state lives in LDS and the loops over tokens are not unrolled.  (Inlined
 // by force, like every helper of this kernel: a real call gives the kernel a stack,
 // and every wave of it a slower start.)
-__device__ __forceinline__ int finish_fast(int block, FastShared& fs, unsigned long long fm_mine,
+__device__ __forceinline__ int finish_fast(int group, FastShared& fs, unsigned long long fm_mine,
                                            const int (&wg_cnt)[kChainWaves - 1], int (*sh_before)[64],
                                            int (*sh_all)[64], int (*own_base)[64], int* own_offsets,
                                            const RouteArgs& a, const Workspace& ws,
@@ -2384,7 +2766,7 @@ __device__ __forceinline__ int finish_fast(int block, FastShared& fs, unsigned l
                                            int32_t* __restrict__ expert_offsets) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int ntiles = a.ntiles;
-  const int t0 = (block - 1) * kChainWaves;
+  const int t0 = group * kChainWaves;
   const int tile = t0 + wave;
 
   // ---- the flexible tiles (wave w looked at tiles 64w .. 64w+63) ---------------------
@@ -2582,7 +2964,7 @@ __device__ __forceinline__ int finish_fast(int block, FastShared& fs, unsigned l
       if (lane >= d) incl += up;
     }
     own_offsets[lane] = incl - cnt;
-    if (block == 1) {
+    if (group == 0) {
       // the chain workgroup leaves such calls alone: the totals are written here
       if (lane < a.E) {
         loads_inout[lane] = lin + cnt;
@@ -2595,24 +2977,42 @@ __device__ __forceinline__ int finish_fast(int block, FastShared& fs, unsigned l
   return ntok;
 }
 
-// What workgroup `block` of the tail grid does (kTailThreads threads): 0 is the chain,
-// b >= 1 finishes tiles kChainWaves * (b - 1) ... .  tail_lds: kChainLdsBytes of LDS.
-template <bool CHAIN>  // block 0 is among them
-__device__ __forceinline__ void tail_role(int block, uint8_t* tail_lds, const RouteArgs& a,
-                                          const Workspace& ws, int32_t* __restrict__ loads_inout,
-                                          int32_t* __restrict__ expert_offsets,
-                                          int32_t* __restrict__ expert_ids, float* __restrict__ weights,
-                                          int32_t* __restrict__ permutation) {
-  if (CHAIN && block == 0) {
-    chain_segments<false, 0>(tail_lds, a, ws, loads_inout, expert_offsets);
-    return;
+// Load-dependent tokens of a call of at most kSelfPrefixTiles tiles, by the whole workgroup.
+__device__ __forceinline__ int count_flexible(int ntiles, const Workspace& ws) {
+  __shared__ int found[kChainWaves];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int n = 0;
+#pragma unroll
+  for (int u = 0; u < kSelfPrefixTiles / kTailThreads; ++u) {
+    const int tile = threadIdx.x + u * kTailThreads;
+    n += __builtin_popcountll(tile < ntiles ? ws.flexmask[tile] : 0ull);
   }
-  __shared__ int sh_before[kChainWaves][64], sh_all[kChainWaves][64];
-  __shared__ int own_base[kChainWaves][64], own_offsets[64];
-  __shared__ int sh_anyflex[kChainWaves];  // per wave: some tile it looked at holds flexible tokens
-  __shared__ FastShared fs;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) n += __shfl_xor(n, d, 64);
+  if (lane == 0) found[wave] = n;
+  __syncthreads();
+  n = 0;
+  for (int w = 0; w < kChainWaves; ++w) n += found[w];
+  return __builtin_amdgcn_readfirstlane(n);
+}
+
+// Finishing workgroup `group` of the tail grid (kTailThreads threads): tiles kChainWaves * group ... .
+// tail_lds: kChainLdsBytes of LDS.  EARLY: where the chain is cut into blocks the workgroup leaves its
+// tiles to another one.
+template <bool EARLY>
+__device__ __forceinline__ void finish_role(int group, uint8_t* tail_lds, FinishShared& S, const RouteArgs& a,
+                                           const Workspace& ws, int32_t* __restrict__ loads_inout,
+                                           int32_t* __restrict__ expert_offsets,
+                                           int32_t* __restrict__ expert_ids, float* __restrict__ weights,
+                                           int32_t* __restrict__ permutation) {
+  auto& sh_before = S.sh_before;
+  auto& sh_all = S.sh_all;
+  auto& own_base = S.own_base;
+  auto& own_offsets = S.own_offsets;
+  auto& sh_anyflex = S.sh_anyflex;
+  FastShared& fs = S.fs;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int t0 = (block - 1) * kChainWaves;
+  const int t0 = group * kChainWaves;
   const int tile = t0 + wave;
   // Small problems without flexible tokens need nothing from the chain workgroup:
   // every finishing workgroup sums the byte counts itself.
@@ -2663,7 +3063,7 @@ __device__ __forceinline__ void tail_role(int block, uint8_t* tail_lds, const Ro
     // a handful of flexible tokens: resolved here, by every workgroup for itself
     // (not in a pipelined call: there the chain workgroup walks every flexible token)
     if (__builtin_expect(!self && a.ntiles <= kFastMaxTiles && a.nseg == 0, 0)) {
-      fast_n = finish_fast(block, fs, fm_mine, wg_cnt, sh_before, sh_all, own_base, own_offsets, a, ws, loads_inout,
+      fast_n = finish_fast(group, fs, fm_mine, wg_cnt, sh_before, sh_all, own_base, own_offsets, a, ws, loads_inout,
                            expert_offsets);
       self = fast_n > 0;
     }
@@ -2671,7 +3071,7 @@ __device__ __forceinline__ void tail_role(int block, uint8_t* tail_lds, const Ro
     finish_commit(fl, pro, a.k);
   }
   if (tile >= a.ntiles) return;
-  finish_tile(fl, tile, pro, a, ws, expert_offsets, expert_ids, weights, permutation, self,
+  finish_tile<EARLY>(fl, tile, pro, a, ws, expert_offsets, expert_ids, weights, permutation, self,
               own_base[wave], own_offsets, fast_n, &fs);
 }
 

@@ -1,0 +1,149 @@
+"""Long chains of load-dependent tokens, which are cut into blocks that workgroups walk side by side,
+against the oracle, integers bit for bit: numbers of tokens around where that begins and around whole
+blocks, fixed tokens in between, equal counters and counters far apart, tokens that all compete and
+tokens that hardly do, every width of the records, several problems and streams at once."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from synth import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+FIRST = 3072      # load-dependent tokens from which on a chain is cut
+SHAPES = [(64, 6, 8), (9, 2, 3), (16, 4, 12), (33, 3, 9), (64, 6, 64), (20, 3, 18)]
+
+
+def _check(logits, E, k, c, loads, eps, label):
+    """Against the oracle; the walks of the call's last block (the fourth status word)."""
+    import oracle
+    import torch
+    from paper_2510_03293_amd import binding as B
+    from tests import gpu_util as u
+    dev = torch.from_numpy(np.ascontiguousarray(loads, dtype=np.int32)).cuda()
+    buf = B.route_from_logits(torch.from_numpy(np.ascontiguousarray(logits)).cuda(), B.make_params(k, c, eps, 1e-30), dev)
+    torch.cuda.synchronize()
+    print(label, flush=True)
+    u.assert_discrete_equal(u._collect(buf, dev, None), oracle.route(logits, k, c, eps, 1e-30, loads), label)
+    return int(buf.workspace[:16].view(torch.int32)[3])
+
+
+def _skewed(seed, T, E, scale=0.9):
+    rng = np.random.default_rng(seed)
+    rank = rng.permutation(E) + 1
+    return (-1.1 * np.log(rank)[None, :] + scale * rng.standard_normal((T, E))).astype(np.float32)
+
+
+# (blocks of 128 up to 8192 tokens, of the 64th part rounded up to 32 beyond)
+@pytest.mark.parametrize("T", [FIRST - 1, FIRST, FIRST + 1, 3199, 3201, 4097, 8192, 8193, 10241])
+@pytest.mark.parametrize("E,k,c", SHAPES)
+def test_block_sizes(T, E, k, c):
+    rng = np.random.default_rng(T + E)
+    _check(_skewed(T + c, T, E), E, k, c, np.zeros(E), 2.0, f"T{T} E{E} k{k} c{c} skewed")
+    _check(wl.random_logits(T + c, T, E, kind="normal", scale=0.3), E, k, c, rng.integers(0, 50, size=E), 2.0,
+           f"T{T} E{E} k{k} c{c} flat")
+
+
+@pytest.mark.parametrize("E,k,c", SHAPES + [(64, 2, 4), (64, 9, 16)])
+def test_counters_far_apart_and_fixed_tokens(E, k, c):
+    T = 6000
+    rng = np.random.default_rng(E + c)
+    logits = _skewed(E * c, T, E)
+    _check(logits, E, k, c, rng.permutation(E) * 10 * T, 2.0, f"far E{E} c{c}")
+    _check(logits, E, k, c, np.where(np.arange(E) % 3 == 0, 0, (1 << 27) - 1 - T), 2.0, f"limit E{E} c{c}")
+    logits[rng.random(T) < 0.4, 0] += 30.0   # (their top-k whatever the loads)
+    _check(logits, E, k, c, np.zeros(E), 0.999, f"mixed E{E} c{c}")
+
+
+@pytest.mark.parametrize("T", [8 * FIRST - 1, 8 * FIRST, 40000, 64 * 1024, 64 * 1024 + 1])
+def test_some_tokens_of_long_calls(T):
+    """Thresholds that most tokens pass, a fifth of the rows flat: blocks from 8 * FIRST tokens on,
+    up to 1024 tiles."""
+    rng = np.random.default_rng(T)
+    logits = _skewed(T, T, 64)
+    flat = rng.random(T) < 0.2
+    logits[flat] = (0.05 * rng.standard_normal((int(flat.sum()), 64))).astype(np.float32)
+    import oracle
+    import torch
+    from paper_2510_03293_amd import binding as B
+    from tests import gpu_util as u
+    loads = torch.zeros(64, dtype=torch.int32, device="cuda")
+    buf = B.route_from_logits(torch.from_numpy(logits).cuda(), B.make_params(6, 8, 0.4, 0.8), loads)
+    torch.cuda.synchronize()
+    u.assert_discrete_equal(u._collect(buf, loads, None), oracle.route(logits, 6, 8, 0.4, 0.8, np.zeros(64, np.int32)),
+                            f"T{T}")
+
+
+def test_one_row_for_all_tokens():
+    """Every token has the same candidates: whoever is ahead is passed over, block after block."""
+    for E, k, c in ((64, 6, 8), (16, 4, 12), (64, 6, 64)):
+        logits = np.repeat(wl.random_logits(E + k, 1, E, kind="normal", scale=1.0), 5000, axis=0)
+        _check(logits, E, k, c, np.zeros(E), 2.0, f"one row E{E} c{c}")
+
+
+def test_full_size_calls_take_few_rounds():
+    """16384 tokens, a skewed gate: a call that had to make its 64 blocks final one by one would be
+    right too, but slower than a single walk (12 rounds in a simulation of such a call at most)."""
+    for seed in (1, 2, 3):
+        assert _check(_skewed(seed, 16384, 64), 64, 6, 8, np.zeros(64), 2.0, f"full seed {seed}") <= 20
+    assert _check(_skewed(4, 8192, 64), 64, 6, 64, np.zeros(64), 2.0, "load only") <= 4
+
+
+def test_random_trimming_in_blocks():
+    from tests import gpu_util as u
+    for E, k, c in ((64, 6, 8), (33, 3, 16), (40, 3, 30)):
+        u.check_random_from_logits(_skewed(c, 7001, E), k, c, 2.0, 1e-30, np.zeros(E, np.int32), seed=5, stream=2,
+                                   label=f"random E{E} c{c}")
+
+
+def test_streams_side_by_side_and_replays():
+    """Two calls at once on two streams, then one of them from a HIP graph, several times."""
+    import oracle
+    import torch
+    from paper_2510_03293_amd import binding as B
+    from tests import gpu_util as u
+    E, k, c, T = 64, 6, 8, 6001
+    params = B.make_params(k, c, 2.0, 1e-30)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    z = [_skewed(70 + i, T, E) for i in range(2)]
+    dev = [torch.from_numpy(x).cuda() for x in z]
+    want = [oracle.route(x, k, c, 2.0, 1e-30, np.zeros(E, np.int32)) for x in z]
+    bufs = [B.RouteBuffers(T, 0, E, params) for _ in range(2)]
+    loads = [torch.zeros(E, dtype=torch.int32, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+
+    def call(i, stream):
+        b = bufs[i]
+        B.laser_route_from_logits(dev[i], T, E, params, loads[i], b.expert_ids, b.weights, b.permutation,
+                                  b.expert_offsets, b.workspace, stream)
+
+    for _ in range(3):
+        for i in range(2):
+            with torch.cuda.stream(streams[i]):
+                loads[i].zero_()
+                call(i, streams[i])
+        torch.cuda.synchronize()
+        for i in range(2):
+            u.assert_discrete_equal(u._collect(bufs[i], loads[i], None), want[i], f"stream {i}")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(0, None)
+    for n in range(4):
+        loads[0].zero_()
+        bufs[0].expert_ids.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        u.assert_discrete_equal(u._collect(bufs[0], loads[0], None), want[0], f"replay {n}")
+
+
+def test_batched_problems():
+    from tests import gpu_util as u
+    import oracle
+    nb, T, H, E, k, c = 3, 3500, 64, 64, 6, 8
+    rng = np.random.default_rng(9)
+    hidden = [wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32)) for _ in range(nb)]
+    w = [wl.f32_to_bf16_bits((0.2 * rng.standard_normal((E, H))).astype(np.float32)) for _ in range(nb)]
+    loads = [np.zeros(E, np.int32) for _ in range(nb)]
+    for b, got in enumerate(u.run_route_batched(hidden, w, wl.DTYPE_BF16, k, c, 2.0, 1e-30, loads)):
+        u.assert_discrete_equal(got, oracle.route(got["logits"], k, c, 2.0, 1e-30, loads[b]), f"problem {b}")
