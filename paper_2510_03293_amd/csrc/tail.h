@@ -2530,6 +2530,7 @@ struct FinishShared {
 struct FinishLds {
   unsigned long long mask64[64];
   int before[64];  // per expert: slots of all earlier experts + of this expert in earlier tiles
+  unsigned bits[3][64];  // per expert: the chain's words in which the tile's flexible tokens are
   uint8_t ids[kTile][kMaxC];
 };
 
@@ -2557,117 +2558,65 @@ __device__ __forceinline__ FinishPrologue finish_prologue(int tile, const RouteA
 }
 
 // experts of the tokens that are final already go to LDS (rows of flexible tokens hold
-// stale data; they are overwritten in finish_tile)
+// stale data; they are overwritten in finish_row)
 __device__ __forceinline__ void finish_commit(FinishLds* fl, const FinishPrologue& p, int k) {
   const int lane = threadIdx.x & 63;
-  fl->mask64[lane] = p.tmask;  // the flexible tokens add themselves in finish_tile
+  fl->mask64[lane] = p.tmask;  // the flexible tokens add themselves in finish_row
 #pragma unroll
   for (int j = 0; j < kMaxC; ++j)
     if (j < k) fl->ids[lane][j] = (uint8_t)p.ids[j];
 }
 
-// One wavefront, one tile; `fl` is this wave's private LDS.
-// If `self` is set the caller has already computed, for every expert, the number of
-// assignments in earlier tiles (own_base, LDS, 64 words) and the exclusive prefix over
-// experts of the totals (own_offsets, LDS, 64 words); nothing is awaited then.
-// (EARLY: where the chain is cut into blocks the tile is left to another workgroup, see finish_role)
-template <bool EARLY>
-__device__ __forceinline__ void finish_tile(FinishLds* fl, int tile, const FinishPrologue pro, const RouteArgs& a,
-                            const Workspace& ws, const int32_t* __restrict__ expert_offsets,
-                            int32_t* __restrict__ expert_ids, float* __restrict__ weights,
-                            int32_t* __restrict__ permutation, bool self, const int* own_base,
-                            const int* own_offsets, int fast_n = 0, const FastShared* fast = nullptr) {
+// A flexible token (lane = token) whose choice is known: its experts in score order and their weights,
+// and its bit in the masks of those experts.  `chosen(j)`, `id(j)`, `p(j)`: of rank j < cstar, of which
+// n_ranks are looked at (the loop is the same in every lane).
+template <typename Chosen, typename Id, typename P>
+__device__ __forceinline__ void finish_row(FinishLds* fl, int t, int cstar, int n_ranks, float Z, const RouteArgs& a,
+                                           int32_t* __restrict__ expert_ids, float* __restrict__ weights, Chosen chosen,
+                                           Id id, P p) {
   const int lane = threadIdx.x & 63;
-  const int t = tile * kTile + lane;
-  const bool live = t < a.T;
   const int k = a.k;
-  const int cstar = pro.cstar;
-  const unsigned long long fm = pro.fm;
-
-  bool any_flex = false;
-  if (__builtin_expect(!self, 0)) {
-    if (!poll_flag(&ws.status[kStatusPhase], 1, a.spin_limit)) {
-      ws.status[kStatusError] = kErrorTimeout;
-      return;
-    }
-    const int flex_tiles = load_published(&ws.status[kStatusFlexTiles]);
-    if (EARLY && flex_tiles < 0) return;
-    any_flex = flex_tiles != 0;
-    if (any_flex && !poll_flag(&ws.status[kStatusPhase], 2, a.spin_limit)) {
-      ws.status[kStatusError] = kErrorTimeout;
-      return;
-    }
-  }
-
-  // lane = expert: where this tile's first slot of the expert goes.  With flexible
-  // tokens about, the choices made for the f0 flexible tokens of earlier tiles are
-  // the running count at the last 32-token boundary plus the bits since.
-  const int f0 = any_flex ? load_published(&ws.flex_tok_base[tile]) : 0;
-  {
-    int bef;
-    if (__builtin_expect(self, 1)) {
-      bef = own_offsets[lane] + own_base[lane];
-    } else {
-      bef = (lane < a.E ? load_published(&expert_offsets[lane]) : 0) +
-            load_published(&ws.tile_base[(size_t)tile * 64 + lane]);
-      if (any_flex) {
-        const size_t w = (size_t)(f0 >> 5) * 64 + lane;
-        const unsigned bits = load_published(&ws.chain_bits[w]) & ((1u << (f0 & 31)) - 1u);
-        bef += load_published(&ws.chain_cum[w]) + __builtin_popcount(bits);
+  float denom = Z;
+  if (a.renormalize) {
+    bool first = true;
+#pragma unroll
+    for (int j = 0; j < kMaxC; ++j) {
+      if (j >= n_ranks) break;
+      if (j < cstar && chosen(j)) {
+        denom = first ? p(j) : denom + p(j);
+        first = false;
       }
     }
-    fl->before[lane] = bef;
   }
-
-  if (__builtin_expect(cstar > 0, 0)) {
-    const int f = f0 + __builtin_popcountll(fm & lanes_below(lane));
-    const unsigned* cw = ws.chain_bits + (size_t)(f >> 5) * 64;
-    // (called twice so that each copy knows its address space: LDS or memory)
-    auto write_row = [&](const uint8_t* ids, const float* pv, float Z, unsigned long long chosen) {
-      float denom = Z;
-      if (a.renormalize) {
-        bool first = true;
-        for (int j = 0; j < cstar; ++j) {
-          if ((chosen >> ids[j]) & 1ull) {
-            denom = first ? pv[j] : denom + pv[j];
-            first = false;
-          }
-        }
-      }
-      int n = 0;
-      for (int j = 0; j < cstar; ++j) {
-        const int e = ids[j];
-        if (((chosen >> e) & 1ull) && n < k) {  // (exactly k bits are set; n < k keeps the row)
-          expert_ids[(size_t)t * k + n] = e;
-          weights[(size_t)t * k + n] = pv[j] / denom;
-          fl->ids[lane][n] = (uint8_t)e;
-          ++n;
-        }
-      }
-    };
-    if (fast_n > 0) {
-      // the workgroup resolved the call's few flexible tokens itself: all is in LDS
-      int n = 0;
-      for (int i = 0; i < fast_n; ++i) n = fast->tok[i] == t ? i : n;
-      write_row(fast->rids[n], fast->p[n], fast->Z[n], fast->emask[n]);
-    } else {
-      const uint8_t* ids = ws.rec_ids + (size_t)t * a.cw;
-      unsigned long long chosen = 0ull;
-      for (int j = 0; j < cstar; ++j)
-        chosen |= (unsigned long long)((load_published(&cw[ids[j]]) >> (f & 31)) & 1u) << ids[j];
-      write_row(ids, ws.rec_p + (size_t)t * a.cw, a.renormalize ? 0.0f : ws.rec_Z[t], chosen);
+  int n = 0;
+#pragma unroll
+  for (int j = 0; j < kMaxC; ++j) {
+    if (j >= n_ranks) break;
+    if (j < cstar && chosen(j) && n < k) {  // (exactly k are chosen; n < k keeps the row)
+      const int e = id(j);
+      expert_ids[(size_t)t * k + n] = e;
+      weights[(size_t)t * k + n] = p(j) / denom;
+      fl->ids[lane][n] = (uint8_t)e;
+      atomicOr(&fl->mask64[e], 1ull << lane);
+      ++n;
     }
   }
-  // LDS traffic of one wavefront is processed in order; the fences only stop the
-  // compiler from moving reads above the other lanes' writes
+}
+
+// LDS traffic of one wavefront is processed in order; the fences only stop the
+// compiler from moving reads above the other lanes' writes.
+__device__ __forceinline__ void finish_fence() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __builtin_amdgcn_wave_barrier();
-  // (the masks came from the analysis with the non-flexible tokens in them)
-  if (__builtin_expect(cstar > 0, 0))
-    for (int j = 0; j < k; ++j) atomicOr(&fl->mask64[fl->ids[lane][j]], 1ull << lane);
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  if (live) {
+}
+
+// One wavefront, one tile; `fl` is this wave's private LDS, complete: every slot of the tile.
+__device__ __forceinline__ void finish_slots(FinishLds* fl, int t, const RouteArgs& a, const Workspace& ws,
+                                             int32_t* __restrict__ permutation) {
+  const int lane = threadIdx.x & 63;
+  const int k = a.k;
+  finish_fence();
+  if (t < a.T) {
     const unsigned long long below = lanes_below(lane);
     for (int j = 0; j < k; ++j) {
       const int e = fl->ids[lane][j];
@@ -2680,6 +2629,137 @@ __device__ __forceinline__ void finish_tile(FinishLds* fl, int tile, const Finis
         ws.status[kStatusError] = kErrorInconsistent;
     }
   }
+}
+
+// A tile of a call without flexible tokens, or (fast_n > 0) with a handful of them that this workgroup has
+// decided itself: the caller has computed, for every expert, the number of assignments in earlier
+// tiles (own_base, LDS, 64 words) and the exclusive prefix over experts of the totals (own_offsets).
+__device__ __forceinline__ void finish_tile(FinishLds* fl, int tile, const FinishPrologue& pro, const RouteArgs& a,
+                                            const Workspace& ws, int32_t* __restrict__ expert_ids,
+                                            float* __restrict__ weights, int32_t* __restrict__ permutation,
+                                            const int* own_base, const int* own_offsets, int fast_n,
+                                            const FastShared* fast) {
+  const int lane = threadIdx.x & 63;
+  const int t = tile * kTile + lane;
+  fl->before[lane] = own_offsets[lane] + own_base[lane];
+  if (__builtin_expect(fast_n > 0, 0)) {
+    finish_fence();
+    if (pro.cstar > 0) {
+      int n = 0;
+      for (int i = 0; i < fast_n; ++i) n = fast->tok[i] == t ? i : n;
+      const unsigned long long emask = fast->emask[n];
+      finish_row(fl, t, pro.cstar, a.c, fast->Z[n], a, expert_ids, weights,
+                 [&](int j) { return ((emask >> fast->rids[n][j]) & 1ull) != 0ull; },
+                 [&](int j) { return (int)fast->rids[n][j]; }, [&](int j) { return fast->p[n][j]; });
+    }
+  }
+  finish_slots(fl, t, a, ws, permutation);
+}
+
+// A tile of a call whose chain runs in another workgroup.  What does not depend on the chain's choices
+// is asked for before they are waited for; what does comes in one round trip, a row of experts per
+// load: the tile's flexible tokens are in at most three words of 32.  (A byte and a word per candidate, one
+// after the other, before: 3001 tokens, 287 flexible, from the flag to the last store 7.3 -> 4.3 us.)
+// (EARLY: where the chain is cut into blocks the tile is left to another workgroup, see finish_role)
+template <bool EARLY>
+__device__ __forceinline__ void finish_tile_of_chain(FinishLds* fl, int tile, const FinishPrologue& pro,
+                                                     const RouteArgs& a, const Workspace& ws,
+                                                     const int32_t* __restrict__ expert_offsets,
+                                                     int32_t* __restrict__ expert_ids, float* __restrict__ weights,
+                                                     int32_t* __restrict__ permutation) {
+  const int lane = threadIdx.x & 63;
+  const int t = tile * kTile + lane;
+  const int cstar = pro.cstar;
+  const bool narrow = a.cw == kMaxC;
+  // records of up to 16 candidates: in registers
+  uint4 ids = make_uint4(0, 0, 0, 0);
+  float p[kMaxC] = {};
+  float Z = 0.0f;
+  if (cstar > 0) {
+    Z = ws.rec_Z[t];
+    if (narrow) {
+      ids = reinterpret_cast<const uint4*>(ws.rec_ids)[t];
+#pragma unroll
+      for (int i = 0; i < kMaxC / 4; ++i) {
+        if (4 * i >= a.c) break;
+        const float4 v = reinterpret_cast<const float4*>(ws.rec_p)[(size_t)t * (kMaxC / 4) + i];
+        p[4 * i] = v.x;
+        p[4 * i + 1] = v.y;
+        p[4 * i + 2] = v.z;
+        p[4 * i + 3] = v.w;
+      }
+    }
+  }
+  if (!poll_flag(&ws.status[kStatusPhase], 1, a.spin_limit)) {
+    ws.status[kStatusError] = kErrorTimeout;
+    return;
+  }
+  const int flex_tiles = load_published(&ws.status[kStatusFlexTiles]);
+  if (EARLY && flex_tiles < 0) return;
+  // lane = expert: where this tile's first slot of the expert goes.  With flexible
+  // tokens about, the choices made for the f0 flexible tokens of earlier tiles are
+  // the running count at the last 32-token boundary plus the bits since.
+  int before = load_published(&ws.tile_base[(size_t)tile * 64 + lane]);
+  if (flex_tiles != 0) {
+    const int f0 = load_published(&ws.flex_tok_base[tile]);
+    if (!poll_flag(&ws.status[kStatusPhase], 2, a.spin_limit)) {
+      ws.status[kStatusError] = kErrorTimeout;
+      return;
+    }
+    const size_t w = (size_t)(f0 >> 5) * 64 + lane;
+    unsigned bits[3];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) bits[u] = load_published(&ws.chain_bits[w + 64 * u]);
+    const int cum = load_published(&ws.chain_cum[w]);
+    const int offset = lane < a.E ? load_published(&expert_offsets[lane]) : 0;
+    fl->before[lane] = offset + before + cum + __builtin_popcount(bits[0] & ((1u << (f0 & 31)) - 1u));
+#pragma unroll
+    for (int u = 0; u < 3; ++u) fl->bits[u][lane] = bits[u];
+    finish_fence();
+    if (cstar > 0) {
+      const int f = (f0 & 31) + __builtin_popcountll(pro.fm & lanes_below(lane));
+      const unsigned* row = fl->bits[f >> 5];
+      if (narrow) {
+        const unsigned idw[4] = {ids.x, ids.y, ids.z, ids.w};
+        auto id = [&](int j) { return (int)((idw[j >> 2] >> (8 * (j & 3))) & 255u); };
+        unsigned chosen = 0;
+#pragma unroll
+        for (int j = 0; j < kMaxC; ++j) {
+          if (j >= a.c) break;
+          chosen |= ((row[id(j) & 63] >> (f & 31)) & 1u) << j;
+        }
+        finish_row(fl, t, cstar, a.c, Z, a, expert_ids, weights, [&](int j) { return ((chosen >> j) & 1u) != 0u; }, id,
+                   [&](int j) { return p[j]; });
+      } else {
+        const uint8_t* wide_ids = ws.rec_ids + (size_t)t * kWideC;
+        const float* wide_p = ws.rec_p + (size_t)t * kWideC;
+        float denom = Z;
+        if (a.renormalize) {
+          bool first = true;
+          for (int j = 0; j < cstar; ++j) {
+            if ((row[wide_ids[j]] >> (f & 31)) & 1u) {
+              denom = first ? wide_p[j] : denom + wide_p[j];
+              first = false;
+            }
+          }
+        }
+        int n = 0;
+        for (int j = 0; j < cstar; ++j) {
+          const int e = wide_ids[j];
+          if (((row[e] >> (f & 31)) & 1u) && n < a.k) {
+            expert_ids[(size_t)t * a.k + n] = e;
+            weights[(size_t)t * a.k + n] = wide_p[j] / denom;
+            fl->ids[lane][n] = (uint8_t)e;
+            atomicOr(&fl->mask64[e], 1ull << lane);
+            ++n;
+          }
+        }
+      }
+    }
+  } else {
+    fl->before[lane] = before + (lane < a.E ? load_published(&expert_offsets[lane]) : 0);
+  }
+  finish_slots(fl, t, a, ws, permutation);
 }
 
 // Per-expert assignment counts of the tiles before `t0` and of all tiles, summed by
@@ -3071,8 +3151,10 @@ __device__ __forceinline__ void finish_role(int group, uint8_t* tail_lds, Finish
     finish_commit(fl, pro, a.k);
   }
   if (tile >= a.ntiles) return;
-  finish_tile<EARLY>(fl, tile, pro, a, ws, expert_offsets, expert_ids, weights, permutation, self,
-              own_base[wave], own_offsets, fast_n, &fs);
+  if (__builtin_expect(self, 1))
+    finish_tile(fl, tile, pro, a, ws, expert_ids, weights, permutation, own_base[wave], own_offsets, fast_n, &fs);
+  else
+    finish_tile_of_chain<EARLY>(fl, tile, pro, a, ws, expert_offsets, expert_ids, weights, permutation);
 }
 
 }  // namespace laser
