@@ -68,7 +68,7 @@ __device__ __forceinline__ bool fast_path_applies(int ntiles, int nflex_tiles, i
 }
 
 
-constexpr int kChainLdsBytes = 56 * 1024;  // dynamic LDS of a chain workgroup, used by one phase after the other
+constexpr int kChainLdsBytes = 57 * 1024;  // dynamic LDS of a chain workgroup, used by one phase after the other
 constexpr int kChainStageTiles = kChainLdsBytes / 64;  // tiles of byte counts that fit the LDS
 
 // Data published by the chain workgroup is read with agent-scope atomic loads: they
@@ -1034,7 +1034,6 @@ constexpr int kSpecRing = 3 * kSpecSeg;       // tokens in the LDS ring
 constexpr unsigned kSpecInvalid = 1u << 27;   // counter of a rank beyond the working set
 constexpr int kSpecMinTokens = 256;           // fewer flexible tokens: sequential walk
 constexpr int kSpecCheckSweeps = 8;           // progress is judged over this many sweeps
-constexpr int kSpecGuessProgress = 26 * kSpecCheckSweeps;  // (without guesses at most 32 per sweep retire)
 // Window of 64, up to 8 candidates.  Break-even with the walk: a sweep costs 0.56 / 0.9 us for 4 / 8
 // candidates, a step of the walk 0.052, so 10.8 / 17.3 tokens per sweep.  It is given up when a run of
 // sweeps is below that and the sweeps so far have cost more than walking their tokens -- if the run
@@ -1044,12 +1043,9 @@ constexpr int kSpecGuessProgress = 26 * kSpecCheckSweeps;  // (without guesses a
 // where no tokens compete, 850 walked; where they do, 860 with the attempt.)
 constexpr int spec_break_even(int cp) { return cp <= 4 ? 88 : 140; }  // per kSpecCheckSweeps
 constexpr int kSpecWarmUp = 4;
-// All other windows: fewer than this many tokens in the last run of sweeps, and in all of them on the
-// average.  Far below break-even: these lines are from when a step of the walk cost 0.17 us.
-// A sweep costs 1.0 / 1.7 us in the window of 128 (4 / 8 candidates), so with up to 8 candidates that
-// window is held on to between about 6 and 20 to 32 tokens per sweep, where the walk would be the
-// faster one (16 experts, k = 2, c = 4, 9862 load-dependent tokens, 8 per sweep: 1196 us; walked 525).
-constexpr int spec_min_progress(int cp) { return cp <= 4 ? 40 : cp <= 8 ? 48 : 56; }
+// Window of 64, up to 16 candidates: fewer than this many tokens in the last run of sweeps, and in all of
+// them on the average.
+constexpr int kSpecMinProgress = 56;  // per kSpecCheckSweeps
 
 template <int CP>
 struct SpecTok {
@@ -1318,7 +1314,7 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
             constexpr int line = spec_break_even(CP);
             const int lost = total_sweeps * line / kSpecCheckSweeps - done;  // in tokens walked
             if (left > 64 && progress < line && lost > (progress < line / 2 ? 0 : left / 8)) bail = true;
-          } else if (progress < spec_min_progress(CP) && done * kSpecCheckSweeps < spec_min_progress(CP) * total_sweeps &&
+          } else if (progress < kSpecMinProgress && done * kSpecCheckSweeps < kSpecMinProgress * total_sweeps &&
                      left > 2 * kSpecSeg) {
             bail = true;
           }
@@ -1345,377 +1341,349 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
   return decided;
 }
 
-// ---- window of 128 tokens, two consumer wavefronts -----------------------------------
+// ---- window of 256 tokens, four wavefronts -----------------------------------------------
 //
-// Where tokens rarely compete (many experts behind each candidate: the variants with
-// first guesses) a sweep usually retires most of its window, so a wider window decides
-// more tokens for the same chain of dependent steps.  Waves 0 and 1 each hold 64 of the
-// 128 window positions (position = flexible token number mod 128; wave = position / 64,
-// lane = position mod 64) and evaluate them exactly as above; an expert's tentative
-// choices are a 128-bit mask, of which each consumer wave writes only its own half.
-// A sweep has two workgroup barriers that settle LDS traffic only: after the
-// evaluation both waves publish which of their lanes changed, so that every wave finds
-// the same first changed token; after the retirement (each consumer wave, lane =
-// expert, retires its own half of the masks) the next evaluation may read.  Waves 2
-// and 3 take part in the barriers and in between stage the per-token data into an LDS
-// ring of 512 tokens: each stages 64 tokens per sweep, with the three dependent loads of
-// a token (its slot, its record, the counters of its candidates) spread over three
-// sweeps so that none of them is waited for.  Decided bits go to a small ring of output
-// words in LDS; wave 3 writes out the words that are complete.
-constexpr int kRing2 = 512;         // tokens in the LDS ring
-constexpr int kSpecOutWords = 16;   // output staging ring, words of 32 tokens
-constexpr int kSpecMeetPolls = 1 << 14;  // looks of one consumer wave for the other one, per sweep
+// Where tokens rarely compete (many experts behind each candidate) a sweep retires most of its
+// window, so a wide window decides more tokens for the same chain of dependent steps.  The four
+// wavefronts hold 64 of the 256 window positions each (position = flexible token number mod 256; wave =
+// position / 64, lane = position mod 64) and evaluate them as above.  A wave owns the masks of its
+// positions; what the tokens of the other waves chose enters as one number per expert, summed up
+// once per sweep, so an evaluation costs as much as in the window of 64.
+//
+// A sweep:
+//   count     lane = expert: the masks of all waves, for the wave's own tokens the choices before them
+//   evaluate  lane = token
+//   -- barrier: every wave finds the same first changed token --
+//   retire    lane = expert: the choices up to that token are final, its own being the new one
+//   enter     lane = token: the next tokens, with the choice by the counters as they stand as first
+//             guess (any guess gives the same result); the choices of the wave's tokens become its masks,
+//             in the other of two copies (the other waves still read this one)
+//   stage     a token per thread goes to a ring in LDS, the three dependent loads of a token (its slot, its
+//             record, the counters of its candidates) spread over three sweeps so that none is waited for
+//   -- barrier --
+// Decided bits go to a small ring of output words in LDS; wave 3 writes out the words that are complete.
+// What bounds it: 1.5 / 2.0 / 2.8 us per sweep (4 / 8 / 16 candidates), about 450 instructions, two barriers
+// and, where tokens are staged, their scattered loads.
+// (Before: a window of 128 with two wavefronts that staged tokens and two that evaluated against
+// both masks: 1.65 us per sweep.  12345 tokens, 1214 of them load-dependent: 18 sweeps, 29 us, now 10
+// sweeps, 22 us; a prefill of 131072 tokens, 13150 load-dependent, the call 317 -> 286 us.)
+constexpr int kWinTokens = 256;
 
-
-struct __align__(16) SpecExp2 {
-  unsigned long long mask[2];  // window positions 0..63 / 64..127 that tentatively chose the expert
-  int G;                       // final flexible choices of the expert so far
-  int pad[3];
+// 64 x 64 bits, a row (lo, hi) per lane -> a column per lane.  Blocks of 32, 16, ... 1 bits change places
+// with those of the lane 32, 16, ... 1 away: no LDS, about 40 instructions, and as fast as
+// LDS atomics, a bit per chosen expert, that then need no second copy of the choices.
+struct Transpose64 {
+  unsigned pick16, pick8, mask4, mask2, mask1;
+  int rot4, rot2, rot1;
+  __device__ __forceinline__ explicit Transpose64(int lane)
+      : pick16((lane & 16) ? 0x07060302u : 0x05040100u),
+        pick8((lane & 8) ? 0x03070105u : 0x06020400u),
+        mask4((lane & 4) ? 0xF0F0F0F0u : 0x0F0F0F0Fu),
+        mask2((lane & 2) ? 0xCCCCCCCCu : 0x33333333u),
+        mask1((lane & 1) ? 0xAAAAAAAAu : 0x55555555u),
+        rot4((lane & 4) ? 4 : 28),
+        rot2((lane & 2) ? 2 : 30),
+        rot1((lane & 1) ? 1 : 31) {}
+  __device__ __forceinline__ unsigned within32(unsigned x) const {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int kRowRor8 = 0x128, kQuadReverse = 3 | (2 << 2) | (1 << 4) | (0 << 6);
+    const u32x2 p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = __builtin_amdgcn_perm(p[1], p[0], pick16);
+    x = __builtin_amdgcn_perm((unsigned)dpp_int<kRowRor8>((int)x), x, pick8);
+    auto merge = [](unsigned x, unsigned other, unsigned mask, int rot) {
+      return (x & mask) | (__builtin_amdgcn_alignbit(other, other, rot) & ~mask);
+    };
+    x = merge(x, (unsigned)dpp_int<kQuadReverse>(dpp_int<kRowHalfMirror>((int)x)), mask4, rot4);
+    x = merge(x, (unsigned)dpp_int<kQuadXor2>((int)x), mask2, rot2);
+    return merge(x, (unsigned)dpp_int<kQuadXor1>((int)x), mask1, rot1);
+  }
+  __device__ __forceinline__ unsigned long long operator()(unsigned long long row) const {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 p = __builtin_amdgcn_permlane32_swap((unsigned)row, (unsigned)(row >> 32), false, false);
+    return ((unsigned long long)within32(p[1]) << 32) | within32(p[0]);
+  }
 };
-struct SpecShared2 {
-  SpecExp2 M[64];
-  unsigned obits[kSpecOutWords][64];  // per expert: chosen bits of 32 flexible tokens, not yet written out
-  int met[2];                         // consumer wave: sweeps in which its new tokens' guesses are in the masks
-  unsigned long long bal[2][2];       // [sweep parity][consumer wave]: lanes whose choice changed
-  int staged[2][2];                   // [sweep parity][producer wave]: tokens below this number are in the ring
-  int pub_done[2], pub_flags[2];      // [sweep parity] written by wave 0 before the second barrier
-  int lin_tab[64];
-};
-constexpr int kShared2Offset = kRing2 * (int)sizeof(SpecTok<16>);
-static_assert(kShared2Offset + (int)sizeof(SpecShared2) <= kChainLdsBytes, "ring and state must fit the chain LDS");
 
-// The positions before x of the 128-position ring, as two 64-bit halves.
-__device__ __forceinline__ void below128(int x, unsigned long long& lo, unsigned long long& hi) {
-  lo = x >= 64 ? ~0ull : (1ull << x) - 1ull;
-  hi = x > 64 ? (x >= 128 ? ~0ull : (1ull << (x - 64)) - 1ull) : 0ull;
+// Given up where the walk is faster, judged as in the window of 64: a sweep costs as much as 28, 38 and 21
+// steps of the walk with up to 4, 8 and 16 candidates; the lines are lower, because the first sweeps
+// of a call, and those that end it, retire less than the others.
+constexpr int win_break_even(int cp) { return cp <= 4 ? 190 : cp <= 8 ? 230 : 130; }  // per kSpecCheckSweeps
+constexpr int win_ring(int cp) { return cp <= 8 ? 768 : 512; }                        // tokens in the LDS ring
+constexpr int kWinWords = 16;                                                         // output ring
+
+template <int CP>
+struct WinShared {
+  uint4 b[CP / 4][win_ring(CP)];       // counters of the candidates without flexible choices
+  unsigned ids[win_ring(CP)][CP / 4];  // their experts, a byte each
+  uint4 chose[2][kChainWaves][64];     // [copy][wave][expert] positions that tentatively chose it (x, y), and
+                                       // choices that became final in the sweep before (z)
+  uint4 count[kChainWaves][64];        // [wave][expert] its positions, choices before the wave's positions, and
+                                       // before those behind the end of the ring
+  unsigned out[kWinWords][64];         // per expert: chosen bits of 32 flexible tokens, not yet written out
+  int4 changed[2];                     // [copy] per wave: the first token that changed, from the window's head on
+  unsigned long long first[2][kChainWaves];  // [copy][wave] experts that token chooses now
+};
+static_assert(sizeof(WinShared<4>) <= kChainLdsBytes && sizeof(WinShared<8>) <= kChainLdsBytes &&
+                  sizeof(WinShared<16>) <= kChainLdsBytes,
+              "ring and state fit the chain LDS");
+
+// What a thread has under way of the tokens it stages.
+template <int CP>
+struct WinStage {
+  int base[CP];                         // of the next token to be staged: assignments in the tiles before its tile
+  unsigned ids[CP / 4], pref[CP / 4];   // ... its candidates
+  unsigned ids1[CP / 4], pref1[CP / 4]; // of the one behind that
+  int slot, slot1, slot2;               // of all three
+};
+template <int CP>
+__device__ __forceinline__ void win_records(unsigned (&ids)[CP / 4], unsigned (&pref)[CP / 4], int slot,
+                                            const Workspace& ws) {
+#pragma unroll
+  for (int i = 0; i < CP / 4; ++i) {
+    ids[i] = reinterpret_cast<const unsigned*>(ws.rec_cids)[(size_t)slot * 4 + i];
+    pref[i] = reinterpret_cast<const unsigned*>(ws.rec_pref)[(size_t)slot * 4 + i];
+  }
 }
+template <int CP>
+__device__ __forceinline__ void win_counters(int (&base)[CP], const unsigned (&ids)[CP / 4], int slot,
+                                             const Workspace& ws) {
+#pragma unroll
+  for (int j = 0; j < CP; ++j)
+    base[j] = ws.tile_base[(size_t)(slot >> 6) * 64 + ((ids[j >> 2] >> (8 * (j & 3))) & 255u)];
+}
+
+// The positions before x (0..64) of a wave.
+__device__ __forceinline__ unsigned long long below64(int x) { return x >= 64 ? ~0ull : (1ull << x) - 1ull; }
 
 // Runs the window evaluation from flexible token 0 (see spec_walk for the contract).
 template <int CP, int KK>
-__device__ __forceinline__ int spec_walk2(uint8_t* lds, int nflex_tok, const RouteArgs& a, const Workspace& ws,
-                                          int wave, int lane, int lin, int& gflex, unsigned& hist) {
+__device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const RouteArgs& a, const Workspace& ws,
+                                           int wave, int lane, int lin, int& gflex, unsigned& hist) {
   own_lane(lane);
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
-  SpecTok<CP>* ring = reinterpret_cast<SpecTok<CP>*>(lds);
-  SpecShared2& S = *reinterpret_cast<SpecShared2*>(lds + kShared2Offset);
-  SpecExp2* M = S.M;
+  WinShared<CP>& S = *reinterpret_cast<WinShared<CP>*>(lds);
+  constexpr int kRing = win_ring(CP);
   const int k = KK > 0 ? KK : a.k;
-  const int tid = threadIdx.x;
-  if (tid < 64) {
-    M[tid].mask[0] = M[tid].mask[1] = 0ull;
-    M[tid].G = 0;
-    S.lin_tab[tid] = lin;
-  }
-  for (int i = tid; i < kSpecOutWords * 64; i += kTailThreads) (&S.obits[0][0])[i] = 0u;
-  if (tid < 4) (&S.bal[0][0])[tid] = 0ull;
-  if (tid < 2) S.met[tid] = 0;
-  if (tid < 4) (&S.staged[0][0])[tid] = 0;
-  if (tid < 2) {
-    S.pub_done[tid] = 0;
-    S.pub_flags[tid] = 2;  // (bit 0: give up, bit 1: first guesses in use)
-  }
-  __syncthreads();
-
-  const bool consumer = wave < 2;
-  const int pw = wave & 1;  // consumer: which half of the window; producer: which half of a batch
+  const int tid = 64 * wave + lane;
   const unsigned long long lb = lanes_below(lane);
-
-  // ---- consumer state ------------------------------------------------------------------
-  int ex[CP];       // candidate experts by rank
-  unsigned b[CP];   // their counters without flexible choices
-#pragma unroll
-  for (int j = 0; j < CP; ++j) {
-    ex[j] = 0;
-    b[j] = kSpecInvalid;
-  }
-  unsigned sel = 0;
-  int cur_f = -1;      // token whose data this lane holds
-  bool fresh = false;  // it came in after the last sweep: its first guess is not in the masks yet
-
-  // ---- producer state: batch n of a producer is the tokens 128 n + 64 pw + lane ----------
-  // in flight: the slot of batch nb + 2, slot and record of batch nb + 1, and for batch
-  // nb the record (arrived) whose candidates' counters are fetched in the sweep it is staged
-  int nb = 0;
-  int slot0 = 0, slot1 = 0, slot2 = 0;
-  uint4 ids1 = make_uint4(0, 0, 0, 0), pref1 = ids1, ids2 = ids1, pref2 = ids1;
-  auto tok = [&](int n) { return 128 * n + 64 * pw + lane; };
-  if (!consumer) {
-    slot2 = tok(0) < nflex_tok ? ws.flex_slot[tok(0)] : 0;
-    slot1 = tok(1) < nflex_tok ? ws.flex_slot[tok(1)] : 0;
-    slot0 = tok(2) < nflex_tok ? ws.flex_slot[tok(2)] : 0;
-    ids2 = reinterpret_cast<const uint4*>(ws.rec_cids)[slot2];
-    pref2 = reinterpret_cast<const uint4*>(ws.rec_pref)[slot2];
-    ids1 = reinterpret_cast<const uint4*>(ws.rec_cids)[slot1];
-    pref1 = reinterpret_cast<const uint4*>(ws.rec_pref)[slot1];
-  }
-
-  int done = 0, avail = 0;  // tokens decided, tokens in the ring (both uniform, the same in every wave)
+  const Transpose64 transpose(lane);
+  int G = 0;               // lane = expert: final flexible choices, as of the sweep before
+  // tokens decided, in the ring, and of these not behind the window (as all that decides the course: the
+  // same in every wave)
+  int done = 0, avail = 0, inside = 0;
   int sweeps = 0, done_mark = 0, total_sweeps = 0;
-  bool bail = false, guess_on = true;
+  bool bail = false;
   int wout = 0, gflushed = 0;  // wave 3, lane = expert: output words written, their bits so far
 
-  for (;;) {
-    const int par = total_sweeps & 1;
-    const int head = done & 127;
-    if (consumer) {
-      // ---- this lane's token of the window [done, done + 128) -----------------------------
-      // (its data was fetched between the barriers of the sweep before, see below)
-      const int pos = 64 * pw + lane;
-      const int f_lane = done + ((pos - head) & 127);
-      const bool valid = cur_f == f_lane;
-      if (!valid) sel = 0;
-      const bool enters = fresh;  // a new token (sel: its first guess, if guesses are on)
-      fresh = false;
-      bool met = true;
-      if (guess_on) {
-        // The guesses join the masks before anybody counts (the lane's bit is clear: the
-        // token that held the lane took its bits along when it retired).  "Anybody" is
-        // both consumer waves: a new token in the other half of the window counts this
-        // half's new guesses too.  The two waves meet here through a pair of sweep numbers
-        // in LDS (the producers are busy staging and take no part).
-        if (enters) {
+  // ---- staging ------------------------------------------------------------------------------
+  // (loads without conditions stay in flight: the last token stands in for none)
+  WinStage<CP> st;
+  int nb = 0, at = tid;  // tokens 256 nb + tid are staged next, at this place of the ring
+  auto slot_of = [&](int n) { return ws.flex_slot[min(kWinTokens * n + tid, nflex_tok - 1)]; };
+  auto stage = [&]() {
+    unsigned b[CP];
 #pragma unroll
-          for (int j = 0; j < CP; ++j)
-            if ((sel >> j) & 1u) flip_lane_bit(&M[ex[j]].mask[pw], lane);
-        }
-        lds_wave_fence();
-        __builtin_amdgcn_wave_barrier();
-        if (lane == 0) S.met[pw] = total_sweeps + 1;
-        met = false;
-        for (int it = 0; it < kSpecMeetPolls && !met; ++it) {
-          lds_wave_fence();
-          // (read as LDS: through a plain volatile pointer the compiler emits a flat load,
-          // which takes the long way through the vector memory pipeline)
-          typedef __attribute__((address_space(3))) volatile int lds_volatile_int;
-          met = __builtin_amdgcn_readfirstlane(*(lds_volatile_int*)&S.met[pw ^ 1]) > total_sweeps;
-        }
+    for (int j = 0; j < CP; ++j) {
+      const int e = (int)((st.ids[j >> 2] >> (8 * (j & 3))) & 255u);
+      const unsigned pf = (st.pref[j >> 2] >> (8 * (j & 3))) & 255u;
+      const unsigned before = (unsigned)(st.base[j] + __builtin_amdgcn_ds_bpermute(4 * e, lin)) + pf;
+      b[j] = pf == 0xFFu ? kSpecInvalid : before;
+    }
+#pragma unroll
+    for (int i = 0; i < CP / 4; ++i) {
+      S.b[i][at] = make_uint4(b[4 * i], b[4 * i + 1], b[4 * i + 2], b[4 * i + 3]);
+      S.ids[at][i] = st.ids[i];
+      st.ids[i] = st.ids1[i];
+      st.pref[i] = st.pref1[i];
+    }
+    at = at + kWinTokens >= kRing ? at + kWinTokens - kRing : at + kWinTokens;
+    win_counters<CP>(st.base, st.ids, st.slot1, ws);
+    win_records<CP>(st.ids1, st.pref1, st.slot2, ws);
+    st.slot1 = st.slot2;
+    st.slot2 = slot_of(nb + 3);
+    ++nb;
+  };
+  st.slot = slot_of(0);
+  st.slot1 = slot_of(1);
+  st.slot2 = slot_of(2);
+  win_records<CP>(st.ids, st.pref, st.slot, ws);
+  win_records<CP>(st.ids1, st.pref1, st.slot1, ws);
+  win_counters<CP>(st.base, st.ids, st.slot, ws);
+  for (int i = tid; i < kWinWords * 64; i += kTailThreads) (&S.out[0][0])[i] = 0u;
+  S.count[wave][lane] = make_uint4(0u, 0u, 0u, 0u);
+  stage();
+  avail = min(nflex_tok, kWinTokens);
+  __syncthreads();
+
+  // ---- the window ---------------------------------------------------------------------------
+  unsigned ids[CP / 4];  // candidate experts by rank, a byte each
+  unsigned b[CP];        // their counters without flexible choices
+  unsigned long long choice = 0ull;  // experts
+  int cur_f = tid - kWinTokens;      // token whose data this lane holds ...
+  int place = tid - kWinTokens;      // ... and its place in the ring (advances by 256 per token)
+#pragma unroll
+  for (int j = 0; j < CP; ++j) b[j] = kSpecInvalid;
+#pragma unroll
+  for (int i = 0; i < CP / 4; ++i) ids[i] = 0u;
+  auto ex = [&](int j) { return (int)((ids[j >> 2] >> (8 * (j & 3))) & 255u); };
+  auto experts = [&](unsigned sel) {
+    unsigned long long m = 0ull;
+#pragma unroll
+    for (int j = 0; j < CP; ++j) m |= (unsigned long long)((sel >> j) & 1u) << (ex(j) & 63);
+    return m;
+  };
+  // The tokens of the window [done, done + 256) that are not in it yet; the wave's masks, and what it
+  // retired, to copy `to`.
+  auto enter = [&](int to, int retired) {
+    const int f = done + ((tid - done) & (kWinTokens - 1));
+    if (cur_f != f) choice = 0ull;
+    if (f < avail && cur_f != f) {
+      cur_f = f;
+      place = place + kWinTokens >= kRing ? place + kWinTokens - kRing : place + kWinTokens;
+      unsigned key[CP];
+#pragma unroll
+      for (int i = 0; i < CP / 4; ++i) {
+        const uint4 bb = S.b[i][place];
+        ids[i] = S.ids[place][i];
+        b[4 * i] = bb.x;
+        b[4 * i + 1] = bb.y;
+        b[4 * i + 2] = bb.z;
+        b[4 * i + 3] = bb.w;
       }
-      // the window positions before this one: from the head up to pos, cyclically
-      unsigned long long bh0, bh1;
-      below128(head, bh0, bh1);
-      const unsigned long long bp0 = pw ? ~0ull : lb, bp1 = pw ? lb : 0ull;
-      const bool ge = pos >= head;
-      const unsigned long long e0 = ge ? (bp0 & ~bh0) : (bp0 | ~bh0);
-      const unsigned long long e1 = ge ? (bp1 & ~bh1) : (bp1 | ~bh1);
+#pragma unroll
+      for (int j = 0; j < CP; ++j) key[j] = ((b[j] + S.count[wave][ex(j)].w) << 4) | (unsigned)j;
+      choice = experts(smallest_k_slots<CP, KK>(key, k));
+    }
+    const unsigned long long m = transpose(choice);
+    S.chose[to][wave][lane] = make_uint4((unsigned)m, (unsigned)(m >> 32), (unsigned)retired, 0u);
+  };
+  int par = 0;
+  enter(0, 0);
+  inside = avail;
+  lds_barrier();
+  for (;;) {
+    const int head = done & (kWinTokens - 1), hw = head >> 6, ho = head & 63;
+    unsigned long long own = 0ull;  // lane = expert: the wave's positions that tentatively chose it
+    {  // ---- count: lane = expert
+      int before = 0, wrap = 0;
+#pragma unroll
+      for (int i = 0; i < kChainWaves; ++i) {
+        // (in the order of the window: the head's wave from the head on, the others)
+        const int w = (hw + i) & (kChainWaves - 1);
+        const uint4 x = S.chose[par][w][lane];
+        const unsigned long long m = ((unsigned long long)x.y << 32) | x.x;
+        const int n = __builtin_popcountll(i == 0 ? m & ~below64(ho) : m);
+        if (w == wave) own = m;
+        if (i < ((wave - hw) & (kChainWaves - 1))) before += n;
+        wrap += n;
+        G += (int)x.z;
+      }
+      S.count[wave][lane] = make_uint4((unsigned)own, (unsigned)(own >> 32), (unsigned)(G + before), (unsigned)(G + wrap));
+    }
+    if (done >= nflex_tok || bail) break;
+    lds_wave_fence();
+    __builtin_amdgcn_wave_barrier();
+    // ---- evaluate: lane = token
+    {
+      const bool behind = wave == hw && lane < ho;  // (behind the end of the ring)
+      const unsigned long long earlier = wave == hw && lane >= ho ? lb & ~below64(ho) : lb;
       unsigned key[CP];
 #pragma unroll
       for (int j = 0; j < CP; ++j) {
-        const uint4 m = *reinterpret_cast<const uint4*>(&M[ex[j]]);  // the two halves of the mask
-        const unsigned g = (unsigned)M[ex[j]].G;
-        const unsigned cnt = (unsigned)(__builtin_popcount(m.x & (unsigned)e0) + __builtin_popcount(m.y & (unsigned)(e0 >> 32)) +
-                                        __builtin_popcount(m.z & (unsigned)e1) + __builtin_popcount(m.w & (unsigned)(e1 >> 32)));
-        key[j] = ((b[j] + g + cnt) << 4) | (unsigned)j;
+        const uint4 m = S.count[wave][ex(j)];
+        const unsigned cnt = (unsigned)(__builtin_popcount(m.x & (unsigned)earlier) +
+                                        __builtin_popcount(m.y & (unsigned)(earlier >> 32)));
+        key[j] = ((b[j] + (behind ? m.w : m.z) + cnt) << 4) | (unsigned)j;
       }
-      unsigned newsel = smallest_k_slots<CP, KK>(key, k);
-      newsel = valid ? newsel : 0u;
-      const unsigned diff = sel ^ newsel;
-      unsigned long long bal = __builtin_amdgcn_ballot_w64(diff != 0u);
-      if (bal != 0ull) {
-        // flip this lane's bit in the masks of the experts whose choice changed
-#pragma unroll
-        for (int j = 0; j < CP; ++j)
-          if ((diff >> j) & 1u) flip_lane_bit(&M[ex[j]].mask[pw], lane);
-      }
-      sel = newsel;
-      // (should the other wave not have shown up in time, which does not happen while both
-      // run: this sweep's new tokens may have missed guesses, so none of them is final yet
-      // but the first -- it counts as changed)
-      if (!met) bal |= __builtin_amdgcn_ballot_w64(enters);
-      if (lane == 0) S.bal[par][pw] = bal;
-    } else {
-      // ---- producer: stage batch nb if the ring has room for it ----------------------------
-      // (the ring holds the tokens [done, done + kRing2); `done` is at most one sweep old)
-      if (128 * nb + 128 <= done + kRing2 && 128 * nb < nflex_tok) {
-        const int f = tok(nb);
-        const bool live = f < nflex_tok;
-        const unsigned idw[4] = {ids2.x, ids2.y, ids2.z, ids2.w};
-        const unsigned pfw[4] = {pref2.x, pref2.y, pref2.z, pref2.w};
-        const int tile = slot2 >> 6;
-        int base[CP];
-#pragma unroll
-        for (int j = 0; j < CP; ++j) {
-          const int e = (idw[j >> 2] >> (8 * (j & 3))) & 255;
-          base[j] = ws.tile_base[(size_t)tile * 64 + e] + S.lin_tab[e];
-        }
-        // the loads of the batches behind it: asked for now, used one and two sweeps on
-        const uint4 ids_n = reinterpret_cast<const uint4*>(ws.rec_cids)[slot0];
-        const uint4 pref_n = reinterpret_cast<const uint4*>(ws.rec_pref)[slot0];
-        const int slot_n = tok(nb + 3) < nflex_tok ? ws.flex_slot[tok(nb + 3)] : 0;
-        unsigned bj[CP], key[CP];
-#pragma unroll
-        for (int j = 0; j < CP; ++j) {
-          const unsigned pf = (pfw[j >> 2] >> (8 * (j & 3))) & 255u;
-          const int e = (idw[j >> 2] >> (8 * (j & 3))) & 255;
-          bj[j] = pf == 0xFFu ? kSpecInvalid : (unsigned)base[j] + pf;
-          // (the guess also counts the flexible choices that are final by now: a few
-          // hundred tokens stale when this token enters the window, better than none)
-          key[j] = ((bj[j] + (unsigned)M[e].G) << 4) | (unsigned)j;
-        }
-        const unsigned guess = smallest_k_slots<CP, KK>(key, k);
-        if (live) {
-          SpecTok<CP>* dst = &ring[f & (kRing2 - 1)];
-          dst->ids = ids2;
-#pragma unroll
-          for (int j = 0; j < CP; ++j) dst->b[j] = bj[j] | (((guess >> j) & 1u) << 31);
-        }
-        slot2 = slot1;
-        ids2 = ids1;
-        pref2 = pref1;
-        slot1 = slot0;
-        ids1 = ids_n;
-        pref1 = pref_n;
-        slot0 = slot_n;
-        ++nb;
-      }
-      // (by sweep parity: a producer that is already in the next sweep must not change what
-      // a consumer still reads after the second barrier of this one)
-      if (lane == 0) S.staged[par][pw] = 128 * nb;
-    }
-    lds_barrier();
-
-    // ---- tokens up to the first changed one are final (every wave works it out) ------------
-    int fin;
-    {
-      unsigned long long c0 = S.bal[par][0], c1 = S.bal[par][1];
-      c0 = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(c0 >> 32)) << 32) |
-           (unsigned)__builtin_amdgcn_readfirstlane((unsigned)c0);
-      c1 = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(c1 >> 32)) << 32) |
-           (unsigned)__builtin_amdgcn_readfirstlane((unsigned)c1);
-      if (head >= 64) {
-        const unsigned long long t = c0;
-        c0 = c1;
-        c1 = t;
-      }
-      const int sh = head & 63;
-      const unsigned long long r0 = sh ? (c0 >> sh) | (c1 << (64 - sh)) : c0;
-      const unsigned long long r1 = sh ? (c1 >> sh) | (c0 << (64 - sh)) : c1;
-      const int q = r0 ? __builtin_ctzll(r0) : r1 ? 64 + __builtin_ctzll(r1) : 128;
-      fin = min(min(q + 1, 128), avail - done);
-    }
-    if (!consumer) {
-      // ---- the producers retire them: lane = expert, wave 2 + pw the half pw of the window
-      // positions head .. head + fin - 1 (the consumers fetch their next tokens meanwhile)
-      if (fin > 0) {
-        unsigned long long lo0, hi0, lo1, hi1;
-        below128(head, lo0, hi0);
-        const int end = head + fin;  // (up to 255: the range may wrap)
-        below128(end > 128 ? 128 : end, lo1, hi1);
-        unsigned long long ret0 = lo1 & ~lo0, ret1 = hi1 & ~hi0;  // head .. min(end, 128) - 1
-        if (end > 128) {
-          unsigned long long wl, wh;
-          below128(end - 128, wl, wh);
-          ret0 |= wl;
-          ret1 |= wh;
-        }
-        const unsigned long long mine = pw ? ret1 : ret0;
-        const unsigned long long mk = M[lane].mask[pw];
-        const unsigned long long fb = mk & mine;
-        // (unconditional: lanes without retiring bits add nothing)
-        atomicAdd(&M[lane].G, __builtin_popcountll(fb));
-        M[lane].mask[pw] = mk & ~mine;
-        // a quarter of the mask (32 positions) is bit-aligned with the output word of its
-        // tokens; only the quarter of the head can hold tokens of two words (the positions
-        // below the head belong to tokens four words on)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int qi = 2 * pw + h;              // quarter of the ring
-          const unsigned qb = (unsigned)(fb >> (32 * h));
-          const int cut = (head >> 5) == qi ? (head & 31) : 0;
-          const int first = (done + ((32 * qi + cut - head) & 127)) >> 5;  // word of the positions >= cut
-          const unsigned below_cut = (1u << cut) - 1u;
-          atomicOr(&S.obits[first & (kSpecOutWords - 1)][lane], qb & ~below_cut);
-          if (cut != 0) atomicOr(&S.obits[(first + 4) & (kSpecOutWords - 1)][lane], qb & below_cut);
-        }
-      }
-    } else {
-      // ---- the consumers fetch the tokens that take the freed positions --------------------
-      // (only their data: the masks belong to the producers until the barrier below; the
-      // first guesses join them at the start of the next sweep)
-      {
-        const int d2 = done + fin;
-        // (the switch for the first guesses, as wave 0 works it out for everybody below)
-        const bool g2 = sweeps + 1 == kSpecCheckSweeps ? d2 - done_mark >= kSpecGuessProgress : guess_on;
-        const int avail2 = min(nflex_tok, min(__builtin_amdgcn_readfirstlane(S.staged[par][0]),
-                                              __builtin_amdgcn_readfirstlane(S.staged[par][1])));
-        const int pos = 64 * pw + lane;
-        const int f2 = d2 + ((pos - (d2 & 127)) & 127);
-        if (f2 < avail2 && cur_f != f2) {
-          const SpecTok<CP>* src = &ring[f2 & (kRing2 - 1)];
-          const uint4 ids = src->ids;
-          const unsigned idw[4] = {ids.x, ids.y, ids.z, ids.w};
-          sel = 0;
-#pragma unroll
-          for (int j = 0; j < CP; ++j) {
-            ex[j] = (idw[j >> 2] >> (8 * (j & 3))) & 255;
-            b[j] = src->b[j];  // (bit 31, the guess, drops out of the key's shift)
-          }
-          if (g2) {
-#pragma unroll
-            for (int j = 0; j < CP; ++j) sel |= (b[j] >> 31) << j;  // the producer's first guess
-          }
-          cur_f = f2;
-          fresh = true;
-        }
-      }
-      if (wave == 0) {
-        int d = done + fin;
-        bool gv = bail, gg = guess_on;
-        int sw = sweeps + 1, dm = done_mark;
-        if (sw == kSpecCheckSweeps) {
-          // give up only if both the last run of sweeps and the average so far are
-          // below break-even: the switch is one-way
-          if (d - dm < spec_min_progress(CP) && d * kSpecCheckSweeps < spec_min_progress(CP) * (total_sweeps + 1) &&
-              nflex_tok - d > 2 * kSpecSeg && avail - done >= 128)
-            gv = true;
-          gg = d - dm >= kSpecGuessProgress;
-        }
-        if (lane == 0) {
-          S.pub_done[par] = d;
-          S.pub_flags[par] = (gv ? 1 : 0) | (gg ? 2 : 0);
-        }
+      unsigned long long now = experts(smallest_k_slots<CP, KK>(key, k));
+      now = cur_f >= done ? now : 0ull;
+      const unsigned long long bal = __builtin_amdgcn_ballot_w64(now != choice);
+      choice = now;
+      const unsigned long long head_part = wave == hw ? bal & ~below64(ho) : bal;
+      const unsigned long long c = head_part != 0ull ? head_part : bal;
+      const int pos = c != 0ull ? __builtin_ctzll(c) : 0;
+      const unsigned lo = __builtin_amdgcn_readlane((unsigned)choice, pos);
+      const unsigned hi = __builtin_amdgcn_readlane((unsigned)(choice >> 32), pos);
+      if (lane == 0) {
+        reinterpret_cast<int*>(&S.changed[par])[wave] =
+            c != 0ull ? (64 * wave + pos - head) & (kWinTokens - 1) : kWinTokens;
+        S.first[par][wave] = ((unsigned long long)hi << 32) | lo;
       }
     }
     lds_barrier();
-
-    // ---- every wave takes over the books ------------------------------------------------
-    done = __builtin_amdgcn_readfirstlane(S.pub_done[par]);
-    const int flags = __builtin_amdgcn_readfirstlane(S.pub_flags[par]);
-    bail = (flags & 1) != 0;
-    avail = min(nflex_tok, min(__builtin_amdgcn_readfirstlane(S.staged[par][0]),
-                               __builtin_amdgcn_readfirstlane(S.staged[par][1])));
+    // ---- retire: tokens up to the first changed one are final (every wave works it out)
+    const int4 cq = S.changed[par];
+    const int q = __builtin_amdgcn_readfirstlane(min(min(cq.x, cq.y), min(cq.z, cq.w)));
+    const int fin = min(min(q + 1, kWinTokens), inside - done);
+    int retired;
+    {  // lane = expert
+      // the wave's positions among head .. head + fin - 1, cyclically
+      const int from = head - 64 * wave, to = from + fin;
+      const unsigned long long ret =
+          (below64(min(max(to, 0), 64)) & ~below64(min(max(from, 0), 64))) | below64(min(max(to - kWinTokens, 0), 64));
+      unsigned long long mine = own & ret;
+      const int qpos = head + q;
+      if (q < fin && ((qpos >> 6) & (kChainWaves - 1)) == wave) {
+        // (the changed token's bits are the old ones in the mask: it goes by its new choice)
+        const unsigned long long bit = 1ull << (qpos & 63);
+        mine = (S.first[par][wave] >> lane) & 1ull ? mine | bit : mine & ~bit;
+      }
+      retired = __builtin_popcountll(mine);
+      // 32 positions are bit-aligned with the output word of their tokens; only those around the
+      // head can hold tokens of two words
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int quarter = 2 * wave + h;
+        const unsigned bits = (unsigned)(mine >> (32 * h));
+        const int cut = (head >> 5) == quarter ? (head & 31) : 0;
+        const int word = (done + ((32 * quarter + cut - head) & (kWinTokens - 1))) >> 5;
+        const unsigned behind_cut = ~((1u << cut) - 1u);
+        S.out[word & (kWinWords - 1)][lane] |= bits & behind_cut;
+        if (cut != 0) S.out[(word + kWinTokens / 32) & (kWinWords - 1)][lane] |= bits & ~behind_cut;
+      }
+    }
+    done += fin;
     ++total_sweeps;
-    if (++sweeps == kSpecCheckSweeps) {
-      guess_on = (flags & 2) != 0;
+    if (total_sweeps == kSpecWarmUp) {
+      sweeps = 0;
+      done_mark = done;
+    } else if (++sweeps == kSpecCheckSweeps) {
+      // (the switch is one-way)
+      constexpr int line = win_break_even(CP);
+      const int progress = done - done_mark, left = nflex_tok - done;
+      const int lost = total_sweeps * line / kSpecCheckSweeps - done;  // in tokens walked
+      if (left > 64 && progress < line && lost > (progress < line / 2 ? 0 : left / 8)) bail = true;
       sweeps = 0;
       done_mark = done;
     }
-    // ---- output words that are complete (wave 3, lane = expert) ---------------------------
+    par ^= 1;
+    enter(par, retired);
+    inside = avail;
+    // (a token's place is free once the token has entered the window, which 256 tokens fit)
+    if (kWinTokens * nb < nflex_tok && kWinTokens * (nb + 1) <= done + kRing) stage();
+    lds_barrier();
+    avail = min(nflex_tok, kWinTokens * nb);
+    // ---- output words that are complete (lane = expert) -----------------------------------------
     if (wave == kChainWaves - 1) {
       while (32 * (wout + 1) <= done) {
-        unsigned* slot = &S.obits[wout & (kSpecOutWords - 1)][lane];
-        const unsigned word = *slot;
-        *slot = 0u;
-        gflushed += __builtin_popcount(word);
-        ws.chain_bits[(size_t)wout * 64 + lane] = word;
+        unsigned* word = &S.out[wout & (kWinWords - 1)][lane];
+        const unsigned bits = *word;
+        *word = 0u;
+        gflushed += __builtin_popcount(bits);
+        ws.chain_bits[(size_t)wout * 64 + lane] = bits;
         ws.chain_cum[(size_t)(wout + 1) * 64 + lane] = gflushed;
         ++wout;
       }
     }
-    // (every sweep with tokens in the ring retires at least one, and the ring refills
-    // within two sweeps; the cap only keeps a mistake from turning into an endless loop:
-    // the sequential walk then takes over, and the result is still exact)
-    if (total_sweeps > nflex_tok + (nflex_tok >> 5) + 64) bail = true;
-    if (done >= nflex_tok || bail) break;
   }
-  const int decided = done;
   if (wave == 0) {
-    gflex = M[lane].G;
-    hist = S.obits[(decided >> 5) & (kSpecOutWords - 1)][lane];  // the decided % 32 bits of the unfinished word
-    if (decided == nflex_tok && (decided & 31) != 0) ws.chain_bits[(size_t)(decided >> 5) * 64 + lane] = hist;
+    gflex = G;
+    hist = (done & 31) != 0 ? S.out[(done >> 5) & (kWinWords - 1)][lane] : 0u;  // the decided bits of the unfinished word
+    if (done == nflex_tok && (done & 31) != 0) ws.chain_bits[(size_t)(done >> 5) * 64 + lane] = hist;
     if (lane == 0) ws.status[kStatusSweeps] = total_sweeps;
   }
-  __syncthreads();  // the ring is dead: the sequential walk may reuse the LDS
-  return decided;
+  __syncthreads();  // (the LDS is free again)
+  return done;
 }
 
 // ---- the chain in blocks, side by side ---------------------------------------------------
@@ -2246,25 +2214,25 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   int decided = 0;
   unsigned hist0 = 0;
   if (use_spec && EP != 8 && a.EP != 8) {
-    // With many experts per candidate tokens rarely compete: first guesses and the window of 128.
+    // With many experts per candidate tokens rarely compete: the window of 256.
     // With fewer a sweep may end at an early conflict: the window of 64, which is given up where the
     // walk is faster.  (Up to 8 experts the walk always is, or nearly: 17.7 ns per token against at least 16.)
     if (a.c <= 4) {
       if (a.E >= 16)
-        decided = a.k == 2 ? spec_walk2<4, 2>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
-                           : spec_walk2<4, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+        decided = a.k == 2 ? window_walk<4, 2>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
+                           : window_walk<4, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
       else if (EP == 0 || EP == 16)
         decided = a.k == 2 ? spec_walk<4, 2>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
                            : spec_walk<4, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else if (a.c <= 8) {
       if ((EP == 0 || EP >= 32) && a.E >= 32)
-        decided = a.k == 6 ? spec_walk2<8, 6>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
-                           : spec_walk2<8, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+        decided = a.k == 6 ? window_walk<8, 6>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
+                           : window_walk<8, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
       else if (EP <= 32)
         decided = a.k == 6 ? spec_walk<8, 6>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
                            : spec_walk<8, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else if ((EP == 0 || EP == 64) && a.E == 64) {
-      decided = spec_walk2<16, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+      decided = window_walk<16, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     } else {
       decided = spec_walk<16, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
     }

@@ -103,6 +103,19 @@ def test_window_gives_way_inside_a_word(E, k, c):
         assert 0 < n < T - 200                  # (fewer sweeps than tokens by far: the walk took the rest)
 
 
+# (the window of 256 tokens: rings of 768 tokens, 512 with more than 8 candidates, staged 256 at a time)
+@pytest.mark.parametrize("T", [256, 257, 511, 512, 513, 767, 768, 769, 1024, 1025, 1281, 3071])
+@pytest.mark.parametrize("E,k,c", [(64, 6, 8), (64, 2, 4), (33, 3, 8), (16, 3, 4), (64, 9, 16), (64, 6, 9)])
+def test_window_of_256_tokens(T, E, k, c):
+    """Counters far apart, where the first guesses hold and a sweep retires the whole window, and groups of
+    experts at nearly equal counters, where tokens of the window change one another's choices."""
+    rng = np.random.default_rng(T + E + c)
+    logits = wl.random_logits(T + c, T, E, kind="normal", scale=1.0)
+    n = _sweeps(T, E, k, c, logits, rng.permutation(E) * 10 * T, f"far T{T} E{E} c{c}")
+    assert n <= T // 256 + 12
+    _check(T, E, k, c, logits, (rng.integers(0, 4, size=E) * 5 * T).astype(np.int32), 2.0, f"groups T{T} E{E} c{c}")
+
+
 # (above 512 tiles four wavefronts share a tile instead of sixteen)
 @pytest.mark.parametrize("T", [1, 15, 16, 17, 49, 64, 65, 127, 512 * 64, 512 * 64 + 21])
 @pytest.mark.parametrize("E,k,c", [(64, 6, 8), (8, 2, 4), (33, 3, 16)])
