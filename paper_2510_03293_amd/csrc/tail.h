@@ -2571,10 +2571,10 @@ __device__ __forceinline__ void finish_row(FinishLds* fl, int t, int cstar, int 
   }
 }
 
-// LDS traffic of one wavefront is processed in order; the fences only stop the
-// compiler from moving reads above the other lanes' writes.
+// LDS traffic of one wavefront is processed in order; this only stops the compiler from moving reads
+// above the other lanes' writes.  (A fence would also wait for the rows' stores: a microsecond.)
 __device__ __forceinline__ void finish_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  lds_wave_fence();
   __builtin_amdgcn_wave_barrier();
 }
 
@@ -2699,28 +2699,45 @@ __device__ __forceinline__ void finish_tile_of_chain(FinishLds* fl, int tile, co
         finish_row(fl, t, cstar, a.c, Z, a, expert_ids, weights, [&](int j) { return ((chosen >> j) & 1u) != 0u; }, id,
                    [&](int j) { return p[j]; });
       } else {
+        // which ranks are chosen, then those k of them
         const uint8_t* wide_ids = ws.rec_ids + (size_t)t * kWideC;
-        const float* wide_p = ws.rec_p + (size_t)t * kWideC;
+        unsigned long long ranks = 0ull;
+        for (int i = 0; 16 * i < cstar; ++i) {
+          const uint4 v = reinterpret_cast<const uint4*>(wide_ids)[i];
+          const unsigned w[4] = {v.x, v.y, v.z, v.w};
+          unsigned some = 0;
+#pragma unroll
+          for (int j = 0; j < 16; ++j)
+            some |= ((row[(w[j >> 2] >> (8 * (j & 3))) & 63u] >> (f & 31)) & 1u) << j;
+          ranks |= (unsigned long long)some << (16 * i);
+        }
+        if (cstar < 64) ranks &= (1ull << cstar) - 1ull;
+        float wp[kMaxK];
+        int we[kMaxK];
+#pragma unroll
+        for (int n = 0; n < kMaxK; ++n) {
+          if (n >= a.k) break;
+          const int j = ranks != 0ull ? __builtin_ctzll(ranks) : 0;  // (exactly k are chosen)
+          ranks &= ranks - 1ull;
+          wp[n] = ws.rec_p[(size_t)t * kWideC + j];
+          we[n] = wide_ids[j];
+        }
         float denom = Z;
         if (a.renormalize) {
-          bool first = true;
-          for (int j = 0; j < cstar; ++j) {
-            if ((row[wide_ids[j]] >> (f & 31)) & 1u) {
-              denom = first ? wide_p[j] : denom + wide_p[j];
-              first = false;
-            }
+          denom = wp[0];
+#pragma unroll
+          for (int n = 1; n < kMaxK; ++n) {
+            if (n >= a.k) break;
+            denom = denom + wp[n];
           }
         }
-        int n = 0;
-        for (int j = 0; j < cstar; ++j) {
-          const int e = wide_ids[j];
-          if (((row[e] >> (f & 31)) & 1u) && n < a.k) {
-            expert_ids[(size_t)t * a.k + n] = e;
-            weights[(size_t)t * a.k + n] = wide_p[j] / denom;
-            fl->ids[lane][n] = (uint8_t)e;
-            atomicOr(&fl->mask64[e], 1ull << lane);
-            ++n;
-          }
+#pragma unroll
+        for (int n = 0; n < kMaxK; ++n) {
+          if (n >= a.k) break;
+          expert_ids[(size_t)t * a.k + n] = we[n];
+          weights[(size_t)t * a.k + n] = wp[n] / denom;
+          fl->ids[lane][n] = (uint8_t)we[n];
+          atomicOr(&fl->mask64[we[n] & 63], 1ull << lane);
         }
       }
     }
