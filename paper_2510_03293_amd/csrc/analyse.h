@@ -270,10 +270,11 @@ __device__ void analyse_tile_ct(float* __restrict__ lz, int zs, unsigned long lo
       K[i] = make_key(z[i], e);
     }
   }
-  if (logits_out != nullptr) {  // (one uniform test instead of one per element)
+  if (__builtin_expect(logits_out != nullptr, 0)) {  // (one uniform test instead of one per element)
 #pragma unroll
     for (int i = 0; i < NE; ++i)
       if (live && owned(i) < a.E) logits_out[(size_t)t * a.E + owned(i)] = z[i];
+    if (a.logits_only) return;
   }
   // masks zeroed before anyone ORs into them  (PUB: the next tile's loads are in flight
   // around this call and must stay so; the barriers order LDS traffic only)

@@ -116,6 +116,7 @@ static RouteArgs make_args(int32_t T, int32_t E, const laser_params_t* p) {
   a.st_entropy = nullptr;
   a.st_pool = nullptr;
   a.pool_in_ws = 0;
+  a.logits_only = 0;
   // the bounded waits of the tail kernel: sized from T unless the caller fixes them
   a.spin_limit = p->poll_budget != 0 ? (long long)p->poll_budget : kSpinFloor + kSpinPerToken * (long long)T;
   a.nbatch = 1;
@@ -273,7 +274,8 @@ int route_impl(const void* hidden, const void* w_gate, int32_t B, int32_t T, int
       }
     }
   }
-  const RouteArgs an = wide ? narrowed(a) : a;  // what the fast analysis kernels are given
+  RouteArgs an = wide ? narrowed(a) : a;  // what the fast analysis kernels are given
+  an.logits_only = general && !wants_stats(a) ? 1 : 0;
   const size_t lstride = logits_out ? (size_t)T * E : ws_one / sizeof(float);
   float* logits;
   if (params->dtype == LASER_DTYPE_BF16) {

@@ -36,6 +36,7 @@ struct RouteArgs {
   int32_t* st_pool;    // pool size m (candidates above the cut, united with the top-k)
   int pool_in_ws;      // 1: nobody asked for st_pool but RANDOM trimming needs the pool sizes:
                        // the kernels write and read them in the workspace (Workspace::pool)
+  int logits_only;     // 1: the fused kernel leaves the analysis to another one
   // batched calls: the kernels run with the problem index in blockIdx.y
   long long spin_limit;  // polls a finishing wavefront spends on one flag of the chain before it gives up
   int nbatch;          // problems in the call (1: all of the above is the one problem's)
