@@ -1705,18 +1705,18 @@ __device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const Ro
 //     (A d)_e = (1 - g_e) d_e + g_e (sum_i g_i d_i) / (sum_i g_i).
 // g comes from a sample of the block's tokens: how often the expert was chosen or passed over with at
 // most one to spare.
-// (Rounds until 16384 load-dependent tokens of 64 experts are decided, k = 6, c = 8, blocks of 256: 8 to
-// 10; without A, 62 to 64 in a simulation.)
-// What bounds a round of that call, 25 us: the walk of 256 tokens 15, the sample 1.7, the rows' way
-// through memory and what is made of them 4, the correction over 63 blocks 4.  The call: 889 -> 239 us; with
-// c = 10, 2279 -> 420; 8192 tokens of 64 candidates each 837 -> 159 (two rounds).  At 3072 tokens the walk alone is
-// about as fast.
+// (Rounds until 16384 load-dependent tokens of 64 experts are decided, k = 6, c = 8, blocks of 256: 7 to 10;
+// without A, 62 to 64 in a simulation.)
+// What bounds a round of that call, 20 us: the walk of 256 tokens 15, the sample 1.7, the rows' way
+// through memory and what is made of them 3, the correction 1.  The call: 889 -> 176 to 210 us; with c = 10,
+// 2279 -> 370; 8192 tokens of 64 candidates each, two rounds, 837 -> 99 with what else has changed.  At 3072 tokens
+// the walk alone is about as fast.
 constexpr int kChainBlocks = 64;         // blocks of a call, at most
 constexpr int kChainBlockMin = 128;      // tokens of a block, at least
 constexpr int kChainBlocksMinTokens = 3072;  // load-dependent tokens from which on a call is walked in blocks
 constexpr int kBlockSamples = 32;        // tokens of a block that are looked at for g
 constexpr int kSamplesPerWave = kBlockSamples / kChainWaves;
-constexpr float kForgetHalf = 4.0f;      // close decisions per block that make g one half
+constexpr float kForgetHalf = 4.0f;      // close decisions per block that make g one half (2 to 5: the same within 3 %; 8: a sixth more rounds)
 
 // What a block tells the others, per expert: where it began (27 bits), what it added (11), close
 // decisions among its samples (6), the round (20; 0: nothing yet, kBlockFinal: it stays so).  Whole
@@ -1786,14 +1786,17 @@ __device__ __forceinline__ float wave_prefix(float v) {
 
 // What a block's workgroup keeps in LDS beside that of the walks.
 struct BlockLds {
-  float inv[kChainBlocks];     // of each block before: 1 / (sum of g)
+  float inv[64];               // of each group of blocks before this one: 1 / (sum of g)
   unsigned open[kChainWaves];  // bit u of wave w's: the boundary behind block 16 w + u does not match
   int first_begin[kChainWaves][64];  // where the first block of a wave began
   int begin[64], begin_next[64];
   int close[kChainWaves][64];
   int ok, state;                // state: 0 go on, 1 the next walk is the last one, 2 this one was
 };
-// In the LDS of the walks, between two of them, for every block before this one { N_q - I_(q+1), g_q }.
+// In the LDS of the walks, between two of them, for every group of blocks before this one what they do to
+// a correction, { added, g }: fewer of the dependent steps, 60 ns each (eight shapes of calls, 4 seeds
+// each, 16384 and 6000 tokens: block by block 324 us on the average, by twos 306, by fours and eights 296).
+constexpr int kBlockGroup = 8;
 typedef float2 BlockRow[64];
 static_assert((kChainBlocks + 8) * sizeof(BlockRow) <= kChainLdsBytes, "the rows of all blocks, and read-ahead, fit the LDS of a walk");
 
@@ -1892,18 +1895,32 @@ __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int b
     // (one reading of every row: a row that is written again meanwhile must not be seen as two)
     S.first_begin[wave][lane] = block_begin(v[0]);
     unsigned open = 0;
+    const float close_scale = (float)tokens / kBlockSamples;
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int end_u = block_begin(v[u]) + block_added(v[u]);
-      const int gap = u + 1 < kPer ? end_u - block_begin(v[u + 1 < kPer ? u + 1 : u]) : 0;
-      const float close = (float)block_close(v[u]) * ((float)tokens / kBlockSamples);
-      const float g = close * __builtin_amdgcn_rcpf(close + kForgetHalf);
-      const float sum = wave_sum(g);
-      if (r0 + u < r1) {
-        if (r0 + u + 1 == r1) last_end = end_u;
-        row[r0 + u][lane] = make_float2((float)gap, g);
-        if (lane == 0) S.inv[r0 + u] = sum > 0.0f ? __builtin_amdgcn_rcpf(sum) : 0.0f;
+    for (int u0 = 0; u0 < kPer; u0 += kBlockGroup) {
+      // a group in one step: what a boundary adds passes the group's blocks behind it
+      // (blocks that do not exist change nothing; the gap behind the wave's last one comes below)
+      float x = 0.0f, keep = 1.0f;
+#pragma unroll
+      for (int u = u0; u < u0 + kBlockGroup; ++u) {
+        const bool there_is = r0 + u < r1;
+        const int end = block_begin(v[u]) + block_added(v[u]);
+        const int gap = r0 + u + 1 < r1 ? end - block_begin(v[u + 1 < kPer ? u + 1 : u]) : 0;
+        const float close = (float)block_close(v[u]) * close_scale;
+        const float g = there_is ? close * __builtin_amdgcn_rcpf(close + kForgetHalf) : 0.0f;
+        if (u != u0) {
+          const float sum = wave_sum(g), mean = wave_sum(g * x) * (sum > 0.0f ? __builtin_amdgcn_rcpf(sum) : 0.0f);
+          x += g * (mean - x);
+        }
+        x += (float)gap;
+        keep *= 1.0f - g;
+        last_end = there_is ? end : last_end;
         open |= (__builtin_amdgcn_ballot_w64(gap != 0) != 0ull ? 1u : 0u) << u;
+      }
+      const float sum = wave_sum(1.0f - keep);
+      if (r0 + u0 < r1) {
+        row[(r0 + u0) / kBlockGroup][lane] = make_float2(x, 1.0f - keep);
+        if (lane == 0) S.inv[(r0 + u0) / kBlockGroup] = sum > 0.0f ? __builtin_amdgcn_rcpf(sum) : 0.0f;
       }
     }
     if (lane == 0) S.open[wave] = open;
@@ -1918,9 +1935,9 @@ __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int b
   if (r0 < r1) {
     // (of the wave's last row the one behind is another wave's, or this block's own)
     const int gap = last_end - (r1 == blk ? begin : S.first_begin[min(wave + 1, kChainWaves - 1)][lane]);
-    row[r1 - 1][lane].x = (float)gap;
+    row[(r1 - 1) / kBlockGroup][lane].x += (float)gap;
     const unsigned open = __builtin_amdgcn_ballot_w64(gap != 0) != 0ull ? 1u : 0u;
-    if (lane == 0) S.open[wave] = (S.open[wave] & ~(1u << (r1 - 1 - r0))) | (open << (r1 - 1 - r0));
+    if (lane == 0) S.open[wave] |= open << (r1 - 1 - r0);
   }
   __syncthreads();
   // ---- the correction of this block's beginning ------------------------------------------------
@@ -1944,10 +1961,11 @@ __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int b
         d = fmaf(share, wave_sum(x.y * d), keep);
       };
       // (four rows ahead; behind the last one: read and not used)
-      const float2* from = &row[q0][lane];
+      const int groups = (blk + kBlockGroup - 1) / kBlockGroup;
+      int q = q0 / kBlockGroup;
+      const float2* from = &row[q][lane];
       float2 x0 = from[0], x1 = from[64], x2 = from[128], x3 = from[192];
-      int q = q0;
-      for (; q + 4 <= blk; q += 4) {
+      for (; q + 4 <= groups; q += 4) {
         from += 256;
         const float2 y0 = from[0], y1 = from[64], y2 = from[128], y3 = from[192];
         __builtin_amdgcn_sched_barrier(0);
@@ -1961,9 +1979,9 @@ __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int b
         x2 = y2;
         x3 = y3;
       }
-      if (q < blk) step(x0, q);
-      if (q + 1 < blk) step(x1, q + 1);
-      if (q + 2 < blk) step(x2, q + 2);
+      if (q < groups) step(x0, q);
+      if (q + 1 < groups) step(x1, q + 1);
+      if (q + 2 < groups) step(x2, q + 2);
       if (q0 == blk - 1) {
         state = 1;  // (the block before ended where everything is decided: this is no guess)
         next = begin + (int)d;
