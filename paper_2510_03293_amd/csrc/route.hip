@@ -141,7 +141,7 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
     const Workspace ws = BATCH ? problem_workspace(own->ws, (size_t)prob * a.ws_stride) : own->ws;
     if (blockIdx.z == 1 ? blockIdx.x >= kChainBlocks : blockIdx.x == 0) return;
     const int flex_tok = count_flexible(a.ntiles, ws);
-    if (flex_tok < kChainBlocksMinTokens) return;
+    if (!chain_in_blocks(flex_tok, a.T)) return;
     int32_t* const loads = own->loads_inout + (size_t)prob * a.E;
     int32_t* const offsets = own->expert_offsets + (size_t)prob * (a.E + 1);
     if (blockIdx.z == 1) {
@@ -194,11 +194,9 @@ static_assert(offsetof(TailArgs, ws) == sizeof(RouteArgs) &&
 // Whether a call may well have a chain that is worth cutting into blocks (how many of its tokens depend
 // on the counters is known on the device only).  The kernel that can do it is no slower where none
 // do, but where a window of tokens is evaluated (12345 tokens, 1200 of them load-dependent: 66.2 -> 66.9
-// us), so it is for calls whose thresholds send most tokens to the load-aware branch, and for
-// those in which the eighth part of the tokens is enough.
+// us), so it is for calls whose thresholds send most tokens to the load-aware branch.
 static bool chain_blocks_possible(const RouteArgs& a) {
-  return a.EP > 8 && a.nseg == 0 && a.ntiles <= kSelfPrefixTiles &&
-         a.T >= (a.eps_high > 0.5f ? 1 : 8) * kChainBlocksMinTokens;
+  return a.EP > 8 && a.nseg == 0 && a.ntiles <= kSelfPrefixTiles && a.T >= kChainBlocksMinTokens && a.eps_high > 0.5f;
 }
 
 template <bool BATCH, bool BLOCKS>
