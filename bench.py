@@ -31,10 +31,10 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, vendor figure
 # kernel sources it was taken on: the record carries their hash and `traffic` is
 # reported as null once the sources differ.
 PMC_TRAFFIC = {
-    "sources_sha256_16": "ea70463b24d577ba",
+    "sources_sha256_16": "27d7a6059e155a5c",
     "workload": "deepseek",
-    "fetch_kib": 33892.99, "fetch_scale": 1.9997,
-    "write_kib": 1024.23, "write_scale": 1.0,
+    "fetch_kib": 33886.86, "fetch_scale": 1.9997,
+    "write_kib": 1024.22, "write_scale": 1.0,
 }
 GATE_SOURCES = ("paper_2510_03293_amd/csrc/gate.hip", "paper_2510_03293_amd/csrc/gate_tile.h",
                 "paper_2510_03293_amd/csrc/analyse.h")
