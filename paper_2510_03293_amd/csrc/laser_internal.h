@@ -144,8 +144,10 @@ __device__ __forceinline__ Workspace problem_workspace(const Workspace& w0, size
   return w;
 }
 
-constexpr int kStatusPhase = 0;      // 1: fixed prefix published, 2: chain finished
-constexpr int kStatusFlexTiles = 1;  // number of tiles that hold flexible tokens; negative: the chain is cut into blocks
+constexpr int kStatusPhase = 0;      // 1: fixed prefix published, then
+constexpr int kPhaseWalked = 2;      // the chain is finished, its choices are in chain_bits and chain_cum
+constexpr int kPhaseBlocks = 3;      // ... in the arrays of its blocks, which were first
+constexpr int kStatusFlexTiles = 1;  // number of tiles that hold flexible tokens; negative: the chain is walked in blocks too
 constexpr int kStatusError = 2;      // 0, or why the outputs of the call are incomplete (kError*)
 constexpr int kErrorTimeout = 1;        // a bounded wait in the tail kernel ran out (LASER_STATUS_TIMEOUT)
 constexpr int kErrorInconsistent = 2;   // a dispatch slot fell outside the table (LASER_STATUS_INCONSISTENT)
@@ -154,7 +156,7 @@ constexpr int kErrorInconsistent = 2;   // a dispatch slot fell outside the tabl
 // plus an allowance per token of the call, far above the chain's cost per token.
 constexpr long long kSpinFloor = 1ll << 22;
 constexpr long long kSpinPerToken = 16;
-constexpr int kStatusSweeps = 3;     // sweeps of the chain's window evaluation, or walks of its last block (diagnostic)
+constexpr int kStatusSweeps = 3;     // (diagnostic) sweeps of the chain's window evaluation; kPhaseBlocks: walks of the last block
 
 // Workspace::seg of a pipelined call.  Cleared by a small kernel before the gate kernel.
 constexpr int kSegNext = 0;     // segments the chain has finished

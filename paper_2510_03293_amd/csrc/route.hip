@@ -112,8 +112,8 @@ struct TailArgs {
 
 // BATCH: blockIdx.y is the problem of a batched call (a kernel of its own: the
 // longer prologue would delay the first loads of the single-problem kernel).
-// BLOCKS: the chain has the first kChainBlocks workgroups (chain_blocks_possible), otherwise the first
-// one (kernels of their own: a number that the kernel had to read first would delay them all).
+// BLOCKS: the chain may be walked in blocks as well (chain_blocks_possible; kernels of their own: a number
+// that the kernel had to read first would delay all workgroups).
 // Two workgroups on a compute unit: with the registers of one a long
 // batch's finishing workgroups ran in two rounds (131072 tokens: 329 -> 339 us)
 template <bool BATCH, bool BLOCKS>
@@ -125,44 +125,29 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
                                                             int32_t* __restrict__ permutation) {
   extern __shared__ __align__(16) uint8_t tail_lds[];
   __shared__ FinishShared finish_shared;
-  // Workgroup 0 is the chain, the others finish tiles.  BLOCKS: the grid has three layers.  Where the
-  // chain is cut into blocks, layer 0 leaves when the lists of tokens are there, the workgroups of
-  // layer 1 take the blocks, and those of layer 2 finish the tiles; otherwise layers 1 and 2 leave at
-  // once.  (A workgroup waits for earlier ones only.  27 layers of 16384 tokens, none of them
-  // load-dependent: 665 us without the layers and with them; with one layer, the blocks ahead of the
-  // finishing workgroups, 673, finishing workgroups that go on with a block, 671.)
-  if (BLOCKS && blockIdx.z != 0) {
-    // (arguments of its own, as below; the finishing pass a second time, for the sake of layer 0)
-    auto* kernarg = __builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(kernarg));
-    const TailArgs* own = (const TailArgs*)kernarg;
-    const int prob = BATCH ? blockIdx.y : 0;
-    const RouteArgs a = BATCH ? problem_args(own->a, prob) : own->a;
-    const Workspace ws = BATCH ? problem_workspace(own->ws, (size_t)prob * a.ws_stride) : own->ws;
-    if (blockIdx.z == 1 ? blockIdx.x >= kChainBlocks : blockIdx.x == 0) return;
-    const int flex_tok = count_flexible(a.ntiles, ws);
-    if (!chain_in_blocks(flex_tok, a.T)) return;
-    int32_t* const loads = own->loads_inout + (size_t)prob * a.E;
-    int32_t* const offsets = own->expert_offsets + (size_t)prob * (a.E + 1);
-    if (blockIdx.z == 1) {
-      chain_block(tail_lds, a, ws, loads, offsets, blockIdx.x, flex_tok);
-    } else {
-      const size_t first = (size_t)prob * a.T * a.k;
-      finish_role<false>(blockIdx.x - 1, tail_lds, finish_shared, a, ws, loads, offsets, own->expert_ids + first, own->weights + first,
-                         own->permutation + first);
-    }
-    return;
-  }
-  if (!BATCH && blockIdx.x == 0) {
+  // Workgroup 0 is the chain, the others finish tiles.  BLOCKS: the grid has layers, in the order of who
+  // waits for whom: the chain and its blocks, then the workgroups that finish tiles.
+  constexpr int kLayers = 2;
+  if (BLOCKS ? blockIdx.z != kLayers - 1 : !BATCH && blockIdx.x == 0) {
     // The chain reads its arguments for itself, through a pointer the compiler knows nothing of:
     // shared with the finishing workgroups they were all loaded, waited for and put aside (20
     // lane writes) before those could begin (27 layers of 16384 tokens, 64 experts: 663 -> 657 us).
     auto* kernarg = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(kernarg));
     const TailArgs* own = (const TailArgs*)kernarg;
-    const RouteArgs a = own->a;
-    const Workspace ws = own->ws;
-    chain_segments<false, 0, BLOCKS>(tail_lds, a, ws, own->loads_inout, own->expert_offsets);
+    const int prob = BATCH ? blockIdx.y : 0;
+    const RouteArgs a = BATCH ? problem_args(own->a, prob) : own->a;
+    const Workspace ws = BATCH ? problem_workspace(own->ws, (size_t)prob * a.ws_stride) : own->ws;
+    int32_t* const loads = own->loads_inout + (size_t)prob * a.E;
+    int32_t* const offsets = own->expert_offsets + (size_t)prob * (a.E + 1);
+    if (blockIdx.z == 0 && blockIdx.x == 0) {
+      chain_segments<false, 0, BLOCKS>(tail_lds, a, ws, loads, offsets);
+    } else if constexpr (BLOCKS) {
+      const int blk = blockIdx.x - 1;
+      if (blk >= kChainBlocks) return;  // (every layer is as wide as the widest)
+      const int flex_tok = count_flexible(a.ntiles, ws);
+      if (chain_in_blocks(flex_tok, a.T)) chain_block(tail_lds, a, ws, loads, offsets, blk, flex_tok);
+    }
     return;
   }
   // (each problem has its own chain workgroup)
@@ -176,11 +161,13 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
     weights += (size_t)prob * a.T * a.k;
     permutation += (size_t)prob * a.T * a.k;
   }
-  if (BATCH && blockIdx.x == 0) {
-    chain_segments<false, 0, BLOCKS>(tail_lds, a, ws, loads_inout, expert_offsets);
+  if (!BLOCKS && BATCH && blockIdx.x == 0) {
+    chain_segments<false, 0>(tail_lds, a, ws, loads_inout, expert_offsets);
     return;
   }
-  finish_role<BLOCKS>(blockIdx.x - 1, tail_lds, finish_shared, a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation);
+  const int group = BLOCKS ? blockIdx.x : blockIdx.x - 1;
+  if (BLOCKS && group >= finish_groups(a.ntiles)) return;
+  finish_role<BLOCKS>(group, tail_lds, finish_shared, a, ws, loads_inout, expert_offsets, expert_ids, weights, permutation);
 }
 // (TailArgs mirrors the signature: whoever changes one has to change the other)
 static_assert(std::is_same<decltype(&tail_kernel<false, false>), void (*)(RouteArgs, Workspace, int32_t*, int32_t*, int32_t*,
@@ -207,10 +194,10 @@ static hipError_t launch_tail_b(const RouteArgs& a, const Workspace& ws, int32_t
   const hipError_t e =
       allow_dynamic_lds(reinterpret_cast<const void*>(&tail_kernel<BATCH, BLOCKS>), kChainLdsBytes, allowed);
   if (e != hipSuccess) return e;
-  // (every layer as wide as the widest)
-  const int width = std::max(1 + finish_groups(a.ntiles), BLOCKS ? kChainBlocks : 0);
+  const int groups = finish_groups(a.ntiles);
+  const int width = BLOCKS ? std::max(1 + kChainBlocks, groups) : 1 + groups;
   clear_stale_error();
-  hipLaunchKernelGGL((tail_kernel<BATCH, BLOCKS>), dim3(width, a.nbatch, BLOCKS ? 3 : 1), dim3(kTailThreads), kChainLdsBytes, s, a, ws,
+  hipLaunchKernelGGL((tail_kernel<BATCH, BLOCKS>), dim3(width, a.nbatch, BLOCKS ? 2 : 1), dim3(kTailThreads), kChainLdsBytes, s, a, ws,
                      loads_inout, expert_offsets, expert_ids, weights, permutation);
   return hipGetLastError();
 }

@@ -14,7 +14,8 @@ namespace laser {
 // ------------------------------------------------------------------ tail -----
 //
 // One kernel after the analysis: workgroup 0 is the chain, every other workgroup
-// finishes 4 tiles (one wavefront each).
+// finishes 4 tiles (one wavefront each).  Calls whose tokens may nearly all be load-dependent have up to
+// 64 more workgroups, which walk the chain in blocks beside workgroup 0 (see "the chain in blocks").
 //
 // Chain workgroup (4 wavefronts):
 //   prefix  (all waves)  exclusive prefix over tiles of the fixed tokens' per-expert
@@ -25,13 +26,14 @@ namespace laser {
 //           inside the tile (carried by its record) + flexible choices so far.
 //           Candidate key = (load << 4) + rank: ascending load, ties by score rank; the
 //           k smallest keys win.  Two evaluations, same result:
-//           - window (wave 0, lane = token): 64 consecutive flexible tokens per sweep,
-//             see "window evaluation" below; used first when there are enough tokens;
+//           - a window of consecutive flexible tokens at once (lane = token), 64 of them in wave 0
+//             ("window evaluation") or 256 in four waves ("window of 256 tokens"); used first when
+//             there are enough tokens;
 //           - sequential (wave 0): a candidate is chosen iff fewer than k candidate keys are
 //             smaller than its own, see "sequential walk" and "walks of up to 8 candidates"
 //             below.  Takes over where the window evaluation stops paying.
-//           The other waves stage the records in LDS ahead of wave 0.
-//   totals  loads and offsets, then flag 2.
+//           Waves that do not evaluate stage the records in LDS ahead of those that do.
+//   totals  loads and offsets, then flag 2 (or 3: the blocks were first).
 //   Output of the chain, per expert: one bit per flexible token of the call in token
 //   order (chain_bits, 32 per word) and the running count of chosen bits at every
 //   32-token boundary (chain_cum).
@@ -47,9 +49,11 @@ namespace laser {
 // (chain_cum at the last boundary + the bits since).
 //
 // The waits are bounded polls of flags that the analysis kernel of the same call
-// cleared; workgroup 0 has the lowest index, is dispatched first and never waits,
-// so the polls end.  A poll that runs out sets ws.status[kStatusError] and the wave
-// leaves without writing; the caller learns of it through laser_status().
+// cleared.  Workgroup 0 waits for nobody, neither for the blocks of its chain, which it does not need, nor for
+// any other workgroup, and it is dispatched ahead of those that wait for it, so the polls
+// end, whatever else is on the GPU.  A poll of a finishing wavefront that runs out sets
+// ws.status[kStatusError] and the wave leaves without writing; the caller learns of it through
+// laser_status().  A block whose wait runs out just leaves.
 
 constexpr int kChainWaves = 4;
 constexpr int kTailThreads = kChainWaves * 64;
@@ -103,15 +107,39 @@ __device__ __forceinline__ bool poll_word(const int* word, int want, long long l
   }
   return false;
 }
-__device__ __forceinline__ bool poll_flag(const int* flag, int want, long long limit) {
+// What the flag holds once it is at least `want` (> 0); 0 where the polls run out.
+__device__ __forceinline__ int poll_flag(const int* flag, int want, long long limit) {
   for (long long it = 0; it < limit; ++it) {
     const int seen = __builtin_amdgcn_readfirstlane(
         __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    if (seen >= want) return true;
+    if (seen >= want) return seen;
     __builtin_amdgcn_s_sleep(4);
   }
-  return false;
+  return 0;
 }
+
+// A chain that is walked in one piece and in blocks at the same time (see "the chain in blocks"):
+// whoever is through first claims the call, and a walk that is under way looks every few microseconds
+// whether somebody has.  One wavefront asks memory for the claim and looks at the answer at its next
+// turn; the others learn of it through LDS, and all of them leave behind the same barrier.
+// ON false: nobody else walks the call (no code).
+template <bool ON>
+struct Race {
+  const int* claim;  // NULL: nobody else walks this call
+  int* stop;         // LDS, two words
+  __device__ __forceinline__ bool on() const { return ON && claim != nullptr; }
+  __device__ __forceinline__ int ask() const {
+    return on() ? __hip_atomic_load(claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  }
+  // (before a barrier of LDS traffic)
+  __device__ __forceinline__ void hand_out(int answer, int lane, int word = 0) const {
+    if (on() && lane == 0) stop[word] = answer;
+  }
+  // (behind that barrier; between reading a word and writing it again there is another one)
+  __device__ __forceinline__ bool over(int word = 0) const {
+    return on() && __builtin_amdgcn_readfirstlane(stop[word]) != 0;
+  }
+};
 
 // cnt += number of the 4 lanes named by the bytes of `w` whose key is smaller than this
 // lane's key.  Written in assembly because the order of the instructions is the
@@ -333,10 +361,11 @@ __device__ __forceinline__ void seq_store(typename SeqTraits<CP>::Tok* dst, cons
 
 // Walks the flexible tokens from token `f0` of the call on.  `hist0`: the bits of output word
 // f0 / 32 that are decided already.  The output (chain_bits, chain_cum) is indexed by the
-// flexible token's number within the call.  CP: 16 candidates, 0: a wide call.
-template <int CP>
-__device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
-                                           const Workspace& ws, int wave, int lane, int lin, int& gflex) {
+// flexible token's number within the call.  CP: 16 candidates, 0: a wide call.  Returns whether the
+// walk has come to its end (see Race).
+template <int CP, bool RACE>
+__device__ __forceinline__ bool chain_walk(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
+                                           const Workspace& ws, int wave, int lane, int lin, int& gflex, Race<RACE> race) {
   own_lane(lane);
   typedef typename SeqTraits<CP>::Tok Tok;
   constexpr int NB = SeqTraits<CP>::batch;
@@ -370,6 +399,14 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
     seq_load<CP, NH>(first, slots_n, 0, a, ws, lane);
     seq_store<CP, NH>(dst, second, NH, pw, a.EP, lane, lin);
   }
+  // (looks at the claim are a few tokens apart: a token of a wide call can take a microsecond)
+  constexpr int kPiece = !RACE ? 32 : CP != 0 ? 16 : 8;
+  int answer = 0;
+  if (RACE && wave == 0) {
+    race.hand_out(0, lane, 0);
+    race.hand_out(0, lane, 1);
+    answer = race.ask();
+  }
   lds_barrier();
   for (int b = b0; b < b1; ++b) {
     if (wave != 0) {
@@ -386,6 +423,13 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
       const Tok* cur = buf + (b & 1) * NB;
       const int n = min(NB, nflex_tok - b * NB);
       int r = f - b * NB;
+      auto look = [&]() {
+        if (!RACE || !race.on()) return false;
+        const bool over = __builtin_amdgcn_readfirstlane(answer) != 0;
+        answer = race.ask();
+        if (over) race.hand_out(1, lane, b & 1);
+        return over;
+      };
       if constexpr (CP != 0) {
         constexpr int kPer = 4;  // keys a lane compares with
         unsigned rec = cur[r].rec[lane];
@@ -422,9 +466,10 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
           for (int u = 0; u < kPer; ++u) aj[u] = aj_n[u];
         };
         while (r < n) {
-          // up to the end of the batch or of the 32-token output word, whichever is first
-          const int end = min(n, r + 32 - (f & 31));
+          // up to the end of the batch or of the 32-token output word (or half of it), whichever is first
+          const int end = min(n, r + kPiece - (f & (kPiece - 1)));
           f += end - r;
+          if (look()) break;
           for (; r + 4 <= end; r += 4) {
             step(cur[r + 1]);
             step(cur[r + 2]);
@@ -516,8 +561,9 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
           base = base_n;
         };
         while (r < n) {
-          const int end = min(n, r + 32 - (f & 31));
+          const int end = min(n, r + kPiece - (f & (kPiece - 1)));
           f += end - r;
+          if (look()) break;
           for (; r + 2 <= end; r += 2) {
             step(cur[r + 1]);
             step(cur[r + 2]);
@@ -533,6 +579,7 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
       }
     }
     lds_barrier();
+    if (RACE && race.over(b & 1)) return false;
   }
   if (wave == 0) {
     gflex = (int)G;
@@ -540,6 +587,7 @@ __device__ __forceinline__ void chain_walk(uint8_t* lds, int f0, unsigned hist0,
     if ((f & 31) != 0)
       ws.chain_bits[(size_t)(f >> 5) * 64 + lane] = __builtin_bitreverse32(hist) >> (32 - (f & 31));
   }
+  return true;
 }
 
 // ---- walks of up to 8 candidates --------------------------------------------------------
@@ -672,8 +720,11 @@ __device__ __forceinline__ void lag_store(LagTok* dst, uint8_t* places, const La
     dst[2 * q + h].v[lane & 31] = make_int4(pair_bound(ki[q], kj[q]), 4 * ci[q], 4 * cj[q], wi[q] | (wj[q] << 8));
 }
 
-__device__ __forceinline__ void chain_walk_lag(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
-                                               const Workspace& ws, int wave, int lane, int lin, int& gflex) {
+// (f0, hist0 and what it returns: as chain_walk)
+template <bool RACE>
+__device__ __forceinline__ bool chain_walk_lag(uint8_t* lds, int f0, unsigned hist0, int nflex_tok, const RouteArgs& a,
+                                               const Workspace& ws, int wave, int lane, int lin, int& gflex,
+                                               Race<RACE> race) {
   own_lane(lane);
   LagTok* const ring = reinterpret_cast<LagTok*>(lds);
   uint8_t* const places = lds + kLagPlaceOffset;
@@ -682,6 +733,10 @@ __device__ __forceinline__ void chain_walk_lag(uint8_t* lds, int f0, unsigned hi
   const int b0 = f0 / kLagBatch, b1 = (nflex_tok + kLagBatch - 1) / kLagBatch;
   int pi, pj;
   lane_pair(lane & 31, pi, pj);
+  // (a look at the claim every four batches, 3.4 us; in loops of their own, since a test in the consumer's
+  // loop over the batches cost the walk 5 %)
+  constexpr int kLook = 4;
+  auto stretch = [&](int b) { return RACE && race.on() ? min(b1, b + kLook) : b1; };
   if (wave == 1 || wave == 2) {
     // ---- producers: two batches ahead of the consumer in LDS, and two more with every load that
     // leads to another one -- where the records are, the records, the counters of the candidates
@@ -731,16 +786,28 @@ __device__ __forceinline__ void chain_walk_lag(uint8_t* lds, int f0, unsigned hi
     fill(b0 + 1, c1, r1, s1);
     lds_barrier();
     // (what is filled behind the last batch is not read)
-    for (int b = b0; b < b1; b += 2) {
-      fill(b + 2, c0, r0, s0);
-      lds_barrier();
-      if (b + 1 >= b1) break;
-      fill(b + 3, c1, r1, s1);
-      lds_barrier();
+    for (int b = b0, be; b < b1; b = be) {
+      be = stretch(b);
+      for (; b < be; b += 2) {
+        fill(b + 2, c0, r0, s0);
+        lds_barrier();
+        if (b + 1 >= be) break;
+        fill(b + 3, c1, r1, s1);
+        lds_barrier();
+      }
+      if (RACE && be < b1 && race.over()) return false;
     }
   } else if (wave != 0) {
     lds_barrier();
-    for (int b = b0; b < b1; ++b) lds_barrier();
+    for (int b = b0, be; b < b1; b = be) {
+      be = stretch(b);
+      const int answer = RACE ? race.ask() : 0;
+      for (; b < be; ++b) {
+        if (RACE && b + 1 == be && be < b1) race.hand_out(answer, lane);
+        lds_barrier();
+      }
+      if (RACE && be < b1 && race.over()) return false;
+    }
   } else {
     // ---- consumer ----------------------------------------------------------------------
     int G = gflex;
@@ -765,68 +832,73 @@ __device__ __forceinline__ void chain_walk_lag(uint8_t* lds, int f0, unsigned hi
     // (the choice before the first token is in G)
     int diff = gather(d0.z) - gather(d0.y);
     unsigned chosen = 0u;  // (lane = expert: of the token before)
-    for (int b = b0; b < b1; ++b) {
-      const bool wrap = cur + kLagBatch == ring_end;
-      const LagTok* const next = wrap ? ring : cur + kLagBatch;
-      const uint8_t* const next_places = wrap ? places + lane : cur_places + 2 * kLagPlaceRows * 64;
-#pragma unroll
-      for (int u = 0; u < kLagBatch; ++u) {
-        // From the difference to W and the choice of the lane's expert, in assembly because the
-        // order is the point: what is read out of a comparison's scalar must be two instructions
-        // behind it, and these do something.
-        unsigned next_j;
-        unsigned long long won;
-        asm("v_cmp_le_i32 vcc, %[diff], %[U]\n\t"
-            "v_lshl_or_b32 %[hist], %[hist], 1, %[chosen]\n\t"  // (the token before)
-            "v_lshrrev_b32 %[nj], 8, %[w1]\n\t"
-            "v_bitop3_b32 %[diff], %[flip], %[mask], vcc_lo bitop3:0x48\n\t"  // (pairs ^ flip) & mask
-            "v_bcnt_u32_b32 %[diff], %[diff], %[start]\n\t"
-            "v_cmp_gt_i32 s[98:99], %[k], %[diff]\n\t"
-            : [diff] "+v"(diff), [hist] "+v"(hist), [nj] "=&v"(next_j), [won] "={s[98:99]}"(won)
-            : [chosen] "v"(chosen), [U] "v"(d0.x), [w1] "v"(d1.w), [flip] "v"(rank.flip), [mask] "v"(rank.mask),
-              [start] "v"(start), [k] "s"(k)
-            : "vcc");
-        // (two blocks, so that the difference gathered for the next token is waited for here only)
-        asm("v_sub_u32 %[diff], %[j1], %[i1]\n\t"
-            "s_nop 0\n\t"
-            "v_bfe_u32 %[chosen], s98, %[place], 1\n\t"
-            "v_add_u32 %[G], %[G], %[chosen]\n\t"
-            : [diff] "=&v"(diff), [chosen] "=&v"(chosen), [G] "+v"(G)
-            : [i1] "v"(i1), [j1] "v"(j1), [place] "v"(place), [won] "{s[98:99]}"(won));
-        // (a scalar instruction that read it would wait for 16 cycles)
-        const unsigned W = (unsigned)won;
-        const int i2 = gather(d2.y), j2 = gather(d2.z);
-        __builtin_amdgcn_sched_barrier(0);
-        const int next_chose_i = (int)__builtin_amdgcn_sbfe((int)W, (unsigned)d1.w, 1);
-        const int next_chose_j = (int)__builtin_amdgcn_ubfe(W, next_j, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        diff = diff + next_chose_i + next_chose_j;
-        place = place1;
-        place1 = u + 2 < kLagBatch ? cur_places[row(u + 2)] : next_places[row(u + 2 - kLagBatch)];
-        i1 = i2;
-        j1 = j2;
-        d0 = d1;
-        d1 = d2;
-        d2 = d3;
-        // (behind the last token of the call: read and not used)
-        d3 = u + 4 < kLagBatch ? cur[u + 4].v[pair] : next[u + 4 - kLagBatch].v[pair];
-        __builtin_amdgcn_sched_barrier(0);
+    for (int b = b0, be; b < b1;) {
+      be = stretch(b);
+      for (; b < be; ++b) {
+        const bool wrap = cur + kLagBatch == ring_end;
+        const LagTok* const next = wrap ? ring : cur + kLagBatch;
+        const uint8_t* const next_places = wrap ? places + lane : cur_places + 2 * kLagPlaceRows * 64;
+  #pragma unroll
+        for (int u = 0; u < kLagBatch; ++u) {
+          // From the difference to W and the choice of the lane's expert, in assembly because the
+          // order is the point: what is read out of a comparison's scalar must be two instructions
+          // behind it, and these do something.
+          unsigned next_j;
+          unsigned long long won;
+          asm("v_cmp_le_i32 vcc, %[diff], %[U]\n\t"
+              "v_lshl_or_b32 %[hist], %[hist], 1, %[chosen]\n\t"  // (the token before)
+              "v_lshrrev_b32 %[nj], 8, %[w1]\n\t"
+              "v_bitop3_b32 %[diff], %[flip], %[mask], vcc_lo bitop3:0x48\n\t"  // (pairs ^ flip) & mask
+              "v_bcnt_u32_b32 %[diff], %[diff], %[start]\n\t"
+              "v_cmp_gt_i32 s[98:99], %[k], %[diff]\n\t"
+              : [diff] "+v"(diff), [hist] "+v"(hist), [nj] "=&v"(next_j), [won] "={s[98:99]}"(won)
+              : [chosen] "v"(chosen), [U] "v"(d0.x), [w1] "v"(d1.w), [flip] "v"(rank.flip), [mask] "v"(rank.mask),
+                [start] "v"(start), [k] "s"(k)
+              : "vcc");
+          // (two blocks, so that the difference gathered for the next token is waited for here only)
+          asm("v_sub_u32 %[diff], %[j1], %[i1]\n\t"
+              "s_nop 0\n\t"
+              "v_bfe_u32 %[chosen], s98, %[place], 1\n\t"
+              "v_add_u32 %[G], %[G], %[chosen]\n\t"
+              : [diff] "=&v"(diff), [chosen] "=&v"(chosen), [G] "+v"(G)
+              : [i1] "v"(i1), [j1] "v"(j1), [place] "v"(place), [won] "{s[98:99]}"(won));
+          // (a scalar instruction that read it would wait for 16 cycles)
+          const unsigned W = (unsigned)won;
+          const int i2 = gather(d2.y), j2 = gather(d2.z);
+          __builtin_amdgcn_sched_barrier(0);
+          const int next_chose_i = (int)__builtin_amdgcn_sbfe((int)W, (unsigned)d1.w, 1);
+          const int next_chose_j = (int)__builtin_amdgcn_ubfe(W, next_j, 1);
+          __builtin_amdgcn_sched_barrier(0);
+          diff = diff + next_chose_i + next_chose_j;
+          place = place1;
+          place1 = u + 2 < kLagBatch ? cur_places[row(u + 2)] : next_places[row(u + 2 - kLagBatch)];
+          i1 = i2;
+          j1 = j2;
+          d0 = d1;
+          d1 = d2;
+          d2 = d3;
+          // (behind the last token of the call: read and not used)
+          d3 = u + 4 < kLagBatch ? cur[u + 4].v[pair] : next[u + 4 - kLagBatch].v[pair];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const int w = b >> 1;
+        if ((b & 1) != 0 || b + 1 == b1) {
+          hist = (hist << 1) | chosen;
+          if ((b & 1) == 0) hist <<= kLagBatch;
+          const unsigned word = __builtin_bitreverse32(hist) | (w == (f0 >> 5) ? hist0 : 0u);
+          ws.chain_bits[(size_t)w * 64 + lane] = word;
+          if (32 * (w + 1) <= nflex_tok) ws.chain_cum[(size_t)(w + 1) * 64 + lane] = G;
+          hist = chosen = 0u;
+        }
+        cur = next;
+        cur_places = next_places;
+        lds_barrier();
       }
-      const int w = b >> 1;
-      if ((b & 1) != 0 || b + 1 == b1) {
-        hist = (hist << 1) | chosen;
-        if ((b & 1) == 0) hist <<= kLagBatch;
-        const unsigned word = __builtin_bitreverse32(hist) | (w == (f0 >> 5) ? hist0 : 0u);
-        ws.chain_bits[(size_t)w * 64 + lane] = word;
-        if (32 * (w + 1) <= nflex_tok) ws.chain_cum[(size_t)(w + 1) * 64 + lane] = G;
-        hist = chosen = 0u;
-      }
-      cur = next;
-      cur_places = next_places;
-      lds_barrier();
+      if (RACE && be < b1 && race.over()) return false;
     }
     gflex = G;
   }
+  return true;
 }
 
 // Up to 8 experts (all of a call's flexible tokens).  A pair is one of experts: the lane itself
@@ -1169,9 +1241,9 @@ __device__ __forceinline__ void spec_fill(SpecTok<CP>* ring, int seg, int half, 
 }
 
 // Runs the window evaluation from flexible token 0.  All four waves call it.  Returns
-// (to every wave) the number of flexible tokens decided; wave 0 leaves the flexible
-// choices so far in `gflex` (lane = expert) and the bits of the unfinished output
-// word in `hist`.  KK = k when known at compile time, else 0.
+// (to every wave) the number of flexible tokens decided, or -1 where somebody else has claimed the
+// call (see Race); wave 0 leaves the flexible choices so far in `gflex` (lane = expert), the bits of the
+// unfinished output word in `hist` and the number of sweeps in `nsweeps`.  KK = k when known at compile time, else 0.
 // LDS of the window evaluation beside the ring (one copy for all compiled variants).
 struct SpecShared {
   SpecExp M[64];
@@ -1179,9 +1251,10 @@ struct SpecShared {
   int sh_done[2], sh_bail[2];  // by segment parity: written before, read after a barrier
 };
 
-template <int CP, int KK>
+template <int CP, int KK, bool RACE>
 __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex_tok, const RouteArgs& a,
-                         const Workspace& ws, int wave, int lane, int lin, int& gflex, unsigned& hist) {
+                         const Workspace& ws, int wave, int lane, int lin, int& gflex, unsigned& hist, int& nsweeps,
+                         Race<RACE> race) {
   own_lane(lane);
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
   SpecTok<CP>* ring = reinterpret_cast<SpecTok<CP>*>(lds);
@@ -1219,10 +1292,11 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
   unsigned long long pend = 0ull;  // lane = expert: decided bits not yet written, from token 32*w
   int pn = 0, w = 0, gflushed = 0;
   int sweeps = 0, done_mark = 0, total_sweeps = 0;
-  bool bail = false;
+  bool bail = false, stop = false;
   int decided = 0;
   const unsigned long long lb = lanes_below(lane);
 
+  int answer = RACE && !producer ? race.ask() : 0;
   const int nep = (nflex_tok + kSpecSeg - 1) / kSpecSeg;
   for (int ep = 0; ep < nep; ++ep) {
     if (producer) {
@@ -1231,6 +1305,11 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
       const int avail = min(nflex_tok, (ep + 2) * kSpecSeg);
       const int target = min(nflex_tok, (ep + 1) * kSpecSeg);
       while (done < target && !bail) {
+        if (RACE && race.on() && (total_sweeps & 3) == 3) {  // (every two to four microseconds)
+          stop = __builtin_amdgcn_readfirstlane(answer) != 0;
+          answer = race.ask();
+          if (stop) break;
+        }
         const int head = done & 63;
         // this lane's token of the window [done, done + 64)
         const int f_lane = done + ((lane - head) & 63);
@@ -1324,18 +1403,20 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
       }
       if (lane == 0) {
         sh_done[ep & 1] = done;
-        sh_bail[ep & 1] = bail ? 1 : 0;
+        sh_bail[ep & 1] = stop ? 2 : bail ? 1 : 0;
       }
     }
     __syncthreads();
     decided = __builtin_amdgcn_readfirstlane(sh_done[ep & 1]);
-    if (__builtin_amdgcn_readfirstlane(sh_bail[ep & 1])) break;
+    const int why = __builtin_amdgcn_readfirstlane(sh_bail[ep & 1]);
+    if (RACE && why == 2) return -1;
+    if (why != 0) break;
   }
   if (wave == 0) {
     gflex = G;
     hist = (unsigned)pend;  // the decided % 32 bits of the unfinished word
     if (decided == nflex_tok && pn > 0) ws.chain_bits[(size_t)w * 64 + lane] = (unsigned)pend;
-    if (lane == 0) ws.status[kStatusSweeps] = total_sweeps;
+    nsweeps = total_sweeps;
   }
   __syncthreads();  // the ring is dead: the sequential walk may reuse the LDS
   return decided;
@@ -1456,9 +1537,10 @@ __device__ __forceinline__ void win_counters(int (&base)[CP], const unsigned (&i
 __device__ __forceinline__ unsigned long long below64(int x) { return x >= 64 ? ~0ull : (1ull << x) - 1ull; }
 
 // Runs the window evaluation from flexible token 0 (see spec_walk for the contract).
-template <int CP, int KK>
+template <int CP, int KK, bool RACE>
 __device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const RouteArgs& a, const Workspace& ws,
-                                           int wave, int lane, int lin, int& gflex, unsigned& hist) {
+                                           int wave, int lane, int lin, int& gflex, unsigned& hist, int& nsweeps,
+                                           Race<RACE> race) {
   own_lane(lane);
   nflex_tok = __builtin_amdgcn_readfirstlane(nflex_tok);
   WinShared<CP>& S = *reinterpret_cast<WinShared<CP>*>(lds);
@@ -1558,6 +1640,7 @@ __device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const Ro
     S.chose[to][wave][lane] = make_uint4((unsigned)m, (unsigned)(m >> 32), (unsigned)retired, 0u);
   };
   int par = 0;
+  int answer = RACE && wave == kChainWaves - 1 ? race.ask() : 0;
   enter(0, 0);
   inside = avail;
   lds_barrier();
@@ -1661,7 +1744,12 @@ __device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const Ro
     inside = avail;
     // (a token's place is free once the token has entered the window, which 256 tokens fit)
     if (kWinTokens * nb < nflex_tok && kWinTokens * (nb + 1) <= done + kRing) stage();
+    if (RACE && wave == kChainWaves - 1) {
+      race.hand_out(answer, lane);
+      answer = race.ask();
+    }
     lds_barrier();
+    if (RACE && race.over()) return -1;
     avail = min(nflex_tok, kWinTokens * nb);
     // ---- output words that are complete (lane = expert) -----------------------------------------
     if (wave == kChainWaves - 1) {
@@ -1680,7 +1768,7 @@ __device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const Ro
     gflex = G;
     hist = (done & 31) != 0 ? S.out[(done >> 5) & (kWinWords - 1)][lane] : 0u;  // the decided bits of the unfinished word
     if (done == nflex_tok && (done & 31) != 0) ws.chain_bits[(size_t)(done >> 5) * 64 + lane] = hist;
-    if (lane == 0) ws.status[kStatusSweeps] = total_sweeps;
+    nsweeps = total_sweeps;
   }
   __syncthreads();  // (the LDS is free again)
   return done;
@@ -1694,6 +1782,12 @@ __device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const Ro
 // the first (whose beginning is known), all of it is what one walk would have decided.  Nothing
 // but that equality, expert by expert, ends the rounds, so the guesses decide about time only;
 // every round makes at least one more block final.
+//
+// Nobody depends on the blocks.  The chain workgroup walks such a call like any other one, the blocks write
+// their choices to arrays of their own beside it, and whoever is through first claims the call, writes
+// the totals and raises the last flag; the others see the claim and leave.  So a call whose rounds are
+// many takes what one walk takes, and one whose blocks are not even on the GPU (other calls', other streams'
+// workgroups in the way) waits for none of them: the chain workgroup waits for nobody.
 //
 // The guess.  Block q says where it began (I_q), where it ended (N_q) and how closely its tokens were
 // decided.  A correction d_q of I_q moves N_q by A_q d_q, so the correction of the next block is
@@ -1741,23 +1835,47 @@ __device__ __forceinline__ int block_begin(unsigned long long w) { return (int)(
 
 // The rows stand where the logits were: nothing reads those any more.  Behind the rows of
 // all blocks: per expert the assignments of all tokens that are not load-dependent, then how many
-// blocks have written out their final choices.
+// blocks have written out their final choices, and the claim; then the choices of the blocks, as in
+// Workspace::chain_bits and chain_cum.
 __device__ __forceinline__ unsigned long long* block_rows(const Workspace& ws) {
   return reinterpret_cast<unsigned long long*>(ws.logits);
 }
 __device__ __forceinline__ int* blocks_done(const Workspace& ws) {
   return reinterpret_cast<int*>(block_rows(ws) + kChainBlocks * 64 + 64);
 }
-static_assert((kChainBlocks * 64 + 64 + 1) * 8 <= kChainBlocksMinTokens * 9 * 4, "the rows fit the logits (9 experts at least)");
+__device__ __forceinline__ int* chain_claim(const Workspace& ws) { return blocks_done(ws) + 1; }
+constexpr int kBlockRowsBytes = ((kChainBlocks * 64 + 64 + 1) * 8 + 255) / 256 * 256;
+// (the finishing pass reads up to two words beyond that of a token)
+__host__ __device__ constexpr size_t block_words(int T) { return (size_t)T / 32 + 3; }
+__device__ __forceinline__ uint32_t* block_bits(const Workspace& ws) {
+  return reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(ws.logits) + kBlockRowsBytes);
+}
+__device__ __forceinline__ int32_t* block_cum(const Workspace& ws, int T) {
+  return reinterpret_cast<int32_t*>(block_bits(ws)) + block_words(T) * 64;
+}
+// (9 experts at least; 36 bytes of logits per token, 16 of choices)
+static_assert(kBlockRowsBytes + 2 * 64 * 4 * block_words(kChainBlocksMinTokens) <= kChainBlocksMinTokens * 9 * 4,
+              "the rows and choices fit the logits");
 // (by the chain workgroup, before the first flag; fixed: lane = expert, every wave the same)
-__device__ __forceinline__ void clear_block_rows(const Workspace& ws, int lane, int wave, int fixed) {
+__device__ __forceinline__ void clear_block_rows(const Workspace& ws, int T, int lane, int wave, int fixed) {
   unsigned long long* const rows = block_rows(ws);
   for (int i = threadIdx.x; i < kChainBlocks * 64; i += kTailThreads)
     __hip_atomic_store(&rows[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (wave == 0)
+  if (wave == 0) {
     __hip_atomic_store(&rows[kChainBlocks * 64 + lane], (unsigned long long)fixed, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
-  if (threadIdx.x == 0) __hip_atomic_store(blocks_done(ws), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    block_cum(ws, T)[lane] = 0;
+  }
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(blocks_done(ws), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(chain_claim(ws), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+// (one wavefront) Whether the call is this workgroup's to finish.
+__device__ __forceinline__ bool claim_chain(const Workspace& ws, int lane) {
+  int before = 0;
+  if (lane == 0) before = atomicExch(chain_claim(ws), 1);
+  return __builtin_amdgcn_readfirstlane(before) == 0;
 }
 __device__ __forceinline__ int chain_block_tokens(int nflex_tok) {
   return max(kChainBlockMin, ((nflex_tok + kChainBlocks - 1) / kChainBlocks + 31) & ~31);
@@ -1857,7 +1975,8 @@ __device__ __forceinline__ int block_close_decisions(int f0, int n, int slots, i
 
 // After a walk of the block [f0, f0 + n) from `begin` to `end` (wave 0, lane = expert), which was walk
 // number `round`: tells the others, waits for the blocks before this one to have come as far, and
-// works out the next beginning.  (tokens: of every block but the last.)  Returns the state (see BlockLds), or -1 where a wait ran out.
+// works out the next beginning.  (tokens: of every block but the last.)  Returns the state (see BlockLds), or -1
+// where the call has been claimed or a wait ran out.
 __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int blk, int tokens, unsigned round,
                                                bool last_walk, int f0, int n, int slots, int end, const RouteArgs& a, const Workspace& ws, int wave,
                                                int lane, int lin) {
@@ -1890,11 +2009,15 @@ __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int b
   if (r0 < r1) {
     unsigned long long v[kPer];
     bool there = false;
+    int claimed = 0;
     for (long long it = 0; it < a.spin_limit && !there; ++it) {
       // (the last of them first: it is the one that is waited for)
       const unsigned long long probe =
           __hip_atomic_load(&rows[(size_t)(r1 - 1) * 64 + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      claimed = __hip_atomic_load(chain_claim(ws), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (__builtin_amdgcn_ballot_w64(block_round(probe) < round) != 0ull) {
+        // (a block that has seen the claim tells no more)
+        if (__builtin_amdgcn_readfirstlane(claimed) != 0) break;
         __builtin_amdgcn_s_sleep(2);
         continue;
       }
@@ -1909,8 +2032,9 @@ __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int b
         whole = whole && r >= round && r == (unsigned)__builtin_amdgcn_readfirstlane(r);
       }
       there = __builtin_amdgcn_ballot_w64(!whole) == 0ull;
+      if (__builtin_amdgcn_readfirstlane(claimed) != 0) break;
     }
-    if (!there) {
+    if (!there || __builtin_amdgcn_readfirstlane(claimed) != 0) {
       S.ok = 0;
 #pragma unroll
       for (int u = 0; u < kPer; ++u) v[u] = 0ull;
@@ -1951,10 +2075,7 @@ __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int b
     S.open[wave] = 0u;
   }
   __syncthreads();
-  if (S.ok == 0) {
-    if (threadIdx.x == 0) ws.status[kStatusError] = kErrorTimeout;
-    return -1;
-  }
+  if (S.ok == 0) return -1;
   if (r0 < r1) {
     // (of the wave's last row the one behind is another wave's, or this block's own)
     const int gap = last_end - (r1 == blk ? begin : S.first_begin[min(wave + 1, kChainWaves - 1)][lane]);
@@ -2053,8 +2174,8 @@ struct ChainSeg {
 };
 
 // EP: the padded number of experts where it is known (the gate kernel of a pipelined call, whose
-// registers the walks that cannot occur would cost), else 0.  BLOCKS: a long chain is left to the
-// workgroups of its blocks (chain_block) once the lists of tokens are there.
+// registers the walks that cannot occur would cost), else 0.  BLOCKS: a long chain is walked by the
+// workgroups of its blocks (chain_block) as well, once the lists of tokens are there.
 template <int EP, bool BLOCKS>
 __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
                                 int32_t* __restrict__ loads_inout,
@@ -2232,6 +2353,7 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   };
 
   if (wave == 0 && (nflex_tiles > 0 || seg.on)) ws.chain_cum[lane] = 0;  // nothing chosen before flexible token 0
+  bool blocks = false;
   if (seg.on) {
     if (nflex_tiles == 0) {
       if (wave == 0) segment_result();
@@ -2240,19 +2362,23 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
     __syncthreads();  // tile_base, flex_slot written by every wave
   } else {
     if (nflex_tiles == 0 && wave == 0) write_totals();  // already final
-    const bool blocks = BLOCKS && chain_in_blocks(nflex_tok, a.T);
-    if (blocks) clear_block_rows(ws, lane, wave, total_fixed);
+    blocks = BLOCKS && chain_in_blocks(nflex_tok, a.T);
+    if (blocks) clear_block_rows(ws, a.T, lane, wave, total_fixed);
     __syncthreads();  // tile_base, flex_slot (and the totals) written by every wave
     if (threadIdx.x == 0) {
       ws.status[kStatusFlexTiles] = blocks ? -nflex_tiles : nflex_tiles;
       __hip_atomic_store(&ws.status[kStatusPhase], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (blocks) return;
     if (nflex_tiles == 0) return;
   }
 
-
-  int decided = 0;
+  Race<BLOCKS> race = {};
+  if constexpr (BLOCKS) {
+    __shared__ int race_stop[2];
+    race.claim = blocks ? chain_claim(ws) : nullptr;
+    race.stop = race_stop;
+  }
+  int decided = 0, nsweeps = 0;
   unsigned hist0 = 0;
   if (use_spec && EP != 8 && a.EP != 8) {
     // With many experts per candidate tokens rarely compete: the window of 256.
@@ -2260,47 +2386,54 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
     // walk is faster.  (Up to 8 experts the walk always is, or nearly: 17.7 ns per token against at least 16.)
     if (a.c <= 4) {
       if (a.E >= 16)
-        decided = a.k == 2 ? window_walk<4, 2>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
-                           : window_walk<4, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+        decided = a.k == 2 ? window_walk<4, 2>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race)
+                           : window_walk<4, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race);
       else if (EP == 0 || EP == 16)
-        decided = a.k == 2 ? spec_walk<4, 2>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
-                           : spec_walk<4, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+        decided = a.k == 2 ? spec_walk<4, 2>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race)
+                           : spec_walk<4, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race);
     } else if (a.c <= 8) {
       if ((EP == 0 || EP >= 32) && a.E >= 32)
-        decided = a.k == 6 ? window_walk<8, 6>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
-                           : window_walk<8, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+        decided = a.k == 6 ? window_walk<8, 6>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race)
+                           : window_walk<8, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race);
       else if (EP <= 32)
-        decided = a.k == 6 ? spec_walk<8, 6>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0)
-                           : spec_walk<8, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+        decided = a.k == 6 ? spec_walk<8, 6>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race)
+                           : spec_walk<8, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race);
     } else if ((EP == 0 || EP == 64) && a.E == 64) {
-      decided = window_walk<16, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+      decided = window_walk<16, 0>(lds, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race);
     } else {
-      decided = spec_walk<16, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0);
+      decided = spec_walk<16, 0>(lds, spec_sh, nflex_tok, a, ws, wave, lane, lin, gflex, hist0, nsweeps, race);
     }
   }
+  if (BLOCKS && decided < 0) return;  // (the blocks were first)
+  bool whole = true;
   if (decided < nflex_tok) {
     // the rest (or everything) one token after the other
     if (EP == 8 || (EP == 0 && a.EP == 8))  // (nothing is decided yet)
       chain_walk_pairs(lds, nflex_tok, ws, a.k, wave, lane, lin, gflex);
     else if (a.c <= 8)
-      chain_walk_lag(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
+      whole = chain_walk_lag(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex, race);
     else if (EP == 0 && wide)
-      chain_walk<0>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
+      whole = chain_walk<0>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex, race);
     else
-      chain_walk<16>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex);
+      whole = chain_walk<16>(lds, decided, hist0, nflex_tok, a, ws, wave, lane, lin, gflex, race);
   }
+  if (BLOCKS && !whole) return;
   if (seg.on) {
     if (wave == 0) segment_result();
     return;
   }
-  if (wave == 0) write_totals();
+  const bool mine = !blocks || wave != 0 || claim_chain(ws, lane);
+  if (wave == 0 && mine) {
+    write_totals();
+    if (lane == 0) ws.status[kStatusSweeps] = nsweeps;
+  }
   __syncthreads();
-  if (threadIdx.x == 0)
-    __hip_atomic_store(&ws.status[kStatusPhase], 2, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0 && mine)
+    __hip_atomic_store(&ws.status[kStatusPhase], kPhaseWalked, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Block `blk` of a chain of nflex_tok tokens (kTailThreads threads), see "the chain in blocks".
-__device__ __forceinline__ void chain_block(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
+__device__ __forceinline__ void chain_block(uint8_t* lds, const RouteArgs& a, const Workspace& call,
                                             int32_t* __restrict__ loads_inout, int32_t* __restrict__ expert_offsets,
                                             int blk, int nflex_tok) {
   __shared__ BlockLds S;
@@ -2309,14 +2442,18 @@ __device__ __forceinline__ void chain_block(uint8_t* lds, const RouteArgs& a, co
   const int tokens = chain_block_tokens(nflex_tok);  // of every block but the last
   const int f0 = blk * tokens, f1 = min(nflex_tok, f0 + tokens);
   if (f0 >= nflex_tok) return;
+  // (a claim is looked for between the walks: looks inside them cost the blocks 4 to 8 %, and a walk of
+  // a block is a 64th of the claimant's, a 24th where the call is short)
+  const Race<false> no_race = {};
+  Workspace ws = call;  // (with the blocks' own choices)
+  ws.chain_bits = block_bits(call);
+  ws.chain_cum = block_cum(call, a.T);
   const int lin = ws.lin_copy[lane];
   // the lists of tokens, from the chain workgroup
+  // (a wait that runs out is no error: the chain workgroup walks the call)
   if (wave == 0) {
-    const bool ok = poll_flag(&ws.status[kStatusPhase], 1, a.spin_limit);
-    if (lane == 0) {
-      S.ok = ok ? 1 : 0;
-      if (!ok) ws.status[kStatusError] = kErrorTimeout;
-    }
+    const bool ok = poll_flag(&ws.status[kStatusPhase], 1, a.spin_limit) != 0;
+    if (lane == 0) S.ok = ok ? 1 : 0;
     S.begin[lane] = 0;
   }
   __syncthreads();
@@ -2336,11 +2473,11 @@ __device__ __forceinline__ void chain_block(uint8_t* lds, const RouteArgs& a, co
   unsigned round = 1;
   for (;; ++round) {
     if (a.c <= 8)
-      chain_walk_lag(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex);
+      chain_walk_lag(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex, no_race);
     else if (a.cw > kMaxC)
-      chain_walk<0>(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex);
+      chain_walk<0>(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex, no_race);
     else
-      chain_walk<16>(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex);
+      chain_walk<16>(lds, f0, 0u, f1, a, ws, wave, lane, lin, gflex, no_race);
     const int state = block_round_end(S, reinterpret_cast<BlockRow*>(lds), blk, tokens, round, last_walk, f0, f1 - f0,
                                       slots, gflex, a, ws, wave, lane, lin);
     if (state < 0) return;
@@ -2354,21 +2491,28 @@ __device__ __forceinline__ void chain_block(uint8_t* lds, const RouteArgs& a, co
     if (threadIdx.x == 0) __hip_atomic_fetch_add(done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  // the last block: the totals and the second flag, when all the others have written theirs
+  // the last block, when all the others have written their choices: the totals and the last flag
   if (wave == 0) {
-    const bool ok = poll_flag(done, blk, a.spin_limit);
-    if (lane == 0) {
-      S.ok = ok ? 1 : 0;
-      if (!ok) ws.status[kStatusError] = kErrorTimeout;
-      ws.status[kStatusSweeps] = (int)round;
-    }
     const int fixed = (int)__hip_atomic_load(&block_rows(ws)[kChainBlocks * 64 + lane], __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
-    if (ok) chain_totals(lane, lin, lane < a.E ? fixed + gflex : 0, a.E, loads_inout, expert_offsets);
+    bool ok = false;
+    for (long long it = 0; it < a.spin_limit; ++it) {
+      const int n = __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int claimed = __hip_atomic_load(chain_claim(ws), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ok = __builtin_amdgcn_readfirstlane(n) >= blk;
+      if (ok || __builtin_amdgcn_readfirstlane(claimed) != 0) break;
+      __builtin_amdgcn_s_sleep(2);
+    }
+    ok = ok && claim_chain(ws, lane);
+    if (ok) {
+      chain_totals(lane, lin, lane < a.E ? fixed + gflex : 0, a.E, loads_inout, expert_offsets);
+      if (lane == 0) ws.status[kStatusSweeps] = (int)round;
+    }
+    if (lane == 0) S.ok = ok ? 1 : 0;
   }
   __syncthreads();
   if (S.ok != 0 && threadIdx.x == 0)
-    __hip_atomic_store(&ws.status[kStatusPhase], 2, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&ws.status[kStatusPhase], kPhaseBlocks, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---- pipelined calls: the chain segment by segment ---------------------------------
@@ -2423,7 +2567,7 @@ constexpr int kGateSignals = 8;
 // The chain of a call, by the chain workgroup (kTailThreads threads) of the gate kernel
 // (IN_GATE: as far as the analysed tiles allow, nothing is published) or of the tail
 // kernel (the rest, then the totals and the flags the finishing workgroups wait for).
-template <bool IN_GATE, int EP, bool BLOCKS = false>  // EP, BLOCKS, blk: see chain_workgroup
+template <bool IN_GATE, int EP, bool BLOCKS = false>  // EP, BLOCKS: see chain_workgroup
 __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a, const Workspace& ws,
                                                int32_t* __restrict__ loads_inout,
                                                int32_t* __restrict__ expert_offsets) {
@@ -2504,7 +2648,7 @@ __device__ __forceinline__ void chain_segments(uint8_t* lds, const RouteArgs& a,
   __syncthreads();
   if (threadIdx.x == 0) {
     status[kStatusFlexTiles] = ordbase;
-    __hip_atomic_store(&status[kStatusPhase], 2, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&status[kStatusPhase], kPhaseWalked, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -2676,8 +2820,8 @@ __device__ __forceinline__ void finish_tile(FinishLds* fl, int tile, const Finis
 // is asked for before they are waited for; what does comes in one round trip, a row of experts per
 // load: the tile's flexible tokens are in at most three words of 32.  (A byte and a word per candidate, one
 // after the other, before: 3001 tokens, 287 flexible, from the flag to the last store 7.3 -> 4.3 us.)
-// (EARLY: where the chain is cut into blocks the tile is left to another workgroup, see finish_role)
-template <bool EARLY>
+// (BLOCKS: the choices may be those of the chain's blocks)
+template <bool BLOCKS>
 __device__ __forceinline__ void finish_tile_of_chain(FinishLds* fl, int tile, const FinishPrologue& pro,
                                                      const RouteArgs& a, const Workspace& ws,
                                                      const int32_t* __restrict__ expert_offsets,
@@ -2711,22 +2855,25 @@ __device__ __forceinline__ void finish_tile_of_chain(FinishLds* fl, int tile, co
     return;
   }
   const int flex_tiles = load_published(&ws.status[kStatusFlexTiles]);
-  if (EARLY && flex_tiles < 0) return;
   // lane = expert: where this tile's first slot of the expert goes.  With flexible
   // tokens about, the choices made for the f0 flexible tokens of earlier tiles are
   // the running count at the last 32-token boundary plus the bits since.
   int before = load_published(&ws.tile_base[(size_t)tile * 64 + lane]);
   if (flex_tiles != 0) {
     const int f0 = load_published(&ws.flex_tok_base[tile]);
-    if (!poll_flag(&ws.status[kStatusPhase], 2, a.spin_limit)) {
+    const int phase = poll_flag(&ws.status[kStatusPhase], kPhaseWalked, a.spin_limit);
+    if (phase == 0) {
       ws.status[kStatusError] = kErrorTimeout;
       return;
     }
+    const bool by_blocks = BLOCKS && phase == kPhaseBlocks;
+    const uint32_t* const chain_bits = by_blocks ? block_bits(ws) : ws.chain_bits;
+    const int32_t* const chain_cum = by_blocks ? block_cum(ws, a.T) : ws.chain_cum;
     const size_t w = (size_t)(f0 >> 5) * 64 + lane;
     unsigned bits[3];
 #pragma unroll
-    for (int u = 0; u < 3; ++u) bits[u] = load_published(&ws.chain_bits[w + 64 * u]);
-    const int cum = load_published(&ws.chain_cum[w]);
+    for (int u = 0; u < 3; ++u) bits[u] = load_published(&chain_bits[w + 64 * u]);
+    const int cum = load_published(&chain_cum[w]);
     const int offset = lane < a.E ? load_published(&expert_offsets[lane]) : 0;
     fl->before[lane] = offset + before + cum + __builtin_popcount(bits[0] & ((1u << (f0 & 31)) - 1u));
 #pragma unroll
@@ -3110,9 +3257,8 @@ __device__ __forceinline__ int count_flexible(int ntiles, const Workspace& ws) {
 }
 
 // Finishing workgroup `group` of the tail grid (kTailThreads threads): tiles kChainWaves * group ... .
-// tail_lds: kChainLdsBytes of LDS.  EARLY: where the chain is cut into blocks the workgroup leaves its
-// tiles to another one.
-template <bool EARLY>
+// tail_lds: kChainLdsBytes of LDS.  BLOCKS: see finish_tile_of_chain.
+template <bool BLOCKS>
 __device__ __forceinline__ void finish_role(int group, uint8_t* tail_lds, FinishShared& S, const RouteArgs& a,
                                            const Workspace& ws, int32_t* __restrict__ loads_inout,
                                            int32_t* __restrict__ expert_offsets,
@@ -3187,7 +3333,7 @@ __device__ __forceinline__ void finish_role(int group, uint8_t* tail_lds, Finish
   if (__builtin_expect(self, 1))
     finish_tile(fl, tile, pro, a, ws, expert_ids, weights, permutation, own_base[wave], own_offsets, fast_n, &fs);
   else
-    finish_tile_of_chain<EARLY>(fl, tile, pro, a, ws, expert_offsets, expert_ids, weights, permutation);
+    finish_tile_of_chain<BLOCKS>(fl, tile, pro, a, ws, expert_offsets, expert_ids, weights, permutation);
 }
 
 }  // namespace laser

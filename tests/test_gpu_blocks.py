@@ -156,3 +156,57 @@ def test_batched_problems():
     loads = [np.zeros(E, np.int32) for _ in range(nb)]
     for b, got in enumerate(u.run_route_batched(hidden, w, wl.DTYPE_BF16, k, c, 2.0, 1e-30, loads)):
         u.assert_discrete_equal(got, oracle.route(got["logits"], k, c, 2.0, 1e-30, loads[b]), f"problem {b}")
+
+
+def _microseconds(call, reset, n=9):
+    import torch
+    took = []
+    for _ in range(n):
+        reset()
+        torch.cuda.synchronize()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        torch.cuda.synchronize()
+        took.append(1e3 * a.elapsed_time(b))
+    return float(np.median(took))
+
+
+@pytest.mark.parametrize("T,E,k,c", [(4096, 64, 6, 8), (3072, 64, 6, 8), (16384, 64, 1, 2), (4096, 64, 2, 4)])
+def test_many_rounds_take_no_longer_than_no_blocks(T, E, k, c):
+    """A gate without skew: the rounds of such calls are nearly as many as the blocks, so that they took 1.3
+    to 2 times what the call takes in one piece.  The same tokens, all of them load-dependent too, go without
+    blocks where the threshold is one half: the k best hold far less than half of the mass.  (1.1 and
+    less is measured.)"""
+    import torch
+    from paper_2510_03293_amd import binding as B
+    z = torch.from_numpy(wl.random_logits(T + c, T, E, kind="normal", scale=0.3)).cuda()
+    loads = torch.zeros(E, dtype=torch.int32, device="cuda")
+    took, outs = {}, {}
+    for eps in (2.0, 0.5, 2.0, 0.5):
+        params = B.make_params(k, c, eps, 1e-30)
+        buf = B.RouteBuffers(T, 0, E, params)
+        us = _microseconds(lambda: B.route_from_logits(z, params, loads, buf), loads.zero_)
+        took[eps] = min(us, took.get(eps, us))
+        outs[eps] = buf.expert_ids.cpu().numpy()
+    print(T, k, c, took, flush=True)
+    assert np.array_equal(outs[2.0], outs[0.5])
+    assert took[2.0] < 1.25 * took[0.5]
+
+
+def test_counters_are_written_whoever_gives_up():
+    """With a poll budget of one, finishing workgroups and blocks give up at once; the chain workgroup
+    waits for nobody, so the counters and offsets are those of the whole call all the same."""
+    import oracle
+    import torch
+    from paper_2510_03293_amd import binding as B
+    for T, E, k, c in ((16384, 64, 6, 8), (5000, 33, 3, 9), (4096, 64, 6, 64)):
+        z = wl.random_logits(11 + c, T, E, scale=0.3)
+        want = oracle.route(z, k, c, 2.0, 1e-30, np.zeros(E, np.int32))
+        loads = torch.zeros(E, dtype=torch.int32, device="cuda")
+        buf = B.route_from_logits(torch.from_numpy(z).cuda(), B.make_params(k, c, 2.0, 1e-30, poll_budget=1), loads)
+        torch.cuda.synchronize()
+        assert B.laser_status(buf.workspace) == B.STATUS_TIMEOUT
+        assert np.array_equal(loads.cpu().numpy(), want["loads"])
+        assert np.array_equal(buf.expert_offsets.cpu().numpy(), want["expert_offsets"])
