@@ -126,8 +126,10 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
   extern __shared__ __align__(16) uint8_t tail_lds[];
   __shared__ FinishShared finish_shared;
   // Workgroup 0 is the chain, the others finish tiles.  BLOCKS: the grid has layers, in the order of who
-  // waits for whom: the chain and its blocks, then the workgroups that finish tiles.
-  constexpr int kLayers = 2;
+  // waits for whom: the chain and its blocks, then the workgroups that finish tiles.  BATCH: the chains of
+  // all problems, their blocks, the workgroups that finish tiles (problem by problem, those of the first
+  // ones held the places that the last ones' chains needed).
+  constexpr int kLayers = BATCH ? 3 : 2;
   if (BLOCKS ? blockIdx.z != kLayers - 1 : !BATCH && blockIdx.x == 0) {
     // The chain reads its arguments for itself, through a pointer the compiler knows nothing of:
     // shared with the finishing workgroups they were all loaded, waited for and put aside (20
@@ -143,8 +145,8 @@ __global__ __launch_bounds__(kTailThreads, 2) void tail_kernel(const RouteArgs a
     if (blockIdx.z == 0 && blockIdx.x == 0) {
       chain_segments<false, 0, BLOCKS>(tail_lds, a, ws, loads, offsets);
     } else if constexpr (BLOCKS) {
-      const int blk = blockIdx.x - 1;
-      if (blk >= kChainBlocks) return;  // (every layer is as wide as the widest)
+      const int blk = BATCH ? blockIdx.x : blockIdx.x - 1;
+      if (blk >= kChainBlocks || (BATCH && blockIdx.z == 0)) return;  // (every layer is as wide as the widest)
       const int flex_tok = count_flexible(a.ntiles, ws);
       if (chain_in_blocks(flex_tok, a.T)) chain_block(tail_lds, a, ws, loads, offsets, blk, flex_tok);
     }
@@ -197,7 +199,7 @@ static hipError_t launch_tail_b(const RouteArgs& a, const Workspace& ws, int32_t
   const int groups = finish_groups(a.ntiles);
   const int width = BLOCKS ? std::max(1 + kChainBlocks, groups) : 1 + groups;
   clear_stale_error();
-  hipLaunchKernelGGL((tail_kernel<BATCH, BLOCKS>), dim3(width, a.nbatch, BLOCKS ? 2 : 1), dim3(kTailThreads), kChainLdsBytes, s, a, ws,
+  hipLaunchKernelGGL((tail_kernel<BATCH, BLOCKS>), dim3(width, a.nbatch, BLOCKS ? BATCH ? 3 : 2 : 1), dim3(kTailThreads), kChainLdsBytes, s, a, ws,
                      loads_inout, expert_offsets, expert_ids, weights, permutation);
   return hipGetLastError();
 }

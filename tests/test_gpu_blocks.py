@@ -210,3 +210,36 @@ def test_counters_are_written_whoever_gives_up():
         assert B.laser_status(buf.workspace) == B.STATUS_TIMEOUT
         assert np.array_equal(loads.cpu().numpy(), want["loads"])
         assert np.array_equal(buf.expert_offsets.cpu().numpy(), want["expert_offsets"])
+
+
+@pytest.mark.parametrize("T,line", [(4096, 1.5), (16384, 1.6)])
+def test_many_problems_side_by_side(T, line):
+    """Sixteen problems with slow rounds, whose blocks are twice the workgroups that the GPU holds at once: the
+    chains of all of them start at once and the blocks keep none of them waiting, so the call takes little
+    more than one problem does in one piece (thresholds: see above).  (16384 tokens: 1.3 times
+    as long; with a problem's workgroups behind all those of the problem before it, twice.)"""
+    import torch
+    from paper_2510_03293_amd import binding as B
+    H, E, k, c = 64, 64, 6, 8
+    took, outs = {}, {}
+    for nb, eps in ((16, 2.0), (16, 0.5), (1, 0.5)):
+        gen = torch.Generator(device="cuda").manual_seed(T)
+        hidden = torch.randn((nb, T, H), generator=gen, device="cuda").bfloat16()
+        gen = torch.Generator(device="cuda").manual_seed(T + 1)
+        w = (0.03 * torch.randn((nb, E, H), generator=gen, device="cuda")).bfloat16()
+        ids = torch.empty((nb, T, k), dtype=torch.int32, device="cuda")
+        weights = torch.empty((nb, T, k), device="cuda")
+        permutation = torch.empty((nb, T * k), dtype=torch.int32, device="cuda")
+        offsets = torch.empty((nb, E + 1), dtype=torch.int32, device="cuda")
+        loads = torch.zeros((nb, E), dtype=torch.int32, device="cuda")
+        params = B.make_params(k, c, eps, 1e-30, dtype=B.DTYPE_BF16)
+        one = B.laser_workspace_bytes(T, H, E, params)
+        workspace = torch.empty(one * nb, dtype=torch.uint8, device="cuda")
+        took[nb, eps] = _microseconds(
+            lambda: B.laser_route_batched(hidden, w, nb, T, H, E, params, loads, ids, weights, permutation, offsets, None,
+                                          workspace), loads.zero_, n=5)
+        outs[nb, eps] = (ids, permutation, loads)
+        assert all(B.laser_status(workspace[b * one:]) == B.STATUS_COMPLETE for b in range(nb))
+    print(T, took, flush=True)
+    assert all(torch.equal(x, y) for x, y in zip(outs[16, 2.0], outs[16, 0.5]))
+    assert took[16, 2.0] < line * took[1, 0.5]
