@@ -1823,6 +1823,7 @@ constexpr float kForgetHalf = 4.0f;      // close decisions per block that make 
 // decisions among its samples (6), the round (20; 0: nothing yet, kBlockFinal: it stays so).  Whole
 // words travel at once, a row of them that shows one round in all of its words is of one piece.
 constexpr unsigned kBlockFinal = 0xFFFFFu;
+static_assert(kSelfPrefixTiles * kTile < (1 << 27), "where a block begins, at most a choice per token, fits its field");
 static_assert(kSelfPrefixTiles * kTile / kChainBlocks < (1 << 11), "what a block adds fits its field");
 __device__ __forceinline__ unsigned long long block_word(int begin, int added, int close, unsigned round) {
   return ((unsigned long long)(unsigned)begin << 37) | ((unsigned long long)(unsigned)added << 26) |
@@ -1909,8 +1910,11 @@ __device__ __forceinline__ float wave_prefix(float v) {
   return v;
 }
 
-// `units` poured on the levels of the first E lanes: what each of them gets.
-__device__ __forceinline__ int first_guess(float level, int lane, int E, float units) {
+// k choices of each of `tokens` tokens poured on the levels of the first E lanes: what each of them gets, at
+// most one per token.  (What the bound cuts off is left out.  Poured on the others instead: a round
+// less for some calls, one or two more for others, 64 experts, c = 10, one of them far below: 299 -> 384 us.)
+__device__ __forceinline__ int first_guess(float level, int lane, int E, int k, int tokens) {
+  const float units = (float)(k * tokens);
   bool in = lane < E;
   float surface = 0.0f;
   for (int it = 0; it < E; ++it) {
@@ -1922,7 +1926,7 @@ __device__ __forceinline__ int first_guess(float level, int lane, int E, float u
   }
   const int sum = (int)floorf(wave_prefix(in ? surface - level : 0.0f) + 0.5f);  // (whole numbers, of the same sum)
   const int before = __shfl_up(sum, 1, 64);
-  return max(sum - (lane > 0 ? before : 0), 0);
+  return min(max(sum - (lane > 0 ? before : 0), 0), tokens);
 }
 
 // What a block's workgroup keeps in LDS beside that of the walks.
@@ -2130,10 +2134,11 @@ __device__ __forceinline__ int block_round_end(BlockLds& S, BlockRow* row, int b
         state = 1;  // (the block before ended where everything is decided: this is no guess)
         next = begin + (int)d;
       } else {
-        // whole numbers, of the same sum; a correction that is one stays as it is
+        // whole numbers, of the same sum; a correction that is one stays as it is; nobody has more
+        // choices than there are tokens before the block
         const int sum = (int)floorf(wave_prefix(d) + 0.5f);
         const int before = __shfl_up(sum, 1, 64);
-        next = max(begin + sum - (lane > 0 ? before : 0), 0);
+        next = min(max(begin + sum - (lane > 0 ? before : 0), 0), f0);
       }
     }
     S.begin_next[lane] = next;
@@ -2465,7 +2470,7 @@ __device__ __forceinline__ void chain_block(uint8_t* lds, const RouteArgs& a, co
   if (wave == 0 && blk != 0) {
     // the first guess: all choices before the block have gone to whoever was lowest
     gflex = first_guess(lane < a.E ? (float)(lin + ws.tile_base[(size_t)(ws.flex_slot[f0] >> 6) * 64 + lane]) : 0.0f, lane,
-                        a.E, (float)(a.k * f0));
+                        a.E, a.k, f0);
     S.begin[lane] = gflex;
   }
   __syncthreads();

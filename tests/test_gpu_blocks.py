@@ -84,6 +84,17 @@ def test_three_quarters_of_the_tokens(share):
     _check(logits, E, k, c, rng.permutation(E) * 500, 0.999, f"share {share}")
 
 
+def test_one_counter_far_below_or_above():
+    """All guessed choices go to one expert, which can have one per token at most; or to none but it."""
+    for E, k, c in ((64, 6, 64), (64, 6, 8), (40, 3, 30)):
+        T = 8192
+        logits = _skewed(E + c, T, E)
+        for low, others in ((0, 40 * T), (0, (1 << 27) - 1 - T), ((1 << 27) - 1 - T, 0)):
+            loads = np.full(E, others, np.int32)
+            loads[E // 3] = low
+            _check(logits, E, k, c, loads, 2.0, f"E{E} c{c} {low} {others}")
+
+
 def test_one_row_for_all_tokens():
     """Every token has the same candidates: whoever is ahead is passed over, block after block."""
     for E, k, c in ((64, 6, 8), (16, 4, 12), (64, 6, 64)):
