@@ -4,8 +4,11 @@ blocks, fixed tokens in between, equal counters and counters far apart, tokens t
 tokens that hardly do, every width of the records, several problems and streams at once."""
 from __future__ import annotations
 
+from typing import NamedTuple
+
 import numpy as np
 import pytest
+import torch
 
 from synth import workloads as wl
 
@@ -15,18 +18,34 @@ FIRST = 3072      # load-dependent tokens from which on a chain is cut
 SHAPES = [(64, 6, 8), (9, 2, 3), (16, 4, 12), (33, 3, 9), (64, 6, 64), (20, 3, 18)]
 
 
-def _check(logits, E, k, c, loads, eps, label):
-    """Against the oracle; the walks of the call's last block (the fourth status word)."""
+class Path(NamedTuple):
+    """How a call was routed, from the workspace's status words."""
+    cut: bool     # its chain was walked in blocks too (the second word is negative)
+    blocks: bool  # ... which were through before the chain workgroup (the first one is 3)
+    count: int    # then: walks of the last block; else sweeps of the window evaluation
+
+
+def _path(buf):
+    words = buf.workspace[:16].view(torch.int32).tolist()
+    return Path(words[1] < 0, words[0] == 3, words[3])
+
+
+def _check(logits, E, k, c, loads, eps, label, t_fix=1e-30, renormalize=True):
+    """Against the oracle: integers bit for bit, weights as everywhere; the call's path."""
     import oracle
-    import torch
     from paper_2510_03293_amd import binding as B
     from tests import gpu_util as u
     dev = torch.from_numpy(np.ascontiguousarray(loads, dtype=np.int32)).cuda()
-    buf = B.route_from_logits(torch.from_numpy(np.ascontiguousarray(logits)).cuda(), B.make_params(k, c, eps, 1e-30), dev)
+    buf = B.route_from_logits(torch.from_numpy(np.ascontiguousarray(logits)).cuda(),
+                              B.make_params(k, c, eps, t_fix, renormalize=renormalize), dev)
     torch.cuda.synchronize()
     print(label, flush=True)
-    u.assert_discrete_equal(u._collect(buf, dev, None), oracle.route(logits, k, c, eps, 1e-30, loads), label)
-    return int(buf.workspace[:16].view(torch.int32)[3])
+    got, want = u._collect(buf, dev, None), oracle.route(logits, k, c, eps, t_fix, loads, renormalize)
+    u.assert_discrete_equal(got, want, label)
+    assert np.abs(got["weights"].astype(np.float64) - want["weights"]).max() <= 1e-5, label
+    path = _path(buf)
+    assert path.cut or not path.blocks
+    return path
 
 
 def _skewed(seed, T, E, scale=0.9):
@@ -40,9 +59,20 @@ def _skewed(seed, T, E, scale=0.9):
 @pytest.mark.parametrize("E,k,c", SHAPES)
 def test_block_sizes(T, E, k, c):
     rng = np.random.default_rng(T + E)
-    _check(_skewed(T + c, T, E), E, k, c, np.zeros(E), 2.0, f"T{T} E{E} k{k} c{c} skewed")
-    _check(wl.random_logits(T + c, T, E, kind="normal", scale=0.3), E, k, c, rng.integers(0, 50, size=E), 2.0,
-           f"T{T} E{E} k{k} c{c} flat")
+    for path in (_check(_skewed(T + c, T, E), E, k, c, np.zeros(E), 2.0, f"T{T} E{E} k{k} c{c} skewed"),
+                 _check(wl.random_logits(T + c, T, E, kind="normal", scale=0.3), E, k, c, rng.integers(0, 50, size=E), 2.0,
+                        f"T{T} E{E} k{k} c{c} flat")):
+        assert path.cut == (T >= FIRST)
+
+
+@pytest.mark.parametrize("E,k,c", SHAPES)
+def test_raw_weights(E, k, c):
+    """Weights over the scores of all experts: another denominator, from another record."""
+    assert _check(_skewed(c, 4500, E), E, k, c, np.zeros(E), 2.0, f"raw E{E} c{c}", renormalize=False).cut
+
+
+def test_up_to_eight_experts_are_not_cut():
+    assert not _check(_skewed(3, 4500, 8), 8, 2, 4, np.zeros(8), 2.0, "8 experts").cut
 
 
 @pytest.mark.parametrize("E,k,c", SHAPES + [(64, 2, 4), (64, 9, 16)])
@@ -53,7 +83,7 @@ def test_counters_far_apart_and_fixed_tokens(E, k, c):
     _check(logits, E, k, c, rng.permutation(E) * 10 * T, 2.0, f"far E{E} c{c}")
     _check(logits, E, k, c, np.where(np.arange(E) % 3 == 0, 0, (1 << 27) - 1 - T), 2.0, f"limit E{E} c{c}")
     logits[rng.random(T) < 0.2, 0] += 30.0   # (their top-k whatever the loads)
-    _check(logits, E, k, c, np.zeros(E), 0.999, f"mixed E{E} c{c}")
+    assert _check(logits, E, k, c, np.zeros(E), 0.999, f"mixed E{E} c{c}").cut
 
 
 @pytest.mark.parametrize("T", [24576, 40000, 64 * 1024, 64 * 1024 + 1])
@@ -63,15 +93,7 @@ def test_some_tokens_of_long_calls(T):
     logits = _skewed(T, T, 64)
     flat = rng.random(T) < 0.2
     logits[flat] = (0.05 * rng.standard_normal((int(flat.sum()), 64))).astype(np.float32)
-    import oracle
-    import torch
-    from paper_2510_03293_amd import binding as B
-    from tests import gpu_util as u
-    loads = torch.zeros(64, dtype=torch.int32, device="cuda")
-    buf = B.route_from_logits(torch.from_numpy(logits).cuda(), B.make_params(6, 8, 0.4, 0.8), loads)
-    torch.cuda.synchronize()
-    u.assert_discrete_equal(u._collect(buf, loads, None), oracle.route(logits, 6, 8, 0.4, 0.8, np.zeros(64, np.int32)),
-                            f"T{T}")
+    assert not _check(logits, 64, 6, 8, np.zeros(64, np.int32), 0.4, f"T{T}", t_fix=0.8).cut
 
 
 @pytest.mark.parametrize("share", [0.0, 0.2, 0.24, 0.26])
@@ -81,7 +103,7 @@ def test_three_quarters_of_the_tokens(share):
     rng = np.random.default_rng(5)
     logits = _skewed(11, T, E)
     logits[rng.random(T) < share, 0] += 30.0
-    _check(logits, E, k, c, rng.permutation(E) * 500, 0.999, f"share {share}")
+    assert _check(logits, E, k, c, rng.permutation(E) * 500, 0.999, f"share {share}").cut == (share < 0.25)
 
 
 def test_one_counter_far_below_or_above():
@@ -99,15 +121,23 @@ def test_one_row_for_all_tokens():
     """Every token has the same candidates: whoever is ahead is passed over, block after block."""
     for E, k, c in ((64, 6, 8), (16, 4, 12), (64, 6, 64)):
         logits = np.repeat(wl.random_logits(E + k, 1, E, kind="normal", scale=1.0), 5000, axis=0)
-        _check(logits, E, k, c, np.zeros(E), 2.0, f"one row E{E} c{c}")
+        assert _check(logits, E, k, c, np.zeros(E), 2.0, f"one row E{E} c{c}").cut
 
 
 def test_full_size_calls_take_few_rounds():
-    """16384 tokens, a skewed gate: a call that had to make its 64 blocks final one by one would be
-    right too, but slower than a single walk (12 rounds in a simulation of such a call at most)."""
+    """16384 tokens, a skewed gate: with a round per block the 64 blocks would be slower than the one walk
+    (12 rounds in a simulation of such a call at most)."""
     for seed in (1, 2, 3):
-        assert _check(_skewed(seed, 16384, 64), 64, 6, 8, np.zeros(64), 2.0, f"full seed {seed}") <= 20
-    assert _check(_skewed(4, 8192, 64), 64, 6, 64, np.zeros(64), 2.0, "load only") <= 4
+        path = _check(_skewed(seed, 16384, 64), 64, 6, 8, np.zeros(64), 2.0, f"full seed {seed}")
+        assert path.blocks and 1 <= path.count <= 20
+    path = _check(_skewed(4, 8192, 64), 64, 6, 64, np.zeros(64), 2.0, "load only")
+    assert path.blocks and 1 <= path.count <= 4
+
+
+def test_slow_rounds_are_left_to_the_chain_workgroup():
+    """A gate without skew: as many rounds as blocks, or nearly; the one walk is through long before."""
+    path = _check(wl.random_logits(5, 16384, 64, kind="normal", scale=0.3), 64, 1, 2, np.zeros(64), 2.0, "flat")
+    assert path.cut and not path.blocks
 
 
 def test_random_trimming_in_blocks():
@@ -120,7 +150,6 @@ def test_random_trimming_in_blocks():
 def test_streams_side_by_side_and_replays():
     """Two calls at once on two streams, then one of them from a HIP graph, several times."""
     import oracle
-    import torch
     from paper_2510_03293_amd import binding as B
     from tests import gpu_util as u
     E, k, c, T = 64, 6, 8, 6001
@@ -170,7 +199,6 @@ def test_batched_problems():
 
 
 def _microseconds(call, reset, n=9):
-    import torch
     took = []
     for _ in range(n):
         reset()
@@ -190,7 +218,6 @@ def test_many_rounds_take_no_longer_than_no_blocks(T, E, k, c):
     to 2 times what the call takes in one piece.  The same tokens, all of them load-dependent too, go without
     blocks where the threshold is one half: the k best hold far less than half of the mass.  (1.1 and
     less is measured.)"""
-    import torch
     from paper_2510_03293_amd import binding as B
     z = torch.from_numpy(wl.random_logits(T + c, T, E, kind="normal", scale=0.3)).cuda()
     loads = torch.zeros(E, dtype=torch.int32, device="cuda")
@@ -210,7 +237,6 @@ def test_counters_are_written_whoever_gives_up():
     """With a poll budget of one, finishing workgroups and blocks give up at once; the chain workgroup
     waits for nobody, so the counters and offsets are those of the whole call all the same."""
     import oracle
-    import torch
     from paper_2510_03293_amd import binding as B
     for T, E, k, c in ((16384, 64, 6, 8), (5000, 33, 3, 9), (4096, 64, 6, 64)):
         z = wl.random_logits(11 + c, T, E, scale=0.3)
@@ -229,7 +255,6 @@ def test_many_problems_side_by_side(T, line):
     chains of all of them start at once and the blocks keep none of them waiting, so the call takes little
     more than one problem does in one piece (thresholds: see above).  (16384 tokens: 1.3 times
     as long; with a problem's workgroups behind all those of the problem before it, twice.)"""
-    import torch
     from paper_2510_03293_amd import binding as B
     H, E, k, c = 64, 64, 6, 8
     took, outs = {}, {}
