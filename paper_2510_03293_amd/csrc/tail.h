@@ -733,10 +733,21 @@ __device__ __forceinline__ bool chain_walk_lag(uint8_t* lds, int f0, unsigned hi
   const int b0 = f0 / kLagBatch, b1 = (nflex_tok + kLagBatch - 1) / kLagBatch;
   int pi, pj;
   lane_pair(lane & 31, pi, pj);
-  // (a look at the claim every four batches, 3.4 us; in loops of their own, since a test in the consumer's
-  // loop over the batches cost the walk 5 %)
+  // (a look at the claim every four batches, 3.4 us; in loops around those over the batches, and only where
+  // it is RACE: a test in the consumer's loop over the batches cost the walk 5 %, loops around it 1.4 %)
   constexpr int kLook = 4;
-  auto stretch = [&](int b) { return RACE && race.on() ? min(b1, b + kLook) : b1; };
+  bool whole = true;
+  auto stretches = [&](auto batches) {  // batches(b, be): from b on, before be
+    if constexpr (RACE) {
+      for (int b = b0, be; b < b1 && whole; b = be) {
+        be = race.on() ? min(b1, b + kLook) : b1;
+        batches(b, be);
+        if (be < b1 && race.over()) whole = false;
+      }
+    } else {
+      batches(b0, b1);
+    }
+  };
   if (wave == 1 || wave == 2) {
     // ---- producers: two batches ahead of the consumer in LDS, and two more with every load that
     // leads to another one -- where the records are, the records, the counters of the candidates
@@ -786,8 +797,7 @@ __device__ __forceinline__ bool chain_walk_lag(uint8_t* lds, int f0, unsigned hi
     fill(b0 + 1, c1, r1, s1);
     lds_barrier();
     // (what is filled behind the last batch is not read)
-    for (int b = b0, be; b < b1; b = be) {
-      be = stretch(b);
+    stretches([&](int b, int be) {
       for (; b < be; b += 2) {
         fill(b + 2, c0, r0, s0);
         lds_barrier();
@@ -795,19 +805,16 @@ __device__ __forceinline__ bool chain_walk_lag(uint8_t* lds, int f0, unsigned hi
         fill(b + 3, c1, r1, s1);
         lds_barrier();
       }
-      if (RACE && be < b1 && race.over()) return false;
-    }
+    });
   } else if (wave != 0) {
     lds_barrier();
-    for (int b = b0, be; b < b1; b = be) {
-      be = stretch(b);
-      const int answer = RACE ? race.ask() : 0;
+    stretches([&](int b, int be) {
+      const int answer = race.ask();
       for (; b < be; ++b) {
         if (RACE && b + 1 == be && be < b1) race.hand_out(answer, lane);
         lds_barrier();
       }
-      if (RACE && be < b1 && race.over()) return false;
-    }
+    });
   } else {
     // ---- consumer ----------------------------------------------------------------------
     int G = gflex;
@@ -832,8 +839,7 @@ __device__ __forceinline__ bool chain_walk_lag(uint8_t* lds, int f0, unsigned hi
     // (the choice before the first token is in G)
     int diff = gather(d0.z) - gather(d0.y);
     unsigned chosen = 0u;  // (lane = expert: of the token before)
-    for (int b = b0, be; b < b1;) {
-      be = stretch(b);
+    stretches([&](int b, int be) {
       for (; b < be; ++b) {
         const bool wrap = cur + kLagBatch == ring_end;
         const LagTok* const next = wrap ? ring : cur + kLagBatch;
@@ -894,11 +900,10 @@ __device__ __forceinline__ bool chain_walk_lag(uint8_t* lds, int f0, unsigned hi
         cur_places = next_places;
         lds_barrier();
       }
-      if (RACE && be < b1 && race.over()) return false;
-    }
+    });
     gflex = G;
   }
-  return true;
+  return whole;
 }
 
 // Up to 8 experts (all of a call's flexible tokens).  A pair is one of experts: the lane itself
@@ -1243,7 +1248,8 @@ __device__ __forceinline__ void spec_fill(SpecTok<CP>* ring, int seg, int half, 
 // Runs the window evaluation from flexible token 0.  All four waves call it.  Returns
 // (to every wave) the number of flexible tokens decided, or -1 where somebody else has claimed the
 // call (see Race); wave 0 leaves the flexible choices so far in `gflex` (lane = expert), the bits of the
-// unfinished output word in `hist` and the number of sweeps in `nsweeps`.  KK = k when known at compile time, else 0.
+// unfinished output word in `hist` and the number of sweeps in `nsweeps` (a status word where nobody
+// else walks the call).  KK = k when known at compile time, else 0.
 // LDS of the window evaluation beside the ring (one copy for all compiled variants).
 struct SpecShared {
   SpecExp M[64];
@@ -1416,7 +1422,10 @@ __device__ __forceinline__ int spec_walk(uint8_t* lds, SpecShared& sp, int nflex
     gflex = G;
     hist = (unsigned)pend;  // the decided % 32 bits of the unfinished word
     if (decided == nflex_tok && pn > 0) ws.chain_bits[(size_t)w * 64 + lane] = (unsigned)pend;
-    nsweeps = total_sweeps;
+    if constexpr (RACE)
+      nsweeps = total_sweeps;
+    else if (lane == 0)
+      ws.status[kStatusSweeps] = total_sweeps;
   }
   __syncthreads();  // the ring is dead: the sequential walk may reuse the LDS
   return decided;
@@ -1768,7 +1777,10 @@ __device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const Ro
     gflex = G;
     hist = (done & 31) != 0 ? S.out[(done >> 5) & (kWinWords - 1)][lane] : 0u;  // the decided bits of the unfinished word
     if (done == nflex_tok && (done & 31) != 0) ws.chain_bits[(size_t)(done >> 5) * 64 + lane] = hist;
-    nsweeps = total_sweeps;
+    if constexpr (RACE)
+      nsweeps = total_sweeps;
+    else if (lane == 0)
+      ws.status[kStatusSweeps] = total_sweeps;
   }
   __syncthreads();  // (the LDS is free again)
   return done;
@@ -2430,7 +2442,7 @@ __device__ __forceinline__ void chain_workgroup(uint8_t* lds, const RouteArgs& a
   const bool mine = !blocks || wave != 0 || claim_chain(ws, lane);
   if (wave == 0 && mine) {
     write_totals();
-    if (lane == 0) ws.status[kStatusSweeps] = nsweeps;
+    if (BLOCKS && lane == 0) ws.status[kStatusSweeps] = nsweeps;
   }
   __syncthreads();
   if (threadIdx.x == 0 && mine)
