@@ -5,6 +5,7 @@ from __future__ import annotations
 
 import numpy as np
 import pytest
+import torch
 
 from synth import workloads as wl
 
@@ -20,7 +21,6 @@ def _sweeps(T, E, k, c, logits, loads_in, label):
     """_check with every token load-dependent; the sweeps of the window evaluation (the fourth of
     the workspace's status words)."""
     import oracle
-    import torch
     from paper_2510_03293_amd import binding as B
     from tests import gpu_util as u
     loads = torch.from_numpy(np.ascontiguousarray(loads_in, dtype=np.int32)).cuda()
@@ -126,3 +126,47 @@ def test_resampling_of_a_whole_tile(T, E, k, c):
     _, ref = u.check_random_from_logits(logits, k, c, 2.0, 1e-30, np.zeros(E, np.int32), seed=77 + T, stream=3,
                                         token_offset=(1 << 32) - 5, label=f"resample T{T} E{E}")
     assert (ref["cstar"] == c).all()
+
+
+def _rounded(seed, T, E, step):
+    """Normal logits rounded to multiples of `step`, zeros of either sign: many are equal."""
+    rng = np.random.default_rng(seed)
+    z = (np.round(wl.random_logits(seed, T, E, kind="normal", scale=0.9) / step) * step).astype(np.float32)
+    return np.where(z == 0, np.where(rng.random(z.shape) < 0.5, np.float32(-0.0), np.float32(0.0)), z)
+
+
+@pytest.mark.parametrize("E,k,c", [(64, 6, 6), (64, 6, 8), (33, 3, 3), (9, 2, 2), (40, 3, 5)])
+@pytest.mark.parametrize("step", [0.25, 4.0])
+def test_equal_logits_are_ranked_by_expert(E, k, c, step):
+    """The ranks by counting, where counts are equal too: samples, weights and dispatch."""
+    from tests import gpu_util as u
+    for T in (65, 1000):
+        u.check_random_from_logits(_rounded(T + E, T, E, step), k, c, 0.4, 0.3, np.zeros(E, np.int32), seed=7, stream=1,
+                                   label=f"equal E{E} c{c} step {step}")
+
+
+def test_equal_logits_take_no_longer():
+    """Logits that were rounded to bf16 have equal ones in nearly every token: the ranks were then counted
+    twice, the second time with double keys, and the call took 1.6 times as long (1.3 times what it took
+    when it only counted with keys)."""
+    from paper_2510_03293_amd import binding as B
+    T, E, k = 40000, 64, 6
+    z = torch.from_numpy(wl.random_logits(3, T, E, kind="normal", scale=0.9)).cuda()
+    params = B.make_params(k, k, 0.4, 0.55, trim_mode=B.TRIM_RANDOM, seed=3)
+    loads = torch.zeros(E, dtype=torch.int32, device="cuda")
+    took = {}
+    for name, logits in (("distinct", z), ("equal", z.bfloat16().float())) * 2:
+        buf = B.RouteBuffers(T, 0, E, params)
+        us = []
+        for _ in range(9):
+            loads.zero_()
+            torch.cuda.synchronize()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            B.route_from_logits(logits, params, loads, buf)
+            b.record()
+            torch.cuda.synchronize()
+            us.append(1e3 * a.elapsed_time(b))
+        took[name] = min(took.get(name, 1e9), float(np.median(us)))
+    print(took, flush=True)
+    assert took["equal"] < 1.25 * took["distinct"]
