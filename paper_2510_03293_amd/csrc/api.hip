@@ -143,11 +143,12 @@ static RandomArgs make_random(const laser_params_t* p) {
 // The segments of a pipelined call (a.seg_tiles == 0: the call is not pipelined), from
 // laser_params_t.pipeline_tiles.  Left to itself the library pipelines batches of at least
 // six rounds of the persistent grid (one workgroup per compute unit but one): a first
-// segment of one round, so that the chain starts early, then segments of one or two rounds -- a
-// segment is complete when its last round is, so whole rounds it is.  One where the chain is ahead of
-// the stream, for the sake of what is left behind it (the window of 256 tokens; 131072 tokens, 64
-// experts, a tenth load-dependent: 285 -> 276 us), two where it is the longer of the two and every
-// segment's start costs 5 us (8 experts: 340 against 362 us).  (Measured on the
+// segment of one round, so that the chain starts early, then segments of two rounds -- a
+// segment is complete when its last round is, so whole rounds it is.  (Segments of one round
+// leave less behind the stream where the window of 256 tokens keeps ahead of it, 131072 tokens, H = 4096, 64
+// experts, a tenth load-dependent: 285 -> 276 us; but every segment's start costs 5 us, and segments
+// of fewer than kSpecMinTokens load-dependent tokens are walked one by one: H = 2048, c = 10, 150 to 250 of them per
+// round, 178 -> 348 us, and 2 to 7 % where the chain is the longer of the two.)  (Measured on the
 // prefill shape: with many load-dependent tokens pipelining pays from three rounds on,
 // -12 % at four, -24 % at eight; with none it costs 15 % at four rounds -- the compute
 // unit given to the chain and the clearing launch -- and gains 5 % at eight, where the
@@ -162,8 +163,7 @@ static void choose_segments(RouteArgs& a, uint32_t wanted) {
     const int round = pipeline_workgroups();
     if (a.ntiles < 6 * round) return;
     a.seg_first = round;
-    const bool window = a.c <= 4 ? a.E >= 16 : a.c <= 8 ? a.E >= 32 : a.E == 64;  // (chain_workgroup's)
-    a.seg_tiles = window ? round : 2 * round;
+    a.seg_tiles = 2 * round;
   }
   a.nseg = 1 + (a.ntiles - a.seg_first + a.seg_tiles - 1) / a.seg_tiles;
 }

@@ -284,3 +284,37 @@ def test_pipelined_call_replayed_from_a_hip_graph():
         for x, y in zip(want, got):
             assert torch.equal(x.view(torch.int32), y.view(torch.int32)), f"replay {rep}"
         assert B.laser_status(buf.workspace) == B.STATUS_COMPLETE
+
+
+def test_default_segments_are_long_enough_for_the_window():
+    """131072 tokens, a few hundred of every 16 K of them load-dependent: segments of one round of the grid were
+    too short for the window evaluation and walked token by token, at twice the time of segments of two
+    rounds (348 against 178 us)."""
+    import torch
+    from paper_2510_03293_amd import binding as B
+    T, H, E, k, c = 131072, 2048, 64, 6, 10
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    hidden = torch.randn((T, H), generator=gen, device="cuda")
+    w = (0.02 * torch.randn((E, H), generator=gen, device="cuda")).bfloat16()
+    hidden *= (torch.rand((T, 1), generator=gen, device="cuda") < 0.1) * 0.6 + 0.7
+    hidden = hidden.bfloat16()
+    loads = torch.zeros(E, dtype=torch.int32, device="cuda")
+    took, ids = {}, {}
+    for tiles in (0, 510, 0, 510):
+        params = B.make_params(k, c, 0.4, 0.8, pipeline_tiles=tiles)
+        buf = B.RouteBuffers(T, H, E, params)
+        us = []
+        for _ in range(7):
+            loads.zero_()
+            torch.cuda.synchronize()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            B.route(hidden, w, params, loads, buf)
+            b.record()
+            torch.cuda.synchronize()
+            us.append(1e3 * a.elapsed_time(b))
+        took[tiles] = min(took.get(tiles, 1e9), float(np.median(us)))
+        ids[tiles] = buf.expert_ids
+    print(took, flush=True)
+    assert torch.equal(ids[0], ids[510])
+    assert took[0] < 1.25 * took[510]
