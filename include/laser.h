@@ -37,14 +37,18 @@
  *     c <= 16 (the paper evaluates c <= 10) run on the fast kernels; 16 < c <= E
  *     (up to the load-only baseline of the paper's evaluation, c = n) is routed
  *     exactly by general ones: another kernel per call, and a walk of about 100 ns
- *     per load-dependent token where up to 8 candidates take 18 to 53.
+ *     per load-dependent token where up to 8 candidates take 18 to 53.  A call whose
+ *     tokens are nearly all load-dependent (eps_high above 0.5, more than 8 experts,
+ *     3072 to 65536 tokens) is also walked in blocks side by side, which is up to ten
+ *     times as fast; whichever of the two is through first finishes the call.
  *   - Completion.  The kernels of a call hand data to one another through the
  *     workspace; the workgroups that write the dispatch tables wait for the
  *     workgroup that walks the load-dependent tokens with a bounded number of
  *     polls (laser_params_t.poll_budget) and, should that bound ever run out, leave
- *     without writing: the call's outputs are then incomplete.  This is recorded
- *     in the workspace and reported by laser_status(); it does not happen while
- *     the GPU makes progress on the call's own kernels.
+ *     without writing: the call's ids, weights and permutation are then incomplete
+ *     (the counters and offsets are not: the workgroup that is waited for waits for
+ *     nobody).  This is recorded in the workspace and reported by laser_status(); it
+ *     does not happen while the GPU makes progress on the call's own kernels.
  */
 #ifndef LASER_H_
 #define LASER_H_
@@ -105,16 +109,17 @@ typedef struct laser_params {
   uint64_t token_offset; /* caller's index of token 0 of this call (split calls)    */
   uint32_t stream;       /* caller's stream id, e.g. the layer                      */
   uint32_t poll_budget;  /* 0: the library sizes its bounded waits from T (millions of */
-                         /* polls); otherwise the number of polls after which a waiting */
-                         /* workgroup gives up (see "Completion" above)                 */
+                         /* polls); otherwise the number of polls of any one wait after */
+                         /* which the waiting workgroup gives up (see "Completion"      */
+                         /* above; a block of tokens that gives up costs time only)     */
   uint32_t pipeline_tiles; /* Large bf16 calls of laser_route are pipelined: the walk over */
                          /* the load-dependent tokens of a segment of the batch (Algorithm */
                          /* 1 orders the tokens, so it needs nothing of later tokens) runs */
                          /* while the projection of the later segments still streams.      */
-                         /* 0: the library decides (segments of about 32 K tokens for      */
-                         /* batches of 96 K tokens or more); 1: never; n >= 2: segments of */
-                         /* n tiles of 64 tokens whenever the batch has more tiles.  The   */
-                         /* results do not depend on it.                                   */
+                         /* 0: the library decides (segments of about 32 K tokens, the     */
+                         /* first one half of that, for batches of 96 K tokens or more);   */
+                         /* 1: never; n >= 2: segments of n tiles of 64 tokens whenever    */
+                         /* the batch has more tiles.  The results do not depend on it.    */
   uint32_t split_k;      /* Small bf16 calls (up to 64 tiles of 64 tokens in all): the      */
                          /* contraction axis of the projection is cut over eight workgroups */
                          /* per tile (four beyond 32 tiles; batched calls: where H is long  */

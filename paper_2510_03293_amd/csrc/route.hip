@@ -10,9 +10,10 @@
 //            cannot depend on loads ("fixed": top-k mass reached, or working set
 //            no larger than k) gets its final experts here.  The others
 //            ("flexible") leave a record.
-//   chain    (one wavefront, lane = expert)  walks the flexible tokens in token
-//            order against the live counters; fixed tokens enter as per-tile
-//            per-expert counts plus, inside a tile, a per-record prefix count.
+//   chain    (one workgroup; long chains in blocks as well, see tail.h)  decides the
+//            flexible tokens in token order against the live counters; fixed tokens
+//            enter as per-tile per-expert counts plus, inside a tile, a per-record
+//            prefix count.
 //   finish   (parallel over tiles)  expands the chain's choices into expert ids
 //            and weights and scatters the stable counting-sort permutation.
 //

@@ -1811,18 +1811,25 @@ __device__ __forceinline__ int window_walk(uint8_t* lds, int nflex_tok, const Ro
 //     (A d)_e = (1 - g_e) d_e + g_e (sum_i g_i d_i) / (sum_i g_i).
 // g comes from a sample of the block's tokens: how often the expert was chosen or passed over with at
 // most one to spare.
-// (Rounds until 16384 load-dependent tokens of 64 experts are decided, k = 6, c = 8, blocks of 256: 7 to 10;
-// without A, 62 to 64 in a simulation.)
+// (Rounds until 16384 load-dependent tokens of 64 experts are decided, k = 6, c = 8, blocks of 256: 6 to 12 where
+// the gate is skewed and the counters begin at zero, without A 62 to 64 in a simulation; 30 to 42 where
+// the counters begin random in 0..2000 or the gate is flat, because several groups of experts are then level
+// at heights of their own and A takes them for one.)
 // What bounds a round of that call, 20 us: the walk of 256 tokens 15, the sample 1.7, the rows' way
-// through memory and what is made of them 3, the correction 1.  The call: 889 -> 176 to 210 us; with c = 10,
-// 2279 -> 370; 8192 tokens of 64 candidates each, two rounds, 837 -> 99 with what else has changed.  At 3072 tokens
-// the walk alone is about as fast.
+// through memory and what is made of them 3, the correction 1.  The call from logits: 888 us in one piece, 172
+// to 238 in 6 to 9 rounds; with c = 10, 2194 and 383; 8192 tokens of 64 candidates, one round, 777 and 70; 3072
+// tokens, c = 8, seven rounds, 206 and 132.  Where the chain workgroup is first the blocks cost the call 2 to 9 %,
+// and up to 20 % (7 to 37 us) where it is through in windows: they leave between two of their walks
+// only, and the kernel ends with them.
 constexpr int kChainBlocks = 64;         // blocks of a call, at most
 constexpr int kChainBlockMin = 128;      // tokens of a block, at least
 // A call is walked in blocks where at least this many of its tokens, and three quarters, are
-// load-dependent.  Where the others set the pace, many experts may be level with one another and hardly ever
-// compared: no block forgets its beginning, and the rounds are nearly as many as the blocks (60534 tokens,
-// 64 experts, 14400 load-dependent: 47 rounds, 1118 us, in windows 600 at most).
+// load-dependent.  The other tokens' choices set experts apart that the load-dependent ones hardly ever
+// compare: blocks forget less of their beginning and the rounds are more.  The line lies where a call of up to 8
+// candidates stops gaining (16384 tokens, 64 experts, k = 6, c = 8, skewed gate; in one piece and with blocks
+// beside it: no other tokens 888 and 238 us, 10 % of them 808 and 172, 24 % 690 and 694, 26 % 674 and 704, 40 %
+// 559 and 587).  Longer calls and more candidates would still gain beyond it (60000 tokens, 26 %: 2325 and 1824;
+// c = 10, 26 %: 1632 and 1408; 33 experts, k = 3, c = 9, 26 %: 1630 and 345), which is given away here.
 constexpr int kChainBlocksMinTokens = 3072;
 __device__ __forceinline__ bool chain_in_blocks(int nflex_tok, int T) {
   return nflex_tok >= kChainBlocksMinTokens && 4ll * nflex_tok >= 3ll * T;
